@@ -447,7 +447,6 @@ struct sg_ctx {
     size_t sk_lds = 0;
     int period = 64;
     int* err_d = nullptr;
-    int sk_threads = 256;
     bool sk_real = false;                 // SK with real couplings (sg_skg.hip)
     double* bondr_d = nullptr;            // [n_chains][K] real bond sums
     double* bpart_d = nullptr;            // their partial sums
@@ -1474,13 +1473,12 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     }
 
     Arena A;
-    std::vector<size_t> off_J(jrep.size()), off_Jb(jrep.size()), off_Jt(jrep.size());
-    const int tile_words = sk_tile_words();
+    std::vector<size_t> off_J(jrep.size()), off_Jw(jrep.size());
     for (size_t j = 0; j < jrep.size(); ++j) {
         const int64_t n = d[jrep[j]].n;
         off_J[j] = A.take((size_t)(n * n));
-        off_Jb[j] = A.take((size_t)n * (size_t)((n + 31) / 32) * 4);
-        off_Jt[j] = A.take((size_t)((n + 63) / 64) * 64 * (size_t)tile_words * 4);
+        const size_t nb = (size_t)sk_blocks((int32_t)n);
+        off_Jw[j] = A.take(nb * nb * 64 * 8);
     }
     std::vector<size_t> off_thr((size_t)count);
     for (int32_t i = 0; i < count; ++i) off_thr[(size_t)i] = A.take(thr[(size_t)i].size() * 8);
@@ -1508,18 +1506,18 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     const size_t off_gram = A.take((size_t)c->n_chains * c->K * c->K * 8);
     const size_t off_acc = A.take((size_t)c->n_chains * 8);
     const size_t off_err = A.take(8);
+    A.take(kSkOverread);   // the sweep kernel reads past the words of a matrix
     c->arena_bytes = A.size;
     c->arena = c->dev_alloc(A.size);
 
     // couplings: generated on the host in parallel, or copied; int8 rows for
-    // the MFMA contractions and bit-packed rows (bit 1 = -1, 8x fewer bytes)
-    // for the field updates of the sweep
+    // the MFMA contractions and bit-packed words for the sweep
     // (a few samples: each one's passes run on several threads; many: the
     // samples do)
     const bool inner = jrep.size() < 4;
     maybe_parallel(!inner, jrep.size(), [&](size_t j) {
         const sg_sk_desc& r = d[jrep[j]];
-        const int64_t n = r.n, wn = (n + 31) / 32;
+        const int64_t n = r.n;
         std::vector<int8_t> J;
         const int8_t* src = r.J;
         if (!src) {
@@ -1528,31 +1526,22 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
             src = J.data();
         }
         hip_check(hipMemcpy(c->at<void>(off_J[j]), src, (size_t)(n * n), hipMemcpyHostToDevice));
-        std::vector<uint32_t> Jb((size_t)(n * wn), 0u);
-        maybe_parallel(inner, (size_t)n, [&](size_t ii) {
-            const int64_t i = (int64_t)ii;
-            for (int64_t k = 0; k < n; ++k)
-                if (src[i * n + k] < 0) Jb[(size_t)(i * wn + (k >> 5))] |= 1u << (k & 31);
-        });
-        hip_check(hipMemcpy(c->at<void>(off_Jb[j]), Jb.data(), Jb.size() * 4, hipMemcpyHostToDevice));
-        // the decider's tiles: row 64 b + l, words 2 bb and 2 bb + 1 for
-        // bb = b - d (cyclic), d = 0..DW with DW = min(window, blocks - 1)
-        const int64_t nb = (n + 63) / 64;
-        const int64_t dw = std::min<int64_t>(sk_window(), nb - 1);
-        std::vector<uint32_t> Jt((size_t)(nb * 64 * tile_words), 0u);
-        for (int64_t b = 0; b < nb; ++b)
-            for (int64_t l = 0; l < 64; ++l) {
-                const int64_t row = 64 * b + l;
-                if (row >= n) continue;
-                for (int64_t dd = 0; dd <= dw; ++dd) {
-                    const int64_t bb = (b - dd + nb) % nb;
-                    for (int64_t h = 0; h < 2; ++h) {
-                        const int64_t w = 2 * bb + h;
-                        if (w < wn) Jt[(size_t)((b * 64 + l) * tile_words + 2 * dd + h)] = Jb[(size_t)(row * wn + w)];
-                    }
+        // words by block columns: bit j of word k of block b is the sign of
+        // row k's coupling in column 64 b + j
+        const int64_t nb = sk_blocks((int32_t)n);
+        std::vector<uint64_t> Jw((size_t)(nb * nb * 64), 0ull);
+        maybe_parallel(inner, (size_t)nb, [&](size_t kb) {
+            // (a tile of 64 rows at a time: its words of one block are contiguous)
+            for (int64_t b = 0; b < nb; ++b)
+                for (int64_t k = 64 * (int64_t)kb; k < std::min(n, 64 * (int64_t)kb + 64); ++k) {
+                    const int8_t* row = src + k * n + 64 * b;
+                    const int64_t m = std::min<int64_t>(64, n - 64 * b);   // (none in a block past n)
+                    uint64_t w = 0ull;
+                    for (int64_t q = 0; q < m; ++q) w |= (uint64_t)(row[q] < 0) << q;
+                    Jw[(size_t)sk_word((int32_t)nb, b, k)] = w;
                 }
-            }
-        hip_check(hipMemcpy(c->at<void>(off_Jt[j]), Jt.data(), Jt.size() * 4, hipMemcpyHostToDevice));
+        });
+        hip_check(hipMemcpy(c->at<void>(off_Jw[j]), Jw.data(), Jw.size() * 8, hipMemcpyHostToDevice));
     });
     for (int32_t i = 0; i < count; ++i)
         hip_check(hipMemcpy(c->at<void>(off_thr[(size_t)i]), thr[(size_t)i].data(), thr[(size_t)i].size() * 8,
@@ -1568,8 +1557,7 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
             SkChain S;
             std::memset(&S, 0, sizeof(S));
             S.J = c->at<int8_t>(off_J[(size_t)jslot[(size_t)i]]);
-            S.Jb = c->at<uint32_t>(off_Jb[(size_t)jslot[(size_t)i]]);
-            S.Jt = c->at<uint32_t>(off_Jt[(size_t)jslot[(size_t)i]]);
+            S.Jw = c->at<uint64_t>(off_Jw[(size_t)jslot[(size_t)i]]);
             S.state = c->at<uint32_t>(off_state[ch]);
             S.H = c->at<int32_t>(off_H[ch]);
             S.snap = c->at<uint32_t>(off_snap[ch]);
@@ -1622,7 +1610,6 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     hip_check(zero_i64(c->bond_d, (size_t)c->n_chains * c->K, nullptr));
     hip_check(zero_i64((long long*)c->acc_d, (size_t)c->n_chains, nullptr));
     hip_check(zero_i64((long long*)c->err_d, 1, nullptr));
-    c->sk_threads = sk_threads();
     c->sk_lds = sk_lds_bytes(c->sk_max_n);
     hip_check(sk_init(c->sk_d, c->n_chains, 256, nullptr));
     hip_check(sk_recompute(c->sks_d, count, c->sk_d, c->sk_max_n, 0, c->err_d, nullptr));
@@ -1849,11 +1836,13 @@ sg_status sg_sweep(sg_ctx* c, int64_t n_sweeps, void* stream)
             int64_t left = n_sweeps;
             while (left > 0) {
                 const int64_t to_check = c->period - (c->t_done % c->period);
-                const int64_t chunk = std::min(left, to_check);
+                // (a launch counts its blocks of 64 spins in 32 bits)
+                const int64_t chunk = std::min(std::min(left, to_check),
+                                               std::max<int64_t>(1, ((int64_t)1 << 30) / sk_blocks(c->sk_max_n)));
                 if (c->sk_real)
                     hip_check(skg_sweep(c->sk_d, c->n_chains, c->sk_lds, c->t_done, (int32_t)chunk, c->t_max, s));
                 else
-                    hip_check(sk_sweep(c->sk_d, c->n_chains, c->sk_threads, c->sk_lds, c->t_done, (int32_t)chunk,
+                    hip_check(sk_sweep(c->sk_d, c->n_chains, c->sk_max_n, c->sk_lds, c->t_done, (int32_t)chunk,
                                        c->t_max, c->err_d, s));
                 c->t_done += chunk;
                 left -= chunk;

@@ -42,11 +42,20 @@ struct VbmUnit {
     uint64_t seed;
 };
 
+// SK couplings as bits, by block columns of 64 spins: bit j of word k of block b
+// is 1 where the coupling of spins k and 64 b + j is -1 (0 on the diagonal and
+// past n).  The number of blocks is even, and a spin's words of blocks 2 p and 2 p
+// + 1 are neighbours (one 16-byte load).
+__host__ __device__ __forceinline__ int32_t sk_blocks(int32_t n) { return 2 * ((n + 127) >> 7); }
+__host__ __device__ __forceinline__ int64_t sk_word(int32_t n_blocks, int64_t b, int64_t k)
+{
+    return ((b >> 1) * 64 * n_blocks + k) * 2 + (b & 1);
+}
+
 // One SK chain (a replica of an instance).
 struct SkChain {
     const int8_t* J;           // [n][n]
-    const uint32_t* Jb;        // [n][words_n] bit-packed rows, bit 1 = coupling -1
-    const uint32_t* Jt;        // [n_blocks][64][sk_tile_words()] the decider's tiles, contiguous
+    const uint64_t* Jw;        // coupling words, see sk_word
     uint32_t* state;           // [words_n] position-order bits (1 = spin -1)
     int32_t* H;                // [n] local fields between launches
     uint32_t* snap;            // [K][words_n]
@@ -62,7 +71,7 @@ struct SkChain {
     const uint32_t* given;     // position-order bits when GIVEN
     int32_t sample;            // index of the instance in the context
     float xslope;              // 2 beta / sqrt(N): thr[x] ~ 2^32 exp(-xslope x)
-    // real couplings (sg_skg.hip): J, J_b, J_t, H, thr unused
+    // real couplings (sg_skg.hip): J, Jw, H, thr unused
     const float* Jf;           // [n][n]
     double* Hd;                // [n] local fields between launches
     double beta;               // 1 / T
@@ -122,14 +131,12 @@ hipError_t sk_recompute(const SkSample* samples, int n_samples, const SkChain* c
                         int max_n, int check, int* err_flag, hipStream_t s);
 hipError_t sk_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n,
                    int max_nch, int k_done, int k_cap, long long* out, hipStream_t s);
-hipError_t sk_sweep(const SkChain* chains, int n_chains, int threads, size_t lds_bytes, int64_t t0,
+hipError_t sk_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0,
                     int32_t n_sweeps, int64_t t_max, int* err_flag, hipStream_t s);
 size_t sk_lds_bytes(int32_t n);
-int sk_threads();
-// Decider tiles: words per row of a 64-spin block (its own columns, then those
-// of the sk_window() blocks before it, two words each).
-int sk_tile_words();
-int sk_window();
+// Bytes that the sweep kernel may read (and not use) past a matrix Jw: readable
+// memory of the context follows each.
+constexpr size_t kSkOverread = (size_t)12 * 48 * 1024;
 
 // SK with real couplings (sg_skg.hip): sweeps, direct field recomputation
 // (with `check`, error bit 0 when a field drifted by more than 1e-9 (1 + |h|))

@@ -1,32 +1,51 @@
 // Sherrington-Kirkpatrick Metropolis sweeps on gfx950.
 //
 // The SK sweep visits i = 0..N-1 in a fixed order (SI, SK section), so a chain
-// is sequential.  One workgroup runs one chain with its integer local fields
-// H_i = sum_j J_ij s_j resident in LDS, split into three roles that form a
-// pipeline over blocks of 64 consecutive spins (block g of the launch is block
-// b = g mod NB of sweep t0 + g / NB):
+// is sequential.  One workgroup runs one chain, as a pipeline of three roles
+// over blocks of 64 consecutive spins (block g of the launch is block b = g mod
+// NB of sweep t0 + g / NB).  The couplings are bit-packed by block columns:
+// word k of block b holds the signs of J between spin k and the 64 spins of
+// block b (bit 1 = -1), so a field's change from the flips of one block is a
+// masked popcount of one 64-bit word.  The number of blocks NB is even: spins past
+// N are there to fill it and never flip.
 //
-//  * prep wavefront (ahead of the decider by up to kRing blocks): draws the
-//    acceptance uniform r of every position of the block (two Philox streams)
-//    and turns it into xmax = max{x : r < thr[x]}, so that a spin with
-//    x = s_i H_i flips iff x <= xmax; it also fetches, from the bit-packed
-//    couplings, lane i's own row 64 b + i restricted to the columns of block b
-//    and of the kWin blocks before it (J is symmetric: these are the
-//    couplings of those blocks' spins to spin i).
-//  * decider wavefront: lane i owns spin 64 b + i.  It corrects the block's
-//    fields for the flips of the previous kWin blocks (masked popcounts of
-//    their flip masks against its own row), then decides the block in rounds:
-//    a lane whose decision cannot change whichever way the undecided lanes
-//    before it go (each moves its field by at most 2) is decided now, the
-//    first undecided lane always is, and the flips decided in a round change
-//    the fields of the later lanes by masked popcounts against the own-block
-//    row.  The result is exactly the plain sequential sweep.  The block's
-//    flips are published to a ring buffer.
-//  * updater wavefronts: apply each published block's flips to all other fields
-//    (H_k += 2 s_j J_jk, rows read bit-packed, a few fields per lane), up to
-//    kWin blocks behind the decider; they skip the flipped block (patched in
-//    the decider) and the next kWin blocks (corrected by the decider), except
-//    for blocks decided after the end of the launch.
+//  * prep wavefronts (three, ahead of the decider by up to kRing blocks): draw
+//    the acceptance uniform r of every position of a block (two Philox streams)
+//    and turn it into xmax = max{x : r < thr[x]}, so that a spin with x = s_i
+//    H_i flips iff x <= xmax; they also fetch the words of the block's spins
+//    for its own columns and for those of the kWin blocks before it.
+//  * decider wavefront: lane i owns spin 64 b + i.  It takes the block's fields
+//    as published, adds the flips of the blocks since (masked popcounts; for even
+//    g the kWin - 1 blocks before, for odd g kWin), and finds the block's flips F as the fixpoint of
+//    F = {i : x_i + (change by the flips of F before i) <= xmax_i}.  Lane i's
+//    condition depends on lanes before it only, so the fixpoint is unique and is
+//    the sequential result; each iteration settles at least one more lane and
+//    usually two or three settle all of them (a flip moves x by 2, and few lanes
+//    are that close to their bound).  The flips go to a ring buffer.
+//  * updater wavefronts (twelve): wavefront w keeps the fields of blocks w, w +
+//    12, ... in registers, one field per lane and block, and applies the flips
+//    of every pair of blocks to all of them.  The words it needs do not depend on
+//    the decisions, so they stream from memory ahead of use, N / 8 bytes per spin
+//    and sweep, a spin's words of two blocks in one 16-byte load.  The owners of
+//    two coming blocks publish their fields for the decider.
+//
+// A field is kept as H0 + 2 P - 4 a: P counts the flips applied so far (the
+// same for every field) and a the flips that lower it, so that a block costs
+// four VALU instructions per field (two three-input logic operations, two
+// accumulating popcounts).  A spin's own flips go through the diagonal, which the
+// words hold as J_ii = +1: they add 2 s' each, s(now) - s(start) in all, so the
+// tracked field is H + s when it starts as H + s.
+//
+// What bounds it: up to about N = 4096 the decider's own instruction chain (0.42
+// to 0.46 us a block: LDS reads, the corrections, 1.5 iterations), above it the
+// rate at which one CU takes in words, about 90 GB/s (0.54 us a block at N = 6001,
+// 1.42 at 16384).  With 8-byte loads the loads themselves were the bound (N = 4096:
+// 0.55 us), and applying flips by reading the coupling rows of the flipped spins,
+// as an earlier version did, cost a memory latency per block after each decision
+// (1.45 us at N = 512 to 4096, 1.86 at 6001).  Sweeps of 64 x 2 chains, N = 4096:
+// 27.2 us, before 97; one chain pair, N = 512: 3.7 us, before 11.4.  A window of 5
+// blocks costs the decider more than the slack gives (N = 4096: 31.1 us).  The
+// replicas of a sample run on one XCD, so that they share its L2.
 //
 // Every `period` sweeps the fields are recomputed exactly as H = J S with int8
 // MFMA (v_mfma_i32_16x16x64_i8, int32 accumulation) and compared with the
@@ -41,33 +60,34 @@
 namespace sg {
 namespace {
 
+#define SG_L __attribute__((address_space(3)))
+
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-// Pipeline depth (compile-time tuning parameters).
-#ifndef SG_SK_RING
-#define SG_SK_RING 4
-#endif
 #ifndef SG_SK_WIN
-#define SG_SK_WIN 1
+#define SG_SK_WIN 3
 #endif
-constexpr int kRing = SG_SK_RING;   // blocks in flight between the roles
-constexpr int kWin = SG_SK_WIN;     // previous blocks the decider corrects for itself
-constexpr int kTileWords = (2 + 2 * kWin + 3) & ~3;   // per lane: own-block row, kWin previous rows (16-byte multiple)
+#ifndef SG_SK_RING
+#define SG_SK_RING 6
+#endif
+constexpr int kWin = SG_SK_WIN;     // previous blocks whose flips the decider adds itself (odd)
+constexpr int kRing = SG_SK_RING;   // blocks the prep wavefronts are ahead at most
+constexpr int kHRing = 8;           // published fields of coming blocks
+constexpr int kFRing = 64;          // flips of past blocks
+constexpr int kEmpty = 4;           // blocks of no flips after the last one
 constexpr int kThrCache = 512;      // threshold entries cached in LDS
-// Updater wavefronts: a lane owns 8 fields per pass, so 14 wavefronts (a
-// workgroup of 1024 threads) apply a block to up to 7168 fields in one pass.
-// Measured, us per sweep with 8 / 12 / 14: N = 4096 100.6 / 100.8 / 100.9
-// (one pass each), N = 5944 203 / 169 / 169, N = 8192 364 / 326 / 314.
-#ifndef SG_SK_UPD
-#define SG_SK_UPD 14
-#endif
-#ifndef SG_SK_SLEEP
-#define SG_SK_SLEEP 1   // s_sleep units (64 clocks) between polls of a wait
-#endif
-#ifndef SG_SK_UPB
-#define SG_SK_UPB 1
-#endif
+constexpr int kPrepWaves = 3;
+constexpr int kUpdWaves = 12;
+constexpr int kSkThreads = 64 * (1 + kPrepWaves + kUpdWaves);
+constexpr int kSpinLimit = 1 << 22; // bounded waits: a stuck pipeline aborts
+static_assert(kWin % 2 == 1 && kWin + 3 <= kHRing, "published fields are read before their slots are used again");
+// An updater's blocks are at most 2 kUpdWaves - 1 apart, and the decider waits for
+// the fields of each, published once the flips kWin + 1 blocks before are applied:
+// no updater is further behind than that.
+static_assert(kFRing >= kWin + 1 + 2 * kUpdWaves + kEmpty, "flips outlive the slowest updater");
+static_assert(kSkOverread >= (size_t)kUpdWaves * 48 * 1024, "slots of the largest variant");
 #ifndef SG_SK_PROF
 #define SG_SK_PROF 0    // 1: per-role cycle counters, printed by workgroups 0..2 after a launch
 #endif
@@ -78,94 +98,81 @@ constexpr int kThrCache = 512;      // threshold entries cached in LDS
 #define SK_CLK(v)
 #define SK_ACC(acc, a, b)
 #endif
-constexpr int kUpdWaves = SG_SK_UPD;   // updater wavefronts
-constexpr int kUpdBlocks = SG_SK_UPB;  // decided blocks an updater pass takes at most
-static_assert(kUpdBlocks >= 1 && kUpdBlocks <= kRing, "updater pass width");
-constexpr int kSkThreads = 64 * (2 + kUpdWaves);
-constexpr int kSpinLimit = 1 << 22; // bounded waits: a stuck pipeline aborts
-static_assert(kRing >= kWin + 1, "flip batches must outlive the correction window");
 
+// Previous blocks the decider corrects for in a chain of NB blocks: fewer than NB,
+// so that a block never corrects for its own earlier visit (J_ii is not in Jw).
+__device__ __forceinline__ int32_t sk_window(int32_t NB) { return min(kWin, NB - 1); }
+
+// LDS byte offsets from the start of the workgroup's dynamic array.
 struct SkLds {
-    int32_t* H;                 // [n]
-    uint32_t* bits;             // [wn + 2]
-    unsigned long long* thr;    // [kThrCache]
-    int32_t* xm;                // [kRing][64]
-    uint32_t* tile;             // [kRing][64][kTileWords]
-    int32_t* flips;             // [kRing][64]: local row | (new spin -1) << 31
-    int32_t* nflip;             // [kRing]: flips | flips to +1 << 8
-    int32_t* sync;              // decided, prepared, abort, progress[kUpdWaves]
-    uint4* pr;                  // [64] Philox blocks of the prep's current 4 spin blocks
-    unsigned long long* spr;    // [512] byte-spread table of the updaters
+    uint32_t h0;      // int32 [64 NB]: field constants H0 (see above)
+    uint32_t bits;    // uint64 [NB]: spins, bit 1 = -1
+    uint32_t thr;     // uint64 [kThrCache]
+    uint32_t xm;      // int32 [kRing][64]: xmax + 1 of a block's spins
+    uint32_t row;     // uint64 [kRing][kWin + 1][64]: their words of blocks b, b - 1, ...
+    uint32_t hr;      // int32 [kHRing][64]: published fields
+    uint32_t flip;    // v4u [kFRing]: flips, spins after the block (two words each)
+    uint32_t seqp;    // int32 [kRing]: 1 + block whose xm and row are in the slot
+    uint32_t seqh;    // int32 [kHRing]: 1 + block whose fields are in the slot
+    uint32_t sync;    // int32 [2]: blocks decided, abort
+    uint32_t pr;      // uint4 [kPrepWaves][64]: Philox blocks
+    uint32_t total;
 };
 
-__device__ __forceinline__ SkLds sk_carve(uint8_t* base, int32_t n, int32_t wn)
+__host__ __device__ __forceinline__ SkLds sk_layout(int32_t n)
 {
+    const uint32_t nb = (uint32_t)sk_blocks(n);
     SkLds L;
-    size_t off = 0;
-    auto take = [&](size_t bytes) {
-        uint8_t* p = base + off;
-        off += (bytes + 15) & ~(size_t)15;
+    uint32_t off = 0;
+    auto take = [&](uint32_t bytes) {
+        const uint32_t p = off;
+        off += (bytes + 15u) & ~15u;
         return p;
     };
-    L.H = (int32_t*)take((size_t)n * 4);
-    L.bits = (uint32_t*)take((size_t)(wn + 2) * 4);
-    L.thr = (unsigned long long*)take((size_t)kThrCache * 8);
-    L.xm = (int32_t*)take((size_t)kRing * 64 * 4);
-    L.tile = (uint32_t*)take((size_t)kRing * 64 * kTileWords * 4);
-    L.flips = (int32_t*)take((size_t)kRing * 64 * 4);
-    L.nflip = (int32_t*)take((size_t)kRing * 4);
-    L.sync = (int32_t*)take((size_t)(3 + kUpdWaves) * 4);
-    L.pr = (uint4*)take(64 * 16);
-    L.spr = (unsigned long long*)take(512 * 8);
+    L.h0 = take(nb * 256u);
+    L.bits = take(nb * 8u);
+    L.thr = take(kThrCache * 8);
+    L.xm = take(kRing * 256);
+    L.row = take(kRing * (kWin + 1) * 512);
+    L.hr = take(kHRing * 256);
+    L.flip = take(kFRing * 16);
+    L.seqp = take(kRing * 4);
+    L.seqh = take(kHRing * 4);
+    L.sync = take(8);
+    L.pr = take(kPrepWaves * 64 * 16);
+    L.total = off;
     return L;
 }
 
-enum { kDecided = 0, kPrepared = 1, kAbort = 2, kProg = 3 };
-
-__device__ __forceinline__ int ld_acq(int32_t* p)
+// LDS accesses of the pipeline.  The LDS executes one wavefront's operations in
+// order, so data written before a flag is there once the flag is seen, and data
+// read after a flag is no older than it: the accesses only have to stay in program
+// order, which volatile accesses do, with no wait between them.
+template <class T>
+__device__ __forceinline__ T lds_get(uint32_t off)
 {
-    return __hip_atomic_load(p, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return *(const volatile SG_L T*)(size_t)off;
 }
-
-__device__ __forceinline__ void st_rel(int32_t* p, int32_t v)
+template <class T>
+__device__ __forceinline__ void lds_put(uint32_t off, T v)
 {
-    __hip_atomic_store(p, v, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+    *(volatile SG_L T*)(size_t)off = v;
 }
 
 // One poll of a wait that has not been met yet: true when the wait must end
 // without its condition (abort raised, or this wait was the one that ran out
 // of polls: after kSpinLimit polls the pipeline is declared stuck, the abort
-// flag releases every other wait and the context's error flag reports it).
-__device__ __forceinline__ bool wait_giveup(const SkLds& L, int& spins, int* err)
+// flag releases every other wait and is reported at the end of the kernel: a
+// global atomic here would count as a memory operation that may be in flight
+// after every wait, and make each wait for the streamed words a wait for all).
+__device__ __forceinline__ bool wait_giveup(uint32_t sync, int& spins)
 {
-    if (ld_acq(&L.sync[kAbort])) return true;
-    if (SG_SK_SLEEP > 0) __builtin_amdgcn_s_sleep(SG_SK_SLEEP);
+    if (__builtin_amdgcn_readfirstlane(lds_get<int32_t>(sync + 4))) return true;
     if (++spins > kSpinLimit) {
-        st_rel(&L.sync[kAbort], 1);
-        atomicOr(err, 2);
+        lds_put<int32_t>(sync + 4, 1);
         return true;
     }
     return false;
-}
-
-// Waits (whole wavefront) until *p >= target.
-__device__ __forceinline__ void wait_ge(const SkLds& L, int32_t idx, int32_t target, int* err)
-{
-    int spins = 0;
-    while (ld_acq(&L.sync[idx]) < target) {
-        if (wait_giveup(L, spins, err)) return;
-    }
-}
-
-// Waits (whole wavefront) until every updater wavefront has applied the
-// first `target` blocks of the launch (lane w reads wavefront w's progress).
-__device__ __forceinline__ void wait_applied(const SkLds& L, int32_t target, int* err)
-{
-    const int lane = threadIdx.x & 63;
-    int spins = 0;
-    while (__builtin_amdgcn_ballot_w64(lane < kUpdWaves && ld_acq(&L.sync[kProg + lane]) < target) != 0ull) {
-        if (wait_giveup(L, spins, err)) return;
-    }
 }
 
 __device__ __forceinline__ void wave_sync_sk()
@@ -175,437 +182,439 @@ __device__ __forceinline__ void wave_sync_sk()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-__device__ __forceinline__ void wave_release()
+// The chain a workgroup runs: workgroups go to the 8 XCDs in turn, and the
+// chains of an XCD are consecutive, so that the replicas of a sample share an L2.
+__device__ __forceinline__ int32_t sk_chain_of(int32_t bid, int32_t n_chains)
 {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-    __builtin_amdgcn_wave_barrier();
+    const int32_t x = bid & 7, i = bid >> 3, q = n_chains >> 3, r = n_chains & 7;
+    return x * q + min(x, r) + i;
 }
 
-__device__ __forceinline__ unsigned long long thr_at(const SkLds& L, const SkChain* ch,
-                                                      int32_t cached, int32_t x)
+// popcount(v) + acc in the one instruction that does both (left to itself the
+// compiler counts from 0 and adds afterwards)
+__device__ __forceinline__ uint32_t popc_add(uint32_t v, uint32_t acc)
 {
-    if (x >= ch->thr_len) return 0ull;
-    return x < cached ? L.thr[x] : gl(ch->thr)[x];
+    uint32_t r;
+    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(r) : "v"(v), "v"(acc));
+    return r;
 }
 
-__global__ void __launch_bounds__(kSkThreads) sk_sweep_kernel(const SkChain* __restrict__ chains,
-                                                              int64_t t0, int32_t nsw,
-                                                              int64_t t_max, int* err)
+// ---------------- prep ----------------
+__device__ __forceinline__ void sk_prep(const SkChain* ch, const SkLds& L, uint32_t lds, int pw, int64_t t0,
+                                        int32_t total)
+{
+    const int lane = threadIdx.x & 63;
+    const int32_t NB = sk_blocks(ch->n), n = ch->n;
+    const int32_t cached = min(ch->thr_len, kThrCache), thr_len = ch->thr_len;
+    const SG_G uint64_t* __restrict__ gthr = gl(ch->thr);
+    const SG_G v2u* __restrict__ Jw = (const SG_G v2u*)gl(ch->Jw);
+    const uint32_t thr_o = lds + L.thr;
+    auto thr_at = [&](int32_t x) -> unsigned long long {
+        return x >= thr_len ? 0ull : x < cached ? *(const SG_L unsigned long long*)(size_t)(thr_o + 8u * (uint32_t)x) : gthr[x];
+    };
+    v2u tw[kWin + 1];
+    auto load_rows = [&](int32_t bq) {
+        int32_t c = bq;
+#pragma unroll
+        for (int d = 0; d <= kWin; ++d) {
+            tw[d] = Jw[(((int64_t)(c >> 1) * NB + bq) * 64 + lane) * 2 + (c & 1)];
+            c = c == 0 ? NB - 1 : c - 1;
+        }
+    };
+    // block g = (sweep s, index b), advanced by kPrepWaves blocks a turn
+    int32_t b = pw, s = 0, slot = pw;
+    auto wrap = [&](int32_t& bq, int32_t& sq) {
+        while (bq >= NB) {
+            bq -= NB;
+            ++sq;
+        }
+    };
+    wrap(b, s);
+    if (pw < total) load_rows(b);
+    for (int32_t g = pw, it = 0; g < total; g += kPrepWaves, ++it) {
+        if ((it & 3) == 0) {
+            // one pass of the 64 lanes draws both streams' blocks of this
+            // wavefront's next four spin blocks: lane 16 j + 8 h + q holds stream
+            // h (high / low half-words) of 8-position group q of block g + 3 j
+            const int j = lane >> 4;
+            int32_t bq = b + kPrepWaves * j, sq = s;
+            wrap(bq, sq);
+            const uint32_t dom = (lane >> 3) & 1 ? kDomSweepLo : kDomSweepHi;
+            const U4 A = philox_stream(ch->seed, (uint32_t)(bq * 8 + (lane & 7)), (uint32_t)(t0 + sq), dom, ch->rep,
+                                       ch->inst);
+            wave_sync_sk();
+            *(SG_L v4u*)(size_t)(lds + L.pr + (uint32_t)(pw * 64 + lane) * 16u) = v4u{A.x, A.y, A.z, A.w};
+            wave_sync_sk();
+        }
+        const uint32_t po = lds + L.pr + (uint32_t)(pw * 64 + (it & 3) * 16 + (lane >> 3)) * 16u + (uint32_t)(lane & 7) * 2u;
+        const uint32_t r = ((uint32_t) * (const SG_L uint16_t*)(size_t)po << 16) |
+                           (uint32_t) * (const SG_L uint16_t*)(size_t)(po + 128u);
+        // starting guess from the logarithm, then exact fix-up on the table
+        int32_t x0;
+        const float slope = ch->xslope;
+        if (slope <= 0.0f) {
+            x0 = thr_len - 1;
+        } else {
+            const float lv = 22.18070977791825f - __logf((float)r + 1.0f);
+            const float xf = lv / slope;
+            x0 = xf >= (float)(thr_len - 1) ? thr_len - 1 : (xf <= 0.0f ? 0 : (int32_t)xf);
+        }
+        // (entries cached in LDS first; a long table's tail is read from
+        // HBM on a path of its own, so that the common path holds no
+        // wait for this wavefront's outstanding loads)
+        if (x0 < cached) {
+            auto thr_c = [&](int32_t x) { return *(const SG_L unsigned long long*)(size_t)(thr_o + 8u * (uint32_t)x); };
+            while (x0 > 0 && !((unsigned long long)r < thr_c(x0))) --x0;
+            while (x0 + 1 < cached && (unsigned long long)r < thr_c(x0 + 1)) ++x0;
+        }
+        if (x0 + 1 >= cached && cached < thr_len) {
+            while (x0 > 0 && !((unsigned long long)r < thr_at(x0))) --x0;
+            while (x0 + 1 < thr_len && (unsigned long long)r < thr_at(x0 + 1)) ++x0;
+        }
+        // a lane past the last spin never flips
+        if ((b << 6) + lane >= n) x0 = -(1 << 29);
+        if (g >= kRing) {
+            int spins = 0;
+            while (__builtin_amdgcn_readfirstlane(lds_get<int32_t>(lds + L.sync)) < g - kRing + 1) {
+                if (wait_giveup(lds + L.sync, spins)) break;
+                __builtin_amdgcn_s_sleep(1);
+            }
+        }
+        // (one more: the tracked field is H + s, so s times it is x + 1)
+        lds_put<int32_t>(lds + L.xm + (uint32_t)(slot * 64 + lane) * 4u, x0 + 1);
+#pragma unroll
+        for (int d = 0; d <= kWin; ++d)
+            lds_put<v2u>(lds + L.row + (uint32_t)((slot * (kWin + 1) + d) * 64 + lane) * 8u, tw[d]);
+        if (lane == 0) lds_put<int32_t>(lds + L.seqp + 4u * (uint32_t)slot, g + 1);
+        slot += kPrepWaves;
+        if (slot >= kRing) slot -= kRing;
+        b += kPrepWaves;
+        wrap(b, s);
+        if (g + kPrepWaves < total) load_rows(b);
+    }
+}
+
+// ---------------- decider ----------------
+struct SkIn {
+    int32_t xm, h, sp, sh;
+    v2u row[kWin + 1];
+    v2u sb;
+};
+
+__device__ __forceinline__ void sk_decide(const SkChain* ch, const SkLds& L, uint32_t lds, int64_t t0, int32_t total,
+                                          int64_t t_max)
+{
+    // the sequential critical path: issue ahead of the wavefronts that share
+    // its SIMD
+    __builtin_amdgcn_s_setprio(3);
+    const int lane = threadIdx.x & 63;
+    const int32_t NB = sk_blocks(ch->n), wn = ch->words_n;
+    const int32_t DW = sk_window(NB);
+    const unsigned long long lt = (1ull << lane) - 1ull;   // lanes before this one
+    const uint32_t ltl = (uint32_t)lt, lth = (uint32_t)(lt >> 32);
+    uint32_t acc = 0;
+    // flips and new spins of the last kWin blocks (d = 0: the block before)
+    unsigned long long pF[kWin], pN[kWin];
+#pragma unroll
+    for (int d = 0; d < kWin; ++d) pF[d] = pN[d] = 0ull;
+#if SG_SK_PROF
+    unsigned long long tp[4] = {0, 0, 0, 0};   // waiting for inputs, corrections, iterations, their number
+#endif
+    auto fetch = [&](SkIn& in, int32_t slot, int32_t hslot, int32_t b) __attribute__((always_inline)) {
+        in.sp = lds_get<int32_t>(lds + L.seqp + 4u * (uint32_t)slot);
+        in.sh = lds_get<int32_t>(lds + L.seqh + 4u * (uint32_t)hslot);
+        in.h = lds_get<int32_t>(lds + L.hr + (uint32_t)(hslot * 64 + lane) * 4u);
+        in.xm = lds_get<int32_t>(lds + L.xm + (uint32_t)(slot * 64 + lane) * 4u);
+#pragma unroll
+        for (int d = 0; d <= kWin; ++d)
+            in.row[d] = lds_get<v2u>(lds + L.row + (uint32_t)((slot * (kWin + 1) + d) * 64 + lane) * 8u);
+        in.sb = lds_get<v2u>(lds + L.bits + 8u * (uint32_t)b);
+    };
+    int32_t g = 0, b = 0, s = 0, slot = 0;
+    SkIn A, B;
+    fetch(A, 0, 0, 0);
+    // one block: `in` holds (at least an attempt at) its inputs, `nx` gets the next block's
+    auto step = [&](SkIn& in, SkIn& nx, auto odd) __attribute__((always_inline)) {
+        SK_CLK(c0);
+        int spins = 0;
+        while (__builtin_amdgcn_readfirstlane((in.sp ^ (g + 1)) | (in.sh ^ (g + 1))) != 0) {
+            if (wait_giveup(lds + L.sync, spins)) break;
+            fetch(in, slot, g & (kHRing - 1), b);
+        }
+        SK_CLK(c1);
+        SK_ACC(tp[0], c0, c1);
+        const unsigned long long SB = ((unsigned long long)(uint32_t)__builtin_amdgcn_readfirstlane((int)in.sb.y) << 32) |
+                                      (uint32_t)__builtin_amdgcn_readfirstlane((int)in.sb.x);
+        const int32_t nslot = slot + 1 == kRing ? 0 : slot + 1, nb = b + 1 == NB ? 0 : b + 1;
+        fetch(nx, nslot, (g + 1) & (kHRing - 1), nb);
+        // the flips of the blocks since the fields were published
+        uint32_t low = 0;
+        int32_t pc = 0;
+#pragma unroll
+        for (int d = odd ? kWin : kWin - 1; d >= 1; --d) {
+            low = popc_add((in.row[d].x ^ (uint32_t)pN[d - 1]) & (uint32_t)pF[d - 1], low);
+            low = popc_add((in.row[d].y ^ (uint32_t)(pN[d - 1] >> 32)) & (uint32_t)(pF[d - 1] >> 32), low);
+            pc += __popcll(pF[d - 1]);
+        }
+        const int32_t h = in.h + 2 * pc - 4 * (int32_t)low;
+        // x = s h; a flip of lane j < lane raises it by 2 where spins and
+        // coupling XOR to 1, else lowers it by 2: lane flips iff
+        // 2 (2 up - all) <= xmax - x, up and all counting flips before it
+        const int32_t neg = __builtin_amdgcn_inverse_ballot_w64(SB) ? -1 : 0;
+        const int32_t m2 = (in.xm - ((h ^ neg) - neg)) >> 1;
+        const uint32_t ql = ((uint32_t)SB ^ in.row[0].x ^ (uint32_t)neg) & ltl;
+        const uint32_t qh = ((uint32_t)(SB >> 32) ^ in.row[0].y ^ (uint32_t)neg) & lth;
+        SK_CLK(c2);
+        SK_ACC(tp[1], c1, c2);
+        unsigned long long F = __builtin_amdgcn_ballot_w64(m2 >= 0), Fo;
+        do {
+            Fo = F;
+            const uint32_t up = popc_add((uint32_t)(F >> 32) & qh, popc_add((uint32_t)F & ql, 0u));
+            const int32_t lim = (int32_t)__builtin_amdgcn_mbcnt_hi((uint32_t)(F >> 32),
+                                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)F, (uint32_t)m2));
+            F = __builtin_amdgcn_ballot_w64((int32_t)(2u * up) <= lim);
+#if SG_SK_PROF
+            ++tp[3];
+#endif
+        } while (F != Fo);
+        SK_CLK(c3);
+        SK_ACC(tp[2], c2, c3);
+        const unsigned long long SN = SB ^ F;
+        if (lane == 0) {
+            lds_put<v4u>(lds + L.flip + 16u * ((uint32_t)g & (kFRing - 1)),
+                         v4u{(uint32_t)F, (uint32_t)(F >> 32), (uint32_t)SN, (uint32_t)(SN >> 32)});
+            lds_put<v2u>(lds + L.bits + 8u * (uint32_t)b, v2u{(uint32_t)SN, (uint32_t)(SN >> 32)});
+            lds_put<int32_t>(lds + L.sync, g + 1);
+        }
+        acc += (uint32_t)__popcll(F);
+#pragma unroll
+        for (int d = kWin - 1; d > 0; --d) {
+            pF[d] = d < (odd ? DW - 1 : DW) ? pF[d - 1] : 0ull;
+            pN[d] = pN[d - 1];
+        }
+        pF[0] = !odd || DW > 1 ? F : 0ull;
+        pN[0] = SN;
+        ++g;
+        slot = nslot;
+        b = nb;
+        if (b == 0) {
+            ++s;
+            const int64_t tn = t0 + s;
+            if (tn <= t_max && (tn & (tn - 1)) == 0) {
+                const int k = 1 + (63 - __clzll((unsigned long long)tn));
+                for (int32_t w = lane; w < wn; w += 64)
+                    gl(ch->snap)[(int64_t)k * wn + w] = lds_get<uint32_t>(lds + L.bits + 4u * (uint32_t)w);
+            }
+        }
+    };
+    while (g < total) {   // (total is even)
+        step(A, B, std::false_type{});
+        step(B, A, std::true_type{});
+    }
+    if (lane == 0) {
+        for (int e = 0; e < kEmpty; ++e)
+            lds_put<v4u>(lds + L.flip + 16u * ((uint32_t)(total + e) & (kFRing - 1)), v4u{0u, 0u, 0u, 0u});
+        lds_put<int32_t>(lds + L.sync, total + kEmpty);
+    }
+    for (int32_t w = lane; w < wn; w += 64) gl(ch->state)[w] = lds_get<uint32_t>(lds + L.bits + 4u * (uint32_t)w);
+    if (lane == 0 && acc) atomicAdd(ch->accepted, (unsigned long long)acc);
+#if SG_SK_PROF
+    if (lane == 0 && blockIdx.x < 3)
+        printf("[sk-prof] wg %d decider blocks %d cycles: wait %llu correct %llu iterate %llu; iterations %llu\n",
+               (int)blockIdx.x, total, tp[0], tp[1], tp[2], tp[3]);
+#endif
+}
+
+// ---------------- updaters ----------------
+// Wavefront uw holds the fields of blocks uw + kUpdWaves j, j < NG GS, and takes
+// them in NG groups of GS; the words of the next D groups are in flight.  (For up
+// to 8 fields per lane a group is the whole pair of blocks and D pairs are in
+// flight; for more, the groups of one pair take turns in D buffers.)  Slots past
+// the last block read the memory after the pair's words (past the last pair, up
+// to kSkOverread bytes of the context's memory); what they hold is not used.
+template <int NG, int GS, int D>
+__device__ __forceinline__ void sk_update(const SkChain* ch, const SkLds& L, uint32_t lds, int uw, int32_t total)
+{
+    static_assert(NG == 1 || NG % D == 0, "buffers line up with the groups");
+    static_assert(NG > 1 || 2 * (D - 1) <= kEmpty, "a last round of D pairs is filled up");
+    const int lane = threadIdx.x & 63;
+    const int32_t n = ch->n, NB = sk_blocks(n);
+    const int32_t ahead = sk_window(NB) + 1;   // fields published after pair (k, k + 1): blocks k + ahead and the next
+    if (uw >= NB) return;
+    // words of the pair loaded next (index lb)
+    const uint64_t Jw = (uint64_t)ch->Jw + (uint64_t)uw * 1024;
+    uint64_t src = Jw;
+    int32_t lb = 0;
+    uint32_t a[NG * GS];
+#pragma unroll
+    for (int j = 0; j < NG * GS; ++j) a[j] = 0u;
+    uint32_t pcs = 0;
+    v4u buf[D][GS];
+    auto load_next = [&](v4u* dst, int grp) __attribute__((always_inline)) {
+        // (scalar bases and one lane offset, made opaque here so that the loads
+        // take them as they are: no address arithmetic per lane)
+        uint64_t base = src + (uint64_t)(grp * GS * kUpdWaves * 1024);
+        uint32_t lofs = 16u * (uint32_t)lane;
+        asm("" : "+s"(base), "+v"(lofs));
+#pragma unroll
+        for (int i = 0; i < GS; ++i)
+            dst[i] = *(const SG_G v4u*)((const SG_G char*)(base + (uint64_t)(i * kUpdWaves * 1024)) + lofs);
+        __builtin_amdgcn_sched_barrier(0);   // (in order: a wait counts the loads after the ones it waits for)
+        if (grp == NG - 1) {
+            src += (size_t)NB * 1024;
+            if (++lb == NB / 2) {
+                lb = 0;
+                src = Jw;
+            }
+        }
+    };
+    // first block of the pair being applied: k of the launch; block to publish
+    // after it: index pb (owner pm, slot pj)
+    int32_t k = 0;
+    int32_t pb = ahead % NB, pm = pb % kUpdWaves, pj = pb / kUpdWaves;
+    auto next = [&](int32_t& x, int32_t& m, int32_t& j) __attribute__((always_inline)) {
+        ++x;
+        ++m;
+        if (m == kUpdWaves) {
+            m = 0;
+            ++j;
+        }
+        if (x == NB) x = m = j = 0;
+    };
+#pragma unroll
+    for (int q = 0; q < D; ++q) load_next(buf[q], q % NG);
+#if SG_SK_PROF
+    unsigned long long tu[2] = {0, 0};   // cycles waiting for decided blocks
+#endif
+    // flips of the pair's blocks (x, y) and spins after them (z, w), the same
+    // in every lane
+    v4u f0, f1;
+    auto take = [&]() __attribute__((always_inline)) {
+        SK_CLK(u0);
+        int spins = 0;
+        const uint32_t fo = lds + L.flip + 16u * ((uint32_t)k & (kFRing - 1));
+#pragma unroll 1
+        for (;;) {
+            const int32_t dec = lds_get<int32_t>(lds + L.sync);
+            f0 = lds_get<v4u>(fo);
+            f1 = lds_get<v4u>(fo + 16u);
+            if (__builtin_amdgcn_readfirstlane(dec) > k + 1) break;
+            if (wait_giveup(lds + L.sync, spins)) break;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        SK_CLK(u1);
+        SK_ACC(tu[0], u0, u1);
+    };
+    auto apply = [&](const v4u* w, int grp) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < GS; ++i) {
+            uint32_t c = a[grp * GS + i];
+            c = popc_add(f0.x & (w[i].x ^ f0.z), c);
+            c = popc_add(f0.y & (w[i].y ^ f0.w), c);
+            c = popc_add(f1.x & (w[i].z ^ f1.z), c);
+            a[grp * GS + i] = popc_add(f1.y & (w[i].w ^ f1.w), c);
+        }
+    };
+    auto field = [&](int32_t blk, uint32_t cnt) {
+        return lds_get<int32_t>(lds + L.h0 + (uint32_t)(blk * 64 + lane) * 4u) + (int32_t)(2u * pcs) - (int32_t)(4u * cnt);
+    };
+    // after the last group of the pair
+    auto finish = [&]() __attribute__((always_inline)) {
+        pcs = popc_add(f0.x, popc_add(f0.y, popc_add(f1.x, popc_add(f1.y, pcs))));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int32_t g = k + ahead + h;
+            if (pm == uw && g < total) {
+                uint32_t c = a[0];
+#pragma unroll
+                for (int j = 1; j < NG * GS; ++j) {
+                    c = pj == j ? a[j] : c;
+                    asm("" : "+v"(c));   // (selects: a chain seen as an indexed read would go through scratch memory)
+                }
+                lds_put<int32_t>(lds + L.hr + (uint32_t)((g & (kHRing - 1)) * 64 + lane) * 4u, field(pb, c));
+                if (lane == 0) lds_put<int32_t>(lds + L.seqh + 4u * (uint32_t)(g & (kHRing - 1)), g + 1);
+            }
+            next(pb, pm, pj);
+        }
+        k += 2;
+    };
+    // (whole rounds of D pairs: a way out of the middle of a round would join
+    // the loop's end with other loads in flight, and the waits for the oldest words
+    // would become waits for all; the decider ends with kEmpty blocks of no flips)
+    while (k < total) {
+        if (NG == 1) {
+#pragma unroll
+            for (int q = 0; q < D; ++q) {
+                take();
+                apply(buf[q], 0);
+                finish();
+                load_next(buf[q], 0);
+            }
+        } else {
+            take();
+#pragma unroll
+            for (int grp = 0; grp < NG; ++grp) {
+                apply(buf[grp % D], grp);
+                load_next(buf[grp % D], (grp + D) % NG);
+            }
+            finish();
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NG * GS; ++j) {
+        const int32_t blk = uw + kUpdWaves * j, i = blk * 64 + lane;
+        if (i < n) {
+            const uint32_t w = lds_get<uint32_t>(lds + L.bits + 4u * (uint32_t)(i >> 5));
+            gl(ch->H)[i] = field(blk, a[j]) - 1 + 2 * (int32_t)((w >> (lane & 31)) & 1u);
+        }
+    }
+#if SG_SK_PROF
+    if (lane == 0 && blockIdx.x < 3)
+        printf("[sk-prof] wg %d updater %d cycles waiting %llu\n", (int)blockIdx.x, uw, tu[0]);
+#endif
+}
+
+template <int NG, int GS, int D>
+__global__ void __launch_bounds__(kSkThreads) sk_sweep_kernel(const SkChain* __restrict__ chains, int64_t t0,
+                                                              int32_t nsw, int64_t t_max, int* err)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t sk_smem[];
-    const SkChain* ch = (const SkChain*)(gl(chains) + blockIdx.x);
-    const int32_t n = ch->n, wn = ch->words_n;
+    const SkChain* ch = (const SkChain*)(gl(chains) + sk_chain_of(blockIdx.x, gridDim.x));
+    const uint32_t lds = (uint32_t)(size_t)(SG_L uint8_t*)sk_smem;
+    const int32_t n = ch->n, wn = ch->words_n, NB = sk_blocks(n);
     const int tid = threadIdx.x, nthr = blockDim.x;
-    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const SkLds L = sk_carve(sk_smem, n, wn);
-    const int32_t cached = min(ch->thr_len, kThrCache);
-
-    for (int32_t i = tid; i < n; i += nthr) L.H[i] = gl(ch->H)[i];
-    for (int32_t w = tid; w < wn + 2; w += nthr) L.bits[w] = w < wn ? gl(ch->state)[w] : 0u;
-    for (int32_t x = tid; x < cached; x += nthr) L.thr[x] = gl(ch->thr)[x];
-    if (tid < 3 + kUpdWaves) L.sync[tid] = 0;
-    for (int e = tid; e < 512; e += nthr) {
-        // byte c of entry b + 256 m: bit c of b, in the low nibble (m = 0) or
-        // the high nibble (m = 1)
-        unsigned long long v = 0ull;
-        for (int c = 0; c < 8; ++c) v |= (unsigned long long)((e >> c) & 1) << (8 * c + 4 * (e >> 8));
-        L.spr[e] = v;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const SkLds L = sk_layout(n);
+    const int32_t total = nsw * NB;   // (bounded by the host)
+    const int32_t DW = sk_window(NB);
+    const SG_G int32_t* gH = gl(ch->H);
+    const SG_G uint32_t* gst = gl(ch->state);
+    const SG_G uint64_t* gthr = gl(ch->thr);
+    // (the diagonal counts as J_ii = +1 in the sweep: tracked fields are H + s)
+    for (int32_t i = tid; i < 64 * NB; i += nthr) {
+        const int32_t h = i < n ? gH[i] + 1 - 2 * (int32_t)((gst[i >> 5] >> (i & 31)) & 1u) : 0;
+        lds_put<int32_t>(lds + L.h0 + 4u * (uint32_t)i, h);
+        // the fields of the first blocks, which no flip precedes by more than
+        // the window
+        if (i < 64 * (DW + 1)) lds_put<int32_t>(lds + L.hr + 4u * (uint32_t)i, h);
     }
+    for (int32_t w = tid; w < 2 * NB; w += nthr) lds_put<uint32_t>(lds + L.bits + 4u * (uint32_t)w, w < wn ? gst[w] : 0u);
+    for (int32_t x = tid; x < min(ch->thr_len, kThrCache); x += nthr)
+        lds_put<uint64_t>(lds + L.thr + 8u * (uint32_t)x, gthr[x]);
+    if (tid < kRing) lds_put<int32_t>(lds + L.seqp + 4u * (uint32_t)tid, 0);
+    if (tid < kHRing) lds_put<int32_t>(lds + L.seqh + 4u * (uint32_t)tid, tid <= DW ? tid + 1 : 0);
+    if (tid < 2) lds_put<int32_t>(lds + L.sync + 4u * (uint32_t)tid, 0);
     __syncthreads();
-
-    const int32_t NB = (n + 63) >> 6;
-    // correction window: the decider adds the flips of the previous DW blocks
-    // itself; the updaters skip those blocks' columns (DW < NB keeps a block
-    // from correcting for its own earlier visit)
-    const int32_t DW = min(kWin, NB - 1);
-    const int64_t total = (int64_t)nsw * NB;
-    const SG_G uint32_t* __restrict__ Jb = gl(ch->Jb);
-
-    if (wave == 1) {
-        // ---------------- prep ----------------
-        // coupling tiles (bit-packed, bit 1 = J -1) of lane i's own row
-        // 64 b + i: its columns in block b, then in blocks b - d, d = 1..DW
-        // (J is symmetric, so bit j is the coupling of spin j of that block to
-        // spin i), stored contiguously per block by the host (zero past the
-        // last row or column and beyond DW); the tiles of the next block are
-        // loaded while this block's uniforms are drawn
-        static_assert(kTileWords % 4 == 0, "tiles are read as 16-byte vectors");
-        uint32_t tw[kTileWords];
-        const SG_G v4u* __restrict__ Jt = (const SG_G v4u*)gl(ch->Jt);
-        auto load_tiles = [&](int32_t bq) {
-            const SG_G v4u* src = Jt + ((size_t)((bq << 6) + lane) * kTileWords) / 4;
-#pragma unroll
-            for (int v = 0; v < kTileWords / 4; ++v) {
-                const v4u q = src[v];
-                tw[4 * v] = q.x;
-                tw[4 * v + 1] = q.y;
-                tw[4 * v + 2] = q.z;
-                tw[4 * v + 3] = q.w;
-            }
-        };
-        if (total > 0) load_tiles(0);
-        int32_t b = 0, s = 0, slot = 0;
-        for (int64_t g = 0; g < total; ++g) {
-            if (g >= kRing) wait_ge(L, kDecided, (int32_t)(g - kRing + 1), err);
-            uint32_t* tl = L.tile + ((size_t)slot * 64 + lane) * kTileWords;
-#pragma unroll
-            for (int d = 0; d < 2 * (kWin + 1); ++d) tl[d] = tw[d];
-            if (g + 1 < total) load_tiles(b + 1 == NB ? 0 : b + 1);
-            if ((g & 3) == 0) {
-                // one pass of the 64 lanes draws both streams' blocks of the
-                // next four spin blocks: lane 16 j + 8 h + q holds stream h
-                // (high / low half-words) of 8-position group q of block g + j
-                const int32_t j = lane >> 4;
-                int32_t bq = b + j, sq = s;
-                while (bq >= NB) {
-                    bq -= NB;
-                    ++sq;
-                }
-                const uint32_t dom = (lane >> 3) & 1 ? kDomSweepLo : kDomSweepHi;
-                const U4 A = philox_stream(ch->seed, (uint32_t)(bq * 8 + (lane & 7)), (uint32_t)(t0 + sq), dom,
-                                           ch->rep, ch->inst);
-                L.pr[lane] = make_uint4(A.x, A.y, A.z, A.w);
-                wave_sync_sk();
-            }
-            const uint32_t* pw = (const uint32_t*)(L.pr + (int)(g & 3) * 16 + (lane >> 3));
-            const uint32_t hsel = (uint32_t)lane & 7u;
-            const uint32_t r = (__builtin_amdgcn_ubfe(pw[hsel >> 1], 16u * (hsel & 1u), 16u) << 16) |
-                               __builtin_amdgcn_ubfe(pw[32 + (hsel >> 1)], 16u * (hsel & 1u), 16u);
-            // starting guess from the logarithm, then exact fix-up on the table
-            int32_t x0;
-            const float slope = ch->xslope;
-            if (slope <= 0.0f) {
-                x0 = ch->thr_len - 1;
-            } else {
-                const float lv = 22.18070977791825f - __logf((float)r + 1.0f);
-                const float xf = lv / slope;
-                x0 = xf >= (float)(ch->thr_len - 1) ? ch->thr_len - 1 : (xf <= 0.0f ? 0 : (int32_t)xf);
-            }
-            // (entries cached in LDS first; a long table's tail is read from
-            // HBM on a path of its own, so that the common path holds no
-            // wait for this wavefront's outstanding loads)
-            if (x0 < cached) {
-                while (x0 > 0 && !((unsigned long long)r < L.thr[x0])) --x0;
-                while (x0 + 1 < cached && (unsigned long long)r < L.thr[x0 + 1]) ++x0;
-            }
-            if (x0 + 1 >= cached && cached < ch->thr_len) {
-                while (x0 > 0 && !((unsigned long long)r < thr_at(L, ch, cached, x0))) --x0;
-                while (x0 + 1 < ch->thr_len && (unsigned long long)r < thr_at(L, ch, cached, x0 + 1)) ++x0;
-            }
-            L.xm[slot * 64 + lane] = x0;
-            wave_release();
-            if (lane == 0) st_rel(&L.sync[kPrepared], (int32_t)(g + 1));
-            if (++slot == kRing) slot = 0;
-            if (++b == NB) {
-                b = 0;
-                ++s;
-            }
-        }
-    } else if (wave == 0) {
-        // ---------------- decider ----------------
-        // the sequential critical path: issue ahead of the wavefronts that
-        // share its SIMD
-        __builtin_amdgcn_s_setprio(3);
-        uint32_t acc = 0;
-        int32_t b = 0, s = 0, slot = 0;
-        // flips of the previous kWin blocks (d = 0: the block before this
-        // one): to spin +1 (bit 1 -> 0) and to -1
-        unsigned long long pFp[kWin], pFn[kWin];
-#pragma unroll
-        for (int d = 0; d < kWin; ++d) pFp[d] = pFn[d] = 0ull;
-        const unsigned long long lt = (1ull << lane) - 1ull;   // lanes before this one
-        const unsigned long long gt = ~lt & ~(1ull << lane);   // lanes after it
-        // field change of this lane from flips F+ (to +1) and F- (to -1) with
-        // coupling bits row (bit j = 1: J = -1): sum over j of 2 s_j' J_jk
-        auto delta = [](unsigned long long fp, unsigned long long fn, unsigned long long row) -> int32_t {
-            return 2 * (__popcll(fp) - __popcll(fn)) - 4 * (__popcll(fp & row) - __popcll(fn & row));
-        };
-#if SG_SK_PROF
-        // cycles waiting for the prep, reading its outputs, waiting for the
-        // updaters, correcting the fields, deciding, publishing; rounds
-        unsigned long long tp[7] = {0, 0, 0, 0, 0, 0, 0};
-#endif
-        for (int64_t g = 0; g < total; ++g) {
-            SK_CLK(c0);
-            wait_ge(L, kPrepared, (int32_t)(g + 1), err);
-            SK_CLK(c1);
-            SK_ACC(tp[0], c0, c1);
-            // the prep's outputs and the spins (written by this wavefront
-            // only) are read before waiting for the updaters
-            const int32_t p = (b << 6) + lane;
-            const bool act = p < n;
-            const int32_t xm = L.xm[slot * 64 + lane];
-            const uint32_t* tl = L.tile + ((size_t)slot * 64 + lane) * kTileWords;
-            const unsigned long long D = ((unsigned long long)tl[1] << 32) | tl[0];   // own row, this block
-            uint32_t sb = act ? (L.bits[p >> 5] >> (p & 31)) & 1u : 0u;
-            SK_CLK(c2);
-            SK_ACC(tp[1], c1, c2);
-            if (g > DW) wait_applied(L, (int32_t)(g - DW), err);
-            SK_CLK(c3);
-            SK_ACC(tp[2], c2, c3);
-            int32_t Hp = act ? L.H[p] : 0;
-            // this block's fields still miss the flips of the previous DW
-            // blocks (own row restricted to block b - d, d = 1..DW)
-#pragma unroll
-            for (int d = 1; d <= kWin; ++d) {
-                if (d <= DW && g >= d) {
-                    const unsigned long long C = ((unsigned long long)tl[2 * d + 1] << 32) | tl[2 * d];
-                    Hp += delta(pFp[d - 1], pFn[d - 1], C);
-                }
-            }
-            // Decisions in rounds.  A lane's decision is certain once it
-            // cannot change whichever way the undecided lanes before it go:
-            // each of them would move its x by 2, in a direction known from
-            // the spins and the coupling.  The first undecided lane is always
-            // certain, so every round decides at least one lane (the exact
-            // sequential result, in about three rounds).  The flips decided in
-            // a round change the fields of the lanes after them at once; after
-            // the last round every lane adds the flips after it.
-            SK_CLK(c4);
-            SK_ACC(tp[3], c3, c4);
-            unsigned long long SB = __builtin_amdgcn_ballot_w64(sb != 0u);
-            unsigned long long und = __builtin_amdgcn_ballot_w64(act);
-            unsigned long long Fp = 0ull, Fn = 0ull;
-            int32_t nf = 0;
-            while (und != 0ull) {
-                const uint32_t below = __builtin_amdgcn_mbcnt_hi(
-                    (uint32_t)(und >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)und, 0u));
-                const bool mine = (und >> lane) & 1ull;
-                const int32_t x = sb ? -Hp : Hp;
-                // a flip of an undecided lane j before this one changes x by
-                // -2 s s_j J_j: down where s s_j J_j > 0 (spin and coupling
-                // bits XOR to 0), up elsewhere
-                const unsigned long long own = sb ? ~0ull : 0ull;
-                const int32_t dn = __popcll(~(SB ^ D ^ own) & und & lt);
-                const int32_t upc = (int32_t)below - dn;
-                const unsigned long long F = __builtin_amdgcn_ballot_w64(mine && x + 2 * upc <= xm);
-                const unsigned long long K = __builtin_amdgcn_ballot_w64(mine && x - 2 * dn > xm);
-                und &= ~(F | K);
-                const unsigned long long fp = F & SB, fn = F & ~SB;
-                Hp += delta(fp & lt, fn & lt, D);
-                if ((F >> lane) & 1ull) {
-                    // flip entry: local row | (new spin -1) << 31, in lane order
-                    L.flips[slot * 64 + nf + __popcll(F & lt)] = lane | (int32_t)((sb ^ 1u) << 31);
-                    sb ^= 1u;
-                }
-                nf += __popcll(F);
-#if SG_SK_PROF
-                ++tp[6];
-#endif
-                SB ^= F;
-                Fp |= fp;
-                Fn |= fn;
-            }
-            SK_CLK(c5);
-            SK_ACC(tp[4], c4, c5);
-            Hp += delta(Fp & gt, Fn & gt, D);
-#pragma unroll
-            for (int d = kWin - 1; d > 0; --d) {
-                pFp[d] = pFp[d - 1];
-                pFn[d] = pFn[d - 1];
-            }
-            pFp[0] = Fp;
-            pFn[0] = Fn;
-            if (act) L.H[p] = Hp;
-            const unsigned long long mask = __ballot(sb != 0u);
-            if (lane == 0) {
-                L.bits[2 * b] = (uint32_t)mask;
-                if (2 * b + 1 < wn) L.bits[2 * b + 1] = (uint32_t)(mask >> 32);
-                L.nflip[slot] = nf | (__popcll(Fp) << 8);
-                acc += (uint32_t)nf;
-            }
-            wave_release();
-            if (lane == 0) st_rel(&L.sync[kDecided], (int32_t)(g + 1));
-            SK_CLK(c6);
-            SK_ACC(tp[5], c5, c6);
-            if (++slot == kRing) slot = 0;
-            if (++b == NB) {
-                b = 0;
-                ++s;
-                const int64_t tn = t0 + s;
-                if (tn <= t_max && (tn & (tn - 1)) == 0) {
-                    const int k = 1 + (63 - __clzll((unsigned long long)tn));
-                    for (int32_t w = lane; w < wn; w += 64) gl(ch->snap)[(int64_t)k * wn + w] = L.bits[w];
-                }
-            }
-        }
-        if (lane == 0 && acc) atomicAdd(ch->accepted, (unsigned long long)acc);
-#if SG_SK_PROF
-        if (lane == 0 && blockIdx.x < 3)
-            printf("[sk-prof] wg %d decider blocks %lld cycles: wait-prep %llu reads %llu wait-updaters %llu "
-                   "correct %llu rounds %llu publish %llu; rounds %llu\n",
-                   (int)blockIdx.x, (long long)total, tp[0], tp[1], tp[2], tp[3], tp[4], tp[5], tp[6]);
-#endif
-    } else {
-        // ---------------- updaters ----------------
-        // An updater lane owns items of 8 consecutive fields (one byte of a
-        // coupling-row word).  L.spr spreads the row byte of a flip over the
-        // bytes of a 64-bit word: bit c goes to byte c, in its low nibble for a
-        // flip to +1 and its high nibble for a flip to -1, so one 64-bit add
-        // per flip counts the couplings of all 8 fields (8 flips per batch:
-        // no nibble overflows).  A wavefront takes every decided block it
-        // finds, up to kUpdBlocks, in one pass: their row loads share one
-        // memory latency.  Its progress word tells the decider how many blocks
-        // of the launch it has applied.
-        const int uw = wave - 2;   // updater index
-        const int ut = uw * 64 + lane;
-        const int32_t nitem = (n + 7) >> 3;
-        const char* sprb = (const char*)L.spr;
-        int32_t bk = 0, slot = 0;
-#if SG_SK_PROF
-        unsigned long long tu[2] = {0, 0};   // cycles waiting for decided blocks, applying them
-#endif
-        for (int64_t k = 0; k < total;) {
-            SK_CLK(u0);
-            wait_ge(L, kDecided, (int32_t)(k + 1), err);
-            SK_CLK(u1);
-            SK_ACC(tu[0], u0, u1);
-            int32_t np = 1;
-            if (kUpdBlocks > 1) {
-                const int32_t dec = __builtin_amdgcn_readfirstlane(ld_acq(&L.sync[kDecided]));
-                np = (int32_t)max((int64_t)1, min((int64_t)kUpdBlocks, min((int64_t)dec, total) - k));
-            }
-            // per block j of the pass: ring slot, block index, first flip in
-            // the concatenated list, sum of 2 s' over its flips, and the
-            // blocks after it whose columns the decider corrects itself
-            int32_t sl[kUpdBlocks], bq[kUpdBlocks], cum[kUpdBlocks + 1], s2[kUpdBlocks], dsk[kUpdBlocks];
-            cum[0] = 0;
-#pragma unroll
-            for (int j = 0; j < kUpdBlocks; ++j) {
-                sl[j] = j == 0 ? slot : (sl[j - 1] + 1 == kRing ? 0 : sl[j - 1] + 1);
-                bq[j] = j == 0 ? bk : (bq[j - 1] + 1 == NB ? 0 : bq[j - 1] + 1);
-                const int32_t w = j < np ? __builtin_amdgcn_readfirstlane(L.nflip[sl[j]]) : 0;
-                const int32_t nfj = w & 0xff;
-                cum[j + 1] = cum[j] + nfj;
-                s2[j] = 2 * (2 * (w >> 8) - nfj);
-                dsk[j] = (int32_t)min((int64_t)DW, total - 1 - (k + j));
-            }
-            const int32_t ntot = cum[kUpdBlocks];
-            if (ntot > 0) {
-                for (int32_t h = ut; h < nitem; h += 64 * kUpdWaves) {
-                    const int32_t col0 = h << 3;
-                    // the item takes a block's flips unless it lies in the
-                    // flipped block (patched in the decider) or in one of the
-                    // next dsk blocks (corrected by the decider)
-                    bool use[kUpdBlocks];
-                    bool any = false;
-                    int32_t sum2 = 0;
-#pragma unroll
-                    for (int j = 0; j < kUpdBlocks; ++j) {
-                        int32_t dist = (col0 >> 6) - bq[j];
-                        if (dist < 0) dist += NB;
-                        use[j] = j < np && dist > dsk[j];
-                        any = any || use[j];
-                        sum2 += use[j] ? s2[j] : 0;
-                    }
-                    if (!any) continue;
-                    const int32_t wi = col0 >> 5;
-                    const uint32_t shift = (uint32_t)col0 & 31u;
-                    int32_t dlt[8];   // per field: flips to +1 minus flips to -1 with coupling bit 1
-#pragma unroll
-                    for (int c = 0; c < 8; ++c) dlt[c] = 0;
-                    // One batch: NL row loads in flight, all issued before any
-                    // is used (the NL flip entries are read from LDS first, so
-                    // their latencies overlap too); entries past the last flip
-                    // re-read its row with a zero-width byte.  Batches of 16
-                    // when more than 8 flips are left, so that a block with up
-                    // to 16 flips costs one memory latency.
-                    auto batch = [&](int32_t f0, auto nlc) {
-                        constexpr int NL = decltype(nlc)::value;
-                        uint32_t wv[NL], wd[NL], tb[NL];
-                        int32_t fe[NL], rb[NL];
-#pragma unroll
-                        for (int i = 0; i < NL; ++i) {
-                            const int32_t fi = min(f0 + i, ntot - 1);
-                            int32_t slj = sl[0], bqj = bq[0], cj = 0;
-                            bool uj = use[0];
-#pragma unroll
-                            for (int j = 1; j < kUpdBlocks; ++j) {
-                                if (fi >= cum[j]) {
-                                    slj = sl[j];
-                                    bqj = bq[j];
-                                    cj = cum[j];
-                                    uj = use[j];
-                                }
-                            }
-                            fe[i] = L.flips[slj * 64 + fi - cj];
-                            rb[i] = bqj << 6;
-                            wd[i] = (f0 + i < ntot && uj) ? 8u : 0u;
-                        }
-#pragma unroll
-                        for (int i = 0; i < NL; ++i) {
-                            const int32_t fv = __builtin_amdgcn_readfirstlane(fe[i]);
-                            tb[i] = fv < 0 ? 2048u : 0u;
-                            wv[i] = Jb[(int64_t)(rb[i] + (fv & 63)) * wn + wi];
-                        }
-                        // nibble counts of 8 flips at a time (at most 8: no carry)
-#pragma unroll
-                        for (int i0 = 0; i0 < NL; i0 += 8) {
-                            unsigned long long acc = 0ull;
-#pragma unroll
-                            for (int i = i0; i < i0 + 8; ++i) {
-                                const uint32_t byte = __builtin_amdgcn_ubfe(wv[i], shift, wd[i]);
-                                acc += *(const unsigned long long*)(sprb + tb[i] + (byte << 3));
-                            }
-                            const uint32_t lo = (uint32_t)acc, hi = (uint32_t)(acc >> 32);
-#pragma unroll
-                            for (int c = 0; c < 4; ++c) {
-                                dlt[c] += (int32_t)__builtin_amdgcn_ubfe(lo, 8u * c, 4u) -
-                                          (int32_t)__builtin_amdgcn_ubfe(lo, 8u * c + 4u, 4u);
-                                dlt[c + 4] += (int32_t)__builtin_amdgcn_ubfe(hi, 8u * c, 4u) -
-                                              (int32_t)__builtin_amdgcn_ubfe(hi, 8u * c + 4u, 4u);
-                            }
-                        }
-                    };
-                    for (int32_t f0 = 0; f0 < ntot;) {
-                        if (ntot - f0 > 8) {
-                            batch(f0, std::integral_constant<int, 16>{});
-                            f0 += 16;
-                        } else {
-                            batch(f0, std::integral_constant<int, 8>{});
-                            f0 += 8;
-                        }
-                    }
-                    // H_c += sum over flips of 2 s' J_fc, J = 1 - 2 bit
-                    if (col0 + 8 <= n) {
-                        int4* hp = (int4*)(L.H + col0);
-                        int4 u0 = hp[0], u1 = hp[1];
-                        u0.x += sum2 - 4 * dlt[0];
-                        u0.y += sum2 - 4 * dlt[1];
-                        u0.z += sum2 - 4 * dlt[2];
-                        u0.w += sum2 - 4 * dlt[3];
-                        u1.x += sum2 - 4 * dlt[4];
-                        u1.y += sum2 - 4 * dlt[5];
-                        u1.z += sum2 - 4 * dlt[6];
-                        u1.w += sum2 - 4 * dlt[7];
-                        hp[0] = u0;
-                        hp[1] = u1;
-                    } else {
-#pragma unroll
-                        for (int c = 0; c < 8; ++c)
-                            if (col0 + c < n) L.H[col0 + c] += sum2 - 4 * dlt[c];
-                    }
-                }
-            }
-            wave_release();
-            k += np;
-            if (lane == 0) st_rel(&L.sync[kProg + uw], (int32_t)k);
-            SK_CLK(u2);
-            SK_ACC(tu[1], u1, u2);
-            slot += np;
-            if (slot >= kRing) slot -= kRing;
-            bk += np;
-            while (bk >= NB) bk -= NB;
-        }
-#if SG_SK_PROF
-        if (lane == 0 && blockIdx.x < 3)
-            printf("[sk-prof] wg %d updater %d cycles: wait %llu apply %llu\n", (int)blockIdx.x, uw, tu[0], tu[1]);
-#endif
-    }
+    // Wavefronts go to the four SIMDs in turn: the decider shares its SIMD with
+    // the prep wavefronts, the updaters have the other three.
+    if (wave == 0)
+        sk_decide(ch, L, lds, t0, total, t_max);
+    else if ((wave & 3) == 0)
+        sk_prep(ch, L, lds, (wave >> 2) - 1, t0, total);
+    else
+        sk_update<NG, GS, D>(ch, L, lds, wave - 1 - (wave >> 2), total);
     __syncthreads();
-
-    for (int32_t i = tid; i < n; i += nthr) gl(ch->H)[i] = L.H[i];
-    for (int32_t w = tid; w < wn; w += nthr) gl(ch->state)[w] = L.bits[w];
+    if (tid == 0 && lds_get<int32_t>(lds + L.sync + 4)) atomicOr(err, 2);
 }
 
 // Initial configuration and the t = 0 snapshot of every chain.
@@ -751,18 +760,7 @@ __global__ void __launch_bounds__(256) sk_bond_kernel(const SkSample* __restrict
 
 }  // namespace
 
-size_t sk_lds_bytes(int32_t n)
-{
-    const size_t wn = (size_t)(n + 31) / 32;
-    auto r16 = [](size_t b) { return (b + 15) & ~(size_t)15; };
-    return r16((size_t)n * 4) + r16((wn + 2) * 4) + r16((size_t)kThrCache * 8) + r16(kRing * 64 * 4) +
-           r16((size_t)kRing * 64 * kTileWords * 4) + r16(kRing * 64 * 4) + r16(kRing * 4) +
-           r16((3 + kUpdWaves) * 4) + 64 * 16 + 512 * 8;
-}
-
-int sk_threads() { return kSkThreads; }
-int sk_tile_words() { return kTileWords; }
-int sk_window() { return kWin; }
+size_t sk_lds_bytes(int32_t n) { return sk_layout(n).total; }
 
 hipError_t sk_init(const SkChain* chains, int n_chains, int threads, hipStream_t s)
 {
@@ -789,17 +787,38 @@ hipError_t sk_bond(const SkSample* samples, int n_samples, const SkChain* chains
     return hipGetLastError();
 }
 
-hipError_t sk_sweep(const SkChain* chains, int n_chains, int, size_t lds_bytes, int64_t t0,
+// Fields per lane of an updater: ceil(blocks / 12), held in NG groups of GS.
+template <int NG, int GS, int D>
+static hipError_t sk_launch(const SkChain* chains, int n_chains, size_t lds_bytes, int64_t t0, int32_t n_sweeps,
+                            int64_t t_max, int* err_flag, hipStream_t s)
+{
+    // set once (thread-safe initialisation of a local static)
+    static const hipError_t attr = hipFuncSetAttribute((const void*)sk_sweep_kernel<NG, GS, D>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (attr != hipSuccess) return attr;
+    sk_sweep_kernel<NG, GS, D><<<dim3(n_chains), dim3(kSkThreads), lds_bytes, s>>>(chains, t0, n_sweeps, t_max, err_flag);
+    return hipGetLastError();
+}
+
+hipError_t sk_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0,
                     int32_t n_sweeps, int64_t t_max, int* err_flag, hipStream_t s)
 {
     if (n_chains <= 0 || n_sweeps <= 0) return hipSuccess;
-    // set once (thread-safe initialisation of a local static)
-    static const hipError_t attr = hipFuncSetAttribute((const void*)sk_sweep_kernel,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(sk_sweep_kernel, dim3(n_chains), dim3(kSkThreads), lds_bytes, s, chains, t0,
-                       n_sweeps, t_max, err_flag);
-    return hipGetLastError();
+    const int per = (sk_blocks(max_n) + kUpdWaves - 1) / kUpdWaves;
+    auto launch = per <= 1    ? sk_launch<1, 1, 3>
+                  : per <= 2  ? sk_launch<1, 2, 3>
+                  : per <= 3  ? sk_launch<1, 3, 3>
+                  : per <= 4  ? sk_launch<1, 4, 3>
+                  : per <= 5  ? sk_launch<1, 5, 3>
+                  : per <= 6  ? sk_launch<1, 6, 3>
+                  : per <= 7  ? sk_launch<1, 7, 2>
+                  : per <= 8  ? sk_launch<1, 8, 2>
+                  : per <= 12 ? sk_launch<2, 6, 2>
+                  : per <= 16 ? sk_launch<4, 4, 4>
+                  : per <= 24 ? sk_launch<6, 4, 2>
+                  : per <= 32 ? sk_launch<8, 4, 2>
+                              : sk_launch<12, 4, 2>;
+    return launch(chains, n_chains, lds_bytes, t0, n_sweeps, t_max, err_flag, s);
 }
 
 }  // namespace sg
