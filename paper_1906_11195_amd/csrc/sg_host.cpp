@@ -1473,10 +1473,9 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     }
 
     Arena A;
-    std::vector<size_t> off_J(jrep.size()), off_Jw(jrep.size());
+    std::vector<size_t> off_Jw(jrep.size());
     for (size_t j = 0; j < jrep.size(); ++j) {
         const int64_t n = d[jrep[j]].n;
-        off_J[j] = A.take((size_t)(n * n));
         const size_t nb = (size_t)sk_blocks((int32_t)n);
         off_Jw[j] = A.take(nb * nb * 64 * 8);
     }
@@ -1510,9 +1509,8 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     c->arena_bytes = A.size;
     c->arena = c->dev_alloc(A.size);
 
-    // couplings: generated on the host in parallel, or copied; int8 rows for
-    // the MFMA contractions and bit-packed words for the sweep
-    // (a few samples: each one's passes run on several threads; many: the
+    // couplings: generated on the host in parallel, or taken as given, and
+    // packed into words (a few samples: each one's passes run on several threads; many: the
     // samples do)
     const bool inner = jrep.size() < 4;
     maybe_parallel(!inner, jrep.size(), [&](size_t j) {
@@ -1525,7 +1523,6 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
             sk_generate(n, r.seed, r.graph_id, J.data(), inner);
             src = J.data();
         }
-        hip_check(hipMemcpy(c->at<void>(off_J[j]), src, (size_t)(n * n), hipMemcpyHostToDevice));
         // words by block columns: bit j of word k of block b is the sign of
         // row k's coupling in column 64 b + j
         const int64_t nb = sk_blocks((int32_t)n);
@@ -1550,13 +1547,12 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     c->sk.resize((size_t)c->n_chains);
     c->sks.resize((size_t)count);
     for (int32_t i = 0; i < count; ++i) {
-        c->sks[(size_t)i] = SkSample{c->at<int8_t>(off_J[(size_t)jslot[(size_t)i]]), (int32_t)d[i].n, c->R,
+        c->sks[(size_t)i] = SkSample{c->at<uint64_t>(off_Jw[(size_t)jslot[(size_t)i]]), (int32_t)d[i].n, c->R,
                                      i * c->R, 0};
         for (int32_t r = 0; r < c->R; ++r) {
             const size_t ch = (size_t)(i * c->R + r);
             SkChain S;
             std::memset(&S, 0, sizeof(S));
-            S.J = c->at<int8_t>(off_J[(size_t)jslot[(size_t)i]]);
             S.Jw = c->at<uint64_t>(off_Jw[(size_t)jslot[(size_t)i]]);
             S.state = c->at<uint32_t>(off_state[ch]);
             S.H = c->at<int32_t>(off_H[ch]);
@@ -1612,7 +1608,7 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     hip_check(zero_i64((long long*)c->err_d, 1, nullptr));
     c->sk_lds = sk_lds_bytes(c->sk_max_n);
     hip_check(sk_init(c->sk_d, c->n_chains, 256, nullptr));
-    hip_check(sk_recompute(c->sks_d, count, c->sk_d, c->sk_max_n, 0, c->err_d, nullptr));
+    hip_check(sk_recompute(c->sks_d, count, c->sk_d, c->sk_max_n, c->R, 0, c->err_d, nullptr));
     hip_check(hipStreamSynchronize(nullptr));
 }
 
@@ -1635,7 +1631,7 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, long long* overlap, lon
         hip_check(skg_bond(c->sks_d, c->count, c->sk_d, c->sk_max_n, c->R, kd, K, c->bpart_d, c->bondr_d, s));
     } else {
         hip_check(zero_i64(bond, (size_t)c->n_chains * K, s));
-        hip_check(sk_bond(c->sks_d, c->count, c->sk_d, c->sk_max_n, c->R, kd, K, bond, s));
+        hip_check(sk_bond(c->sks_d, c->count, c->sk_d, c->sk_max_n, kd, K, bond, s));
     }
     hip_check(measure_overlap(c->mc_d, c->pairs_d, c->n_pairs, kd, K, overlap, s));
     hip_check(zero_i64(gram, (size_t)c->n_chains * K * K, s));
@@ -1850,7 +1846,7 @@ sg_status sg_sweep(sg_ctx* c, int64_t n_sweeps, void* stream)
                     if (c->sk_real)
                         hip_check(skg_recompute(c->sks_d, c->count, c->sk_d, c->sk_max_n, 1, c->err_d, s));
                     else
-                        hip_check(sk_recompute(c->sks_d, c->count, c->sk_d, c->sk_max_n, 1, c->err_d, s));
+                        hip_check(sk_recompute(c->sks_d, c->count, c->sk_d, c->sk_max_n, c->R, 1, c->err_d, s));
                 }
             }
         }

@@ -54,7 +54,6 @@ __host__ __device__ __forceinline__ int64_t sk_word(int32_t n_blocks, int64_t b,
 
 // One SK chain (a replica of an instance).
 struct SkChain {
-    const int8_t* J;           // [n][n]
     const uint64_t* Jw;        // coupling words, see sk_word
     uint32_t* state;           // [words_n] position-order bits (1 = spin -1)
     int32_t* H;                // [n] local fields between launches
@@ -71,7 +70,7 @@ struct SkChain {
     const uint32_t* given;     // position-order bits when GIVEN
     int32_t sample;            // index of the instance in the context
     float xslope;              // 2 beta / sqrt(N): thr[x] ~ 2^32 exp(-xslope x)
-    // real couplings (sg_skg.hip): J, Jw, H, thr unused
+    // real couplings (sg_skg.hip): Jw, H, thr unused
     const float* Jf;           // [n][n]
     double* Hd;                // [n] local fields between launches
     double beta;               // 1 / T
@@ -79,7 +78,7 @@ struct SkChain {
 
 // SK instance (sample) for the exact field recompute: all its chains.
 struct SkSample {
-    const int8_t* J;
+    const uint64_t* Jw;
     int32_t n;
     int32_t nch;
     int32_t chain0;            // index of its first chain in the chain array
@@ -128,9 +127,9 @@ hipError_t vbm_bond(const VbmUnit* units, int n_units, int k_first, int k_done, 
 // err_flag bit 0: recompute mismatch; bit 1: the sweep pipeline stalled.
 hipError_t sk_init(const SkChain* chains, int n_chains, int threads, hipStream_t s);
 hipError_t sk_recompute(const SkSample* samples, int n_samples, const SkChain* chains,
-                        int max_n, int check, int* err_flag, hipStream_t s);
+                        int max_n, int max_nch, int check, int* err_flag, hipStream_t s);
 hipError_t sk_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n,
-                   int max_nch, int k_done, int k_cap, long long* out, hipStream_t s);
+                   int k_done, int k_cap, long long* out, hipStream_t s);
 hipError_t sk_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0,
                     int32_t n_sweeps, int64_t t_max, int* err_flag, hipStream_t s);
 size_t sk_lds_bytes(int32_t n);

@@ -47,11 +47,9 @@
 // blocks costs the decider more than the slack gives (N = 4096: 31.1 us).  The
 // replicas of a sample run on one XCD, so that they share its L2.
 //
-// Every `period` sweeps the fields are recomputed exactly as H = J S with int8
-// MFMA (v_mfma_i32_16x16x64_i8, int32 accumulation) and compared with the
-// incremental ones; a mismatch raises the context's error flag.  Bond sums
-// B = (1/2) s^T J s of the snapshots are computed the same way at measurement
-// time.
+// Every `period` sweeps the fields are recomputed exactly as H = J S and compared
+// with the incremental ones; a mismatch raises the context's error flag.  Bond
+// sums B = (1/2) s^T J s of the snapshots are computed at measurement time.
 #include <type_traits>
 
 #include "sg_internal.h"
@@ -62,7 +60,6 @@ namespace {
 
 #define SG_L __attribute__((address_space(3)))
 
-typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
@@ -639,123 +636,148 @@ __global__ void sk_init_kernel(const SkChain* __restrict__ chains)
     }
 }
 
-// 16 spins (bits, 1 = -1) -> 16 int8 of +-1, zeroed where keep_mask bit is 0.
-__device__ __forceinline__ v4i expand16(uint32_t bits, uint32_t keep_mask)
+// ---------------- exact sums ----------------
+// H = J S and the bond sums s^T J s are +-1 contractions.  They run on the packed
+// words: 32 products are one XOR and one accumulating popcount of a lane, on an
+// eighth of the bytes that int8 couplings take, and the words are there for the
+// sweep already.  64 x 2 chains of N = 4096: fields 38 us (3.5 TB/s of words) and 12
+// snapshots a chain 179 us, against 263 and 460 us by int8 MFMA on int8 couplings,
+// which read N^2 bytes per sample and column tile and expanded every spin; 4 x 2
+// chains of N = 6001, whose int8 rows were not 16-byte aligned: 13.5 and 36 us
+// against 377 and 446.
+// Four words of spins of pair p (zeros past the last word).
+__device__ __forceinline__ v4u sk_spins(const SG_G uint32_t* st, int32_t p, int32_t wn)
 {
-    v4i r;
+    if (4 * p + 3 < wn) {
+        const SG_G uint32_t* q = st + 4 * p;
+        return v4u{q[0], q[1], q[2], q[3]};
+    }
+    return v4u{4 * p < wn ? st[4 * p] : 0u, 4 * p + 1 < wn ? st[4 * p + 1] : 0u, 4 * p + 2 < wn ? st[4 * p + 2] : 0u, 0u};
+}
+
+__device__ __forceinline__ uint32_t sk_differ(const v4u& w, const v4u& s, uint32_t acc)
+{
+    return popc_add(w.x ^ s.x, popc_add(w.y ^ s.y, popc_add(w.z ^ s.z, popc_add(w.w ^ s.w, acc))));
+}
+
+// Words of spin k for the pairs p0 + wave, p0 + wave + 4, ... (8 of them, fewer at
+// the end): bits that differ from a column's spins are products -1.
+constexpr int kDotPairs = 8;   // pairs per wavefront and pass: 4 wavefronts cover 4096 columns
+
+struct SkWords {
+    v4u w[kDotPairs];
+    int32_t np;   // (wave-uniform)
+};
+
+__device__ __forceinline__ void sk_words(SkWords& W, const SG_G v4u* Jw, int32_t NB, int32_t k, int32_t p0, int wave)
+{
+    W.np = max(0, min(kDotPairs, (NB / 2 - p0 - wave + 3) / 4));
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t nib = (bits >> (4 * q)) & 0xFu;
-        const uint32_t spread = (nib * 0x00204081u) & 0x01010101u;
-        uint32_t v = (spread * 0xFEu) ^ 0x01010101u;
-        const uint32_t km = (keep_mask >> (4 * q)) & 0xFu;
-        const uint32_t kb = ((km * 0x00204081u) & 0x01010101u) * 0xFFu;
-        r[q] = (int)(v & kb);
-    }
-    return r;
+    for (int i = 0; i < kDotPairs; ++i)
+        if (i < W.np) W.w[i] = Jw[(int64_t)(p0 + wave + 4 * i) * 64 * NB + k];
 }
 
-// A operand of v_mfma_i32_16x16x64_i8: 16 bytes of row `row` of J from column k0.
-__device__ __forceinline__ v4i j_bytes(const int8_t* __restrict__ J, int32_t n, int32_t row, int32_t k0)
-{
-    v4i a = {0, 0, 0, 0};
-    if (row >= n) return a;
-    const int8_t* src = J + (int64_t)row * n + k0;
-    if ((n & 15) == 0 && k0 + 16 <= n) {
-        const int4 v = *(const int4*)src;
-        a[0] = v.x; a[1] = v.y; a[2] = v.z; a[3] = v.w;
-    } else {
-        uint32_t w4[4] = {0, 0, 0, 0};
-        for (int b = 0; b < 16; ++b)
-            if (k0 + b < n) w4[b >> 2] |= (uint32_t)(uint8_t)src[b] << (8 * (b & 3));
-        a[0] = (int)w4[0]; a[1] = (int)w4[1]; a[2] = (int)w4[2]; a[3] = (int)w4[3];
-    }
-    return a;
-}
-
-// Exact fields H = J S for all chains of one sample, by int8 MFMA.
-// Block = 4 wavefronts = 64 rows; grid = (row blocks, samples).
+// Exact fields for all chains of one sample, compared with the incremental ones
+// when `check`.  Block = 64 spins, its four wavefronts share the columns;
+// grid = (blocks of 64 spins, samples).
+template <int C>
 __global__ void __launch_bounds__(256) sk_recompute_kernel(const SkSample* __restrict__ samples,
                                                            const SkChain* __restrict__ chains,
                                                            int check, int* err)
 {
-    const SkSample* sm = samples + blockIdx.y;
-    const int32_t n = sm->n, nch = sm->nch;
-    const int32_t i0 = blockIdx.x * 64 + (threadIdx.x >> 6) * 16;
-    if (i0 >= n) return;
-    const int lane = threadIdx.x & 63;
-    const int kg = lane >> 4;
-    const int jc = lane & 15;               // chain column of operand B
-    const SkChain* cj = jc < nch ? &chains[sm->chain0 + jc] : nullptr;
-    v4i acc = {0, 0, 0, 0};
-    for (int32_t kc = 0; kc < n; kc += 64) {
-        const int32_t k0 = kc + 16 * kg;
-        const v4i a = j_bytes(sm->J, n, i0 + (lane & 15), k0);
-        v4i bv = {0, 0, 0, 0};
-        if (cj != nullptr && k0 < n) {
-            const uint32_t bits = (cj->state[k0 >> 5] >> (k0 & 31)) & 0xffffu;
-            const int32_t valid = min(16, n - k0);
-            bv = expand16(bits, valid >= 16 ? 0xffffu : ((1u << valid) - 1u));
-        }
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv, acc, 0, 0, 0);
-    }
-    if (cj == nullptr) return;
+    __shared__ uint32_t part[4][C][64];
+    const SkSample* sm = (const SkSample*)(gl(samples) + blockIdx.y);
+    const int32_t n = sm->n, nch = sm->nch, NB = sk_blocks(n), wn = (n + 31) >> 5;
+    if ((int32_t)blockIdx.x >= NB) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const SkChain* ch = (const SkChain*)(gl(chains) + sm->chain0);
+    uint32_t cnt[C];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int32_t i = i0 + 4 * kg + r;
-        if (i < n) {
-            if (check && cj->H[i] != acc[r]) atomicOr(err, 1);
-            cj->H[i] = acc[r];
+    for (int c = 0; c < C; ++c) cnt[c] = 0u;
+    for (int32_t p0 = 0; p0 < NB / 2; p0 += 4 * kDotPairs) {
+        SkWords W;
+        sk_words(W, (const SG_G v4u*)gl(sm->Jw), NB, (int32_t)blockIdx.x * 64 + lane, p0, wave);
+#pragma unroll
+        for (int i = 0; i < kDotPairs; ++i) {
+            if (i >= W.np) break;
+#pragma unroll
+            for (int c = 0; c < C; ++c)
+                if (c < nch) cnt[c] = sk_differ(W.w[i], sk_spins(gl(ch[c].state), p0 + wave + 4 * i, wn), cnt[c]);
         }
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) part[wave][c][lane] = cnt[c];
+    __syncthreads();
+    const int32_t i = (int32_t)blockIdx.x * 64 + lane;
+    for (int c = wave; c < nch; c += 4) {
+        if (i >= n) break;
+        const uint32_t d = part[0][c][lane] + part[1][c][lane] + part[2][c][lane] + part[3][c][lane];
+        // (the diagonal counts as +1 in the words: s_i taken off)
+        const int32_t si = 1 - 2 * (int32_t)((gl(ch[c].state)[i >> 5] >> (i & 31)) & 1u);
+        const int32_t h = n - 2 * (int32_t)d - si;
+        SG_G int32_t* H = gl(ch[c].H);
+        if (check && H[i] != h) atomicOr(err, 1);
+        H[i] = h;
     }
 }
 
-// Bond sums of the snapshots: D = J S for the columns (chain r, snapshot k) of
-// one sample by int8 MFMA, then sum_i S_ic D_ic.  Accumulates 2 B into
-// out[chain][k]; grid = (row blocks, column tiles of 16, samples).
+// Bond sums of the snapshots: adds 2 B = sum_i s_i (J s)_i of every column (chain
+// r, snapshot k) of one sample into out[chain][k].  A block takes the products of
+// 64 spins with up to 4096 others, whose words it holds in registers while the
+// columns pass in tiles of 8; grid = (blocks of 64 spins, passes, samples).
 __global__ void __launch_bounds__(256) sk_bond_kernel(const SkSample* __restrict__ samples,
                                                       const SkChain* __restrict__ chains, int kd,
                                                       int k_cap, long long* __restrict__ out)
 {
-    const SkSample* sm = samples + blockIdx.z;
-    const int32_t n = sm->n, nch = sm->nch;
-    const int32_t i0 = blockIdx.x * 64 + (threadIdx.x >> 6) * 16;
-    const int32_t ncol = nch * kd;
-    if (i0 >= n || (int32_t)blockIdx.y * 16 >= ncol) return;
-    const int lane = threadIdx.x & 63;
-    const int kg = lane >> 4;
-    const int32_t col = blockIdx.y * 16 + (lane & 15);
-    const bool live = col < ncol;
-    const int32_t cr = live ? col / kd : 0, ck = live ? col - (col / kd) * kd : 0;
-    const SkChain* cj = &chains[sm->chain0 + cr];
-    const uint32_t* snap = cj->snap + (int64_t)ck * cj->words_n;
-    v4i acc = {0, 0, 0, 0};
-    for (int32_t kc = 0; kc < n; kc += 64) {
-        const int32_t k0 = kc + 16 * kg;
-        const v4i a = j_bytes(sm->J, n, i0 + (lane & 15), k0);
-        v4i bv = {0, 0, 0, 0};
-        if (live && k0 < n) {
-            const uint32_t bits = (snap[k0 >> 5] >> (k0 & 31)) & 0xffffu;
-            const int32_t valid = min(16, n - k0);
-            bv = expand16(bits, valid >= 16 ? 0xffffu : ((1u << valid) - 1u));
-        }
-        acc = __builtin_amdgcn_mfma_i32_16x16x64_i8(a, bv, acc, 0, 0, 0);
-    }
-    long long part = 0;
+    constexpr int CT = 8;
+    __shared__ int32_t part[CT][256];
+    const SkSample* sm = (const SkSample*)(gl(samples) + blockIdx.z);
+    const int32_t n = sm->n, NB = sk_blocks(n), wn = (n + 31) >> 5, ncol = sm->nch * kd;
+    const int32_t p0 = (int32_t)blockIdx.y * 4 * kDotPairs;
+    if ((int32_t)blockIdx.x >= NB || p0 >= NB / 2) return;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int32_t i = (int32_t)blockIdx.x * 64 + lane;
+    SkWords W;
+    sk_words(W, (const SG_G v4u*)gl(sm->Jw), NB, i, p0, wave);
+    const SkChain* ch = (const SkChain*)(gl(chains) + sm->chain0);
+    for (int32_t c0 = 0; c0 < ncol; c0 += CT) {
+        uint32_t cnt[CT];
+        const SG_G uint32_t* col[CT];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const int32_t i = i0 + 4 * kg + r;
-        if (live && i < n) {
-            const int32_t si = ((snap[i >> 5] >> (i & 31)) & 1u) ? -1 : 1;
-            part += (long long)si * acc[r];
+        for (int c = 0; c < CT; ++c) {
+            const int32_t q = min(c0 + c, ncol - 1), cr = q / kd;
+            col[c] = gl(ch[cr].snap) + (int64_t)(q - cr * kd) * wn;
+            cnt[c] = 0u;
         }
+#pragma unroll
+        for (int w = 0; w < kDotPairs; ++w) {
+            if (w >= W.np) break;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) cnt[c] = sk_differ(W.w[w], sk_spins(col[c], p0 + wave + 4 * w, wn), cnt[c]);
+        }
+        // s_i (products) of this wavefront's columns; the first pass's first
+        // wavefront adds s_i (n - s_i), the count of products less the diagonal
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const int32_t si = i < n ? 1 - 2 * (int32_t)((col[c][i >> 5] >> (i & 31)) & 1u) : 0;
+            const int32_t base = p0 == 0 && wave == 0 ? n - si : 0;
+            part[c][threadIdx.x] = si * (base - 2 * (int32_t)cnt[c]);
+        }
+        __syncthreads();
+        // 32 threads per column
+        const int c = threadIdx.x >> 5, t = threadIdx.x & 31;
+        int32_t v = 0;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v += part[c][t + 32 * q];
+#pragma unroll
+        for (int o = 16; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+        if (t == 0 && c0 + c < ncol && v != 0) {
+            const int32_t q = c0 + c, cr = q / kd;
+            atomicAdd((unsigned long long*)&out[(int64_t)(sm->chain0 + cr) * k_cap + (q - cr * kd)],
+                      (unsigned long long)(long long)v);
+        }
+        __syncthreads();
     }
-    // lanes l, l+16, l+32, l+48 hold the same column
-    part += __shfl_xor(part, 16);
-    part += __shfl_xor(part, 32);
-    if (live && kg == 0)
-        atomicAdd((unsigned long long*)&out[(int64_t)(sm->chain0 + cr) * k_cap + ck],
-                  (unsigned long long)part);
 }
 
 }  // namespace
@@ -769,20 +791,24 @@ hipError_t sk_init(const SkChain* chains, int n_chains, int threads, hipStream_t
     return hipGetLastError();
 }
 
-hipError_t sk_recompute(const SkSample* samples, int n_samples, const SkChain* chains, int max_n,
+hipError_t sk_recompute(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int max_nch,
                         int check, int* err_flag, hipStream_t s)
 {
     if (n_samples <= 0) return hipSuccess;
-    dim3 grid((max_n + 63) / 64, n_samples);
-    hipLaunchKernelGGL(sk_recompute_kernel, grid, dim3(256), 0, s, samples, chains, check, err_flag);
+    auto k = max_nch <= 1   ? sk_recompute_kernel<1>
+             : max_nch <= 2 ? sk_recompute_kernel<2>
+             : max_nch <= 4 ? sk_recompute_kernel<4>
+                            : sk_recompute_kernel<8>;
+    hipLaunchKernelGGL(k, dim3(sk_blocks(max_n), n_samples), dim3(256), 0, s, samples, chains, check, err_flag);
     return hipGetLastError();
 }
 
-hipError_t sk_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int max_nch,
-                   int k_done, int k_cap, long long* out, hipStream_t s)
+hipError_t sk_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int k_done, int k_cap,
+                   long long* out, hipStream_t s)
 {
     if (n_samples <= 0 || k_done <= 0) return hipSuccess;
-    dim3 grid((max_n + 63) / 64, (max_nch * k_done + 15) / 16, n_samples);
+    const int nb = sk_blocks(max_n), pass = 2 * 4 * kDotPairs;
+    dim3 grid(nb, (nb + pass - 1) / pass, n_samples);
     hipLaunchKernelGGL(sk_bond_kernel, grid, dim3(256), 0, s, samples, chains, k_done, k_cap, out);
     return hipGetLastError();
 }
