@@ -1308,8 +1308,12 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
         jslot[(size_t)i] = it->second;
     }
     Arena A;
-    std::vector<size_t> off_J(jrep.size());
-    for (size_t j = 0; j < jrep.size(); ++j) off_J[j] = A.take((size_t)(d[jrep[j]].n * d[jrep[j]].n) * 4);
+    std::vector<size_t> off_J(jrep.size()), off_Jd(jrep.size());
+    for (size_t j = 0; j < jrep.size(); ++j) {
+        const int64_t n = d[jrep[j]].n;
+        off_J[j] = A.take((size_t)n * (size_t)skg_pitch((int32_t)n) * 4);
+        off_Jd[j] = A.take((size_t)((n + 63) / 64) * 64 * 64 * 4);
+    }
     std::vector<size_t> off_state((size_t)c->n_chains), off_H((size_t)c->n_chains), off_snap((size_t)c->n_chains),
         off_given((size_t)c->n_chains, 0);
     for (int32_t i = 0; i < count; ++i) {
@@ -1340,7 +1344,25 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     c->arena = c->dev_alloc(A.size);
     for (size_t j = 0; j < jrep.size(); ++j) {
         const int64_t n = d[jrep[j]].n;
-        hip_check(hipMemcpy(c->at<void>(off_J[j]), d[jrep[j]].Jf, (size_t)(n * n) * 4, hipMemcpyHostToDevice));
+        const int64_t np = skg_pitch((int32_t)n);
+        if (np == n) {
+            hip_check(hipMemcpy(c->at<void>(off_J[j]), d[jrep[j]].Jf, (size_t)(n * n) * 4, hipMemcpyHostToDevice));
+        } else {
+            // rows padded on the host, up to 32 MiB at a time (a strided copy to
+            // the device goes row by row: 66 ms against 10 for 6 x 1021^2)
+            const int64_t rows = std::min<int64_t>(n, std::max<int64_t>(1, ((int64_t)1 << 23) / np));
+            std::vector<float> pad((size_t)(rows * np), 0.0f);
+            for (int64_t r0 = 0; r0 < n; r0 += rows) {
+                const int64_t m = std::min(rows, n - r0), parts = (m * n + (1 << 20) - 1) >> 20;
+                maybe_parallel(parts > 1, (size_t)parts, [&](size_t q) {
+                    for (int64_t r = m * (int64_t)q / parts; r < m * ((int64_t)q + 1) / parts; ++r)
+                        std::memcpy(pad.data() + r * np, d[jrep[j]].Jf + (r0 + r) * n, (size_t)n * 4);
+                });
+                hip_check(hipMemcpy(c->at<float>(off_J[j]) + r0 * np, pad.data(), (size_t)(m * np) * 4,
+                                    hipMemcpyHostToDevice));
+            }
+        }
+        hip_check(skg_diag(c->at<float>(off_J[j]), c->at<float>(off_Jd[j]), (int32_t)n, nullptr));
     }
     c->sk.resize((size_t)c->n_chains);
     c->sks.resize((size_t)count);
@@ -1357,6 +1379,7 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
             SkChain S;
             std::memset(&S, 0, sizeof(S));
             S.Jf = sm.Jf;
+            S.Jd = c->at<float>(off_Jd[(size_t)jslot[(size_t)i]]);
             S.Hd = c->at<double>(off_H[ch]);
             S.beta = 1.0 / d[i].T;
             S.state = c->at<uint32_t>(off_state[ch]);
@@ -1836,7 +1859,8 @@ sg_status sg_sweep(sg_ctx* c, int64_t n_sweeps, void* stream)
                 const int64_t chunk = std::min(std::min(left, to_check),
                                                std::max<int64_t>(1, ((int64_t)1 << 30) / sk_blocks(c->sk_max_n)));
                 if (c->sk_real)
-                    hip_check(skg_sweep(c->sk_d, c->n_chains, c->sk_lds, c->t_done, (int32_t)chunk, c->t_max, s));
+                    hip_check(skg_sweep(c->sk_d, c->n_chains, c->sk_max_n, c->sk_lds, c->t_done, (int32_t)chunk,
+                                        c->t_max, c->err_d, s));
                 else
                     hip_check(sk_sweep(c->sk_d, c->n_chains, c->sk_max_n, c->sk_lds, c->t_done, (int32_t)chunk,
                                        c->t_max, c->err_d, s));

@@ -52,6 +52,18 @@ __host__ __device__ __forceinline__ int64_t sk_word(int32_t n_blocks, int64_t b,
     return ((b >> 1) * 64 * n_blocks + k) * 2 + (b & 1);
 }
 
+// Real couplings: floats from one row to the next on the device.
+__host__ __device__ __forceinline__ int32_t skg_pitch(int32_t n) { return (n + 255) & ~255; }
+
+// The chain that workgroup `bid` of a launch of one workgroup per chain runs:
+// workgroups go to the 8 XCDs in turn, and the chains of an XCD are consecutive,
+// so that the replicas of a sample, which read the same couplings, share an L2.
+__device__ __forceinline__ int32_t chain_of_block(int32_t bid, int32_t n_chains)
+{
+    const int32_t x = bid & 7, i = bid >> 3, q = n_chains >> 3, r = n_chains & 7;
+    return x * q + min(x, r) + i;
+}
+
 // One SK chain (a replica of an instance).
 struct SkChain {
     const uint64_t* Jw;        // coupling words, see sk_word
@@ -71,7 +83,8 @@ struct SkChain {
     int32_t sample;            // index of the instance in the context
     float xslope;              // 2 beta / sqrt(N): thr[x] ~ 2^32 exp(-xslope x)
     // real couplings (sg_skg.hip): Jw, H, thr unused
-    const float* Jf;           // [n][n]
+    const float* Jf;           // [n][skg_pitch(n)], zero past n
+    const float* Jd;           // [ceil(n / 64)][64][64] strict upper triangles of the diagonal tiles
     double* Hd;                // [n] local fields between launches
     double beta;               // 1 / T
 };
@@ -142,8 +155,9 @@ constexpr size_t kSkOverread = (size_t)12 * 48 * 1024;
 // and bond sums of the snapshots (partials `part` of max_samples x
 // ceil(max_n / 16) x max_nch x k_cap doubles; out[chain][k]).
 size_t skg_lds_bytes(int32_t n);
-hipError_t skg_sweep(const SkChain* chains, int n_chains, size_t lds_bytes, int64_t t0, int32_t n_sweeps,
-                     int64_t t_max, hipStream_t s);
+hipError_t skg_diag(const float* J, float* Jd, int32_t n, hipStream_t s);
+hipError_t skg_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0, int32_t n_sweeps,
+                     int64_t t_max, int* err_flag, hipStream_t s);
 hipError_t skg_recompute(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int check,
                          int* err_flag, hipStream_t s);
 hipError_t skg_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int max_nch,

@@ -179,14 +179,6 @@ __device__ __forceinline__ void wave_sync_sk()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The chain a workgroup runs: workgroups go to the 8 XCDs in turn, and the
-// chains of an XCD are consecutive, so that the replicas of a sample share an L2.
-__device__ __forceinline__ int32_t sk_chain_of(int32_t bid, int32_t n_chains)
-{
-    const int32_t x = bid & 7, i = bid >> 3, q = n_chains >> 3, r = n_chains & 7;
-    return x * q + min(x, r) + i;
-}
-
 // popcount(v) + acc in the one instruction that does both (left to itself the
 // compiler counts from 0 and adds afterwards)
 __device__ __forceinline__ uint32_t popc_add(uint32_t v, uint32_t acc)
@@ -576,7 +568,7 @@ __global__ void __launch_bounds__(kSkThreads) sk_sweep_kernel(const SkChain* __r
                                                               int32_t nsw, int64_t t_max, int* err)
 {
     extern __shared__ __attribute__((aligned(16))) uint8_t sk_smem[];
-    const SkChain* ch = (const SkChain*)(gl(chains) + sk_chain_of(blockIdx.x, gridDim.x));
+    const SkChain* ch = (const SkChain*)(gl(chains) + chain_of_block(blockIdx.x, gridDim.x));
     const uint32_t lds = (uint32_t)(size_t)(SG_L uint8_t*)sk_smem;
     const int32_t n = ch->n, wn = ch->words_n, NB = sk_blocks(n);
     const int tid = threadIdx.x, nthr = blockDim.x;
