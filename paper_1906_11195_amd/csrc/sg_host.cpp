@@ -1339,7 +1339,7 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     const size_t off_acc = A.take((size_t)c->n_chains * 8);
     const size_t off_err = A.take(8);
     const size_t off_bondr = A.take((size_t)c->n_chains * c->K * 8);
-    const size_t off_part = A.take((size_t)count * (size_t)((c->sk_max_n + 15) / 16) * (size_t)c->R * c->K * 8);
+    const size_t off_part = A.take((size_t)count * (size_t)skg_row_blocks(c->sk_max_n) * (size_t)c->R * c->K * 8);
     c->arena_bytes = A.size;
     c->arena = c->dev_alloc(A.size);
     for (size_t j = 0; j < jrep.size(); ++j) {

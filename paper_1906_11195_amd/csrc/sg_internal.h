@@ -152,8 +152,9 @@ constexpr size_t kSkOverread = (size_t)12 * 48 * 1024;
 
 // SK with real couplings (sg_skg.hip): sweeps, direct field recomputation
 // (with `check`, error bit 0 when a field drifted by more than 1e-9 (1 + |h|))
-// and bond sums of the snapshots (partials `part` of max_samples x
-// ceil(max_n / 16) x max_nch x k_cap doubles; out[chain][k]).
+// and bond sums of the snapshots (partials `part` of samples x max_nch x k_cap x
+// skg_row_blocks(max_n) doubles; out[chain][k]).
+int skg_row_blocks(int32_t n);
 size_t skg_lds_bytes(int32_t n);
 hipError_t skg_diag(const float* J, float* Jd, int32_t n, hipStream_t s);
 hipError_t skg_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0, int32_t n_sweeps,

@@ -544,115 +544,199 @@ __global__ void __launch_bounds__(256) skg_diag_kernel(const float* __restrict__
     }
 }
 
-// Direct fields h = J s of every chain of one sample, in a fixed order (rows
-// by wavefronts, columns strided over lanes, then a fixed butterfly), in
-// double; with `check`, a field that differs from the incremental one by more
-// than 1e-9 (1 + |h|) raises bit 0 of the error word (the rounding drift of a
-// period is many orders of magnitude below that).  grid = (row blocks of 16,
-// samples), one wavefront per block.
-__global__ void __launch_bounds__(64) skg_recompute_kernel(const SkSample* __restrict__ samples,
-                                                           const SkChain* __restrict__ chains, int check,
-                                                           int* err)
+// ---------------- direct sums ----------------
+// A wavefront takes 8 rows of J, 256 columns (16-byte loads) at a time, and the
+// block's four wavefronts share the spins of the columns, staged in LDS as bits.
+// 32 samples of N = 4096 (2.1 GB of couplings), 2 chains: fields 0.39 ms (5.5 TB/s),
+// 16 to 20 snapshots 0.8 to 1.1 ms (arithmetic in double); 1.26 and 2.5 to 3.6 ms
+// with one row of 4-byte loads at a time, each row read once per chain and once per
+// 8 snapshots, and 0.12 ms for adding the partial sums one after another (now
+// 0.005).  6 x 2 chains of N = 1021: 10 and 25 us, before 155 and 240.
+constexpr int kRows = 8;
+constexpr int kDirect = 256;                        // threads
+constexpr int kRowsBlk = kRows * (kDirect / 64);    // rows of a block
+constexpr int kCols = 16;                           // snapshots taken at once by skg_bond_kernel
+
+typedef float v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t m)
 {
-    const SkSample* sm = samples + blockIdx.y;
-    const int32_t n = sm->n;
-    const int lane = threadIdx.x;
-    const int32_t i0 = blockIdx.x * 16;
-    if (i0 >= n) return;
-    const int32_t np = skg_pitch(n);
-    const SG_G float* __restrict__ J = gl(sm->Jf);
-    for (int32_t c = 0; c < sm->nch; ++c) {
-        const SkChain* ch = chains + sm->chain0 + c;
-        const SG_G uint32_t* st = gl(ch->state);
-        for (int32_t i = i0; i < min(n, i0 + 16); ++i) {
-            const SG_G float* row = J + (int64_t)i * np;
-            double part = 0.0;
-            for (int32_t j = lane; j < n; j += 64) {
-                const double v = (double)row[j];
-                part += ((st[j >> 5] >> (j & 31)) & 1u) ? -v : v;
+    return __hiloint2double(__double2hiint(v) ^ (int)m, __double2loint(v));
+}
+
+// Sums a[0 .. 15] over the wavefront, in a fixed order: each step halves the values
+// a lane carries (17 exchanges; 96 if each value were summed by itself).  Lane l
+// gets the sum of value sum_index(l).
+__device__ __forceinline__ double wave_sum16(double* a)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int s = 32, cnt = 8; cnt >= 1; s >>= 1, cnt >>= 1) {
+        const bool up = (lane & s) != 0;
+#pragma unroll
+        for (int i = 0; i < cnt; ++i) {
+            const double keep = up ? a[i + cnt] : a[i], give = up ? a[i] : a[i + cnt];
+            a[i] = keep + __shfl_xor(give, s);
+        }
+    }
+    double v = a[0];
+    v += __shfl_xor(v, 2);
+    v += __shfl_xor(v, 1);
+    return v;
+}
+// the value whose sum lane l holds (l & 3: copies)
+__device__ __forceinline__ int sum_index(int lane) { return lane >> 2; }
+
+// Direct fields h = J s of every chain of one sample, in a fixed order (columns by
+// lanes in steps of 256, then wave_sum16), in double; with `check`, a field that
+// differs from the incremental one by more than 1e-9 (1 + |h|) raises bit 0 of the
+// error word (the rounding drift of a period is many orders of magnitude below
+// that).  Two chains share each read of a row; bound by the couplings' bytes.
+// grid = (blocks of 32 rows, samples).
+__global__ void __launch_bounds__(kDirect) skg_recompute_kernel(const SkSample* __restrict__ samples,
+                                                                const SkChain* __restrict__ chains, int check,
+                                                                int* err)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t skg_bits[];   // [2][np / 32]
+    const SkSample* sm = (const SkSample*)(gl(samples) + blockIdx.y);
+    const int32_t n = sm->n, np = skg_pitch(n), nw = np >> 5, wn = (n + 31) >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int32_t)blockIdx.x * kRowsBlk >= n) return;
+    const int32_t i0 = (int32_t)blockIdx.x * kRowsBlk + wave * kRows;
+    const SG_G float* J = gl(sm->Jf) + 4 * lane;
+    for (int32_t c0 = 0; c0 < sm->nch; c0 += 2) {
+        const int nc = min(2, sm->nch - c0);
+        const SkChain* ch = (const SkChain*)(gl(chains) + sm->chain0 + c0);
+        __syncthreads();
+        for (int32_t w = threadIdx.x; w < 2 * nw; w += kDirect) {
+            const int c = w >= nw ? 1 : 0;
+            const int32_t q = w - c * nw;
+            skg_bits[w] = c < nc && q < wn ? gl(ch[c].state)[q] : 0u;
+        }
+        __syncthreads();
+        double acc[2 * kRows];
+#pragma unroll
+        for (int i = 0; i < 2 * kRows; ++i) acc[i] = 0.0;
+        for (int32_t q = 0; q < np; q += 256) {
+            v4f v[kRows];
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) v[r] = *(const SG_G v4f*)(J + (int64_t)min(i0 + r, n - 1) * np + q);
+            uint32_t m[2][4];
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const uint32_t nib = skg_bits[c * nw + (q >> 5) + (lane >> 3)] >> (4 * (lane & 7));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) m[c][e] = (nib << (31 - e)) & 0x80000000u;
             }
 #pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) part += __shfl_xor(part, o);
-            if (lane == 0) {
-                const double old = ch->Hd[i];
-                if (check && fabs(old - part) > 1e-9 * (1.0 + fabs(part))) atomicOr(err, 1);
-                ch->Hd[i] = part;
-            }
+            for (int r = 0; r < kRows; ++r)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const double x = (double)v[r][e];
+                    acc[r] += flip_sign(x, m[0][e]);
+                    acc[kRows + r] += flip_sign(x, m[1][e]);
+                }
+        }
+        const double h = wave_sum16(acc);
+        const int idx = sum_index(lane), c = idx / kRows;
+        const int32_t i = i0 + idx % kRows;
+        if ((lane & 3) == 0 && c < nc && i < n) {
+            SG_G double* Hd = gl(ch[c].Hd);
+            if (check && fabs(Hd[i] - h) > 1e-9 * (1.0 + fabs(h))) atomicOr(err, 1);
+            Hd[i] = h;
         }
     }
 }
 
 // Bond sums B = (1/2) sum_i s_i (J s)_i of every snapshot (chain c, grid time
-// k) of one sample, in double and in a fixed order: each wavefront forms
-// partial sums over 16 rows, written to part[sample][row block][column], then
-// skg_bond_reduce adds the row blocks in order.  The columns (snapshots) go in
-// tiles of 8, so a row of J is read once per tile: lane l adds, for its
-// entries j = l, l + 64, ..., the signed couplings s_j J_ij of each column,
-// multiplies by the row's spin s_i (the same on every lane) and keeps the
-// sum; the wavefront sum is formed once per tile.  grid = (row blocks of 16,
-// samples).
-__global__ void __launch_bounds__(64) skg_bond_kernel(const SkSample* __restrict__ samples,
-                                                      const SkChain* __restrict__ chains, int kd, int nrb,
-                                                      int ncol_cap, double* __restrict__ part)
+// k) of one sample, in double and in a fixed order: each block forms partial sums
+// over 32 rows, written to part[sample][column][block], then skg_bond_reduce adds
+// the blocks.  The columns (snapshots) go in tiles of 16, so a row of J is read once
+// per tile.  Per column the 8 rows of a wavefront are added with their signs (the
+// same on every lane: factors +-1 in scalar registers), then the sum takes the
+// signs of the lane's columns: about one fused multiply-add per coupling and
+// snapshot.  grid = (blocks of 32 rows, samples).
+__global__ void __launch_bounds__(kDirect) skg_bond_kernel(const SkSample* __restrict__ samples,
+                                                           const SkChain* __restrict__ chains, int kd, int nrb,
+                                                           int ncol_cap, double* __restrict__ part)
 {
-    constexpr int CT = 8;   // columns per tile
-    const SkSample* sm = samples + blockIdx.y;
-    const int32_t n = sm->n;
-    const int lane = threadIdx.x;
-    const int32_t i0 = blockIdx.x * 16;
-    if (i0 >= n) return;
-    const int32_t np = skg_pitch(n);
-    const SG_G float* __restrict__ J = gl(sm->Jf);
+    extern __shared__ __attribute__((aligned(16))) uint32_t skg_bits[];   // [kCols][np / 32]
+    __shared__ double sums[kDirect / 64][kCols];
+    const SkSample* sm = (const SkSample*)(gl(samples) + blockIdx.y);
+    const int32_t n = sm->n, np = skg_pitch(n), nw = np >> 5, wn = (n + 31) >> 5;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if ((int32_t)blockIdx.x * kRowsBlk >= n) return;
+    const int32_t i0 = (int32_t)blockIdx.x * kRowsBlk + wave * kRows;   // (8 rows of one word of bits)
+    const SG_G float* J = gl(sm->Jf) + 4 * lane;
     const int32_t ncol = sm->nch * kd;
-    const int32_t i1 = min(n, i0 + 16);
-    for (int32_t c0 = 0; c0 < ncol; c0 += CT) {
-        const SG_G uint32_t* sn[CT];
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            const int32_t col = min(c0 + c, ncol - 1);
-            const SkChain* ch = chains + sm->chain0 + col / kd;
-            sn[c] = gl(ch->snap) + (int64_t)(col % kd) * ch->words_n;
+    for (int32_t c0 = 0; c0 < ncol; c0 += kCols) {
+        __syncthreads();
+        for (int32_t w = threadIdx.x; w < kCols * nw; w += kDirect) {
+            const int32_t c = w / nw, q = w - c * nw, col = c0 + c, cr = col / kd;
+            const SkChain* ch = (const SkChain*)(gl(chains) + sm->chain0 + min(cr, sm->nch - 1));
+            skg_bits[w] = col < ncol && q < wn ? gl(ch->snap)[(int64_t)(col - cr * kd) * wn + q] : 0u;
         }
-        double acc[CT];
+        __syncthreads();
+        // bit r: spin i0 + r (rows past n are left out below)
+        uint32_t rs[kCols];
 #pragma unroll
-        for (int c = 0; c < CT; ++c) acc[c] = 0.0;
-        for (int32_t i = i0; i < i1; ++i) {
-            const SG_G float* row = J + (int64_t)i * np;
-            double d[CT];
+        for (int c = 0; c < kCols; ++c)
+            rs[c] = (uint32_t)__builtin_amdgcn_readfirstlane((int)(skg_bits[c * nw + min(i0 >> 5, nw - 1)] >> (i0 & 31)));
+        double acc[kCols];
 #pragma unroll
-            for (int c = 0; c < CT; ++c) d[c] = 0.0;
-            for (int32_t j = lane; j < n; j += 64) {
-                const double v = (double)row[j];
+        for (int c = 0; c < kCols; ++c) acc[c] = 0.0;
+        for (int32_t q = 0; q < np; q += 256) {
+            double x[kRows][4];
 #pragma unroll
-                for (int c = 0; c < CT; ++c) d[c] += ((sn[c][j >> 5] >> (j & 31)) & 1u) ? -v : v;
+            for (int r = 0; r < kRows; ++r) {
+                v4f v = v4f{0.f, 0.f, 0.f, 0.f};
+                if (i0 + r < n) v = *(const SG_G v4f*)(J + (int64_t)(i0 + r) * np + q);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[r][e] = (double)v[e];
             }
 #pragma unroll
-            for (int c = 0; c < CT; ++c) acc[c] += ((sn[c][i >> 5] >> (i & 31)) & 1u) ? -d[c] : d[c];
+            for (int c = 0; c < kCols; ++c) {
+                if (c0 + c >= ncol) break;
+                const uint32_t nib = skg_bits[c * nw + (q >> 5) + (lane >> 3)] >> (4 * (lane & 7));
+                double t[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+                for (int r = 0; r < kRows; ++r) {
+                    const double s = __hiloint2double((int)(((rs[c] << (31 - r)) & 0x80000000u) | 0x3ff00000u), 0);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) t[e] = fma(s, x[r][e], t[e]);
+                }
+                acc[c] += (flip_sign(t[0], nib << 31) + flip_sign(t[1], (nib << 30) & 0x80000000u)) +
+                          (flip_sign(t[2], (nib << 29) & 0x80000000u) + flip_sign(t[3], (nib << 28) & 0x80000000u));
+            }
         }
+        const double v = wave_sum16(acc);
+        if ((lane & 3) == 0) sums[wave][sum_index(lane)] = v;
+        __syncthreads();
+        if (threadIdx.x < kCols && c0 + (int32_t)threadIdx.x < ncol) {
+            double t = 0.0;
 #pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            double a = acc[c];
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) a += __shfl_xor(a, o);
-            if (lane == 0 && c0 + c < ncol) part[((int64_t)blockIdx.y * nrb + blockIdx.x) * ncol_cap + c0 + c] = a;
+            for (int w = 0; w < kDirect / 64; ++w) t += sums[w][threadIdx.x];
+            part[((int64_t)blockIdx.y * ncol_cap + c0 + threadIdx.x) * nrb + blockIdx.x] = t;
         }
     }
 }
 
-// out[chain][k] = (1/2) sum over row blocks (in order) of the partial sums.
-__global__ void skg_bond_reduce(const SkSample* __restrict__ samples, int n_samples, int kd, int nrb,
-                                int ncol_cap, int k_cap, const double* __restrict__ part,
-                                double* __restrict__ out)
+// out[chain][k] = (1/2) sum over the row blocks' partial sums, a wavefront each, in
+// a fixed order.  grid = (samples, columns)
+__global__ void __launch_bounds__(64) skg_bond_reduce(const SkSample* __restrict__ samples, int kd, int nrb,
+                                                      int ncol_cap, int k_cap, const double* __restrict__ part,
+                                                      double* __restrict__ out)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_samples * ncol_cap) return;
-    const int32_t smp = (int32_t)(idx / ncol_cap), col = (int32_t)(idx % ncol_cap);
-    const SkSample* sm = samples + smp;
+    const SkSample* sm = samples + blockIdx.x;
+    const int32_t col = blockIdx.y;
     if (col >= sm->nch * kd) return;
-    const int32_t rbs = (sm->n + 15) / 16;
-    double s = 0.0;
-    for (int32_t rb = 0; rb < rbs; ++rb) s += part[((int64_t)smp * nrb + rb) * ncol_cap + col];
-    out[(int64_t)(sm->chain0 + col / kd) * k_cap + col % kd] = 0.5 * s;
+    const int32_t blocks = (sm->n + kRowsBlk - 1) / kRowsBlk;
+    const double* p = part + ((int64_t)blockIdx.x * ncol_cap + col) * nrb;
+    double v = 0.0;
+    for (int32_t i = threadIdx.x; i < blocks; i += 64) v += p[i];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if (threadIdx.x == 0) out[(int64_t)(sm->chain0 + col / kd) * k_cap + col % kd] = 0.5 * v;
 }
 
 }  // namespace
@@ -699,21 +783,22 @@ hipError_t skg_recompute(const SkSample* samples, int n_samples, const SkChain* 
                          int* err_flag, hipStream_t s)
 {
     if (n_samples <= 0) return hipSuccess;
-    hipLaunchKernelGGL(skg_recompute_kernel, dim3((max_n + 15) / 16, n_samples), dim3(64), 0, s, samples, chains,
-                       check, err_flag);
+    hipLaunchKernelGGL(skg_recompute_kernel, dim3((max_n + kRowsBlk - 1) / kRowsBlk, n_samples), dim3(kDirect),
+                       (size_t)2 * skg_pitch(max_n) / 8, s, samples, chains, check, err_flag);
     return hipGetLastError();
 }
+
+int skg_row_blocks(int32_t n) { return (n + kRowsBlk - 1) / kRowsBlk; }
 
 hipError_t skg_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int max_nch,
                     int k_done, int k_cap, double* part, double* out, hipStream_t s)
 {
     if (n_samples <= 0 || k_done <= 0) return hipSuccess;
-    const int nrb = (max_n + 15) / 16, ncol_cap = max_nch * k_cap;
-    hipLaunchKernelGGL(skg_bond_kernel, dim3(nrb, n_samples), dim3(64), 0, s, samples, chains, k_done, nrb,
-                       ncol_cap, part);
-    const int64_t tot = (int64_t)n_samples * ncol_cap;
-    hipLaunchKernelGGL(skg_bond_reduce, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, samples, n_samples,
-                       k_done, nrb, ncol_cap, k_cap, part, out);
+    const int nrb = skg_row_blocks(max_n), ncol_cap = max_nch * k_cap;
+    hipLaunchKernelGGL(skg_bond_kernel, dim3(nrb, n_samples), dim3(kDirect), (size_t)kCols * skg_pitch(max_n) / 8, s,
+                       samples, chains, k_done, nrb, ncol_cap, part);
+    hipLaunchKernelGGL(skg_bond_reduce, dim3(n_samples, max_nch * k_done), dim3(64), 0, s, samples, k_done, nrb,
+                       ncol_cap, k_cap, part, out);
     return hipGetLastError();
 }
 
