@@ -658,8 +658,8 @@ void vb_autotune(sg_ctx* c)
             size_t l = 0;
             for (int32_t u = G.first; u < G.first + G.count; ++u) {
                 const VbUnit& U = c->units[(size_t)u];
-                l = std::max(l, vb_lds_bytes(U.n, U.rpad, U.nch, th, U.cpl != 0) +
-                                    (U.resident ? vb_resident_bytes(U.n, U.m2) : 0));
+                l = std::max(l, vb_lds_bytes(U.n, U.rpad, U.nch, th, U.cpl != 0 || U.resident != 0) +
+                                    (U.resident ? vb_resident_bytes(U.n, U.m2, U.ncls) : 0));
             }
             return l;
         };
@@ -863,13 +863,33 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     // Small graphs keep their adjacency LDS-resident.  Units of one size form
     // one launch group, largest work first inside a group
     // (longest-processing-time order).
+    int n_cu = 0;
+    hip_check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
+    const int64_t per_cu = ((int64_t)plan.size() + n_cu - 1) / std::max(1, n_cu);
     for (auto& u : plan) {
         const VbGraph& g = graphs[(size_t)u.group];
         const int32_t n = (int32_t)g.n;
-        const int th = graph_threads[(size_t)u.group];
-        if (vb_lds_bytes(n, u.rpad, (int32_t)u.chains.size(), th) > lds_cap) fail(SG_ENOTSUP);
+        const int32_t nch = (int32_t)u.chains.size();
+        int th = graph_threads[(size_t)u.group];
+        // A resident unit's wavefronts prepare their chunks while others run
+        // theirs, up to one per chunk of a sweep, and 16 wavefronts in all
+        // occupy a CU: shared among the units that a CU holds at once.
+        // Measured, 2 chains, us per sweep with 4 / 8 / 16 wavefronts: N = 1024,
+        // one unit a CU 4.4 / 3.1 / 2.6, two 4.8 / 3.6 / 5.1, four 5.9 / 7.0 /
+        // 10.3; N = 2048 (a CU holds 3), four 15.5 / 10.9 / 13.7; N = 4096 (it
+        // holds 1), two 26.8 / 16.4 / 12.6.
+        if (!(o && o->threads_per_unit)) {
+            auto need = [&](int t) { return vb_lds_bytes(n, u.rpad, nch, t, true) + vb_resident_bytes(n, (int32_t)g.ent.size(), g.ncls); };
+            const int64_t held = std::max<int64_t>(1, std::min<int64_t>(per_cu, (int64_t)(lds_cap / need(256))));
+            int32_t chunks = 0;
+            for (int32_t k = 0; k < g.ncls; ++k) chunks += (g.cls[(size_t)k + 1] + 63) / 64 - g.cls[(size_t)k] / 64;
+            int waves = 1;
+            while (waves < 16 && waves * held < 16 && waves < chunks) waves *= 2;
+            if (need(64 * waves) <= lds_cap) th = 64 * waves;
+        }
+        if (vb_lds_bytes(n, u.rpad, nch, th) > lds_cap) fail(SG_ENOTSUP);
         u.threads = th;
-        u.resident = vb_lds_bytes(n, u.rpad, (int32_t)u.chains.size(), th) + vb_resident_bytes(n, (int32_t)g.ent.size()) <= lds_cap;
+        u.resident = vb_lds_bytes(n, u.rpad, nch, th, true) + vb_resident_bytes(n, (int32_t)g.ent.size(), g.ncls) <= lds_cap;
         u.work = (int64_t)n * (int64_t)u.chains.size();
     }
     // Split units: a unit holding far more than one CU's share of the
@@ -884,8 +904,6 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     // opts.split_members: 0 automatic, 1 never, k >= 2 every unit that has
     // the chunks for k members (tests, tuning).  No effect on any result.
     {
-        int n_cu = 0;
-        hip_check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
         const int forced = o ? o->split_members : 0;
         auto cost_of = [&](const UnitPlan& u) {
             return (int64_t)graphs[(size_t)u.group].n * (10 + (int64_t)u.chains.size());
@@ -1111,8 +1129,8 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
             G.count++;
         }
         G.updates += g.n * U.nch;
-        G.lds = std::max(G.lds, vb_lds_bytes(U.n, U.rpad, U.nch, th, U.cpl != 0) +
-                                    (U.resident ? vb_resident_bytes(U.n, U.m2) : 0));
+        G.lds = std::max(G.lds, vb_lds_bytes(U.n, U.rpad, U.nch, th, U.cpl != 0 || U.resident != 0) +
+                                    (U.resident ? vb_resident_bytes(U.n, U.m2, U.ncls) : 0));
         c->vb_threads = std::max(c->vb_threads, th);
         c->bond_lds = std::max(c->bond_lds, (size_t)(((U.nch * U.words_n + 1) & ~1) * 4 + kVbMaxChains * 8));
         c->updates_per_sweep += g.n * U.nch;

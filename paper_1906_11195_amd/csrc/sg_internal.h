@@ -124,7 +124,7 @@ size_t vb_lds_bytes(int32_t n, int32_t rpad, int32_t nch, int threads, bool cpl 
 // neighbour's word, of its complement when J < 0, above 5 bits of in-word
 // shift; `pad` entries of position 0 follow the m entries.
 void vb_cpl_entries(const uint32_t* ent, size_t m, size_t pad, int32_t rpad, int32_t n, uint32_t* out);
-size_t vb_resident_bytes(int32_t n, int32_t m2);
+size_t vb_resident_bytes(int32_t n, int32_t m2, int32_t ncls);
 
 // Multispin units (sg_vbm.hip).
 size_t vbm_lds_bytes(int32_t n, int threads);

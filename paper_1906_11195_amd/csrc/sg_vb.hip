@@ -18,7 +18,8 @@
 // unit.  Workgroup barriers separate classes only.  Each wavefront streams
 // the adjacency of its chunks straight from HBM through a two-stage register
 // pipeline: the row starts of the chunk after next and the entries of the
-// next chunk are in flight while the current chunk is updated.
+// next chunk are in flight while the current chunk is updated.  (Units whose
+// adjacency fits in LDS take a loop of their own, vb_loop_res.)
 //
 // Metropolis rule (Methods; SI bipartite-graph section): with x = s_p h_p the
 // move is accepted if x <= 0, else iff r < thr[x], thr[x] = floor(2^32
@@ -31,6 +32,8 @@
 // every A); B is computed only when A ties with it (probability 2^-16).  The
 // flips of a chunk are collected as one ballot per chain and written back by
 // one lane per spin word.
+#include <type_traits>
+
 #include "sg_internal.h"
 #include "sg_philox.h"
 
@@ -41,6 +44,8 @@ constexpr int kDMax = 8;   // adjacency entries prefetched per position
 constexpr int kTab = 128;  // threshold table per chain: index 64 + x, -63 <= x <= 63
 constexpr int kThc = 32;   // compact threshold table per chain: index 15 - x, -16 <= x <= 15
 constexpr int kMaxCls = 64; // colour classes (greedy colouring, degree <= 63)
+constexpr int kResMax = 15; // neighbours of a resident unit's position kept in registers
+constexpr int kResPad = 16; // entries past the resident adjacency (reads past a row stay inside)
 // LDS byte offsets of the flip-spreading table (256 words) and of the spin
 // words: the compact tables come first, so that all three are addressed
 // with the instructions' constant offsets
@@ -202,9 +207,9 @@ __device__ __forceinline__ void load_ents(PE ent, Stage& st)
 // or cB (c odd, RPAD 8, 8-bit fields) at bit fsh(c).  Returns this lane's
 // flips in spin-word form (chain c's flip at bit c P).  The counts index the
 // full tables (x = deg - 2 cnt at word c kTab + 64 - x).
-template <int RPAD>
+template <int RPAD, class HALF>
 __device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up, const VbLds& L,
-                                                   const uint32_t* gx, uint32_t cA, uint32_t cB, int32_t deg,
+                                                   const uint32_t* gx, HALF&& half, uint32_t cA, uint32_t cB, int32_t deg,
                                                    bool act, int32_t q, uint32_t t, int32_t nch, uint64_t key)
 {
     using S = Sl<RPAD>;
@@ -224,18 +229,22 @@ __device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up
     const char* tb = (const char*)L.thr + (uint32_t)(64 - deg) * 4u;
     auto thr_of = [&](int c, uint32_t cnt) -> uint32_t { return *(const uint32_t*)(tb + c * kTab * 4 + (cnt << 3)); };
     const uint32_t hs = 16u * (hsel & 1u);
-    uint32_t fl = 0;
-    bool tie = false;
+    // e = A - thr (|e| < 2^18): a flip iff e < 0, a tie iff e = 0
+    uint32_t fl = 0, emin = 0xFFFFFFFFu;
+    auto chain = [&](int c) {
+        const uint32_t e = half(c) - thr_of(c, count(c));
+        fl |= (e >> 31) << (c * S::P);
+        emin = min(emin, e);
+    };
+    // a unit with RPAD slots has more than RPAD / 2 chains: those are decided
+    // without a test (in one block, so that their LDS reads are issued together)
 #pragma unroll
-    for (int c = 0; c < RPAD; ++c) {
-        if (c < nch) {
-            const uint32_t th = thr_of(c, count(c));
-            const uint32_t rh = __builtin_amdgcn_ubfe(gx[4 * c], hs, 16u);
-            tie = tie || rh == th;
-            fl |= rh < th ? 1u << (c * S::P) : 0u;
-        }
-    }
+    for (int c = 0; c <= RPAD / 2; ++c) chain(c);
+#pragma unroll
+    for (int c = RPAD / 2 + 1; c < RPAD; ++c)
+        if (c < nch) chain(c);
     fl = act ? fl : 0u;
+    const bool tie = emin == 0u;
     if (__builtin_amdgcn_ballot_w64(act && tie) != 0ull) {
         // A equals the high half of the threshold (those lanes did not flip
         // above): decide on the low half (rare: a loop, not unrolled)
@@ -269,8 +278,9 @@ __device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up
 // decides: a flip iff e < 0, a tie iff e = 0.  The sign bits are shifted into a flip vector (bit c: chain c, from
 // the highest chain down), which the spreading table turns into spin-word
 // form; ties are detected by the running unsigned minimum of e.
+template <class HALF>
 __device__ __forceinline__ uint32_t vb_decide_compact(const VbUnit* __restrict__ up, const VbLds& L,
-                                                      const uint32_t* gx, uint32_t cA, int32_t deg, bool act,
+                                                      const uint32_t* gx, HALF&& half, uint32_t cA, int32_t deg, bool act,
                                                       int32_t q, uint32_t t, int32_t nch, uint64_t key)
 {
     typedef const __attribute__((address_space(3))) uint32_t lds_u32;
@@ -283,7 +293,7 @@ __device__ __forceinline__ uint32_t vb_decide_compact(const VbUnit* __restrict__
     uint32_t fv = 0u, emin = 0xFFFFFFFFu;
     auto chain = [&](int c) {
         const uint32_t off = __builtin_amdgcn_ubfe((c & 1) ? oO : oE, 8u * (uint32_t)(c >> 1), 8u);
-        const uint32_t e = (uint32_t)rp[8 * c] - *(lds_u32*)(size_t)(off + (uint32_t)(c * kThc * 4));
+        const uint32_t e = half(c) - *(lds_u32*)(size_t)(off + (uint32_t)(c * kThc * 4));
         fv = __builtin_amdgcn_alignbit(fv, e, 31u);
         emin = min(emin, e);
     };
@@ -319,13 +329,14 @@ __device__ __forceinline__ uint32_t vb_decide_compact(const VbUnit* __restrict__
     return fl;
 }
 
-template <int RPAD>
+// half(c): the lane's random half-word for chain c (a constant in the calls).
+template <int RPAD, class HALF>
 __device__ __forceinline__ uint32_t vb_decide(const VbUnit* __restrict__ up, const VbLds& L, const uint32_t* gx,
-                                              uint32_t cA, uint32_t cB, bool wide, int32_t deg, bool act,
+                                              HALF&& half, uint32_t cA, uint32_t cB, bool wide, int32_t deg, bool act,
                                               int32_t q, uint32_t t, int32_t nch, uint64_t key)
 {
-    if (RPAD == 8 && !wide) return vb_decide_compact(up, L, gx, cA, deg, act, q, t, nch, key);
-    return vb_decide_full<RPAD>(up, L, gx, cA, cB, deg, act, q, t, nch, key);
+    if (RPAD == 8 && !wide) return vb_decide_compact(up, L, gx, half, cA, deg, act, q, t, nch, key);
+    return vb_decide_full<RPAD>(up, L, gx, half, cA, cB, deg, act, q, t, nch, key);
 }
 
 // Updates the positions of one chunk for every chain of the unit and returns
@@ -337,9 +348,6 @@ __device__ __forceinline__ uint32_t vb_chunk(const VbUnit* __restrict__ up, cons
                                              uint64_t key, const uint32_t* gx)
 {
     using S = Sl<RPAD>;
-    // adjacency resident in LDS: such units are small and bound by the
-    // latency of a chunk, not by instruction issue
-    constexpr bool LAT = !__is_same(PE, const SG_G uint32_t*);
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int32_t q = st.q;
@@ -371,26 +379,10 @@ __device__ __forceinline__ uint32_t vb_chunk(const VbUnit* __restrict__ up, cons
     uint32_t cA = 0, cB = 0;
     const bool wide = RPAD == 8 && __any(deg > 15);
     if (!wide) {
-        if (LAT) {
-            // every prefetched neighbour word is read before any is counted,
-            // so that the LDS round trips overlap; a lane past its degree
-            // reads its own word, whose contribution is zero (an inactive
-            // lane reads word 0: its counts stay below 9 and are not used)
-            const uint32_t qa = act ? (uint32_t)q : 0u;
-            uint32_t wv[kDMax];
 #pragma unroll
-            for (int d = 0; d < kDMax; ++d) {
-                const uint32_t en = d < deg ? st.e[d] : qa;
-                wv[d] = (spw(S::boff(en)) >> (en & (uint32_t)(S::P - 1))) ^ (uint32_t)((int32_t)en >> 31);
-            }
-#pragma unroll
-            for (int d = 0; d < kDMax; ++d) cA += (wv[d] ^ o0) & S::M;
-        } else {
-#pragma unroll
-            for (int d = 0; d < kDMax; ++d) {
-                if (!__any(d < deg)) break;
-                if (d < deg) cA += unsat(st.e[d]) & S::M;
-            }
+        for (int d = 0; d < kDMax; ++d) {
+            if (!__any(d < deg)) break;
+            if (d < deg) cA += unsat(st.e[d]) & S::M;
         }
         for (int32_t d = kDMax; d < deg; ++d) cA += unsat(ent[st.r0 + d]) & S::M;
     } else {
@@ -402,7 +394,9 @@ __device__ __forceinline__ uint32_t vb_chunk(const VbUnit* __restrict__ up, cons
         }
     }
 
-    const uint32_t fl = vb_decide<RPAD>(up, L, gx, cA, cB, wide, deg, act, q, t, nch, key);
+    const uint32_t fl = vb_decide<RPAD>(
+        up, L, gx, [&](int c) { return (uint32_t)((const uint16_t*)(gx + 4 * c))[lane & 1]; }, cA, cB, wide, deg, act, q, t,
+        nch, key);
     // write the flips back: every lane XORs its flips into its spin word (the
     // P lanes of a word are in this wavefront's chunk, nothing else writes it)
     if (fl) {
@@ -716,6 +710,18 @@ template <int RPAD, bool SPLIT, bool CPL, class PR, class PE, class PC>
 __device__ bool vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PC cls, int64_t t0,
                         int32_t nsw, int64_t t_max, int lane, int wave, int W);
 
+// A resident unit's chunks, in the order of a sweep (in LDS).
+struct ResTab {
+    int32_t base;     // first position (a multiple of 64)
+    int32_t span;     // first and one past the last active lane: lo | hi << 8
+    int32_t before;   // chunks of the classes before in the sweep
+};
+
+template <int RPAD>
+__device__ void vb_loop_res(const VbUnit* __restrict__ up, const VbLds& L, const int32_t* row, const uint32_t* ent,
+                            const ResTab* tab, uint32_t* done, const int32_t* cls, int64_t t0, int32_t nsw, int64_t t_max,
+                            int lane, int wave, int W);
+
 // (each variant is a function of its own so that its registers are
 // allocated for it alone)
 template <int RPAD, bool RES, bool SPLIT, bool CPL>
@@ -772,15 +778,32 @@ __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, 
     const int32_t* cls = L.cls;
     __syncthreads();
     if (RES) {
-        const int32_t n = up->n;
+        // row starts, and the entries in the form of vb_cpl_entries
+        const int32_t n = up->n, m2 = up->m2;
         const SG_G int32_t* grow = gl(up->row);
         const SG_G uint32_t* gent = gl(up->ent);
         for (int32_t i = tid; i <= n; i += nthr) L.area[i] = grow[i];
         uint32_t* re = (uint32_t*)(L.area + n + 1);
-        for (int32_t i = tid; i < up->m2 + kVbEntPad; i += nthr) re[i] = i < up->m2 ? gent[i] : 0u;
+        const uint32_t cofs = L.cp_lds - L.sp_lds;
+        for (int32_t i = tid; i < m2 + kResPad; i += nthr) {
+            const uint32_t en = i < m2 ? gent[i] : 0u;
+            re[i] = ((L.sp_lds + Sl<RPAD>::boff(en) + ((int32_t)en < 0 ? cofs : 0u)) << 5) | (en & (uint32_t)(Sl<RPAD>::P - 1));
+        }
+        // chunks of the sweep, after the entries
+        ResTab* tab = (ResTab*)(re + m2 + kResPad);
+        int32_t chunks = 0;
+        for (int32_t k = 0; k < ncls; ++k) {
+            const int32_t lo = cls[k], hi = cls[k + 1], b0 = lo & ~63, nck = hi > lo ? ((hi - 1) >> 6) - (lo >> 6) + 1 : 0;
+            for (int32_t j = tid; j < nck; j += nthr) {
+                const int32_t base = b0 + 64 * j;
+                tab[chunks + j] = ResTab{base, max(lo - base, 0) | min(hi - base, 64) << 8, chunks};
+            }
+            chunks += nck;
+        }
+        uint32_t* done = (uint32_t*)L.flag;
+        if (tid == 0) *done = 0u;
         __syncthreads();
-        vb_loop<RPAD, false, CPL>(up, L, (const int32_t*)L.area, (const uint32_t*)(L.area + n + 1), cls, t0, nsw,
-                                  t_max, lane, wave, W);
+        vb_loop_res<RPAD>(up, L, (const int32_t*)L.area, re, tab, done, cls, t0, nsw, t_max, lane, wave, W);
     } else {
         vb_loop<RPAD, SPLIT, CPL>(up, L, gl(up->row), gl(CPL ? up->entc : up->ent), cls, t0, nsw, t_max, lane,
                                   wave, W);
@@ -877,6 +900,23 @@ __device__ __forceinline__ void acc_add(VbAcc<RPAD>& a, uint32_t fl, const VbLds
         if (a.cn == 255) acc_flush(a, L, nch);
     } else if (RPAD == 2) {
         if (a.cn == 65535) acc_flush(a, L, nch);
+    }
+}
+
+// The end of a sweep: snapshot at a grid time, windowed correlation.
+template <int RPAD, bool SPLIT>
+__device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, const VbLds& L, int64_t tn, int64_t t_max)
+{
+    const bool grid = tn <= t_max && (tn & (tn - 1)) == 0;
+    const int32_t kn = grid ? 1 + (63 - __clzll((unsigned long long)tn)) : -1;
+    if (grid) {
+        if (!SPLIT || up->member == 0) vb_snapshot<RPAD>(up, L.sp, kn);
+        __syncthreads();
+    }
+    if (up->kw > 0 && tn <= t_max) {
+        vb_window<RPAD>(up, L.sp_lds, L.sp_lds + (uint32_t)((const char*)L.wacc - (const char*)L.sp), tn,
+                        kn < up->kw ? kn : -1);
+        __syncthreads();
     }
 }
 
@@ -987,20 +1027,214 @@ __device__ bool vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, P
         }
         acc_fold(acc);
         acc_flush(acc, L, nch);
-        const int64_t tn = t0 + s + 1;
-        const bool grid = tn <= t_max && (tn & (tn - 1)) == 0;
-        const int32_t kn = grid ? 1 + (63 - __clzll((unsigned long long)tn)) : -1;
-        if (grid) {
-            if (!SPLIT || up->member == 0) vb_snapshot<RPAD>(up, L.sp, kn);
-            __syncthreads();
-        }
-        if (up->kw > 0 && tn <= t_max) {
-            vb_window<RPAD>(up, L.sp_lds, L.sp_lds + (uint32_t)((const char*)L.wacc - (const char*)L.sp), tn,
-                            kn < up->kw ? kn : -1);
-            __syncthreads();
-        }
+        vb_sweep_end<RPAD, SPLIT>(up, L, t0 + s + 1, t_max);
     }
     return true;
+}
+
+// Resident units: small graphs whose adjacency stays in LDS.  A sweep is a chain
+// of colour classes, and a wavefront issues an instruction about every 8 cycles
+// whatever else runs: what counts is the number of instructions between the last
+// flip of a class and the first read of the next.  So nothing but the reads of the
+// spin words, the counts, the decision and the write-back stands there: the
+// wavefronts meet at no barrier but at a counter of finished chunks in LDS
+// (wavefronts not needed for a class are not waited for), and each chunk is
+// prepared ahead, while other wavefronts do the classes between a wavefront's
+// chunks: its neighbours' addresses (the own word's past the degree: no
+// contribution) and its random half-words are then in registers.
+// The update itself (about 60 instructions for 2 chains) runs at a raised wave
+// priority.  Measured for one unit of 1024 spins in 5 classes, us per sweep, against
+// the same unit with a barrier after each class (the wavefronts then wait at every
+// barrier for the ones that prepare): 1 chain 1.94 (8.0), 2 chains 2.06 (8.3), 4
+// chains 2.4 (9.0), 8 chains 3.4 (8.4); 2048 such units of 2 chains 11.2 (27).  What
+// bounds it now is the chain counter - spin words - count - threshold - flip of
+// each class, about 960 cycles.
+//
+// The chunks of a sweep are numbered through its classes and dealt to the
+// wavefronts in turn, so that a wavefront's chunks lie in different classes while
+// they can.  A chunk waits until all chunks of the classes before are finished;
+// the wavefronts take their chunks in order, so the lowest unfinished one never
+// waits for another and every wait ends.
+template <int RPAD>
+struct ResChunk {
+    uint32_t own;            // own word's entry (LDS address << 5 | shift)
+    uint32_t ad[kResMax];    // neighbours: LDS addresses of their words (of the complements when J < 0)
+    uint32_t sh[kResMax];    // ... and shifts (low 5 bits)
+    uint32_t rh[RPAD];       // random half-words (2^17 in inactive lanes: above every threshold)
+    int32_t q, r0, deg;      // deg 0 for inactive lanes
+    int32_t before;
+    int32_t size;            // neighbours read: 4, 8, 12, kResMax; -1: rows of any length
+};
+
+template <int RPAD>
+__device__ __forceinline__ void res_prepare(ResChunk<RPAD>& C, const VbLds& L, const int32_t* row,
+                                            const uint32_t* ent, const ResTab* tab, int32_t nch, const uint32_t* gx)
+{
+    using S = Sl<RPAD>;
+    const int lane = threadIdx.x & 63;
+    const int32_t base = tab->base, span = tab->span;
+    C.before = __builtin_amdgcn_readfirstlane(tab->before);
+    C.q = base + lane;
+    const bool act = lane >= (span & 255) && lane < (span >> 8);
+    const int32_t qa = act ? C.q : base;
+    const int32_t r0 = row[qa], deg = act ? row[qa + 1] - r0 : 0;
+    C.r0 = r0;
+    C.deg = deg;
+    C.own = ((L.sp_lds + S::boff((uint32_t)C.q)) << 5) | ((uint32_t)C.q & (uint32_t)(S::P - 1));
+    C.size = !__any(deg > 4) ? 4 : !__any(deg > 8) ? 8 : !__any(deg > 12) ? 12 : !__any(deg > kResMax) ? kResMax : -1;
+    auto take = [&](int d0, int d1) __attribute__((always_inline)) {
+        uint32_t en[4];
+#pragma unroll
+        for (int d = d0; d < d1; ++d) en[d - d0] = ent[r0 + d];
+#pragma unroll
+        for (int d = d0; d < d1; ++d) {
+            const uint32_t e = d < deg ? en[d - d0] : C.own;
+            C.ad[d] = e >> 5;
+            C.sh[d] = e;
+        }
+    };
+    const uint16_t* rp = (const uint16_t*)gx + (lane & 1);
+#pragma unroll
+    for (int c = 0; c < RPAD; ++c) C.rh[c] = act && c < nch ? (uint32_t)rp[8 * c] : 0x20000u;
+    if (C.size < 0) return;
+    take(0, 4);
+    if (C.size > 4) {
+        take(4, 8);
+        if (C.size > 8) {
+            take(8, 12);
+            if (C.size > 12) take(12, kResMax);
+        }
+    }
+}
+
+// Returns this lane's flips in spin-word form.
+template <int RPAD>
+__device__ __forceinline__ uint32_t res_update(const ResChunk<RPAD>& C, const VbUnit* __restrict__ up, const VbLds& L,
+                                               const uint32_t* ent, uint32_t t, int32_t nch, uint64_t key,
+                                               const uint32_t* gx)
+{
+    using S = Sl<RPAD>;
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    auto word = [&](uint32_t a) -> uint32_t { return *(const lds_u32*)(size_t)a; };
+    const uint32_t oa = C.own >> 5;
+    uint32_t cA = 0u, cB = 0u;
+    bool wide = false;
+    auto sum = [&](auto nd) __attribute__((always_inline)) {
+        constexpr int N = decltype(nd)::value;
+        uint32_t w[N];
+        const uint32_t ow = word(oa);
+#pragma unroll
+        for (int d = 0; d < N; ++d) w[d] = word(C.ad[d]);
+        const uint32_t o0 = ow >> (C.own & 31u);
+#pragma unroll
+        for (int d = 0; d < N; ++d) cA += ((w[d] >> (C.sh[d] & 31u)) ^ o0) & S::M;
+    };
+    if (C.size == 4) {
+        sum(std::integral_constant<int, 4>{});
+    } else if (C.size == 8) {
+        sum(std::integral_constant<int, 8>{});
+    } else if (C.size == 12) {
+        sum(std::integral_constant<int, 12>{});
+    } else if (C.size > 0) {
+        sum(std::integral_constant<int, kResMax>{});
+    } else {
+        // (with 8 slots the 4-bit counts would overflow: bytes, even chains in
+        // cA and odd ones in cB)
+        wide = RPAD == 8;
+        const uint32_t o0 = word(oa) >> (C.own & 31u);
+        for (int32_t d = 0; d < C.deg; ++d) {
+            const uint32_t en = ent[C.r0 + d];
+            const uint32_t f = (word(en >> 5) >> (en & 31u)) ^ o0;
+            cA += f & (RPAD == 8 ? 0x01010101u : S::M);
+            if (RPAD == 8) cB += (f >> 4) & 0x01010101u;
+        }
+    }
+    const uint32_t fl = vb_decide<RPAD>(up, L, gx, [&](int c) { return C.rh[c]; }, cA, cB, wide, C.deg, true, C.q, t, nch, key);
+    if (fl) {
+        const uint32_t f = fl << (C.own & 31u);
+        __atomic_fetch_xor((lds_u32*)(size_t)oa, f, __ATOMIC_RELAXED);
+        __atomic_fetch_xor((lds_u32*)(size_t)(oa + (L.cp_lds - L.sp_lds)), f, __ATOMIC_RELAXED);
+    }
+    return fl;
+}
+
+template <int RPAD>
+__device__ void vb_loop_res(const VbUnit* __restrict__ up, const VbLds& L, const int32_t* row, const uint32_t* ent,
+                            const ResTab* tab, uint32_t* done, const int32_t* cls, int64_t t0, int32_t nsw, int64_t t_max,
+                            int lane, int wave, int W)
+{
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    const int32_t nch = __builtin_amdgcn_readfirstlane(up->nch), ncls = __builtin_amdgcn_readfirstlane(up->ncls);
+    nsw = __builtin_amdgcn_readfirstlane(nsw);
+    W = __builtin_amdgcn_readfirstlane(W);
+    t0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)((uint64_t)t0 >> 32)) << 32) |
+                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)t0));
+    const uint64_t key = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(up->key >> 32)) << 32) |
+                         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)up->key);
+    const bool win = __builtin_amdgcn_readfirstlane(up->kw) > 0;
+    int32_t chunks = 0;
+    for (int32_t k = 0; k < ncls; ++k) chunks += n_chunks(cls, k);
+    // (wavefronts past the chunks of a sweep only take part in its end)
+    const int32_t step = min(W, chunks);
+    const int32_t B = vb_batch_chunks(nch);
+    const uint32_t mul = (65536u + (uint32_t)nch - 1u) / (uint32_t)nch;
+    const uint32_t fdq = ((uint32_t)lane * mul) >> 16;           // lane / nch = 8 i + g
+    const uint32_t fc = (uint32_t)lane - fdq * (uint32_t)nch, fi = min(fdq >> 3, (uint32_t)(B - 1));
+    const uint32_t frep = L.ri[2 * fc], finst = L.ri[2 * fc + 1];
+    const uint32_t* xg = (const uint32_t*)(L.xch + wave * 64) + (uint32_t)(lane >> 3) * (uint32_t)nch * 4u + ((uint32_t)(lane & 7) >> 1);
+    VbAcc<RPAD> acc;
+    ResChunk<RPAD> C;
+    int32_t id = wave, ps = wave < step ? 0 : nsw;   // the prepared chunk and its sweep
+    int32_t bi = B;                                  // its place in the batch of random numbers
+    auto prepare = [&]() __attribute__((always_inline)) {
+        if (bi >= B) {
+            // lane m draws group g of chain c for this wavefront's i-th chunk from here on, m = (8 i + g) nch + c
+            int32_t fid = id + (int32_t)fi * step;
+            uint32_t ft = (uint32_t)t0 + (uint32_t)ps;
+            while (fid >= chunks) {
+                fid -= chunks;
+                ++ft;
+            }
+            const U4 A = philox_stream(key, ((uint32_t)tab[fid].base >> 3) + (fdq & 7u), ft, kDomSweepHi, frep, finst);
+            L.xch[wave * 64 + lane] = make_uint4(A.x, A.y, A.z, A.w);
+            wave_sync();
+            bi = 0;
+        }
+        res_prepare<RPAD>(C, L, row, ent, tab + id, nch, xg + (uint32_t)bi * 32u * (uint32_t)nch);
+    };
+    if (ps < nsw) prepare();
+    lds_u32* fin = (lds_u32*)done;
+    uint32_t first = 0u;   // number of the sweep's first chunk
+    for (int32_t s = 0; s < nsw; ++s, first += (uint32_t)chunks) {
+        while (ps == s) {
+            const uint32_t need = first + (uint32_t)C.before;
+            while ((int32_t)(__builtin_amdgcn_readfirstlane(*(volatile lds_u32*)fin) - need) < 0) {}
+            wave_sync();
+            __builtin_amdgcn_s_setprio(3);
+            const uint32_t fl = res_update<RPAD>(C, up, L, ent, (uint32_t)t0 + (uint32_t)s, nch, key, xg + (uint32_t)bi * 32u * (uint32_t)nch);
+            // (the LDS operations of a wavefront take effect in order)
+            wave_sync();
+            if (lane == 0) __atomic_fetch_add(fin, 1u, __ATOMIC_RELAXED);
+            __builtin_amdgcn_s_setprio(0);
+            wave_sync();
+            acc_add(acc, fl, L, nch);
+            ++bi;
+            id += step;
+            if (id >= chunks) {
+                id -= chunks;
+                ++ps;
+            }
+            if (ps < nsw) prepare();
+        }
+        const int64_t tn = t0 + s + 1;
+        if (tn <= t_max && (win || (tn & (tn - 1)) == 0)) {
+            __syncthreads();
+            vb_sweep_end<RPAD, false>(up, L, tn, t_max);
+        }
+    }
+    acc_fold(acc);
+    acc_flush(acc, L, nch);
+    __syncthreads();
 }
 
 // t0p: device-resident number of sweeps done before this launch (read once;
@@ -1024,10 +1258,10 @@ __global__ void __launch_bounds__(1024) vb_sweep_kernel(const VbUnit* __restrict
     const int64_t t0 = *gl(t0p);
     if (up->resident) {
         switch (up->rpad) {
-            case 1: vb_run<1, true, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 2: vb_run<2, true, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 4: vb_run<4, true, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            default: vb_run<8, true, false, false>(up, smem, lds0, t0, nsw, t_max); break;
+            case 1: vb_run<1, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
+            case 2: vb_run<2, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
+            case 4: vb_run<4, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
+            default: vb_run<8, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
         }
     } else if (up->members > 1) {
         switch (up->rpad) {
@@ -1099,9 +1333,11 @@ __global__ void __launch_bounds__(1024) vb_init_kernel(const VbUnit* __restrict_
 
 }  // namespace
 
-size_t vb_resident_bytes(int32_t n, int32_t m2)
+size_t vb_resident_bytes(int32_t n, int32_t m2, int32_t ncls)
 {
-    return ((size_t)(n + 1 + m2 + kVbEntPad) * 4 + 15) & ~(size_t)15;
+    // row starts, entries, chunks (a class boundary inside a block of 64 positions adds one)
+    const size_t chunks = (size_t)n / 64 + 1 + (size_t)ncls;
+    return ((size_t)(n + 1 + m2 + kResPad) * 4 + chunks * sizeof(ResTab) + 15) & ~(size_t)15;
 }
 
 size_t vb_lds_bytes(int32_t n, int32_t rpad, int32_t nch, int threads, bool cpl)
