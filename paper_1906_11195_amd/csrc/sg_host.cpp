@@ -286,21 +286,27 @@ void parallel_for(size_t count, F&& f)
     }
     std::atomic<size_t> next{0};
     std::atomic<int> err{0};
-    std::vector<std::thread> th;
-    for (size_t t = 0; t < nt; ++t)
-        th.emplace_back([&]() {
-            for (;;) {
-                const size_t i = next.fetch_add(1);
-                if (i >= count) break;
-                try {
-                    f(i);
-                } catch (const Fail& e) {
-                    err.store(e.code);
-                } catch (...) {
-                    err.store(SG_ENOMEM);
-                }
+    auto work = [&]() {
+        for (;;) {
+            const size_t i = next.fetch_add(1);
+            if (i >= count) break;
+            try {
+                f(i);
+            } catch (const Fail& e) {
+                err.store(e.code);
+            } catch (...) {
+                err.store(SG_ENOMEM);
             }
-        });
+        }
+    };
+    std::vector<std::thread> th;
+    try {
+        th.reserve(nt - 1);
+        for (size_t t = 1; t < nt; ++t) th.emplace_back(work);
+    } catch (...) {
+        // fewer threads than asked for: the ones there are do the work
+    }
+    work();
     for (auto& x : th) x.join();
     if (err.load() != 0) fail(err.load());
 }
@@ -452,12 +458,14 @@ struct sg_ctx {
     double* bpart_d = nullptr;            // their partial sums
     // measurement
     MeasureChain* mc_d = nullptr;
-    int32_t* pairs_d = nullptr;
     int n_pairs = 0;
     int max_words = 0;
     long long* bond_d = nullptr;
-    long long* overlap_d = nullptr;
-    long long* gram_d = nullptr;
+    // counts behind overlaps and Gram matrices, zero between measurements
+    // (unless one failed: cleared before the next)
+    uint32_t* ovl_cnt_d = nullptr;        // [n_pairs][K]
+    uint32_t* gram_cnt_d = nullptr;       // [n_chains][K (K - 1) / 2]
+    bool cnt_dirty = true;
     unsigned long long* acc_d = nullptr;
 
     void* dev_alloc(size_t bytes)
@@ -502,6 +510,7 @@ struct sg_ctx {
     }
     template <class T>
     T* at(size_t off) { return reinterpret_cast<T*>(static_cast<char*>(arena) + off); }
+    int64_t n_of_chain(size_t ch) const { return n_of[ch / (size_t)R]; }
     int32_t k_done() const
     {
         int32_t k = 0;
@@ -549,6 +558,12 @@ void setup_common(sg_ctx* c, const sg_opts* o)
     hipDeviceProp_t prop;
     hip_check(hipGetDeviceProperties(&prop, c->device));
     if (std::strncmp(prop.gcnArchName, "gfx950", 6) != 0) fail(SG_EDEVICE);
+}
+
+// Words of the measurement counts.
+size_t cnt_words(const sg_ctx* c)
+{
+    return (size_t)c->n_chains * c->K * (c->K - 1) / 2 + (size_t)c->n_pairs * c->K + 2;
 }
 
 // Enqueues `nsw` sweeps of every launch group on stream s: the groups after
@@ -993,10 +1008,8 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     const size_t off_err = A.take(8);
     const size_t off_mc = A.take((size_t)c->n_chains * sizeof(MeasureChain));
     c->n_pairs = count * c->R * (c->R - 1) / 2;
-    const size_t off_pairs = A.take((size_t)std::max(1, c->n_pairs) * 8);
     const size_t off_bond = A.take((size_t)c->n_chains * c->K * 8);
-    const size_t off_ovl = A.take((size_t)std::max(1, c->n_pairs) * c->K * 8);
-    const size_t off_gram = A.take((size_t)c->n_chains * c->K * c->K * 8);
+    const size_t off_cnt = A.take(cnt_words(c) * 4);
     const size_t off_acc = A.take((size_t)c->n_chains * 8);
     const size_t off_t = A.take(16);
 
@@ -1236,26 +1249,16 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         const int64_t n = c->n_of[(size_t)(ch / c->R)];
         mc[(size_t)ch] = MeasureChain{c->at<uint32_t>(off_snap[(size_t)ch]), (int32_t)((n + 31) / 32), (int32_t)n};
     }
-    std::vector<int32_t> pairs;
-    for (int32_t i = 0; i < count; ++i)
-        for (int32_t a = 0; a < c->R; ++a)
-            for (int32_t b = a + 1; b < c->R; ++b) {
-                pairs.push_back(i * c->R + a);
-                pairs.push_back(i * c->R + b);
-            }
     c->units_d = c->at<VbUnit>(off_units);
     c->unit_chain_ids_d = c->at<int32_t>(off_ids);
     c->mc_d = c->at<MeasureChain>(off_mc);
-    c->pairs_d = c->at<int32_t>(off_pairs);
     c->bond_d = c->at<long long>(off_bond);
-    c->overlap_d = c->at<long long>(off_ovl);
-    c->gram_d = c->at<long long>(off_gram);
+    c->gram_cnt_d = c->at<uint32_t>(off_cnt);
+    c->ovl_cnt_d = c->gram_cnt_d + (size_t)c->n_chains * c->K * (c->K - 1) / 2;
     c->acc_d = c->at<unsigned long long>(off_acc);
     hip_check(hipMemcpy(c->units_d, c->units.data(), c->units.size() * sizeof(VbUnit), hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->unit_chain_ids_d, ids.data(), ids.size() * 4, hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->mc_d, mc.data(), mc.size() * sizeof(MeasureChain), hipMemcpyHostToDevice));
-    if (!pairs.empty())
-        hip_check(hipMemcpy(c->pairs_d, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice));
     c->t_dev = c->at<int64_t>(off_t);
     c->win_d = c->at<long long>(off_win);
     if (c->kw > 0) {
@@ -1338,9 +1341,12 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
         const size_t wn = (size_t)((d[i].n + 31) / 32);
         c->max_words = std::max(c->max_words, (int)wn);
         c->sk_max_n = std::max(c->sk_max_n, (int)d[i].n);
+        for (int32_t r = 0; r < c->R; ++r) off_state[(size_t)(i * c->R + r)] = A.take(wn * 4);   // (one range: sg_measure)
+    }
+    for (int32_t i = 0; i < count; ++i) {
+        const size_t wn = (size_t)((d[i].n + 31) / 32);
         for (int32_t r = 0; r < c->R; ++r) {
             const size_t ch = (size_t)(i * c->R + r);
-            off_state[ch] = A.take(wn * 4);
             off_H[ch] = A.take((size_t)d[i].n * 8);
             off_snap[ch] = A.take(wn * (size_t)c->K * 4);
             if (d[i].start == SG_START_GIVEN) off_given[ch] = A.take(wn * 4);
@@ -1350,10 +1356,8 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     const size_t off_samples = A.take((size_t)count * sizeof(SkSample));
     const size_t off_mc = A.take((size_t)c->n_chains * sizeof(MeasureChain));
     c->n_pairs = count * c->R * (c->R - 1) / 2;
-    const size_t off_pairs = A.take((size_t)std::max(1, c->n_pairs) * 8);
     const size_t off_bond = A.take((size_t)c->n_chains * c->K * 8);
-    const size_t off_ovl = A.take((size_t)std::max(1, c->n_pairs) * c->K * 8);
-    const size_t off_gram = A.take((size_t)c->n_chains * c->K * c->K * 8);
+    const size_t off_cnt = A.take(cnt_words(c) * 4);
     const size_t off_acc = A.take((size_t)c->n_chains * 8);
     const size_t off_err = A.take(8);
     const size_t off_bondr = A.take((size_t)c->n_chains * c->K * 8);
@@ -1421,20 +1425,12 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     std::vector<MeasureChain> mc((size_t)c->n_chains);
     for (int32_t ch = 0; ch < c->n_chains; ++ch)
         mc[(size_t)ch] = MeasureChain{c->sk[(size_t)ch].snap, c->sk[(size_t)ch].words_n, c->sk[(size_t)ch].n};
-    std::vector<int32_t> pairs;
-    for (int32_t i = 0; i < count; ++i)
-        for (int32_t a = 0; a < c->R; ++a)
-            for (int32_t b = a + 1; b < c->R; ++b) {
-                pairs.push_back(i * c->R + a);
-                pairs.push_back(i * c->R + b);
-            }
     c->sk_d = c->at<SkChain>(off_chains);
     c->sks_d = c->at<SkSample>(off_samples);
     c->mc_d = c->at<MeasureChain>(off_mc);
-    c->pairs_d = c->at<int32_t>(off_pairs);
     c->bond_d = c->at<long long>(off_bond);
-    c->overlap_d = c->at<long long>(off_ovl);
-    c->gram_d = c->at<long long>(off_gram);
+    c->gram_cnt_d = c->at<uint32_t>(off_cnt);
+    c->ovl_cnt_d = c->gram_cnt_d + (size_t)c->n_chains * c->K * (c->K - 1) / 2;
     c->acc_d = c->at<unsigned long long>(off_acc);
     c->err_d = c->at<int>(off_err);
     c->bondr_d = c->at<double>(off_bondr);
@@ -1442,8 +1438,6 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     hip_check(hipMemcpy(c->sk_d, c->sk.data(), c->sk.size() * sizeof(SkChain), hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->sks_d, c->sks.data(), c->sks.size() * sizeof(SkSample), hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->mc_d, mc.data(), mc.size() * sizeof(MeasureChain), hipMemcpyHostToDevice));
-    if (!pairs.empty())
-        hip_check(hipMemcpy(c->pairs_d, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice));
     hip_check(zero_i64(c->bond_d, (size_t)c->n_chains * c->K, nullptr));
     hip_check(zero_i64((long long*)c->bondr_d, (size_t)c->n_chains * c->K, nullptr));
     hip_check(zero_i64((long long*)c->acc_d, (size_t)c->n_chains, nullptr));
@@ -1528,9 +1522,12 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
         const size_t wn = (size_t)((d[i].n + 31) / 32);
         c->max_words = std::max(c->max_words, (int)wn);
         c->sk_max_n = std::max(c->sk_max_n, (int)d[i].n);
+        for (int32_t r = 0; r < c->R; ++r) off_state[(size_t)(i * c->R + r)] = A.take(wn * 4);   // (one range: sg_measure)
+    }
+    for (int32_t i = 0; i < count; ++i) {
+        const size_t wn = (size_t)((d[i].n + 31) / 32);
         for (int32_t r = 0; r < c->R; ++r) {
             const size_t ch = (size_t)(i * c->R + r);
-            off_state[ch] = A.take(wn * 4);
             off_H[ch] = A.take((size_t)d[i].n * 4);
             off_snap[ch] = A.take(wn * (size_t)c->K * 4);
             if (d[i].start == SG_START_GIVEN) off_given[ch] = A.take(wn * 4);
@@ -1540,10 +1537,8 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     const size_t off_samples = A.take((size_t)count * sizeof(SkSample));
     const size_t off_mc = A.take((size_t)c->n_chains * sizeof(MeasureChain));
     c->n_pairs = count * c->R * (c->R - 1) / 2;
-    const size_t off_pairs = A.take((size_t)std::max(1, c->n_pairs) * 8);
     const size_t off_bond = A.take((size_t)c->n_chains * c->K * 8);
-    const size_t off_ovl = A.take((size_t)std::max(1, c->n_pairs) * c->K * 8);
-    const size_t off_gram = A.take((size_t)c->n_chains * c->K * c->K * 8);
+    const size_t off_cnt = A.take(cnt_words(c) * 4);
     const size_t off_acc = A.take((size_t)c->n_chains * 8);
     const size_t off_err = A.take(8);
     A.take(kSkOverread);   // the sweep kernel reads past the words of a matrix
@@ -1623,27 +1618,17 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     std::vector<MeasureChain> mc((size_t)c->n_chains);
     for (int32_t ch = 0; ch < c->n_chains; ++ch)
         mc[(size_t)ch] = MeasureChain{c->sk[(size_t)ch].snap, c->sk[(size_t)ch].words_n, c->sk[(size_t)ch].n};
-    std::vector<int32_t> pairs;
-    for (int32_t i = 0; i < count; ++i)
-        for (int32_t a = 0; a < c->R; ++a)
-            for (int32_t b = a + 1; b < c->R; ++b) {
-                pairs.push_back(i * c->R + a);
-                pairs.push_back(i * c->R + b);
-            }
     c->sk_d = c->at<SkChain>(off_chains);
     c->sks_d = c->at<SkSample>(off_samples);
     c->mc_d = c->at<MeasureChain>(off_mc);
-    c->pairs_d = c->at<int32_t>(off_pairs);
     c->bond_d = c->at<long long>(off_bond);
-    c->overlap_d = c->at<long long>(off_ovl);
-    c->gram_d = c->at<long long>(off_gram);
+    c->gram_cnt_d = c->at<uint32_t>(off_cnt);
+    c->ovl_cnt_d = c->gram_cnt_d + (size_t)c->n_chains * c->K * (c->K - 1) / 2;
     c->acc_d = c->at<unsigned long long>(off_acc);
     c->err_d = c->at<int>(off_err);
     hip_check(hipMemcpy(c->sk_d, c->sk.data(), c->sk.size() * sizeof(SkChain), hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->sks_d, c->sks.data(), c->sks.size() * sizeof(SkSample), hipMemcpyHostToDevice));
     hip_check(hipMemcpy(c->mc_d, mc.data(), mc.size() * sizeof(MeasureChain), hipMemcpyHostToDevice));
-    if (!pairs.empty())
-        hip_check(hipMemcpy(c->pairs_d, pairs.data(), pairs.size() * 4, hipMemcpyHostToDevice));
     hip_check(zero_i64(c->bond_d, (size_t)c->n_chains * c->K, nullptr));
     hip_check(zero_i64((long long*)c->acc_d, (size_t)c->n_chains, nullptr));
     hip_check(zero_i64((long long*)c->err_d, 1, nullptr));
@@ -1655,12 +1640,10 @@ void create_sk(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
 
 // Enqueues the measurement kernels of every grid time reached (kd of them)
 // on stream s: bond sums into bond[chains][K] (SK: 2 B, halved by the
-// caller), overlaps into overlap[pairs][K], Gram matrices into
-// gram[chains][K][K] (zeroed first: the kernel accumulates).  VB bond sums
-// of the snapshots before k_first are taken as already in `bond` (a
-// snapshot never changes once written).
-void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, long long* overlap, long long* gram, hipStream_t s,
-                 int32_t k_first = 0)
+// caller), overlaps and Gram matrices as counts.  VB bond sums of the snapshots
+// before k_first are taken as already in `bond` (a snapshot never changes once
+// written).
+void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, hipStream_t s, int32_t k_first = 0)
 {
     const int32_t K = c->K;
     if (c->kind == 0) {
@@ -1668,15 +1651,154 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, long long* overlap, lon
                           std::min(1024, c->vb_threads), c->bond_lds, s));
         hip_check(vbm_bond(c->vbm_d, (int)c->vbm.size(), k_first, kd, bond, c->vbm_ids_d, K, s));
     } else if (c->sk_real) {
-        hip_check(zero_i64(bond, (size_t)c->n_chains * K, s));
         hip_check(skg_bond(c->sks_d, c->count, c->sk_d, c->sk_max_n, c->R, kd, K, c->bpart_d, c->bondr_d, s));
     } else {
         hip_check(zero_i64(bond, (size_t)c->n_chains * K, s));
         hip_check(sk_bond(c->sks_d, c->count, c->sk_d, c->sk_max_n, kd, K, bond, s));
     }
-    hip_check(measure_overlap(c->mc_d, c->pairs_d, c->n_pairs, kd, K, overlap, s));
-    hip_check(zero_i64(gram, (size_t)c->n_chains * K * K, s));
-    hip_check(measure_gram(c->mc_d, c->n_chains, kd, K, c->max_words, gram, s));
+    if (c->cnt_dirty) hip_check(zero_i64((long long*)c->gram_cnt_d, cnt_words(c) / 2, s));
+    c->cnt_dirty = true;   // until the counts have been read (and cleared)
+    hip_check(observe(c->mc_d, c->n_chains, c->count, c->R, kd, K, c->max_words, c->gram_cnt_d, c->ovl_cnt_d, s));
+}
+
+// Mapped host memory that measurements are copied through, kept between calls
+// and shared by all contexts, threads and devices of the process: at most 16
+// blocks of 64 MiB together (an allocation costs 0.05 to 0.4 ms, more than the
+// copy itself in small calls).
+class HostBlocks {
+public:
+    struct Block {
+        void* p = nullptr;
+        size_t bytes = 0;
+    };
+    // p null if there is no such memory
+    Block get(size_t bytes)
+    {
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            auto best = free_.end();
+            for (auto it = free_.begin(); it != free_.end(); ++it)
+                if (it->bytes >= bytes && (best == free_.end() || it->bytes < best->bytes)) best = it;
+            if (best != free_.end()) {
+                const Block b = *best;
+                free_.erase(best);
+                return b;
+            }
+        }
+        Block b;
+        b.bytes = (bytes + 65535) & ~(size_t)65535;
+        if (hipHostMalloc(&b.p, b.bytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
+            (void)hipGetLastError();
+            b = Block{};
+        }
+        return b;
+    }
+    void put(const Block& b)
+    {
+        if (!b.p) return;
+        std::vector<Block> drop;
+        try {
+            std::lock_guard<std::mutex> lk(mu_);
+            free_.push_back(b);
+            size_t held = 0;
+            for (const Block& x : free_) held += x.bytes;
+            while (held > kBytes || free_.size() > kBlocks) {   // the longest unused first
+                drop.push_back(free_.front());
+                held -= free_.front().bytes;
+                free_.erase(free_.begin());
+            }
+        } catch (...) {
+            drop.push_back(b);
+        }
+        for (const Block& x : drop) (void)hipHostFree(x.p);
+    }
+
+private:
+    static constexpr size_t kBytes = (size_t)64 << 20, kBlocks = 16;
+    std::mutex mu_;
+    std::vector<Block> free_;
+};
+
+// (never destroyed: a context may outlive the static objects)
+HostBlocks& host_blocks()
+{
+    static HostBlocks* const p = new HostBlocks;
+    return *p;
+}
+
+// Device words of one measurement, brought to host memory together: by a kernel
+// that writes to mapped host memory, or, where there is none, by copies.
+class Fetch {
+public:
+    explicit Fetch(hipStream_t s) : s_(s) { list_.n = 0; }
+    ~Fetch()
+    {
+        if (pending_) (void)hipStreamSynchronize(s_);
+        host_blocks().put(block_);
+    }
+    Fetch(const Fetch&) = delete;
+    Fetch& operator=(const Fetch&) = delete;
+    // `rows` rows of `width` words, `stride` apart; the index to pass to at()
+    int add(const void* src, size_t rows, size_t width, size_t stride, bool clear = false)
+    {
+        PackSeg& g = list_.seg[list_.n];
+        g.src = (uint32_t*)src;
+        g.dst = words_;
+        g.stride = stride;
+        g.rows = (uint32_t)rows;
+        g.width = (uint32_t)width;
+        g.clear = clear ? 1u : 0u;
+        words_ += (rows * width + 1) & ~(size_t)1;
+        return list_.n++;
+    }
+    // enqueues the copies and waits for the stream
+    void run()
+    {
+        block_ = host_blocks().get(std::max<size_t>(8, words_ * 4));
+        pending_ = true;
+        if (block_.p) {
+            void* dev = nullptr;
+            hip_check(hipHostGetDevicePointer(&dev, block_.p, 0));
+            hip_check(observe_pack(list_, (uint32_t*)dev, s_));
+            base_ = (const uint32_t*)block_.p;
+        } else {
+            plain_.resize(std::max<size_t>(2, words_));
+            for (int i = 0; i < list_.n; ++i) {
+                const PackSeg& g = list_.seg[i];
+                if (g.rows && g.width)
+                    hip_check(hipMemcpy2DAsync(plain_.data() + g.dst, (size_t)g.width * 4, g.src, g.stride * 4,
+                                               (size_t)g.width * 4, g.rows, hipMemcpyDeviceToHost, s_));
+            }
+            hip_check(observe_pack(list_, nullptr, s_));
+            base_ = plain_.data();
+        }
+        hip_check(hipStreamSynchronize(s_));
+        pending_ = false;
+    }
+    template <class T>
+    const T* at(int i) const
+    {
+        return reinterpret_cast<const T*>(base_ + list_.seg[i].dst);
+    }
+
+private:
+    hipStream_t s_;
+    PackList list_;
+    size_t words_ = 0;
+    HostBlocks::Block block_;
+    std::vector<uint32_t> plain_;
+    const uint32_t* base_ = nullptr;
+    bool pending_ = false;
+};
+
+// Runs f(first, last) over 0 .. count - 1, `bytes` of output each: on host threads
+// of at least 512 KB where that makes two (fresh pages of the caller's arrays cost
+// 0.2 ms a MB, a thread about 10 us).
+template <class F>
+void in_parts(size_t count, size_t bytes, F&& f)
+{
+    const size_t parts = std::max<size_t>(1, std::min<size_t>({count, 16, count * bytes / ((size_t)512 << 10)}));
+    parallel_for(parts, [&](size_t i) { f(count * i / parts, count * (i + 1) / parts); });
 }
 
 // Number of terms of each windowed sum after the sweeps done so far: the
@@ -1707,33 +1829,10 @@ void window_counts(const sg_ctx* c, int64_t* out)
 
 static_assert(kWindowBinsMax >= 125, "m(t_max) + 1 <= 125 for t_max < 2^31");
 
-// Copies the windowed sums (sg_obs.window, caller's host array, on stream s)
-// and fills the counts; the caller synchronises s.
-void window_out(sg_ctx* c, sg_obs* out, hipStream_t s)
+void window_sizes(const sg_ctx* c, sg_obs* out)
 {
     out->kw = c->kw;
     out->n_bins = c->n_bins;
-    if (c->kw == 0) return;
-    if (out->window)
-        hip_check(hipMemcpyAsync(out->window, c->win_d, (size_t)c->n_chains * c->kw * c->n_bins * 8,
-                                 hipMemcpyDeviceToHost, s));
-    if (out->window_count) window_counts(c, out->window_count);
-}
-
-// Copies the real bond sums (SK with real couplings) into sg_obs.bond_real
-// on stream s; grid times not reached yet are zeroed after the caller's
-// synchronisation (bond_real_finish).
-void bond_real_out(sg_ctx* c, sg_obs* out, hipStream_t s)
-{
-    if (!c->sk_real || !out->bond_real) return;
-    hip_check(hipMemcpyAsync(out->bond_real, c->bondr_d, (size_t)c->n_chains * c->K * 8, hipMemcpyDeviceToHost, s));
-}
-
-void bond_real_finish(sg_ctx* c, sg_obs* out, int32_t kd)
-{
-    if (!c->sk_real || !out->bond_real) return;
-    for (size_t i = 0; i < (size_t)c->n_chains * c->K; ++i)
-        if ((int32_t)(i % c->K) >= kd) out->bond_real[i] = 0.0;
 }
 
 // After a resume (t_start > 0): the entries of the slots not taken (grid
@@ -1910,89 +2009,127 @@ sg_status sg_measure(sg_ctx* c, uint32_t flags, sg_obs* out, void* stream)
         out->k_cap = K;
         out->k_done = kd;
         out->t_done = c->t_done;
-        if (flags & SG_MEASURE_OBS) {
+        const bool obs = (flags & SG_MEASURE_OBS) != 0, spins = (flags & SG_MEASURE_SPINS) && out->spins;
+        if (!obs && !spins) return;
+        Fetch F(s);
+        const size_t nc = (size_t)c->n_chains, np = (size_t)c->n_pairs, tri = (size_t)K * (K - 1) / 2;
+        const size_t kt = (size_t)kd * (kd - 1) / 2;
+        // windowed sums beyond the interval reached are zero
+        const size_t bins = c->kw && out->window && c->t_done > c->t_start ? (size_t)vb_window_bin((uint64_t)std::min(c->t_done, c->t_max)) + 1 : 0;
+        int f_err = 0, f_acc = 0, f_bond = 0, f_real = 0, f_ovl = 0, f_gram = 0, f_win = 0, f_st = 0, f_stm = 0;
+        if (obs) {
+            window_sizes(c, out);
             // the context's bond array keeps the sums of earlier measurements
-            enqueue_obs(c, kd, c->bond_d, c->overlap_d, c->gram_d, s, c->kind == 0 ? c->bond_done : 0);
-            std::vector<long long> bond((size_t)c->n_chains * K), ovl((size_t)std::max(1, c->n_pairs) * K),
-                gram((size_t)c->n_chains * K * K);
-            std::vector<unsigned long long> acc((size_t)c->n_chains);
-            hip_check(hipMemcpyAsync(bond.data(), c->bond_d, bond.size() * 8, hipMemcpyDeviceToHost, s));
-            if (c->n_pairs)
-                hip_check(hipMemcpyAsync(ovl.data(), c->overlap_d, (size_t)c->n_pairs * K * 8, hipMemcpyDeviceToHost, s));
-            hip_check(hipMemcpyAsync(gram.data(), c->gram_d, gram.size() * 8, hipMemcpyDeviceToHost, s));
-            hip_check(hipMemcpyAsync(acc.data(), c->acc_d, acc.size() * 8, hipMemcpyDeviceToHost, s));
-            hip_check(hipMemcpyAsync(&err_flag, c->err_d, sizeof(int), hipMemcpyDeviceToHost, s));
-            window_out(c, out, s);
-            bond_real_out(c, out, s);
-            hip_check(hipStreamSynchronize(s));
+            enqueue_obs(c, kd, c->bond_d, s, c->kind == 0 ? c->bond_done : 0);
+            f_err = F.add(c->err_d, 1, 1, 1);
+            f_acc = F.add(c->acc_d, 1, nc * 2, 0);
+            if (!c->sk_real) f_bond = F.add(c->bond_d, nc, (size_t)kd * 2, (size_t)K * 2);
+            if (c->sk_real && out->bond_real) f_real = F.add(c->bondr_d, nc, (size_t)kd * 2, (size_t)K * 2);
+            f_ovl = F.add(c->ovl_cnt_d, np, (size_t)kd, (size_t)K, true);
+            f_gram = F.add(c->gram_cnt_d, nc, kt, tri, true);
+            if (bins) f_win = F.add(c->win_d, nc * c->kw, bins * 2, (size_t)c->n_bins * 2);
+        }
+        // the spin words of all units (chains), one range each
+        uint32_t *st0 = nullptr, *st1 = nullptr;
+        uint64_t *sm0 = nullptr, *sm1 = nullptr;
+        if (spins) {
+            auto range = [](auto*& lo, auto*& hi, auto* p, size_t words) {
+                if (!lo || p < lo) lo = p;
+                if (!hi || p + words > hi) hi = p + words;
+            };
+            for (const VbUnit& U : c->units) range(st0, st1, U.state, (size_t)U.state_words);
+            for (const VbmUnit& U : c->vbm) range(sm0, sm1, U.state, (size_t)U.n);
+            for (const SkChain& S : c->sk) range(st0, st1, S.state, (size_t)S.words_n);
+            if (st0) f_st = F.add(st0, 1, (size_t)(st1 - st0), 0);
+            if (sm0) f_stm = F.add(sm0, 1, (size_t)(sm1 - sm0) * 2, 0);
+        }
+        F.run();
+        if (obs) {
+            c->cnt_dirty = false;
             c->bond_done = kd;
-            bond_real_finish(c, out, kd);
+            err_flag = *F.at<int>(f_err);
             if (out->times)
                 for (int32_t k = 0; k < K; ++k) out->times[k] = c->times[(size_t)k];
-            if (out->bond)
-                for (size_t i = 0; i < bond.size(); ++i)
-                    out->bond[i] = (int64_t)i % K < kd ? (int64_t)bond[i] / (c->kind == 1 ? 2 : 1) : 0;
-            if (out->overlap && c->n_pairs)
-                for (size_t i = 0; i < (size_t)c->n_pairs * K; ++i)
-                    out->overlap[i] = (int64_t)i % K < kd ? (int64_t)ovl[i] : 0;
-            if (out->gram)
-                for (size_t i = 0; i < gram.size(); ++i) out->gram[i] = (int64_t)gram[i];
-            if (out->accepted)
-                for (size_t i = 0; i < acc.size(); ++i) out->accepted[i] = (int64_t)acc[i];
+            if (out->accepted) std::memcpy(out->accepted, F.at<int64_t>(f_acc), nc * 8);
+            const int64_t* bond = F.at<int64_t>(f_bond);
+            const double* real = F.at<double>(f_real);
+            const uint32_t* cnt = F.at<uint32_t>(f_gram);
+            const int64_t* win = F.at<int64_t>(f_win);
+            const size_t win_row = c->kw ? (size_t)c->n_bins : 0, win_chain = (size_t)c->kw * win_row;
+            in_parts(nc, (size_t)K * K * 8 + win_chain * 8, [&](size_t c0, size_t c1) {
+                for (size_t ch = c0; ch < c1; ++ch) {
+                    if (out->bond)
+                        for (int32_t k = 0; k < K; ++k)
+                            out->bond[ch * K + k] =
+                                k < kd && !c->sk_real ? bond[ch * kd + k] / (c->kind == 1 ? 2 : 1) : 0;
+                    if (c->sk_real && out->bond_real)
+                        for (int32_t k = 0; k < K; ++k) out->bond_real[ch * K + k] = k < kd ? real[ch * kd + k] : 0.0;
+                    if (out->gram) {
+                        const int64_t n = c->n_of_chain(ch);
+                        int64_t* G = out->gram + ch * K * K;
+                        std::memset(G, 0, (size_t)K * K * 8);
+                        const uint32_t* q = cnt + ch * kt;
+                        for (int32_t l = 0; l < kd; ++l) {
+                            for (int32_t k = 0; k < l; ++k) G[l * K + k] = G[k * K + l] = n - 2 * (int64_t)*q++;
+                            G[l * K + l] = n;
+                        }
+                    }
+                    if (c->kw && out->window)
+                        for (int32_t w = 0; w < c->kw; ++w) {
+                            int64_t* o = out->window + ch * win_chain + w * win_row;
+                            if (bins) std::memcpy(o, win + (ch * c->kw + w) * bins, bins * 8);
+                            std::memset(o + bins, 0, (win_row - bins) * 8);
+                        }
+                }
+            });
+            if (out->overlap && np) {
+                const uint32_t* ov = F.at<uint32_t>(f_ovl);
+                const size_t per = np / (size_t)c->count;
+                in_parts(np, (size_t)K * 8, [&](size_t p0, size_t p1) {
+                    for (size_t p = p0; p < p1; ++p) {
+                        const int64_t n = c->n_of_chain(p / per * (size_t)R);
+                        for (int32_t k = 0; k < K; ++k)
+                            out->overlap[p * K + k] = k < kd ? n - 2 * (int64_t)ov[p * kd + k] : 0;
+                    }
+                });
+            }
+            if (c->kw && out->window_count) window_counts(c, out->window_count);
             mask_untaken(c, out);
         }
-        if ((flags & SG_MEASURE_SPINS) && out->spins) {
-            hip_check(hipStreamSynchronize(s));
-            int64_t base = 0;
+        if (spins) {
             std::vector<int64_t> inst_base((size_t)c->count);
+            int64_t total = 0;
             for (int32_t i = 0; i < c->count; ++i) {
-                inst_base[(size_t)i] = base;
-                base += (int64_t)R * c->n_of[(size_t)i];
+                inst_base[(size_t)i] = total;
+                total += (int64_t)R * c->n_of[(size_t)i];
             }
-            if (c->kind == 0) {
-                std::vector<std::vector<uint32_t>> st(c->units.size());
-                for (size_t u = 0; u < c->units.size(); ++u) {
-                    st[u].resize((size_t)c->units[u].state_words);
-                    hip_check(hipMemcpy(st[u].data(), c->units[u].state, st[u].size() * 4, hipMemcpyDeviceToHost));
-                }
-                std::vector<std::vector<uint64_t>> stm(c->vbm.size());
-                for (size_t u = 0; u < c->vbm.size(); ++u) {
-                    stm[u].resize((size_t)c->vbm[u].n);
-                    hip_check(hipMemcpy(stm[u].data(), c->vbm[u].state, stm[u].size() * 8, hipMemcpyDeviceToHost));
-                }
-                for (int32_t ch = 0; ch < c->n_chains; ++ch) {
-                    const int32_t u = c->chain_loc[(size_t)ch].first, k = c->chain_loc[(size_t)ch].second;
-                    if (c->chain_ms[(size_t)ch]) {
-                        const int32_t i = ch / R, r = ch % R;
-                        const auto& order = c->order_of_group[(size_t)c->group_of_inst[(size_t)i]];
-                        const int32_t nn = c->vbm[(size_t)u].n;
-                        int8_t* dst = out->spins + inst_base[(size_t)i] + (int64_t)r * nn;
-                        for (int64_t p = 0; p < nn; ++p)
-                            dst[order[(size_t)p]] = ((stm[(size_t)u][(size_t)p] >> k) & 1ull) ? (int8_t)-1 : (int8_t)1;
+            const uint32_t* st = F.at<uint32_t>(f_st);
+            const uint64_t* stm = F.at<uint64_t>(f_stm);
+            in_parts(nc, (size_t)(total / (int64_t)nc), [&](size_t c0, size_t c1) {
+                for (size_t ch = c0; ch < c1; ++ch) {
+                    const size_t i = ch / (size_t)R, r = ch % (size_t)R;
+                    const int64_t n = c->n_of[i];
+                    int8_t* dst = out->spins + inst_base[i] + (int64_t)r * n;
+                    if (c->kind == 1) {
+                        const uint32_t* w = st + (c->sk[ch].state - st0);
+                        for (int64_t p = 0; p < n; ++p) dst[p] = ((w[p >> 5] >> (p & 31)) & 1u) ? (int8_t)-1 : (int8_t)1;
+                        continue;
+                    }
+                    const int32_t u = c->chain_loc[ch].first, k = c->chain_loc[ch].second;
+                    const auto& order = c->order_of_group[(size_t)c->group_of_inst[i]];
+                    if (c->chain_ms[ch]) {
+                        const uint64_t* w = stm + (c->vbm[(size_t)u].state - sm0);
+                        for (int64_t p = 0; p < n; ++p)
+                            dst[order[(size_t)p]] = ((w[p] >> k) & 1ull) ? (int8_t)-1 : (int8_t)1;
                         continue;
                     }
                     const VbUnit& U = c->units[(size_t)u];
-                    const int32_t i = ch / R, r = ch % R;
-                    const auto& order = c->order_of_group[(size_t)c->group_of_inst[(size_t)i]];
-                    int8_t* dst = out->spins + inst_base[(size_t)i] + (int64_t)r * U.n;
+                    const uint32_t* w = st + (U.state - st0);
                     const VbLayout lay(U.rpad);
-                    for (int64_t p = 0; p < U.n; ++p) {
-                        const uint32_t bit =
-                            (st[(size_t)u][(size_t)lay.word(p, k)] >> lay.bit(p, k)) & 1u;
-                        dst[order[(size_t)p]] = bit ? (int8_t)-1 : (int8_t)1;
-                    }
+                    for (int64_t p = 0; p < n; ++p)
+                        dst[order[(size_t)p]] = ((w[lay.word(p, k)] >> lay.bit(p, k)) & 1u) ? (int8_t)-1 : (int8_t)1;
                 }
-            } else {
-                for (int32_t ch = 0; ch < c->n_chains; ++ch) {
-                    const SkChain& S = c->sk[(size_t)ch];
-                    std::vector<uint32_t> st((size_t)S.words_n);
-                    hip_check(hipMemcpy(st.data(), S.state, st.size() * 4, hipMemcpyDeviceToHost));
-                    const int32_t i = ch / R, r = ch % R;
-                    int8_t* dst = out->spins + inst_base[(size_t)i] + (int64_t)r * S.n;
-                    for (int64_t p = 0; p < S.n; ++p)
-                        dst[p] = ((st[(size_t)(p >> 5)] >> (p & 31)) & 1u) ? (int8_t)-1 : (int8_t)1;
-                }
-            }
+            });
         }
     });
     if (st != SG_OK) return st;
@@ -2023,7 +2160,9 @@ sg_status sg_measure_noalloc(sg_ctx* c, sg_obs* out, void* stream)
         long long* bond = scr;
         long long* ovl = scr + n_bond;
         long long* gram = ovl + n_ovl;
-        enqueue_obs(c, kd, bond, ovl, gram, s);
+        if (c->sk_real) hip_check(zero_i64(bond, n_bond, s));   // (real couplings: no integer sums)
+        enqueue_obs(c, kd, bond, s);
+        hip_check(observe_expand(c->mc_d, c->n_chains, c->n_pairs, c->R, kd, c->K, c->gram_cnt_d, c->ovl_cnt_d, gram, ovl, s));
         // straight into the caller's arrays (int64 on both sides)
         if (out->bond) hip_check(hipMemcpyAsync(out->bond, bond, n_bond * 8, hipMemcpyDeviceToHost, s));
         if (out->overlap && n_ovl)
@@ -2032,10 +2171,20 @@ sg_status sg_measure_noalloc(sg_ctx* c, sg_obs* out, void* stream)
         if (out->accepted)
             hip_check(hipMemcpyAsync(out->accepted, c->acc_d, (size_t)c->n_chains * 8, hipMemcpyDeviceToHost, s));
         hip_check(hipMemcpyAsync(&err_flag, c->err_d, sizeof(int), hipMemcpyDeviceToHost, s));
-        window_out(c, out, s);
-        bond_real_out(c, out, s);
+        window_sizes(c, out);
+        if (c->kw > 0) {
+            if (out->window)
+                hip_check(hipMemcpyAsync(out->window, c->win_d, (size_t)c->n_chains * c->kw * c->n_bins * 8,
+                                         hipMemcpyDeviceToHost, s));
+            if (out->window_count) window_counts(c, out->window_count);
+        }
+        const bool real = c->sk_real && out->bond_real;
+        if (real) hip_check(hipMemcpyAsync(out->bond_real, c->bondr_d, n_bond * 8, hipMemcpyDeviceToHost, s));
         hip_check(hipStreamSynchronize(s));
-        bond_real_finish(c, out, kd);
+        c->cnt_dirty = false;
+        if (real)   // grid times not reached
+            for (size_t i = 0; i < n_bond; ++i)
+                if ((int32_t)(i % K) >= kd) out->bond_real[i] = 0.0;
         if (out->times)
             for (size_t k = 0; k < K; ++k) out->times[k] = c->times[k];
         // entries of grid times not reached hold the previous call's values

@@ -169,10 +169,29 @@ hipError_t skg_bond(const SkSample* samples, int n_samples, const SkChain* chain
 hipError_t vb_bond(const VbUnit* units, int n_units, int k_first, int k_done, long long* bond_out,
                    const int32_t* unit_chain_ids, int k_cap, int threads, size_t lds_bytes,
                    hipStream_t s);
-hipError_t measure_overlap(const MeasureChain* chains, const int32_t* pairs, int n_pairs,
-                           int k_done, int k_cap, long long* out, hipStream_t s);
-hipError_t measure_gram(const MeasureChain* chains, int n_chains, int k_done, int k_cap,
-                        int max_words, long long* out, hipStream_t s);
+// Counts of unequal spins over every pair of a chain's first k_done snapshots
+// (gram_cnt[chain][l (l - 1) / 2 + k], k < l; chains hold k_cap (k_cap - 1) / 2)
+// and of two replicas at each of those times (ovl_cnt[pair][k_cap]).  The counts
+// are zero before; observe_expand and observe_pack clear what they read.
+hipError_t observe(const MeasureChain* chains, int n_chains, int count, int R, int k_done, int k_cap, int max_words,
+                   uint32_t* gram_cnt, uint32_t* ovl_cnt, hipStream_t s);
+// The counts as Gram matrices [chain][k_cap][k_cap] and overlaps [pair][k_cap].
+hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs, int R, int k_done, int k_cap,
+                          uint32_t* gram_cnt, uint32_t* ovl_cnt, long long* gram, long long* ovl, hipStream_t s);
+// Rows of device words to consecutive words of mapped host memory.
+struct PackSeg {
+    uint32_t* src;
+    uint64_t dst;              // word of the destination
+    uint64_t stride;           // words from row to row
+    uint32_t rows, width;
+    uint32_t clear;            // set the words to zero once read
+};
+struct PackList {
+    PackSeg seg[10];
+    int n;
+};
+// (dst null: only clears)
+hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s);
 hipError_t zero_i64(long long* p, size_t n, hipStream_t s);
 // Device address of the fixed staging array (kMeasureScratchElems int64) on
 // the current device; looked up once per device.

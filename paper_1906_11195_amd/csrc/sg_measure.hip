@@ -1,13 +1,10 @@
 // Observables at the grid times, from the device-resident snapshots.
 //
 //  * Gram matrices G[k][l] = sum_i s_i(t_k) s_i(t_l) per chain (the two-time
-//    correlation C = G / N of the introduction and SI Eq. formula1).  The
-//    snapshots of a chain form an N x K matrix S of +-1 with K <= 32, and
-//    G = S^T S is an int8 contraction over N: it runs on the matrix cores as
-//    v_mfma_i32_32x32x32_i8 with int32 accumulation.  Each lane expands 16
-//    packed spins of one snapshot into 16 int8; the same register serves as
-//    the A operand (S^T) and the B operand (S).
-//  * Two-clone overlaps Q = sum_i s^a_i s^b_i = N - 2 popcount(a xor b).
+//    correlation C = G / N of the introduction and SI Eq. formula1) and
+//    two-clone overlaps Q = sum_i s^a_i s^b_i: N - 2 popcount(x xor y) over the
+//    packed spins, for every pair of rows of a set (a chain's snapshots, or the
+//    replicas' snapshots of one time).
 //  * VB bond sums B = sum_{(uv) in E} J_uv s_u s_v (energy -B, Eq. 3), one
 //    pass over the unit's adjacency per snapshot time.
 #include "sg_internal.h"
@@ -24,81 +21,201 @@ static __device__ __align__(256) long long scratch[sg::kMeasureScratchElems];
 namespace sg {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
+// Sum over the 256 threads' pair counts: grid = the Gram sets' tiles (chains x
+// g_tiles), then the overlap sets' tiles (instances x times x o_tiles).  A block
+// stages one tile of a set's rows in LDS and counts popcount(x xor y) for every
+// pair of rows.  A thread takes a 2 x 2 block of pairs (four 16-byte LDS reads
+// for 4 pairs of 128 spins) and one of `parts` interleaved column sets of the
+// tile, so that few rows still occupy the block; parts are added in LDS.  One
+// tile per set: plain stores; more: the counts are added to `gram` / `ovl`,
+// which hold zeros between measurements.
+//
+// With one bit per spin a pair of 32 spins costs an XOR and a count; on the
+// matrix cores the spins would have to be spread to bytes first, at 20
+// instructions per 16 spins of each row (below about 200 rows the pairs are
+// cheaper).  Measured, Gram matrices and overlaps together: 16384 chains of 4096
+// spins, 12 times, 28 pairs an instance 124 us (1410 + 180 us as one block per
+// pair and time and int8 products, one wavefront per 8192 spins); 1536 chains of
+// 65536 spins, 10 times, one pair 91 us (300).  Bound by staging: 2 loads in
+// flight a lane and a barrier before the counting.
+struct ObsPlan {
+    int32_t n_chains, count, R, kd;
+    int32_t g_tiles, g_words;   // tiles per chain, words per tile (a multiple of 64)
+    int32_t o_tiles, o_words;
+    int32_t g_stride, o_stride; // entries per chain (all pairs of K rows), per pair of replicas (K)
+};
 
-__device__ __forceinline__ uint32_t spread4(uint32_t nib)
+__global__ void __launch_bounds__(256) observe_kernel(const MeasureChain* __restrict__ chains, ObsPlan p,
+                                                      uint32_t* __restrict__ gram, uint32_t* __restrict__ ovl)
 {
-    return (nib * 0x00204081u) & 0x01010101u;
-}
-
-// 16 spins (1 = -1) -> 16 int8 +-1, zero where keep bit is 0.
-__device__ __forceinline__ v4i pm1_bytes(uint32_t bits, uint32_t keep)
-{
-    v4i r;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const uint32_t v = (spread4((bits >> (4 * q)) & 0xFu) * 0xFEu) ^ 0x01010101u;
-        const uint32_t kb = spread4((keep >> (4 * q)) & 0xFu) * 0xFFu;
-        r[q] = (int)(v & kb);
+    extern __shared__ __attribute__((aligned(16))) uint32_t osm[];
+    __shared__ uint32_t cnt[kMaxGrid * (kMaxGrid - 1) / 2];
+    const int tid = threadIdx.x;
+    const int32_t g_blocks = p.n_chains * p.g_tiles;
+    const bool is_gram = (int32_t)blockIdx.x < g_blocks;
+    int32_t id, tile, k = 0, chain;
+    if (is_gram) {
+        id = (int32_t)blockIdx.x / p.g_tiles;
+        tile = (int32_t)blockIdx.x - id * p.g_tiles;
+        chain = id;
+    } else {
+        const int32_t b = (int32_t)blockIdx.x - g_blocks;
+        const int32_t set = b / p.o_tiles;
+        tile = b - set * p.o_tiles;
+        id = set / p.kd;
+        k = set - id * p.kd;
+        chain = id * p.R;
     }
-    return r;
-}
-
-// grid = (chains, splits); one wavefront per block.
-__global__ void __launch_bounds__(64) gram_kernel(const MeasureChain* __restrict__ chains, int k_done,
-                                                  int k_cap, int words_per_split,
-                                                  long long* __restrict__ out)
-{
-    const MeasureChain mc = chains[blockIdx.x];
-    const int32_t wn = mc.words_n, n = mc.n;
-    const int32_t w0 = blockIdx.y * words_per_split;
-    const int32_t w1 = min(wn, w0 + words_per_split);
-    if (w0 >= w1) return;
-    const int lane = threadIdx.x;
-    const int snap = lane & 31;      // row/column of G held by this lane
-    const int half = lane >> 5;      // which 16 positions of a 32-position word
-    const bool live = snap < k_done;
-    const uint32_t* __restrict__ src = mc.snap + (int64_t)snap * wn;
-    v16i acc;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0;
-    for (int32_t w = w0; w < w1; ++w) {
-        const uint32_t word = live ? src[w] : 0u;
-        const int32_t first = 32 * w + 16 * half;
-        const int32_t valid = live ? max(0, min(16, n - first)) : 0;
-        const uint32_t keep = valid >= 16 ? 0xffffu : ((1u << valid) - 1u);
-        const v4i a = pm1_bytes((word >> (16 * half)) & 0xffffu, keep);
-        acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a, a, acc, 0, 0, 0);
+    const int32_t wn = chains[chain].words_n, n = chains[chain].n;
+    const int32_t T = is_gram ? p.g_words : p.o_words, rows = is_gram ? p.kd : p.R;
+    const int32_t w0 = tile * T;
+    if (w0 >= wn) return;
+    const int32_t nw = min(T, wn - w0), c4 = (nw + 3) >> 2, ld = T + 4;
+    const int32_t last = w0 + nw == wn && (n & 31) ? nw - 1 : -1;   // the word that ends inside
+    const uint32_t keep = last >= 0 ? (1u << (n & 31)) - 1u : ~0u;
+    // stage the rows; words past the tile are zero in every row
+    for (int32_t r = 0; r < rows; ++r) {
+        const uint32_t* src = (is_gram ? chains[chain].snap + (int64_t)r * wn : chains[chain + r].snap + (int64_t)k * wn) + w0;
+        uint32_t* dst = osm + r * ld;
+        if (((uintptr_t)src & 15) == 0) {
+            for (int32_t j = tid; j < c4; j += 256) {
+                uint4 v = make_uint4(0u, 0u, 0u, 0u);
+                const int32_t w = 4 * j;
+                if (w + 4 <= nw) {
+                    v = *(const uint4*)(src + w);
+                } else {
+                    v.x = src[w];
+                    if (w + 1 < nw) v.y = src[w + 1];
+                    if (w + 2 < nw) v.z = src[w + 2];
+                }
+                *(uint4*)(dst + w) = v;
+            }
+        } else {
+            for (int32_t w = tid; w < 4 * c4; w += 256) dst[w] = w < nw ? src[w] : 0u;
+        }
     }
-    long long* G = out + (int64_t)blockIdx.x * k_cap * k_cap;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        const int row = 8 * (r >> 2) + 4 * half + (r & 3);
-        const int col = snap;
-        if (row < k_done && col < k_done)
-            atomicAdd((unsigned long long*)&G[row * k_cap + col], (unsigned long long)(long long)acc[r]);
-    }
-}
-
-// grid = (pairs, k_done)
-__global__ void __launch_bounds__(256) overlap_kernel(const MeasureChain* __restrict__ chains,
-                                                      const int32_t* __restrict__ pairs, int k_cap,
-                                                      long long* __restrict__ out)
-{
-    __shared__ unsigned int red;
-    const int k = blockIdx.y;
-    const MeasureChain a = chains[pairs[2 * blockIdx.x]];
-    const MeasureChain b = chains[pairs[2 * blockIdx.x + 1]];
-    if (threadIdx.x == 0) red = 0;
+    const int32_t np = rows * (rows - 1) / 2;
+    for (int32_t i = tid; i < np; i += 256) cnt[i] = 0u;
     __syncthreads();
-    unsigned int cnt = 0;
-    const uint32_t* pa = a.snap + (int64_t)k * a.words_n;
-    const uint32_t* pb = b.snap + (int64_t)k * b.words_n;
-    for (int32_t w = threadIdx.x; w < a.words_n; w += blockDim.x) cnt += __popc(pa[w] ^ pb[w]);
-    atomicAdd(&red, cnt);
+    const int32_t g = (rows + 1) >> 1, nb = g * (g + 1) / 2, parts = max(1, 256 / nb);
+    if (tid < nb * parts) {
+        const int32_t part = tid / nb, blk = tid - part * nb;
+        int32_t J = 0, base = 0;
+        while (base + J + 1 <= blk) {
+            base += J + 1;
+            ++J;
+        }
+        const int32_t I = blk - base;   // I <= J
+        const int32_t a0 = 2 * I, a1 = min(2 * I + 1, rows - 1), b0 = 2 * J, b1 = min(2 * J + 1, rows - 1);
+        const uint32_t *pa0 = osm + a0 * ld, *pa1 = osm + a1 * ld, *pb0 = osm + b0 * ld, *pb1 = osm + b1 * ld;
+        uint32_t s00 = 0u, s01 = 0u, s10 = 0u, s11 = 0u;
+        const int32_t last4 = last >= 0 ? last >> 2 : -1;
+        for (int32_t j = part; j < c4; j += parts) {
+            uint4 x0 = *(const uint4*)(pa0 + 4 * j), x1 = *(const uint4*)(pa1 + 4 * j);
+            uint4 y0 = *(const uint4*)(pb0 + 4 * j), y1 = *(const uint4*)(pb1 + 4 * j);
+            if (j == last4) {
+                auto mask = [&](uint4& v) {
+                    uint32_t* e = &v.x;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (4 * j + i == last) e[i] &= keep;
+                };
+                mask(x0);
+                mask(x1);
+                mask(y0);
+                mask(y1);
+            }
+            auto add = [](uint32_t& s, const uint4& x, const uint4& y) {
+                s += __popc(x.x ^ y.x) + __popc(x.y ^ y.y) + __popc(x.z ^ y.z) + __popc(x.w ^ y.w);
+            };
+            add(s00, x0, y0);
+            add(s01, x0, y1);
+            add(s10, x1, y0);
+            add(s11, x1, y1);
+        }
+        // (k < l at l (l - 1) / 2 + k; a doubled last row or a pair of a diagonal block's mirror is dropped)
+        auto put = [&](int32_t a, int32_t b, uint32_t v) {
+            if (a < b && v != 0u) atomicAdd(&cnt[b * (b - 1) / 2 + a], v);
+        };
+        put(a0, b0, s00);
+        if (2 * J + 1 < rows) put(a0, b1, s01);
+        if (2 * I + 1 < rows) {
+            put(a1, b0, s10);
+            if (2 * J + 1 < rows) put(a1, b1, s11);
+        }
+    }
     __syncthreads();
-    if (threadIdx.x == 0) out[(int64_t)blockIdx.x * k_cap + k] = (long long)a.n - 2LL * (long long)red;
+    for (int32_t i = tid; i < np; i += 256) {
+        uint32_t* o;
+        if (is_gram) {
+            o = gram + (int64_t)id * p.g_stride + i;
+        } else {
+            // replicas (a, b) in lexicographic order
+            int32_t b = 1;
+            while ((b + 1) * b / 2 <= i) ++b;
+            const int32_t a = i - b * (b - 1) / 2;
+            const int32_t q = a * p.R - a * (a + 1) / 2 + (b - a - 1);
+            o = ovl + ((int64_t)id * np + q) * p.o_stride + k;
+        }
+        const uint32_t v = cnt[i];
+        if ((is_gram ? p.g_tiles : p.o_tiles) == 1)
+            *o = v;
+        else if (v != 0u)
+            atomicAdd(o, v);
+    }
+}
+
+// Counts to the observables' own form, in device memory: Gram matrices of K x K
+// and overlaps of K entries a pair, zero past the k_done times reached; the
+// counts are cleared.
+__global__ void __launch_bounds__(256) expand_kernel(const MeasureChain* __restrict__ chains, int32_t n_chains,
+                                                     int32_t n_pairs, int32_t per_inst, int32_t R, int32_t kd,
+                                                     int32_t K, uint32_t* __restrict__ gram_cnt,
+                                                     uint32_t* __restrict__ ovl_cnt, long long* __restrict__ gram,
+                                                     long long* __restrict__ ovl)
+{
+    const int32_t np = K * (K - 1) / 2;
+    const int64_t step = (int64_t)gridDim.x * blockDim.x, i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int64_t i = i0; i < (int64_t)n_chains * K * K; i += step) {
+        const int64_t ch = i / (K * K);
+        const int32_t e = (int32_t)(i - ch * (K * K)), l = e / K, k = e - l * K;
+        if (k > l) continue;
+        long long v = 0;
+        if (l < kd) {
+            v = chains[ch].n;
+            if (k < l) {
+                uint32_t* p = gram_cnt + ch * np + l * (l - 1) / 2 + k;
+                v -= 2LL * *p;
+                *p = 0u;
+            }
+        }
+        gram[ch * (K * K) + l * K + k] = v;
+        gram[ch * (K * K) + k * K + l] = v;
+    }
+    for (int64_t i = i0; i < (int64_t)n_pairs * K; i += step) {
+        const int64_t q = i / K;
+        const int32_t k = (int32_t)(i - q * K);
+        ovl[i] = k < kd ? (long long)chains[q / per_inst * R].n - 2LL * ovl_cnt[i] : 0;
+        ovl_cnt[i] = 0u;
+    }
+}
+
+// Copies the segments of a measurement, one after another, to mapped host memory
+// (4 bytes a lane: 53 GB/s, the link's rate, as a DMA copy of one piece; without a
+// destination: nothing), and clears those that hold counts.
+__global__ void __launch_bounds__(256) pack_kernel(PackList L, uint32_t* __restrict__ dst)
+{
+    const uint64_t step = (uint64_t)gridDim.x * blockDim.x, i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    for (int s = 0; s < L.n; ++s) {
+        const PackSeg g = L.seg[s];
+        const uint64_t words = (uint64_t)g.rows * g.width;
+        for (uint64_t i = i0; i < words; i += step) {
+            const uint64_t r = words >> 32 ? i / g.width : (uint32_t)i / g.width;
+            uint32_t* p = g.src + r * g.stride + (i - r * g.width);
+            if (dst) dst[g.dst + i] = *p;
+            if (g.clear) *p = 0u;
+        }
+    }
 }
 
 // grid = (units, k_done).  Snapshot bits of the unit's chains are staged in
@@ -189,23 +306,48 @@ hipError_t measure_scratch(long long** ptr)
     return hipSuccess;
 }
 
-hipError_t measure_gram(const MeasureChain* chains, int n_chains, int k_done, int k_cap,
-                        int max_words, long long* out, hipStream_t s)
+hipError_t observe(const MeasureChain* chains, int n_chains, int count, int R, int k_done, int k_cap, int max_words,
+                   uint32_t* gram_cnt, uint32_t* ovl_cnt, hipStream_t s)
 {
     if (n_chains <= 0 || k_done <= 0) return hipSuccess;
-    const int wps = 256;
-    const int splits = (max_words + wps - 1) / wps;
-    hipLaunchKernelGGL(gram_kernel, dim3(n_chains, splits), dim3(64), 0, s, chains, k_done, k_cap, wps,
-                       out);
+    // tiles of at most 32 KB
+    constexpr int kTile = 8192;
+    auto words = [&](int rows) { return std::min((max_words + 63) & ~63, (kTile / rows) & ~63); };
+    ObsPlan p;
+    p.n_chains = k_done > 1 ? n_chains : 0;
+    p.count = count;
+    p.R = R;
+    p.kd = k_done;
+    p.g_words = words(k_done);
+    p.g_tiles = (max_words + p.g_words - 1) / p.g_words;
+    p.o_words = words(R);
+    p.o_tiles = (max_words + p.o_words - 1) / p.o_words;
+    p.g_stride = k_cap * (k_cap - 1) / 2;
+    p.o_stride = k_cap;
+    const int64_t blocks = (int64_t)p.n_chains * p.g_tiles + (R > 1 ? (int64_t)count * k_done * p.o_tiles : 0);
+    if (blocks <= 0) return hipSuccess;
+    if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const size_t lds = 4 * (size_t)std::max(k_done > 1 ? k_done * (p.g_words + 4) : 0, R > 1 ? R * (p.o_words + 4) : 0);
+    hipLaunchKernelGGL(observe_kernel, dim3((unsigned)blocks), dim3(256), lds, s, chains, p, gram_cnt, ovl_cnt);
     return hipGetLastError();
 }
 
-hipError_t measure_overlap(const MeasureChain* chains, const int32_t* pairs, int n_pairs, int k_done,
-                           int k_cap, long long* out, hipStream_t s)
+hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs, int R, int k_done, int k_cap,
+                          uint32_t* gram_cnt, uint32_t* ovl_cnt, long long* gram, long long* ovl, hipStream_t s)
 {
-    if (n_pairs <= 0 || k_done <= 0) return hipSuccess;
-    hipLaunchKernelGGL(overlap_kernel, dim3(n_pairs, k_done), dim3(256), 0, s, chains, pairs, k_cap,
-                       out);
+    const int64_t work = std::max((int64_t)n_chains * k_cap * k_cap, (int64_t)n_pairs * k_cap);
+    const int blocks = (int)std::max<int64_t>(1, std::min<int64_t>(2048, (work + 255) / 256));
+    hipLaunchKernelGGL(expand_kernel, dim3(blocks), dim3(256), 0, s, chains, n_chains, n_pairs,
+                       std::max(1, R * (R - 1) / 2), R, k_done, k_cap, gram_cnt, ovl_cnt, gram, ovl);
+    return hipGetLastError();
+}
+
+hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s)
+{
+    uint64_t most = 0;
+    for (int i = 0; i < list.n; ++i) most = std::max<uint64_t>(most, (uint64_t)list.seg[i].rows * list.seg[i].width);
+    const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(512, (most + 255) / 256));
+    hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, list, dst);
     return hipGetLastError();
 }
 
