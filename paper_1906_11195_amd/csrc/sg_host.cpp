@@ -187,6 +187,32 @@ void vb_tables(VbGraph& g)
     g.row[(size_t)n] = (int32_t)e;
 }
 
+// The chunks of a graph in sweep order, of `blocks` blocks of 64 positions.
+std::vector<VbChunk> vb_chunks(const VbGraph& g, int32_t blocks)
+{
+    std::vector<VbChunk> out;
+    for (int32_t k = 0; k < g.ncls; ++k) {
+        const int32_t lo = g.cls[(size_t)k], hi = g.cls[(size_t)k + 1], before = (int32_t)out.size();
+        if (hi <= lo) continue;
+        for (int32_t b = lo & ~63; b < hi; b += 64 * blocks) {
+            const int32_t q0 = std::max(lo, b), q1 = std::min(hi, b + 64 * blocks);
+            int32_t degree = 0, least = INT32_MAX;
+            for (int32_t q = q0; q < q1; ++q) {
+                const int32_t m = g.row[(size_t)q + 1] - g.row[(size_t)q];
+                degree = std::max(degree, m);
+                least = std::min(least, m);
+            }
+            // (the update reads a multiple of four words past 8 neighbours, and one for none)
+            const bool full = q1 - q0 == 64 * blocks;
+            const bool even = full && least == degree && degree > 0 && (degree < 9 || degree % 4 == 0);
+            out.push_back(VbChunk{(uint32_t)(b >> 6) | (uint32_t)(q0 - b) << 16 | (uint32_t)(q1 - b - 1) << 22 |
+                                      (uint32_t)even << 29 | (uint32_t)full << 30,
+                                  (uint32_t)before | (uint32_t)degree << 16 | (uint32_t)k << 22, (uint32_t)g.row[(size_t)q0], 0u});
+        }
+    }
+    return out;
+}
+
 bool finite_nonneg_T(double T) { return !(T < 0.0) && !std::isnan(T); }
 
 void check_vb_desc(const sg_vb_desc& d)
@@ -967,11 +993,19 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
 
     // device layout
     Arena A;
-    std::vector<size_t> off_row(n_groups), off_ent(n_groups), off_cls(n_groups);
+    std::vector<size_t> off_row(n_groups), off_ent(n_groups), off_cls(n_groups), off_tab(2 * n_groups);
+    std::vector<std::vector<VbChunk>> tabs(2 * n_groups);
     for (size_t gi = 0; gi < n_groups; ++gi) {
         off_row[gi] = A.take(graphs[gi].row.size() * 4);
         off_ent[gi] = A.take((graphs[gi].ent.size() + kVbEntPad) * 4);
         off_cls[gi] = A.take(graphs[gi].cls.size() * 4);
+    }
+    // chunk tables: one per graph for its resident and one for its other units
+    for (const auto& u : plan) {
+        const size_t ti = 2 * (size_t)u.group + (u.resident ? 1 : 0);
+        if (!tabs[ti].empty()) continue;
+        tabs[ti] = vb_chunks(graphs[(size_t)u.group], u.resident ? 1 : 2);
+        off_tab[ti] = A.take(tabs[ti].size() * sizeof(VbChunk));
     }
     // entries in the complemented-copy form: one array per graph and slot count
     std::map<std::pair<int32_t, int32_t>, size_t> off_entc;
@@ -1050,6 +1084,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         std::copy(g.ent.begin(), g.ent.end(), padded.begin());
         hip_check(hipMemcpy(c->at<void>(off_ent[gi]), padded.data(), padded.size() * 4, hipMemcpyHostToDevice));
         hip_check(hipMemcpy(c->at<void>(off_cls[gi]), g.cls.data(), g.cls.size() * 4, hipMemcpyHostToDevice));
+        for (size_t ti = 2 * gi; ti < 2 * gi + 2; ++ti)
+            if (!tabs[ti].empty())
+                hip_check(hipMemcpy(c->at<void>(off_tab[ti]), tabs[ti].data(), tabs[ti].size() * sizeof(VbChunk), hipMemcpyHostToDevice));
     }
     for (const auto& kv : off_entc) {
         const VbGraph& g = graphs[(size_t)kv.first.first];
@@ -1083,6 +1120,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         U.row = c->at<int32_t>(off_row[(size_t)plan[u].group]);
         U.ent = c->at<uint32_t>(off_ent[(size_t)plan[u].group]);
         U.cls = c->at<int32_t>(off_cls[(size_t)plan[u].group]);
+        const size_t ti = 2 * (size_t)plan[u].group + (plan[u].resident ? 1 : 0);
+        U.chunk = c->at<VbChunk>(off_tab[ti]);
+        U.chunks = (int32_t)tabs[ti].size();
         U.resident = plan[u].resident ? 1 : 0;
         U.cpl = plan[u].cpl ? 1 : 0;
         if (U.cpl) U.entc = c->at<uint32_t>(off_entc.at({plan[u].group, plan[u].rpad}));

@@ -12,26 +12,21 @@
 // sets of 8-bit fields).
 //
 // A sweep visits colour class 0, 1, ...; inside a class all positions are
-// independent (no two are adjacent).  A class is cut into aligned chunks of 64
-// positions; wavefront w of the workgroup updates chunks w, w + W, ... of the
-// class (lane i takes position 64 b + i of block b), for every chain of the
-// unit.  Workgroup barriers separate classes only.  Each wavefront streams
-// the adjacency of its chunks straight from HBM through a two-stage register
-// pipeline: the row starts of the chunk after next and the entries of the
-// next chunk are in flight while the current chunk is updated.  (Units whose
-// adjacency fits in LDS take a loop of their own, vb_loop_res.)
+// independent (no two are adjacent).  A class is cut into chunks of two aligned
+// blocks of 64 positions (one block where the adjacency is resident in LDS), which
+// the wavefronts take in turn; lane i of a wavefront updates position i of each
+// block for every chain of the unit.  vb_loop says how the wavefronts keep the
+// order of the classes and what is in flight when.
 //
 // Metropolis rule (Methods; SI bipartite-graph section): with x = s_p h_p the
 // move is accepted if x <= 0, else iff r < thr[x], thr[x] = floor(2^32
 // exp(-2x/T)).  r = (A << 16) | B with A, B half-words of two Philox streams.
 // One Philox block serves the eight positions of an aligned group for one
-// chain.  A wavefront draws 64 blocks per pass (one per lane) into LDS: the
-// blocks of its next B = max(1, 8 / nch) chunks, so with 1, 2 or 4 chains no
-// lane draws a block nobody uses.  A is compared with the high half of the threshold,
+// chain.  A wavefront draws 64 of them per pass (one per lane): those of its next
+// B = max(1, 8 / nch) blocks of positions, so with 1, 2 or 4 chains no lane draws
+// what nobody uses; they reach the positions' lanes through LDS.  A is compared with the high half of the threshold,
 // read from a per-chain table indexed by 64 + x (entries for x <= 0 exceed
-// every A); B is computed only when A ties with it (probability 2^-16).  The
-// flips of a chunk are collected as one ballot per chain and written back by
-// one lane per spin word.
+// every A); B is computed only when A ties with it (probability 2^-16).
 #include <type_traits>
 
 #include "sg_internal.h"
@@ -40,12 +35,11 @@
 namespace sg {
 namespace {
 
-constexpr int kDMax = 8;   // adjacency entries prefetched per position
+// neighbours of a position kept in registers, adjacency in HBM / in LDS
+constexpr int kHbmMax = 8, kLdsMax = 12;
 constexpr int kTab = 128;  // threshold table per chain: index 64 + x, -63 <= x <= 63
 constexpr int kThc = 32;   // compact threshold table per chain: index 15 - x, -16 <= x <= 15
 constexpr int kMaxCls = 64; // colour classes (greedy colouring, degree <= 63)
-constexpr int kResMax = 15; // neighbours of a resident unit's position kept in registers
-constexpr int kResPad = 16; // entries past the resident adjacency (reads past a row stay inside)
 // LDS byte offsets of the flip-spreading table (256 words) and of the spin
 // words: the compact tables come first, so that all three are addressed
 // with the instructions' constant offsets
@@ -119,122 +113,171 @@ __device__ __forceinline__ VbLds vb_carve(uint32_t* smem, uint32_t smem_lds, int
     return L;
 }
 
-// Class bounds live in LDS and are read wave-uniformly: the cursor stays in
-// scalar registers and its reads never wait on the vector-memory counter that
-// the prefetched adjacency loads use.
+// A value that is the same in every lane, in scalar registers.
+__device__ __forceinline__ int64_t uniform64(int64_t v)
+{
+    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)((uint64_t)v >> 32)) << 32) |
+                     (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)v));
+}
+
+template <class T>
+__device__ __forceinline__ T* uniform(T* p)
+{
+    return (T*)uniform64((int64_t)p);
+}
+
+// Class bounds, wave-uniform.
 __device__ __forceinline__ int32_t cls_at(const int32_t* cls, int32_t k)
 {
     return __builtin_amdgcn_readfirstlane(cls[k]);
 }
 
-// Chunk cursor of one wavefront: sweep s, colour class k, chunk j of the class
-// (the aligned block (cls[k] >> 6) + j of 64 positions).  The class's bounds
-// and chunk count are kept with it, so that a step inside a class reads
-// nothing from LDS.
-struct Cursor {
-    int32_t s, k, j;
-    int32_t lo, hi, nck;
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef v4u v4u_dw __attribute__((aligned(4)));
+
+// Adjacency rows and the first NE entries of one chunk of H blocks of 64
+// positions, as read (from HBM or LDS).
+template <int NE, int H>
+struct Stage {
+    int32_t r0[H], deg[H];     // row start, degree (as requested: the row's end; 0 in lanes outside the class)
+    v4u e[H][NE / 4];
 };
 
-template <class PC>
-__device__ __forceinline__ int32_t n_chunks(PC cls, int32_t k)
+// (HBM: one 16-byte load; rows start at any entry)
+__device__ __forceinline__ v4u entries4(const SG_G uint32_t* ent, int32_t r0, int d)
 {
-    const int32_t lo = cls_at(cls, k), hi = cls_at(cls, k + 1);
-    return hi > lo ? ((hi - 1) >> 6) - (lo >> 6) + 1 : 0;
+    const uint32_t o = (uint32_t)r0 * 4u;
+    return *(const SG_G v4u_dw*)((const SG_G char*)(ent + d) + o);
 }
 
-template <class PC>
-__device__ __forceinline__ void cursor_class(Cursor& c, PC cls)
+__device__ __forceinline__ v4u entries4(const uint32_t* ent, int32_t r0, int d)
 {
-    c.lo = cls_at(cls, c.k);
-    c.hi = cls_at(cls, c.k + 1);
-    c.nck = c.hi > c.lo ? ((c.hi - 1) >> 6) - (c.lo >> 6) + 1 : 0;
+    const uint32_t* p = ent + r0 + d;
+    return v4u{p[0], p[1], p[2], p[3]};
 }
 
-// A cursor before the first chunk of wavefront `wave` (cursor_next moves it
-// there).
-template <class PC>
-__device__ __forceinline__ Cursor cursor_start(int W, int wave, PC cls)
+// The rows of a chunk: requested one chunk ahead, except where every lane has the
+// same degree (most chunks: positions are sorted by degree inside a class), whose
+// rows follow from the first one.
+template <class PR, int NE, int H>
+__device__ __forceinline__ void load_rows(PR row, const VbChunk& T, int lane, Stage<NE, H>& st)
 {
-    Cursor c{0, 0, wave - W, 0, 0, 0};
-    cursor_class(c, cls);
-    return c;
-}
-
-// Moves to the next chunk owned by wavefront `wave`; false past the launch.
-template <class PC>
-__device__ __forceinline__ bool cursor_next(Cursor& c, int W, int wave, int32_t ncls, PC cls, int32_t nsw)
-{
-    c.j += W;
-    for (;;) {
-        if (c.j < c.nck) return true;
-        c.j = wave;
-        if (++c.k == ncls) {
-            c.k = 0;
-            if (++c.s >= nsw) return false;
-        }
-        cursor_class(c, cls);
+    if (T.even()) return;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        // (clamped in lanes past the class)
+        const uint32_t q = (uint32_t)min(T.base() + 64 * h + lane, T.base() + T.hi() - 1);
+        st.r0[h] = row[q];
+        st.deg[h] = row[q + 1];
     }
 }
 
-struct Stage {
-    int32_t q, r0, r1;
-    uint32_t e[kDMax];
-};
-
-// `row` and `ent` point to HBM, or to LDS when the adjacency is resident.
-template <class PR, class PC>
-__device__ __forceinline__ void load_rows(PR row, PC cls, const Cursor& c, int lane, Stage& st)
+__device__ __forceinline__ bool in_class(const VbChunk& T, int lane)
 {
-    st.q = (((c.lo >> 6) + c.j) << 6) + lane;
-    const bool act = st.q >= c.lo && st.q < c.hi;
-    st.r0 = act ? row[st.q] : 0;
-    st.r1 = act ? row[st.q + 1] : 0;
+    return lane >= T.lo() && lane < T.hi();
 }
 
-// Loads kDMax entries from the row start whatever the degree (the adjacency
-// is followed by kVbEntPad zero entries): no load waits behind a branch.
-template <class PE>
-__device__ __forceinline__ void load_ents(PE ent, Stage& st)
+// The rows of chunk T (in `rows`, if they were requested) as row starts and degrees.
+template <int NE, int H>
+__device__ __forceinline__ void rows_ready(Stage<NE, H>& st, const Stage<NE, H>& rows, const VbChunk& T, int lane)
 {
-    static_assert(kDMax <= kVbEntPad, "entry prefetch must stay inside the padded adjacency");
+    if (T.even()) {
 #pragma unroll
-    for (int d = 0; d < kDMax; ++d) st.e[d] = ent[st.r0 + d];
+        for (int h = 0; h < H; ++h) {
+            st.r0[h] = (int32_t)T.r0 + (int32_t)((uint32_t)(64 * h + lane) * (uint32_t)T.degree());
+            st.deg[h] = T.degree();
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            st.r0[h] = rows.r0[h];
+            st.deg[h] = in_class(T, 64 * h + lane) ? rows.deg[h] - rows.r0[h] : 0;
+        }
+    }
+}
+
+// Loads the entries from the row start whatever the lane's degree (the adjacency
+// is followed by kVbEntPad zero entries), four at a time up to the chunk's largest.
+template <class PE, int NE, int H>
+__device__ __forceinline__ void load_ents(PE ent, Stage<NE, H>& st, int32_t degree)
+{
+    static_assert(NE <= kVbEntPad, "entry prefetch must stay inside the padded adjacency");
+#pragma unroll
+    for (int i = 0; i < NE / 4; ++i) {
+        if (i == 0 || degree > 4 * i) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) st.e[h][i] = entries4(ent, st.r0[h], 4 * i);
+        }
+    }
+}
+
+// A lane's random half-words A of a chunk, and the low half-word B that decides a
+// tie (drawn when it is needed: probability 2^-16).
+template <int RPAD, int H>
+struct Draws {
+    // (8 slots, two blocks: the first block's stay in LDS, for want of registers)
+    static constexpr int R0 = RPAD == 8 && H == 2 ? 1 : 0;
+    uint32_t a[H - R0][RPAD];
+    const uint16_t* first;
+    __device__ __forceinline__ uint32_t half(int h, int c) const
+    {
+        return R0 && h == 0 ? (uint32_t)first[8 * c] : a[h - R0 < 0 ? 0 : h - R0][c];
+    }
+};
+
+struct Site {
+    const VbUnit* up;
+    uint64_t key;
+    uint32_t t;
+    int32_t q;      // position (of the first block)
+    int32_t nch;
+};
+
+// Half-word of the lane's position in block h for chain c (not a constant).
+__device__ __forceinline__ uint32_t site_half(const Site& S, uint32_t domain, int h, int c)
+{
+    const uint32_t q = (uint32_t)S.q + 64u * (uint32_t)h;
+    return half_word(philox_stream(S.key, q >> 3, S.t, domain, S.up->rep[c], S.up->inst[c]), q & 7u);
 }
 
 // Metropolis decisions of one chunk for every chain, from the unsatisfied-bond
 // counts: chain c's count is the `width`-bit field of cA (c even or RPAD < 8)
-// or cB (c odd, RPAD 8, 8-bit fields) at bit fsh(c).  Returns this lane's
-// flips in spin-word form (chain c's flip at bit c P).  The counts index the
-// full tables (x = deg - 2 cnt at word c kTab + 64 - x).
-template <int RPAD, class HALF>
-__device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up, const VbLds& L,
-                                                   const uint32_t* gx, HALF&& half, uint32_t cA, uint32_t cB, int32_t deg,
-                                                   bool act, int32_t q, uint32_t t, int32_t nch, uint64_t key)
+// or cB (c odd, RPAD 8, 8-bit fields) at bit fsh(c).  Makes fl this lane's flips
+// in spin-word form (chain c's flip at bit c P).  The counts index the full tables
+// (x = deg - 2 cnt at word c kTab + 64 - x).
+template <int RPAD, int H>
+__device__ __forceinline__ void vb_decide_full(const Site& site, const VbLds& L, const Draws<RPAD, H>& A,
+                                               const uint32_t (&cA)[H], const uint32_t (&cB)[H], const int32_t (&deg)[H],
+                                               const bool (&act)[H], uint32_t (&fl)[H])
 {
     using S = Sl<RPAD>;
-    const int lane = threadIdx.x & 63;
-    const uint32_t hsel = (uint32_t)lane & 7u;
     constexpr uint32_t width = RPAD == 8 ? 8u : (uint32_t)S::P;
     // (the counts are selected as values: a selected reference would put
     // cA and cB in private memory when c is not a constant)
-    auto count = [&](int c) -> uint32_t {
-        const uint32_t a = cA, b = cB;
+    auto count = [&](int h, int c) -> uint32_t {
+        const uint32_t a = cA[h], b = cB[h];
         if (RPAD == 1) return a;
         const uint32_t fsh = RPAD == 8 ? 8u * (uint32_t)(c >> 1) : (uint32_t)(c * S::P);
         return __builtin_amdgcn_ubfe(RPAD == 8 && (c & 1) ? b : a, fsh, width);
     };
-    // `tb` includes the lane's 4 (64 - deg), so each address is a single
-    // shift-add
-    const char* tb = (const char*)L.thr + (uint32_t)(64 - deg) * 4u;
-    auto thr_of = [&](int c, uint32_t cnt) -> uint32_t { return *(const uint32_t*)(tb + c * kTab * 4 + (cnt << 3)); };
-    const uint32_t hs = 16u * (hsel & 1u);
+    // (the address includes the lane's 4 (64 - deg): a single shift-add)
+    auto thr_of = [&](int h, int c, uint32_t cnt) -> uint32_t {
+        return *(const uint32_t*)((const char*)L.thr + (uint32_t)(64 - deg[h]) * 4u + c * kTab * 4 + (cnt << 3));
+    };
     // e = A - thr (|e| < 2^18): a flip iff e < 0, a tie iff e = 0
-    uint32_t fl = 0, emin = 0xFFFFFFFFu;
+    uint32_t emin[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        fl[h] = 0u;
+        emin[h] = 0xFFFFFFFFu;
+    }
     auto chain = [&](int c) {
-        const uint32_t e = half(c) - thr_of(c, count(c));
-        fl |= (e >> 31) << (c * S::P);
-        emin = min(emin, e);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const uint32_t e = A.half(h, c) - thr_of(h, c, count(h, c));
+            fl[h] |= (e >> 31) << (c * S::P);
+            emin[h] = min(emin[h], e);
+        }
     };
     // a unit with RPAD slots has more than RPAD / 2 chains: those are decided
     // without a test (in one block, so that their LDS reads are issued together)
@@ -242,30 +285,24 @@ __device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up
     for (int c = 0; c <= RPAD / 2; ++c) chain(c);
 #pragma unroll
     for (int c = RPAD / 2 + 1; c < RPAD; ++c)
-        if (c < nch) chain(c);
-    fl = act ? fl : 0u;
-    const bool tie = emin == 0u;
-    if (__builtin_amdgcn_ballot_w64(act && tie) != 0ull) {
-        // A equals the high half of the threshold (those lanes did not flip
-        // above): decide on the low half (rare: a loop, not unrolled)
+        if (c < site.nch) chain(c);
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        fl[h] = act[h] ? fl[h] : 0u;
+        if (__builtin_amdgcn_ballot_w64(act[h] && emin[h] == 0u) != 0ull) {
+            // A equals the high half of the threshold (those lanes did not flip
+            // above): decide on the low half (rare: a loop, not unrolled)
+            if (act[h] && emin[h] == 0u) {
 #pragma unroll 1
-        for (int c = 0; c < nch; ++c) {
-            const uint32_t cnt = count(c);
-            const uint32_t th = thr_of(c, cnt);
-            const uint32_t rh = __builtin_amdgcn_ubfe(gx[4 * c], hs, 16u);
-            const bool ti = act && rh == th;
-            if (__builtin_amdgcn_ballot_w64(ti) != 0ull) {
-                bool f2 = false;
-                if (ti) {
-                    const int32_t x = deg - 2 * (int32_t)cnt;
-                    const U4 Bk = philox_stream(key, (uint32_t)q >> 3, t, kDomSweepLo, up->rep[c], up->inst[c]);
-                    f2 = half_word(Bk, hsel) < gl(&up->thr_lo[c][0])[x];
+                for (int c = 0; c < site.nch; ++c) {
+                    const uint32_t cnt = count(h, c);
+                    if (site_half(site, kDomSweepHi, h, c) == thr_of(h, c, cnt) &&
+                        site_half(site, kDomSweepLo, h, c) < gl(&site.up->thr_lo[c][0])[deg[h] - 2 * (int32_t)cnt])
+                        fl[h] |= 1u << (c * S::P);
                 }
-                fl |= f2 ? 1u << (c * S::P) : 0u;
             }
         }
     }
-    return fl;
 }
 
 // The same with 8 chain slots and every degree of the chunk below 16 (the
@@ -273,149 +310,252 @@ __device__ __forceinline__ uint32_t vb_decide_full(const VbUnit* __restrict__ up
 // (even chains in oE, odd chains in oO, chain c at byte c / 2) and each byte
 // is turned, for all chains at once, into the byte offset 4 (15 - x) = 60 -
 // 4 deg + 8 cnt of the chain's entry in its compact table at LDS offset 0,
-// so that one bit-field extract per chain addresses its threshold; the
-// lane's random half-word is read as such, and e = A - thr (|e| < 2^17)
-// decides: a flip iff e < 0, a tie iff e = 0.  The sign bits are shifted into a flip vector (bit c: chain c, from
-// the highest chain down), which the spreading table turns into spin-word
-// form; ties are detected by the running unsigned minimum of e.
-template <class HALF>
-__device__ __forceinline__ uint32_t vb_decide_compact(const VbUnit* __restrict__ up, const VbLds& L,
-                                                      const uint32_t* gx, HALF&& half, uint32_t cA, int32_t deg, bool act,
-                                                      int32_t q, uint32_t t, int32_t nch, uint64_t key)
+// so that one bit-field extract per chain addresses its threshold; e = A - thr
+// (|e| < 2^17) decides: a flip iff e < 0, a tie iff e = 0.  The sign bits are
+// shifted into a flip vector (bit c: chain c, from the highest chain down),
+// which the spreading table turns into spin-word form; ties are detected by the
+// running unsigned minimum of e.
+template <int H>
+__device__ __forceinline__ void vb_decide_compact(const Site& site, const Draws<8, H>& A, const uint32_t (&cA)[H],
+                                                  const int32_t (&deg)[H], const bool (&act)[H], uint32_t (&fl)[H])
 {
     typedef const __attribute__((address_space(3))) uint32_t lds_u32;
-    const int lane = threadIdx.x & 63;
-    // (60 - 4 deg) in every byte
-    const uint32_t bias = __builtin_amdgcn_perm(0u, (uint32_t)(60 - 4 * deg), 0u);
-    const uint32_t oE = ((cA & 0x0F0F0F0Fu) << 3) + bias;          // chain 2k at byte k
-    const uint32_t oO = (((cA >> 4) & 0x0F0F0F0Fu) << 3) + bias;   // chain 2k + 1 at byte k
-    const uint16_t* rp = (const uint16_t*)gx + (lane & 1);        // chain c's A at rp[8 c]
-    uint32_t fv = 0u, emin = 0xFFFFFFFFu;
+    uint32_t oE[H], oO[H], fv[H], emin[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        // (60 - 4 deg) in every byte
+        const uint32_t bias = __builtin_amdgcn_perm(0u, (uint32_t)(60 - 4 * deg[h]), 0u);
+        oE[h] = ((cA[h] & 0x0F0F0F0Fu) << 3) + bias;          // chain 2k at byte k
+        oO[h] = (((cA[h] >> 4) & 0x0F0F0F0Fu) << 3) + bias;   // chain 2k + 1 at byte k
+        fv[h] = 0u;
+        emin[h] = 0xFFFFFFFFu;
+    }
+    auto offset = [&](int h, int c) {
+        return __builtin_amdgcn_ubfe((c & 1) ? oO[h] : oE[h], 8u * (uint32_t)(c >> 1), 8u) + (uint32_t)(c * kThc * 4);
+    };
     auto chain = [&](int c) {
-        const uint32_t off = __builtin_amdgcn_ubfe((c & 1) ? oO : oE, 8u * (uint32_t)(c >> 1), 8u);
-        const uint32_t e = half(c) - *(lds_u32*)(size_t)(off + (uint32_t)(c * kThc * 4));
-        fv = __builtin_amdgcn_alignbit(fv, e, 31u);
-        emin = min(emin, e);
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            const uint32_t e = A.half(h, c) - *(lds_u32*)(size_t)offset(h, c);
+            fv[h] = __builtin_amdgcn_alignbit(fv[h], e, 31u);
+            emin[h] = min(emin[h], e);
+        }
     };
     // a unit with 8 slots has 5 to 8 chains: chains 0..4 are decided without
     // a test (in one block, so that their LDS reads are issued together)
 #pragma unroll
     for (int c = kVbMaxChains - 1; c >= 5; --c)
-        if (c < nch) chain(c);
+        if (c < site.nch) chain(c);
 #pragma unroll
     for (int c = 4; c >= 0; --c) chain(c);
-    fv = act ? fv : 0u;
-    uint32_t fl = *(lds_u32*)(size_t)(kSprOff + fv * 4u);
-    if (__builtin_amdgcn_ballot_w64(act && emin == 0u) != 0ull) {
-        // A equals the high half of the threshold (those lanes did not flip
-        // above): decide on the low half (rare: a loop, not unrolled)
-        const uint32_t hsel = (uint32_t)lane & 7u;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        fv[h] = act[h] ? fv[h] : 0u;
+        fl[h] = *(lds_u32*)(size_t)(kSprOff + fv[h] * 4u);
+    }
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        if (__builtin_amdgcn_ballot_w64(act[h] && emin[h] == 0u) != 0ull) {
+            // A equals the high half of the threshold (those lanes did not flip
+            // above): decide on the low half (rare: a loop, not unrolled)
+            if (act[h] && emin[h] == 0u) {
 #pragma unroll 1
-        for (int c = 0; c < nch; ++c) {
-            const uint32_t src = (c & 1) ? oO : oE;
-            const uint32_t off = __builtin_amdgcn_ubfe(src, 8u * (uint32_t)(c >> 1), 8u);
-            const bool ti = act && (uint32_t)rp[8 * c] == *(lds_u32*)(size_t)(off + (uint32_t)(c * kThc * 4));
-            if (__builtin_amdgcn_ballot_w64(ti) != 0ull) {
-                bool f2 = false;
-                if (ti) {
-                    const int32_t x = 15 - (int32_t)(off >> 2);
-                    const U4 Bk = philox_stream(key, (uint32_t)q >> 3, t, kDomSweepLo, up->rep[c], up->inst[c]);
-                    f2 = half_word(Bk, hsel) < gl(&up->thr_lo[c][0])[x];
+                for (int c = 0; c < site.nch; ++c) {
+                    const uint32_t off = offset(h, c);
+                    const int32_t x = 15 - (int32_t)((off - (uint32_t)(c * kThc * 4)) >> 2);
+                    if (site_half(site, kDomSweepHi, h, c) == *(lds_u32*)(size_t)off &&
+                        site_half(site, kDomSweepLo, h, c) < gl(&site.up->thr_lo[c][0])[x])
+                        fl[h] |= 1u << (4 * c);
                 }
-                fl |= f2 ? 1u << (4 * c) : 0u;
             }
         }
     }
-    return fl;
 }
 
-// half(c): the lane's random half-word for chain c (a constant in the calls).
-template <int RPAD, class HALF>
-__device__ __forceinline__ uint32_t vb_decide(const VbUnit* __restrict__ up, const VbLds& L, const uint32_t* gx,
-                                              HALF&& half, uint32_t cA, uint32_t cB, bool wide, int32_t deg, bool act,
-                                              int32_t q, uint32_t t, int32_t nch, uint64_t key)
-{
-    if (RPAD == 8 && !wide) return vb_decide_compact(up, L, gx, half, cA, deg, act, q, t, nch, key);
-    return vb_decide_full<RPAD>(up, L, gx, half, cA, cB, deg, act, q, t, nch, key);
-}
-
-// Updates the positions of one chunk for every chain of the unit and returns
-// this lane's flips in spin-word form.  gx: this lane's group's Philox blocks
-// of the chunk (chain c at gx + 4 c).
-template <int RPAD, bool SPLIT, bool CPL, class PE>
-__device__ __forceinline__ uint32_t vb_chunk(const VbUnit* __restrict__ up, const VbLds& L, PE ent, const Stage& st,
-                                             int32_t lo, int32_t hi, uint32_t t, int32_t nch,
-                                             uint64_t key, const uint32_t* gx)
+// Where an adjacency entry points: with a complemented copy it is the word's LDS
+// address above 5 bits of in-word shift, else a position and the sign of J.
+template <int RPAD, bool CPL>
+__device__ __forceinline__ void entry_word(uint32_t e, uint32_t sp_lds, uint32_t& ad, uint32_t& sh, uint32_t& sg)
 {
     using S = Sl<RPAD>;
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int32_t q = st.q;
-
-    const bool act = q >= lo && q < hi;
-    const int32_t deg = st.r1 - st.r0;   // 0 on inactive lanes
-    // spin words read through a local-address-space pointer made from the
-    // array's LDS offset (the constant kSpOff), so that the base is neither
-    // kept in a register nor re-read for every neighbour
-    const uint32_t spo = L.sp_lds;
-    auto spw = [&](uint32_t off) -> uint32_t {
-        return *(const __attribute__((address_space(3))) uint32_t*)(size_t)(spo + off);
-    };
-    const uint32_t qsh = (uint32_t)q & (uint32_t)(S::P - 1);
-    // own word, position q at the field bottoms
-    const uint32_t o0 = act ? spw(S::boff((uint32_t)q)) >> qsh : 0u;
-    // bit c P of f: the bond to the neighbour is unsatisfied in chain c.
-    // With a complemented copy of the words the entry holds the LDS byte
-    // address of the neighbour's word (of its complement when J < 0) above
-    // the in-word shift, which the shift takes from its low 5 bits
-    auto unsat = [&](uint32_t en) {
-        if (CPL) return (*(const __attribute__((address_space(3))) uint32_t*)(size_t)(en >> 5) >> (en & 31u)) ^ o0;
-        const uint32_t sh = en & (uint32_t)(S::P - 1);
-        return (spw(S::boff(en)) >> sh) ^ o0 ^ (uint32_t)((int32_t)en >> 31);
-    };
-    // per-chain counts of unsatisfied bonds: cA holds P-bit fields (for RPAD 8
-    // while every degree of the chunk is below 16), else for RPAD 8 cA / cB
-    // hold the even / odd chains in 8-bit fields
-    uint32_t cA = 0, cB = 0;
-    const bool wide = RPAD == 8 && __any(deg > 15);
-    if (!wide) {
-#pragma unroll
-        for (int d = 0; d < kDMax; ++d) {
-            if (!__any(d < deg)) break;
-            if (d < deg) cA += unsat(st.e[d]) & S::M;
-        }
-        for (int32_t d = kDMax; d < deg; ++d) cA += unsat(ent[st.r0 + d]) & S::M;
+    if (CPL) {
+        ad = e >> 5;
+        sh = e;
+        sg = 0u;
     } else {
-        // rare (a degree above 15 in the chunk): entries re-read from the adjacency
-        for (int32_t d = 0; d < deg; ++d) {
-            const uint32_t f = unsat(ent[st.r0 + d]);
-            cA += f & 0x01010101u;
-            cB += (f >> 4) & 0x01010101u;
-        }
+        ad = sp_lds + S::boff(e);
+        sh = e & (uint32_t)(S::P - 1);
+        sg = (uint32_t)((int32_t)e >> 31);
     }
+}
 
-    const uint32_t fl = vb_decide<RPAD>(
-        up, L, gx, [&](int c) { return (uint32_t)((const uint16_t*)(gx + 4 * c))[lane & 1]; }, cA, cB, wide, deg, act, q, t,
-        nch, key);
-    // write the flips back: every lane XORs its flips into its spin word (the
-    // P lanes of a word are in this wavefront's chunk, nothing else writes it)
-    if (fl) {
-        const uint32_t wo = ((uint32_t)q >> S::LP) * 4u;
-        __atomic_fetch_xor((__attribute__((address_space(3))) uint32_t*)(size_t)(spo + wo), fl << qsh,
-                           __ATOMIC_RELAXED);
-        if (CPL)
-            __atomic_fetch_xor((__attribute__((address_space(3))) uint32_t*)(size_t)(L.cp_lds + wo), fl << qsh,
-                               __ATOMIC_RELAXED);
-    }
-    if (SPLIT) {
-        // a member of a split unit also writes the chunk's words through to HBM
-        wave_sync();
-        if (lane < 64 / S::P) {
-            const uint32_t wi = ((uint32_t)(q - lane) >> S::LP) + (uint32_t)lane;
-            if (wi < (uint32_t)up->state_words) gl(up->state)[wi] = spw(wi * 4u);
+// The entry, or the own one in lanes past their degree (in 2.4-cycle operations
+// and a bitop3: a comparison and a selection cost 8 to 25 cycles here).
+__device__ __forceinline__ uint32_t entry_or_own(uint32_t e, uint32_t own, int32_t d, int32_t deg)
+{
+    const uint32_t m = (uint32_t)((int32_t)((uint32_t)d - (uint32_t)deg) >> 31);
+    return (e & m) | (own & ~m);
+}
+
+template <int RPAD, bool CPL>
+__device__ __forceinline__ uint32_t own_entry(int32_t q, const VbLds& L)
+{
+    using S = Sl<RPAD>;
+    return CPL ? ((L.sp_lds + S::boff((uint32_t)q)) << 5) | ((uint32_t)q & (uint32_t)(S::P - 1)) : (uint32_t)q;
+}
+
+// Makes the entries past a lane's degree (up to the chunk's largest) the own one.
+template <int RPAD, bool CPL, int NE, int H>
+__device__ __forceinline__ void entries_ready(Stage<NE, H>& st, const VbChunk& T, int32_t q, const VbLds& L)
+{
+    // (a resident unit reads 4, 8 or 12 words whatever the degree)
+    if (NE == kHbmMax && T.even()) return;
+#pragma unroll
+    for (int i = 0; i < NE / 4; ++i) {
+        if (i == 0 || T.degree() > 4 * i) {
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                const uint32_t own = own_entry<RPAD, CPL>(q + 64 * h, L);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) st.e[h][i][j] = entry_or_own(st.e[h][i][j], own, 4 * i + j, st.deg[h]);
+            }
         }
     }
-    return fl;
+}
+
+// Counts of unsatisfied bonds of chunk T (positions q, q + 64) per chain: cA holds
+// P-bit fields (for RPAD 8 while every degree of the chunk is below 16), else for
+// RPAD 8 (true returned) cA / cB hold the even / odd chains in 8-bit fields.  The
+// words of as many neighbours as the chunk's largest degree asks for, up to NE, are
+// read together; the rest of longer rows follows four entries at a time.
+// nbr(h, d, address, shift, sign): the word of entry d; own_ad, own_sh: the own one.
+template <int RPAD, bool CPL, class PE, class WORD, int NE, int H>
+__device__ __forceinline__ bool chunk_count(const Stage<NE, H>& E, const VbChunk& T, int32_t q, const VbLds& L, PE ent,
+                                            WORD&& nbr, const uint32_t (&own_ad)[H], const uint32_t (&own_sh)[H],
+                                            uint32_t (&cA)[H], uint32_t (&cB)[H])
+{
+    using S = Sl<RPAD>;
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    auto word = [&](uint32_t a) -> uint32_t { return *(const lds_u32*)(size_t)a; };
+    uint32_t o0[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) cA[h] = cB[h] = 0u;
+    auto sum = [&](auto nd) __attribute__((always_inline)) {
+        constexpr int N = decltype(nd)::value;
+        uint32_t w[H][N], sh[H][N], sg[H][N], ow[H];
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            ow[h] = word(own_ad[h]);
+#pragma unroll
+            for (int d = 0; d < N; ++d) {
+                uint32_t ad;
+                nbr(h, d, ad, sh[h][d], sg[h][d]);
+                w[h][d] = word(ad);
+            }
+        }
+#pragma unroll
+        for (int h = 0; h < H; ++h) {
+            o0[h] = ow[h] >> own_sh[h];
+#pragma unroll
+            for (int d = 0; d < N; ++d) cA[h] += ((w[h][d] >> (sh[h][d] & 31u)) ^ o0[h] ^ sg[h][d]) & S::M;
+        }
+        // (the cases stay apart: merged, their entries are read by a computed index
+        // from private memory)
+        asm volatile("" ::"n"(N));
+    };
+    const int32_t md = T.degree();
+    if (NE > kHbmMax) {
+        // (a resident unit's latency: few steps to the right case)
+        if (md <= 4)
+            sum(std::integral_constant<int, 4>{});
+        else if (md <= 8)
+            sum(std::integral_constant<int, 8>{});
+        else
+            sum(std::integral_constant<int, NE>{});
+    } else {
+        switch (md) {
+            case 0:
+            case 1: sum(std::integral_constant<int, 1>{}); break;
+            case 2: sum(std::integral_constant<int, 2>{}); break;
+            case 3: sum(std::integral_constant<int, 3>{}); break;
+            case 4: sum(std::integral_constant<int, 4>{}); break;
+            case 5: sum(std::integral_constant<int, 5>{}); break;
+            case 6: sum(std::integral_constant<int, 6>{}); break;
+            case 7: sum(std::integral_constant<int, 7>{}); break;
+            default: sum(std::integral_constant<int, 8>{}); break;
+        }
+    }
+    const bool wide = RPAD == 8 && md > 15;
+    if (md > NE) {
+        auto rest = [&](auto hc) __attribute__((always_inline)) {
+            constexpr int h = decltype(hc)::value;
+            const uint32_t own = own_entry<RPAD, CPL>(q + 64 * h, L), o = o0[h];
+            const int32_t r0 = E.r0[h], deg = E.deg[h];
+            uint32_t a = cA[h], b = 0u;
+            if (wide) {
+                b = (a >> 4) & 0x0F0F0F0Fu;
+                a &= 0x0F0F0F0Fu;
+            }
+            for (int32_t d0 = NE; d0 < md; d0 += 4) {
+                uint32_t en[4], w[4], sh[4], sg[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) en[i] = ent[(uint32_t)(d0 + i < deg ? r0 + d0 + i : r0)];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t ad;
+                    entry_word<RPAD, CPL>(entry_or_own(en[i], own, d0 + i, deg), L.sp_lds, ad, sh[i], sg[i]);
+                    w[i] = word(ad);
+                }
+                const uint32_t m = wide ? 0x01010101u : S::M;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t f = (w[i] >> (sh[i] & 31u)) ^ o ^ sg[i];
+                    a += f & m;
+                    if (RPAD == 8) b += wide ? (f >> 4) & 0x01010101u : 0u;
+                }
+            }
+            cA[h] = a;
+            cB[h] = b;
+        };
+        rest(std::integral_constant<int, 0>{});
+        if constexpr (H > 1) rest(std::integral_constant<int, 1>{});
+    }
+    return wide;
+}
+
+// Decides the chunk and writes the flips back: every lane XORs its flips into its
+// spin word.  Returns the lane's flips in spin-word form, the blocks' added up.
+template <int RPAD, bool CPL, int H>
+__device__ __forceinline__ uint32_t chunk_flip(const Site& site, const VbChunk& T, const VbLds& L, const Draws<RPAD, H>& A,
+                                               const uint32_t (&cA)[H], const uint32_t (&cB)[H], bool wide,
+                                               const int32_t (&deg)[H], const uint32_t (&own_ad)[H],
+                                               const uint32_t (&own_sh)[H])
+{
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
+    const int lane = (int)threadIdx.x & 63;
+    bool act[H];
+#pragma unroll
+    for (int h = 0; h < H; ++h) act[h] = T.full() || in_class(T, 64 * h + lane);
+    uint32_t fl[H];
+    if constexpr (RPAD == 8) {
+        if (!wide)
+            vb_decide_compact<H>(site, A, cA, deg, act, fl);
+        else
+            vb_decide_full<RPAD, H>(site, L, A, cA, cB, deg, act, fl);
+    } else {
+        vb_decide_full<RPAD, H>(site, L, A, cA, cB, deg, act, fl);
+    }
+    uint32_t sum = 0u;
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+        if (fl[h]) {
+            const uint32_t f = fl[h] << own_sh[h];
+            __atomic_fetch_xor((lds_u32*)(size_t)own_ad[h], f, __ATOMIC_RELAXED);
+            if (CPL) __atomic_fetch_xor((lds_u32*)(size_t)(own_ad[h] + (L.cp_lds - L.sp_lds)), f, __ATOMIC_RELAXED);
+        }
+        sum += fl[h];
+    }
+    return sum;
 }
 
 // Split units: after a colour class, the members publish the words they
@@ -468,67 +608,28 @@ __device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, int32
     return true;
 }
 
-// Draws the Philox blocks of this wavefront's next chunks (up to B =
-// max(1, 8 / nch) of them, following cursor pc) into its LDS batch: block
-// m = i 8 nch + g nch + c is group g of chunk i for chain c (lanes past the
-// last such block draw nothing that is used).
-template <int B, class PC>
-__device__ __forceinline__ void vb_fill(const VbLds& L, Cursor& pc, bool& pc_ok, PC cls, int32_t ncls,
-                                        int32_t nsw, int W, int wave, int wl, int lane, int64_t t0,
-                                        int32_t nch, uint64_t key)
-{
-    // the batch's chunk positions and sweeps stay in scalar registers; each
-    // lane picks its chunk's pair by selection (no table in LDS)
-    uint32_t base[B], tt[B];
-#pragma unroll
-    for (int i = 0; i < B; ++i) {
-        base[i] = 0u;
-        tt[i] = 0u;
-        if (pc_ok) {
-            base[i] = (uint32_t)((((pc.lo >> 6) + pc.j) << 6));
-            tt[i] = (uint32_t)(t0 + pc.s);
-            pc_ok = cursor_next(pc, W, wave, ncls, cls, nsw);
-        }
-    }
-    const uint32_t mul = (65536u + (uint32_t)nch - 1u) / (uint32_t)nch;
-    {
-        const uint32_t m = (uint32_t)lane;
-        const uint32_t dq = (m * mul) >> 16;           // m / nch = 8 i + g
-        const uint32_t c = m - dq * (uint32_t)nch;
-        const uint32_t i = min(dq >> 3, (uint32_t)(B - 1)), g = dq & 7u;
-        uint32_t bq = base[0], tq = tt[0];
-#pragma unroll
-        for (int k = 1; k < B; ++k) {
-            bq = i == (uint32_t)k ? base[k] : bq;
-            tq = i == (uint32_t)k ? tt[k] : tq;
-        }
-        const U4 A = philox_stream(key, (bq >> 3) + g, tq, kDomSweepHi, L.ri[2 * c], L.ri[2 * c + 1]);
-        L.xch[wl * 64 + lane] = make_uint4(A.x, A.y, A.z, A.w);
-    }
-    wave_sync();
-}
-
-// One pass for the chunk at positions base.. of sweep t (the only chunk of a
-// batch when 8 / nch < 2, i.e. for 5 to 8 chains): no cursor, no table.
-// Lane m draws group g of chain c, m = g nch + c (lanes past 8 nch draw
-// blocks nobody reads); `fr` holds (g, replica, instance), fixed per lane.
+// A pass of Philox blocks: lane m draws group g of chain c for block i of a batch, m =
+// (8 i + g) nch + c (lanes past the last block draw what nobody reads).
 struct FillLane {
-    uint32_t g, rep, inst;
+    uint32_t g, i, rep, inst;
 };
 
 __device__ __forceinline__ FillLane fill_lane(const VbLds& L, int lane, int32_t nch)
 {
     const uint32_t mul = (65536u + (uint32_t)nch - 1u) / (uint32_t)nch;
     const uint32_t m = (uint32_t)lane;
-    const uint32_t dq = (m * mul) >> 16;           // m / nch
+    const uint32_t dq = (m * mul) >> 16;           // m / nch = 8 i + g
     const uint32_t c = m - dq * (uint32_t)nch;
-    return FillLane{dq & 7u, L.ri[2 * c], L.ri[2 * c + 1]};
+    return FillLane{dq & 7u, min(dq >> 3, (uint32_t)(vb_batch_chunks(nch) - 1)), L.ri[2 * c], L.ri[2 * c + 1]};
 }
 
-__device__ __forceinline__ void vb_fill_one(const VbLds& L, const FillLane& fr, uint32_t base, uint32_t t, int wl,
-                                            int lane, uint64_t key)
+__device__ __forceinline__ U4 fill_draw(const FillLane& fr, uint32_t base, uint32_t t, uint64_t key)
 {
-    const U4 A = philox_stream(key, (base >> 3) + fr.g, t, kDomSweepHi, fr.rep, fr.inst);
+    return philox_stream(key, (base >> 3) + fr.g, t, kDomSweepHi, fr.rep, fr.inst);
+}
+
+__device__ __forceinline__ void fill_put(const VbLds& L, const U4& A, int wl, int lane)
+{
     L.xch[wl * 64 + lane] = make_uint4(A.x, A.y, A.z, A.w);
     wave_sync();
 }
@@ -706,21 +807,9 @@ __device__ __attribute__((noinline)) void vb_window(const VbUnit* __restrict__ u
     }
 }
 
-template <int RPAD, bool SPLIT, bool CPL, class PR, class PE, class PC>
-__device__ bool vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PC cls, int64_t t0,
-                        int32_t nsw, int64_t t_max, int lane, int wave, int W);
-
-// A resident unit's chunks, in the order of a sweep (in LDS).
-struct ResTab {
-    int32_t base;     // first position (a multiple of 64)
-    int32_t span;     // first and one past the last active lane: lo | hi << 8
-    int32_t before;   // chunks of the classes before in the sweep
-};
-
-template <int RPAD>
-__device__ void vb_loop_res(const VbUnit* __restrict__ up, const VbLds& L, const int32_t* row, const uint32_t* ent,
-                            const ResTab* tab, uint32_t* done, const int32_t* cls, int64_t t0, int32_t nsw, int64_t t_max,
-                            int lane, int wave, int W);
+template <int RPAD, bool RES, bool SPLIT, bool CPL, class PR, class PE, class PT>
+__device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
+                        int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W);
 
 // (each variant is a function of its own so that its registers are
 // allocated for it alone)
@@ -775,6 +864,7 @@ __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, 
         L.ri[2 * tid + 1] = up->inst[tid];
     }
     for (int32_t k = tid; k <= ncls; k += nthr) L.cls[k] = gl(up->cls)[k];
+    if (tid == 0) L.flag[0] = 0;   // chunks finished (split units: abort flag)
     const int32_t* cls = L.cls;
     __syncthreads();
     if (RES) {
@@ -785,28 +875,24 @@ __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, 
         for (int32_t i = tid; i <= n; i += nthr) L.area[i] = grow[i];
         uint32_t* re = (uint32_t*)(L.area + n + 1);
         const uint32_t cofs = L.cp_lds - L.sp_lds;
-        for (int32_t i = tid; i < m2 + kResPad; i += nthr) {
+        for (int32_t i = tid; i < m2 + kVbEntPad; i += nthr) {
             const uint32_t en = i < m2 ? gent[i] : 0u;
             re[i] = ((L.sp_lds + Sl<RPAD>::boff(en) + ((int32_t)en < 0 ? cofs : 0u)) << 5) | (en & (uint32_t)(Sl<RPAD>::P - 1));
         }
-        // chunks of the sweep, after the entries
-        ResTab* tab = (ResTab*)(re + m2 + kResPad);
-        int32_t chunks = 0;
-        for (int32_t k = 0; k < ncls; ++k) {
-            const int32_t lo = cls[k], hi = cls[k + 1], b0 = lo & ~63, nck = hi > lo ? ((hi - 1) >> 6) - (lo >> 6) + 1 : 0;
-            for (int32_t j = tid; j < nck; j += nthr) {
-                const int32_t base = b0 + 64 * j;
-                tab[chunks + j] = ResTab{base, max(lo - base, 0) | min(hi - base, 64) << 8, chunks};
-            }
-            chunks += nck;
-        }
-        uint32_t* done = (uint32_t*)L.flag;
-        if (tid == 0) *done = 0u;
+        // the chunks of the sweep, after the entries
+        int32_t* tab = (int32_t*)(re + m2 + kVbEntPad);
+        const SG_G int32_t* gtab = (const SG_G int32_t*)gl(up->chunk);
+        for (int32_t i = tid; i < 4 * up->chunks; i += nthr) tab[i] = gtab[i];
         __syncthreads();
-        vb_loop_res<RPAD>(up, L, (const int32_t*)L.area, re, tab, done, cls, t0, nsw, t_max, lane, wave, W);
+        vb_loop<RPAD, true, false, CPL>(up, L, (const int32_t*)L.area, (const uint32_t*)re, (const VbChunk*)tab, cls, t0, nsw,
+                                        t_max, lane, wave, W);
     } else {
-        vb_loop<RPAD, SPLIT, CPL>(up, L, gl(up->row), gl(CPL ? up->entc : up->ent), cls, t0, nsw, t_max, lane,
-                                  wave, W);
+        // (wave-uniform addresses: the rows and entries are addressed by a scalar
+        // base and 32-bit offsets, and the chunk records, in constant memory, come
+        // by scalar loads, which do not wait for the entries in flight)
+        vb_loop<RPAD, false, SPLIT, CPL>(up, L, gl(uniform(up->row)), gl(uniform(CPL ? up->entc : up->ent)),
+                                         (const __attribute__((address_space(4))) VbChunk*)uniform(up->chunk), cls, t0, nsw,
+                                         t_max, lane, wave, W);
     }
     // (split units keep `state` current by writing through)
     if (!SPLIT)
@@ -886,20 +972,21 @@ __device__ __forceinline__ void acc_flush(VbAcc<RPAD>& a, const VbLds& L, int32_
     a.cb = 0;
 }
 
-template <int RPAD>
+// (fl: the flips of H blocks added up)
+template <int RPAD, int H>
 __device__ __forceinline__ void acc_add(VbAcc<RPAD>& a, uint32_t fl, const VbLds& L, int32_t nch)
 {
     a.n += fl;
-    ++a.cn;
+    a.cn += H;
     if (RPAD == 8) {
-        if (a.cn == 15) {
+        if (a.cn > 15 - H) {
             acc_fold(a);
             if (++a.cb == 17) acc_flush(a, L, nch);
         }
     } else if (RPAD == 4) {
-        if (a.cn == 255) acc_flush(a, L, nch);
+        if (a.cn > 255 - H) acc_flush(a, L, nch);
     } else if (RPAD == 2) {
-        if (a.cn == 65535) acc_flush(a, L, nch);
+        if (a.cn > 65535 - H) acc_flush(a, L, nch);
     }
 }
 
@@ -920,320 +1007,290 @@ __device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, cons
     }
 }
 
-// The sweep loop of one unit (or of one member of a split unit: `wave` and
-// `W` then count the wavefronts of all members), for adjacency pointers in
-// HBM or in LDS.  False if a split unit's barrier aborted.
-template <int RPAD, bool SPLIT, bool CPL, class PR, class PE, class PC>
-__device__ bool vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PC cls, int64_t t0,
-                        int32_t nsw, int64_t t_max, int lane, int wave, int W)
+// The sweep loop of one unit, or of one member of a split unit (`wave` and `W` then
+// count the wavefronts of all members), for an adjacency in HBM or (RES) in LDS.
+//
+// The chunks of a sweep are numbered through its colour classes and dealt to the
+// wavefronts in turn.  A chunk waits until every chunk of the classes before it is
+// finished: the wavefronts meet at no barrier but at a counter of finished chunks
+// in LDS, and take their chunks in order, so the lowest unfinished one never waits
+// for another and every wait ends.  (Members of a split unit meet at a barrier
+// after every class, where they exchange spin words.)
+//
+// Everything that does not depend on spins is done before the wait: the entries of
+// the chunk after it and the rows of the one after that are requested, the chunk's
+// random numbers drawn and its neighbours' addresses formed.  After the wait all
+// spin words are read at once, counted and decided, and the flips written back.
+// That matters in both regimes: a single wavefront issues an instruction about
+// every 8 cycles whatever else runs, so a small unit is bound by the instructions
+// between the last flip of a class and the first read of the next, and with 4
+// wavefronts a SIMD a large one is bound by exposed latency as much as by issue.  So
+// a large unit's chunk has two blocks, whose latencies overlap (a resident one's has
+// one: fewer instructions between two classes), and chunks of one degree (most:
+// positions are sorted by it inside a class) need no rows, no masks and exactly as
+// many reads as neighbours.
+//
+// Measured, us per sweep, against one barrier per class, one block per chunk and one
+// masked LDS round trip per neighbour: 256 graphs of 65536 spins with 6 chains 73.4
+// (90.0: 139 VALU, 108 SALU and 25 LDS instructions a block, 4 wavefronts a SIMD; with
+// one block a chunk 85.7), 1 chain 49.4 (70.1; 5.5 TB/s of adjacency), 2 chains 54.9
+// (72.8), 4 chains 68.7 (83.2); one unit of 10^6 spins and 1 chain 566 (813).  One
+// resident unit of 1024 spins and 2 chains 2.3 (8.3; the time from counter to
+// counter, about 1000 cycles for each of 5 classes), 2048 of them 11 (27).
+template <int RPAD, bool RES, bool SPLIT, bool CPL, class PR, class PE, class PT>
+__device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
+                        int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W)
 {
+    typedef __attribute__((address_space(3))) uint32_t lds_u32;
     const int tid = threadIdx.x;
+    up = uniform(up);
     // The unit's scalars arrive through a pointer argument, which the
     // compiler cannot take as uniform: made explicitly wave-uniform, the
     // per-chain tests and the sweep loop branch on scalar registers instead
     // of masking lanes
-    const int32_t nch = __builtin_amdgcn_readfirstlane(up->nch), ncls = __builtin_amdgcn_readfirstlane(up->ncls);
+    const int32_t nchains = __builtin_amdgcn_readfirstlane(up->nch), ncls = __builtin_amdgcn_readfirstlane(up->ncls);
+    const int32_t chunks = __builtin_amdgcn_readfirstlane(up->chunks);
     nsw = __builtin_amdgcn_readfirstlane(nsw);
     W = __builtin_amdgcn_readfirstlane(W);
-    t0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)((uint64_t)t0 >> 32)) << 32) |
-                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)t0));
+    t0 = uniform64(t0);
+    t_max = uniform64(t_max);
     // the Philox key is the same for every lane: kept in scalar registers,
     // so that the per-round keys cost no vector registers
-    const uint64_t key = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(up->key >> 32)) << 32) |
-                         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)up->key);
-    const int wl = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront inside the workgroup
-    // Philox batches: cursor of the next chunk to draw for, chunks left in
-    // the current batch and the batch position of the next chunk
-    const int32_t B = vb_batch_chunks(nch);
-    // (with 8 chain slots a batch is one chunk: its blocks are drawn for the
-    // chunk itself, and the cursor is not needed)
-    Cursor pc = cursor_start(W, wave, cls);
-    bool pc_ok = RPAD != 8 && nsw > 0 && cursor_next(pc, W, wave, ncls, cls, nsw);
-    int32_t left = 0, bi = 0;
-    const uint32_t* xg = (const uint32_t*)(L.xch + wl * 64);
-    const uint32_t lane_off = (uint32_t)(lane >> 3) * (uint32_t)nch * 4u + (((uint32_t)lane & 7u) >> 1);
-
-    // pipeline: the chunk being updated and the next one (rows + entries)
-    // take turns in E0 and E1, so that no stage is copied; R holds the rows
-    // of the chunk after next
-    Stage E0, E1, R;
-    E1.q = 0;
-    E1.r0 = 0;
-    E1.r1 = 0;
-    R.q = 0;
-    R.r0 = 0;
-    R.r1 = 0;
-    Cursor cR = cursor_start(W, wave, cls);
-    bool haveR = nsw > 0 && cursor_next(cR, W, wave, ncls, cls, nsw);
-    if (haveR) {
-        load_rows(row, cls, cR, lane, E0);
-        load_ents(ent, E0);
-        haveR = cursor_next(cR, W, wave, ncls, cls, nsw);
-        if (haveR) load_rows(row, cls, cR, lane, R);
-    }
-    __syncthreads();
-    if (nsw <= 0) return true;
-
-    const FillLane fr = fill_lane(L, lane, nch);
-    VbAcc<RPAD> acc;
-
-    // one chunk (j of colour class [lo, hi) in sweep t): C holds it, N
-    // receives the next one.  The stage moves on unconditionally (past the
-    // last chunk of the launch it re-reads valid entries that are not used),
-    // so that the loads issue without branches
-    auto step = [&](const Stage& C, Stage& N, int32_t lo, int32_t hi, int32_t j, uint32_t t)
-                    __attribute__((always_inline)) {
-        N.q = R.q;
-        N.r0 = R.r0;
-        N.r1 = R.r1;
-        load_ents(ent, N);
-        if (haveR) {
-            haveR = cursor_next(cR, W, wave, ncls, cls, nsw);
-            if (haveR) load_rows(row, cls, cR, lane, R);
-        }
-        if (RPAD == 8) {
-            vb_fill_one(L, fr, (uint32_t)(((lo >> 6) + j) << 6), t, wl, lane, key);
-            left = 1;
-            bi = 0;
-        } else if (left == 0) {
-            vb_fill<(RPAD < 8 ? 8 / RPAD : 1)>(L, pc, pc_ok, cls, ncls, nsw, W, wave, wl, lane, t0, nch, key);
-            left = B;
-            bi = 0;
-        }
-        const uint32_t fl = vb_chunk<RPAD, SPLIT, CPL>(up, L, ent, C, lo, hi, t, nch, key,
-                                                  xg + (uint32_t)bi * 32u * (uint32_t)nch + lane_off);
-        acc_add(acc, fl, L, nch);
-        --left;
-        ++bi;
-    };
-
-    for (int32_t s = 0; s < nsw; ++s) {
-        const uint32_t t = (uint32_t)(t0 + s);
-        for (int32_t k = 0; k < ncls; ++k) {
-            const int32_t lo = cls_at(cls, k), hi = cls_at(cls, k + 1);
-            const int32_t nck = n_chunks(cls, k);
-            // chunks in pairs: E0 and E1 take turns; after an odd count the
-            // next chunk is moved back to E0 (once per class)
-            for (int32_t j = wave; j < nck; j += W) {
-                step(E0, E1, lo, hi, j, t);
-                E0 = E1;
-            }
-            if (SPLIT) {
-                if (!vb_exchange<RPAD>(up, L, lo, hi, (uint32_t)up->members * (uint32_t)(s * ncls + k + 1)))
-                    return false;
-            } else {
-                __syncthreads();
-            }
-        }
-        acc_fold(acc);
-        acc_flush(acc, L, nch);
-        vb_sweep_end<RPAD, SPLIT>(up, L, t0 + s + 1, t_max);
-    }
-    return true;
-}
-
-// Resident units: small graphs whose adjacency stays in LDS.  A sweep is a chain
-// of colour classes, and a wavefront issues an instruction about every 8 cycles
-// whatever else runs: what counts is the number of instructions between the last
-// flip of a class and the first read of the next.  So nothing but the reads of the
-// spin words, the counts, the decision and the write-back stands there: the
-// wavefronts meet at no barrier but at a counter of finished chunks in LDS
-// (wavefronts not needed for a class are not waited for), and each chunk is
-// prepared ahead, while other wavefronts do the classes between a wavefront's
-// chunks: its neighbours' addresses (the own word's past the degree: no
-// contribution) and its random half-words are then in registers.
-// The update itself (about 60 instructions for 2 chains) runs at a raised wave
-// priority.  Measured for one unit of 1024 spins in 5 classes, us per sweep, against
-// the same unit with a barrier after each class (the wavefronts then wait at every
-// barrier for the ones that prepare): 1 chain 1.94 (8.0), 2 chains 2.06 (8.3), 4
-// chains 2.4 (9.0), 8 chains 3.4 (8.4); 2048 such units of 2 chains 11.2 (27).  What
-// bounds it now is the chain counter - spin words - count - threshold - flip of
-// each class, about 960 cycles.
-//
-// The chunks of a sweep are numbered through its classes and dealt to the
-// wavefronts in turn, so that a wavefront's chunks lie in different classes while
-// they can.  A chunk waits until all chunks of the classes before are finished;
-// the wavefronts take their chunks in order, so the lowest unfinished one never
-// waits for another and every wait ends.
-template <int RPAD>
-struct ResChunk {
-    uint32_t own;            // own word's entry (LDS address << 5 | shift)
-    uint32_t ad[kResMax];    // neighbours: LDS addresses of their words (of the complements when J < 0)
-    uint32_t sh[kResMax];    // ... and shifts (low 5 bits)
-    uint32_t rh[RPAD];       // random half-words (2^17 in inactive lanes: above every threshold)
-    int32_t q, r0, deg;      // deg 0 for inactive lanes
-    int32_t before;
-    int32_t size;            // neighbours read: 4, 8, 12, kResMax; -1: rows of any length
-};
-
-template <int RPAD>
-__device__ __forceinline__ void res_prepare(ResChunk<RPAD>& C, const VbLds& L, const int32_t* row,
-                                            const uint32_t* ent, const ResTab* tab, int32_t nch, const uint32_t* gx)
-{
-    using S = Sl<RPAD>;
-    const int lane = threadIdx.x & 63;
-    const int32_t base = tab->base, span = tab->span;
-    C.before = __builtin_amdgcn_readfirstlane(tab->before);
-    C.q = base + lane;
-    const bool act = lane >= (span & 255) && lane < (span >> 8);
-    const int32_t qa = act ? C.q : base;
-    const int32_t r0 = row[qa], deg = act ? row[qa + 1] - r0 : 0;
-    C.r0 = r0;
-    C.deg = deg;
-    C.own = ((L.sp_lds + S::boff((uint32_t)C.q)) << 5) | ((uint32_t)C.q & (uint32_t)(S::P - 1));
-    C.size = !__any(deg > 4) ? 4 : !__any(deg > 8) ? 8 : !__any(deg > 12) ? 12 : !__any(deg > kResMax) ? kResMax : -1;
-    auto take = [&](int d0, int d1) __attribute__((always_inline)) {
-        uint32_t en[4];
-#pragma unroll
-        for (int d = d0; d < d1; ++d) en[d - d0] = ent[r0 + d];
-#pragma unroll
-        for (int d = d0; d < d1; ++d) {
-            const uint32_t e = d < deg ? en[d - d0] : C.own;
-            C.ad[d] = e >> 5;
-            C.sh[d] = e;
-        }
-    };
-    const uint16_t* rp = (const uint16_t*)gx + (lane & 1);
-#pragma unroll
-    for (int c = 0; c < RPAD; ++c) C.rh[c] = act && c < nch ? (uint32_t)rp[8 * c] : 0x20000u;
-    if (C.size < 0) return;
-    take(0, 4);
-    if (C.size > 4) {
-        take(4, 8);
-        if (C.size > 8) {
-            take(8, 12);
-            if (C.size > 12) take(12, kResMax);
-        }
-    }
-}
-
-// Returns this lane's flips in spin-word form.
-template <int RPAD>
-__device__ __forceinline__ uint32_t res_update(const ResChunk<RPAD>& C, const VbUnit* __restrict__ up, const VbLds& L,
-                                               const uint32_t* ent, uint32_t t, int32_t nch, uint64_t key,
-                                               const uint32_t* gx)
-{
-    using S = Sl<RPAD>;
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
-    auto word = [&](uint32_t a) -> uint32_t { return *(const lds_u32*)(size_t)a; };
-    const uint32_t oa = C.own >> 5;
-    uint32_t cA = 0u, cB = 0u;
-    bool wide = false;
-    auto sum = [&](auto nd) __attribute__((always_inline)) {
-        constexpr int N = decltype(nd)::value;
-        uint32_t w[N];
-        const uint32_t ow = word(oa);
-#pragma unroll
-        for (int d = 0; d < N; ++d) w[d] = word(C.ad[d]);
-        const uint32_t o0 = ow >> (C.own & 31u);
-#pragma unroll
-        for (int d = 0; d < N; ++d) cA += ((w[d] >> (C.sh[d] & 31u)) ^ o0) & S::M;
-    };
-    if (C.size == 4) {
-        sum(std::integral_constant<int, 4>{});
-    } else if (C.size == 8) {
-        sum(std::integral_constant<int, 8>{});
-    } else if (C.size == 12) {
-        sum(std::integral_constant<int, 12>{});
-    } else if (C.size > 0) {
-        sum(std::integral_constant<int, kResMax>{});
-    } else {
-        // (with 8 slots the 4-bit counts would overflow: bytes, even chains in
-        // cA and odd ones in cB)
-        wide = RPAD == 8;
-        const uint32_t o0 = word(oa) >> (C.own & 31u);
-        for (int32_t d = 0; d < C.deg; ++d) {
-            const uint32_t en = ent[C.r0 + d];
-            const uint32_t f = (word(en >> 5) >> (en & 31u)) ^ o0;
-            cA += f & (RPAD == 8 ? 0x01010101u : S::M);
-            if (RPAD == 8) cB += (f >> 4) & 0x01010101u;
-        }
-    }
-    const uint32_t fl = vb_decide<RPAD>(up, L, gx, [&](int c) { return C.rh[c]; }, cA, cB, wide, C.deg, true, C.q, t, nch, key);
-    if (fl) {
-        const uint32_t f = fl << (C.own & 31u);
-        __atomic_fetch_xor((lds_u32*)(size_t)oa, f, __ATOMIC_RELAXED);
-        __atomic_fetch_xor((lds_u32*)(size_t)(oa + (L.cp_lds - L.sp_lds)), f, __ATOMIC_RELAXED);
-    }
-    return fl;
-}
-
-template <int RPAD>
-__device__ void vb_loop_res(const VbUnit* __restrict__ up, const VbLds& L, const int32_t* row, const uint32_t* ent,
-                            const ResTab* tab, uint32_t* done, const int32_t* cls, int64_t t0, int32_t nsw, int64_t t_max,
-                            int lane, int wave, int W)
-{
-    typedef __attribute__((address_space(3))) uint32_t lds_u32;
-    const int32_t nch = __builtin_amdgcn_readfirstlane(up->nch), ncls = __builtin_amdgcn_readfirstlane(up->ncls);
-    nsw = __builtin_amdgcn_readfirstlane(nsw);
-    W = __builtin_amdgcn_readfirstlane(W);
-    t0 = (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)((uint64_t)t0 >> 32)) << 32) |
-                   (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int32_t)(uint32_t)t0));
-    const uint64_t key = ((uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)(up->key >> 32)) << 32) |
-                         (uint64_t)__builtin_amdgcn_readfirstlane((uint32_t)up->key);
+    const uint64_t unit_key = (uint64_t)uniform64((int64_t)up->key);
     const bool win = __builtin_amdgcn_readfirstlane(up->kw) > 0;
-    int32_t chunks = 0;
-    for (int32_t k = 0; k < ncls; ++k) chunks += n_chunks(cls, k);
+    const int wl = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront inside the workgroup
+    lds_u32* const fin = (lds_u32*)(uint32_t*)L.flag;
+    constexpr int NE = RES ? kLdsMax : kHbmMax, H = RES ? 1 : 2;
     // (wavefronts past the chunks of a sweep only take part in its end)
     const int32_t step = min(W, chunks);
-    const int32_t B = vb_batch_chunks(nch);
-    const uint32_t mul = (65536u + (uint32_t)nch - 1u) / (uint32_t)nch;
-    const uint32_t fdq = ((uint32_t)lane * mul) >> 16;           // lane / nch = 8 i + g
-    const uint32_t fc = (uint32_t)lane - fdq * (uint32_t)nch, fi = min(fdq >> 3, (uint32_t)(B - 1));
-    const uint32_t frep = L.ri[2 * fc], finst = L.ri[2 * fc + 1];
-    const uint32_t* xg = (const uint32_t*)(L.xch + wave * 64) + (uint32_t)(lane >> 3) * (uint32_t)nch * 4u + ((uint32_t)(lane & 7) >> 1);
-    VbAcc<RPAD> acc;
-    ResChunk<RPAD> C;
-    int32_t id = wave, ps = wave < step ? 0 : nsw;   // the prepared chunk and its sweep
-    int32_t bi = B;                                  // its place in the batch of random numbers
-    auto prepare = [&]() __attribute__((always_inline)) {
-        if (bi >= B) {
-            // lane m draws group g of chain c for this wavefront's i-th chunk from here on, m = (8 i + g) nch + c
-            int32_t fid = id + (int32_t)fi * step;
-            uint32_t ft = (uint32_t)t0 + (uint32_t)ps;
-            while (fid >= chunks) {
-                fid -= chunks;
-                ++ft;
-            }
-            const U4 A = philox_stream(key, ((uint32_t)tab[fid].base >> 3) + (fdq & 7u), ft, kDomSweepHi, frep, finst);
-            L.xch[wave * 64 + lane] = make_uint4(A.x, A.y, A.z, A.w);
-            wave_sync();
-            bi = 0;
-        }
-        res_prepare<RPAD>(C, L, row, ent, tab + id, nch, xg + (uint32_t)bi * 32u * (uint32_t)nch);
+    const int32_t B = vb_batch_chunks(nchains);
+
+    auto tab_at = [&](int32_t id) -> VbChunk {
+        VbChunk T;
+        T.a = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tab[id].a);
+        T.b = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tab[id].b);
+        T.r0 = (uint32_t)__builtin_amdgcn_readfirstlane((int32_t)tab[id].r0);
+        return T;
     };
-    if (ps < nsw) prepare();
-    lds_u32* fin = (lds_u32*)done;
-    uint32_t first = 0u;   // number of the sweep's first chunk
-    for (int32_t s = 0; s < nsw; ++s, first += (uint32_t)chunks) {
-        while (ps == s) {
-            const uint32_t need = first + (uint32_t)C.before;
-            while ((int32_t)(__builtin_amdgcn_readfirstlane(*(volatile lds_u32*)fin) - need) < 0) {}
-            wave_sync();
-            __builtin_amdgcn_s_setprio(3);
-            const uint32_t fl = res_update<RPAD>(C, up, L, ent, (uint32_t)t0 + (uint32_t)s, nch, key, xg + (uint32_t)bi * 32u * (uint32_t)nch);
-            // (the LDS operations of a wavefront take effect in order)
-            wave_sync();
-            if (lane == 0) __atomic_fetch_add(fin, 1u, __ATOMIC_RELAXED);
-            __builtin_amdgcn_s_setprio(0);
-            wave_sync();
-            acc_add(acc, fl, L, nch);
-            ++bi;
-            id += step;
-            if (id >= chunks) {
-                id -= chunks;
-                ++ps;
+    auto wrap = [&](int32_t& id) {
+        const bool over = id >= chunks;
+        id -= over ? chunks : 0;
+        return over;
+    };
+    VbAcc<RPAD> acc;
+    // this wavefront's current chunk and its sweep; the sweep the unit is in, its
+    // first chunk's number and (split units) the class the members are in
+    int32_t id = min(wave, chunks - 1), cs = wave < step ? 0 : nsw;
+    int32_t s = 0, k = 0;
+    uint32_t first = 0u;
+    auto exchange = [&]() {
+        const int32_t lo = cls_at(cls, k), hi = cls_at(cls, k + 1);
+        ++k;
+        return vb_exchange<RPAD>(up, L, lo, hi, (uint32_t)up->members * (uint32_t)(s * ncls + k));
+    };
+    // ends the sweeps before `to`
+    auto sweeps = [&](int32_t to) -> bool {
+        while (s < to) {
+            if (SPLIT) {
+                while (k < ncls)
+                    if (!exchange()) return false;
+                k = 0;
             }
-            if (ps < nsw) prepare();
+            ++s;
+            first += (uint32_t)chunks;
         }
-        const int64_t tn = t0 + s + 1;
+        return true;
+    };
+
+    // The sweeps are run in stretches up to one after which all wavefronts meet for a
+    // snapshot or the windowed sums.  Nothing but scalars lives from one stretch to
+    // the next (the lane number is opaque in each, so that what follows from it is
+    // not kept either): no vector register is held, or spilled, over those calls.
+    for (;;) {
+        int32_t stop = nsw;
+        {
+            const int64_t tn = t0 + s + 1;
+            const int64_t te = win || tn <= 1 ? tn : (int64_t)1 << (64 - __clzll((unsigned long long)(tn - 1)));
+            if (te <= t_max && te - t0 < nsw) stop = (int32_t)(te - t0);
+        }
+        if (cs < stop) {
+            int ln = lane;
+            asm volatile("" : "+v"(ln));
+            const FillLane fr = fill_lane(L, ln, nchains);
+            const uint32_t* xg = (const uint32_t*)(L.xch + wl * 64) + (uint32_t)(ln >> 3) * (uint32_t)nchains * 4u + (((uint32_t)ln & 7u) >> 1);
+            // the next chunk and the one after (a chunk's record is read two chunks ahead)
+            int32_t id2 = id;
+            VbChunk T0 = tab_at(id), T1, T2;
+            id2 += step;
+            wrap(id2);
+            T1 = tab_at(id2);
+            id2 += step;
+            wrap(id2);
+            T2 = tab_at(id2);
+            // batches of several chunks (fewer than 5 chains): position and sweep of this
+            // lane's block of the next batch
+            int32_t bi = B, f_id = 0, f_base = 0;
+            uint32_t f_t = 0u;
+            auto ahead = [&](int32_t fid, uint32_t t) {
+                f_id = fid;
+                f_t = t;
+                while (f_id >= chunks) {
+                    f_id -= chunks;
+                    ++f_t;
+                }
+                f_base = VbChunk{tab[f_id].a, 0u, 0u, 0u}.base() + 64 * (H > 1 ? (int32_t)fr.i & 1 : 0);
+            };
+            // E holds the rows and entries of the current chunk (in flight), R the rows of
+            // the next one
+            Stage<NE, H> E, R;
+            auto request = [&]() __attribute__((always_inline)) {
+                // (past the last chunk of the launch these re-read entries that are not
+                // used: no branch)
+                rows_ready(E, R, T0, ln);
+                load_ents(ent, E, T0.degree());
+                load_rows(row, T1, ln, R);
+            };
+            auto one = [&]() __attribute__((always_inline)) -> bool {
+                const VbChunk T = T0;
+                // (opaque: the tests of chain numbers stay scalar comparisons here and the
+                // round keys are formed here, instead of being kept, and spilled, across the
+                // loop)
+                int32_t nch = nchains;
+                uint64_t key = unit_key;
+                asm volatile("" : "+s"(nch), "+s"(key));
+                const uint32_t t = (uint32_t)t0 + (uint32_t)s;
+                const int32_t q = T.base() + ln;
+                T0 = T1;
+                T1 = T2;
+                id2 += step;
+                wrap(id2);
+                T2 = tab_at(id2);
+                Draws<RPAD, H> A;
+                {
+                    auto take = [&](int h, int block) __attribute__((always_inline)) {
+                        const uint32_t* gx = xg + (uint32_t)block * 32u * (uint32_t)nch;
+#pragma unroll
+                        for (int c = 0; c < RPAD; ++c)
+                            if (c <= RPAD / 2 || c < nch) A.a[h][c] = ((const uint16_t*)(gx + 4 * c))[ln & 1];
+                    };
+                    if (RPAD == 8) {
+                        // one block a pass: both passes are drawn together, then go through
+                        // the same LDS in turn, the first block's last
+                        U4 d[H];
+#pragma unroll
+                        for (int h = 0; h < H; ++h) d[h] = fill_draw(fr, (uint32_t)T.base() + 64u * (uint32_t)h, t, key);
+                        fill_put(L, d[H - 1], wl, ln);
+                        take(0, 0);
+                        if (H == 2) {
+                            wave_sync();
+                            fill_put(L, d[0], wl, ln);
+                            A.first = (const uint16_t*)xg + (ln & 1);
+                        }
+                    } else {
+                        if (bi >= B) {
+                            fill_put(L, fill_draw(fr, (uint32_t)f_base, f_t, key), wl, ln);
+                            bi = 0;
+                            ahead(f_id + B / H * step, f_t);
+                        }
+#pragma unroll
+                        for (int h = 0; h < H; ++h) take(h, bi + h);
+                        bi += H;
+                    }
+                }
+                uint32_t own_ad[H], own_sh[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    own_ad[h] = L.sp_lds + Sl<RPAD>::boff((uint32_t)(q + 64 * h));
+                    own_sh[h] = (uint32_t)(q + 64 * h) & (uint32_t)(Sl<RPAD>::P - 1);
+                }
+                entries_ready<RPAD, CPL>(E, T, q, L);
+                // (a resident unit's latency is the time from the wait on: addresses before it)
+                uint32_t ad[RES ? NE : 1];
+                if (RES) {
+#pragma unroll
+                    for (int d = 0; d < NE; ++d) {
+                        ad[RES ? d : 0] = E.e[0][d >> 2][d & 3] >> 5;
+                        asm volatile("" : "+v"(ad[RES ? d : 0]));   // (not after the wait)
+                    }
+                }
+                if (SPLIT) {
+                    while (k < T.cls())
+                        if (!exchange()) return false;
+                } else {
+                    const uint32_t need = first + (uint32_t)T.before();
+                    uint32_t done;
+                    while ((int32_t)((done = __builtin_amdgcn_readfirstlane(*(volatile lds_u32*)fin)) - need) < 0) {}
+                    wave_sync();
+                    if (RES) {
+                        __builtin_amdgcn_s_setprio(3);
+                    } else {
+                        // The scheduler prefers the oldest of a SIMD's wavefronts,
+                        // which would run ahead and wait at the end of each class (1640
+                        // cycles a chunk, the youngest 300): the wavefronts behind
+                        // the unit's average get the higher priority
+                        const int32_t behind = (int32_t)(done - first) - id;
+                        if (behind > 0)
+                            __builtin_amdgcn_s_setprio(3);
+                        else if (behind > -4)
+                            __builtin_amdgcn_s_setprio(2);
+                        else if (behind > -8)
+                            __builtin_amdgcn_s_setprio(1);
+                        else
+                            __builtin_amdgcn_s_setprio(0);
+                    }
+                }
+                uint32_t cA[H], cB[H];
+                auto nbr = [&](int h, int d, uint32_t& a, uint32_t& sh, uint32_t& sg) __attribute__((always_inline)) {
+                    entry_word<RPAD, CPL>(E.e[h][d >> 2][d & 3], L.sp_lds, a, sh, sg);
+                    if (RES) a = ad[RES ? d : 0];
+                };
+                const bool wide = chunk_count<RPAD, CPL>(E, T, q, L, ent, nbr, own_ad, own_sh, cA, cB);
+                int32_t deg[H];
+#pragma unroll
+                for (int h = 0; h < H; ++h) deg[h] = E.deg[h];
+                // the entries have been used: the next chunk's are requested here (HBM), or
+                // once the chunk is finished (LDS: a resident unit's wait is over sooner)
+                if (!RES) request();
+                const uint32_t fl = chunk_flip<RPAD, CPL, H>(Site{up, key, t, q, nch}, T, L, A, cA, cB, wide, deg, own_ad, own_sh);
+                wave_sync();
+                if (SPLIT) {
+                    // a member of a split unit also writes the chunk's words through to HBM
+                    using S = Sl<RPAD>;
+                    if (ln < 64 * H / S::P) {
+                        const uint32_t wi = ((uint32_t)T.base() >> S::LP) + (uint32_t)ln;
+                        if (wi < (uint32_t)up->state_words) gl(up->state)[wi] = L.sp[wi];
+                    }
+                } else {
+                    // (the LDS operations of a wavefront take effect in order)
+                    if (ln == 0) __atomic_fetch_add(fin, 1u, __ATOMIC_RELAXED);
+                    if (RES) __builtin_amdgcn_s_setprio(0);
+                    wave_sync();
+                }
+                if (RES) request();
+                acc_add<RPAD, H>(acc, fl, L, nch);
+                id += step;
+                if (wrap(id) && ++cs < stop) return sweeps(cs);
+                return true;
+            };
+            if (RPAD < 8) ahead(id + (int32_t)fr.i / H * step, (uint32_t)t0 + (uint32_t)cs);
+            load_rows(row, T0, ln, R);
+            rows_ready(E, R, T0, ln);
+            load_ents(ent, E, T0.degree());
+            load_rows(row, T1, ln, R);
+            do {
+                if (!one()) return;
+            } while (cs < stop);
+        }
+        if (!sweeps(stop)) return;
+        acc_fold(acc);
+        acc_flush(acc, L, nchains);
+        const int64_t tn = t0 + stop;
         if (tn <= t_max && (win || (tn & (tn - 1)) == 0)) {
-            __syncthreads();
-            vb_sweep_end<RPAD, false>(up, L, tn, t_max);
+            if (!SPLIT) __syncthreads();
+            vb_sweep_end<RPAD, SPLIT>(up, L, tn, t_max);
         }
+        if (stop >= nsw) break;
     }
-    acc_fold(acc);
-    acc_flush(acc, L, nch);
     __syncthreads();
 }
 
@@ -1337,7 +1394,7 @@ size_t vb_resident_bytes(int32_t n, int32_t m2, int32_t ncls)
 {
     // row starts, entries, chunks (a class boundary inside a block of 64 positions adds one)
     const size_t chunks = (size_t)n / 64 + 1 + (size_t)ncls;
-    return ((size_t)(n + 1 + m2 + kResPad) * 4 + chunks * sizeof(ResTab) + 15) & ~(size_t)15;
+    return ((size_t)(n + 1 + m2 + kVbEntPad) * 4 + chunks * sizeof(VbChunk) + 15) & ~(size_t)15;
 }
 
 size_t vb_lds_bytes(int32_t n, int32_t rpad, int32_t nch, int threads, bool cpl)

@@ -19,7 +19,7 @@ __device__ __forceinline__ SG_G T* gl(T* p)
 }
 
 constexpr int kVbMaxChains = 8;    // chains per VB work unit
-constexpr int kVbEntPad = 8;       // zero entries after the adjacency (loads past a row stay in bounds)
+constexpr int kVbEntPad = 12;      // zero entries after the adjacency (loads past a row stay in bounds)
 constexpr int kVbXMax = 64;        // threshold table length (max degree 63)
 constexpr int kMaxGrid = 32;       // grid times {0} U {2^k <= t_max}, t_max < 2^31
 
@@ -38,6 +38,28 @@ struct VbLayout {
     __host__ __device__ int32_t bit(int64_t p, int32_t c) const { return c * P + (int32_t)(p % P); }
 };
 
+// A chunk: the positions of one colour class inside one aligned block of 64 (units
+// whose adjacency is resident) or inside two consecutive ones.  The chunks of a
+// graph stand in sweep order (n <= 2^20: at most 2^14 + 64).
+struct VbChunk {
+    uint32_t a;   // block | lo << 16 | (hi - 1) << 22 | even << 29 | full << 30
+    uint32_t b;   // chunks of the classes before | degree << 16 | class << 22
+    uint32_t r0;  // row start of the first position
+    uint32_t pad;
+    // first position of the (first) block
+    __host__ __device__ __forceinline__ int32_t base() const { return (int32_t)(a & 0xffffu) << 6; }
+    // first and one past the last of its positions in the class
+    __host__ __device__ __forceinline__ int32_t lo() const { return (int32_t)(a >> 16 & 63u); }
+    __host__ __device__ __forceinline__ int32_t hi() const { return (int32_t)(a >> 22 & 127u) + 1; }
+    // every position has the largest degree, and no entry past it is read; every
+    // position is in the class
+    __host__ __device__ __forceinline__ bool even() const { return (a >> 29 & 1u) != 0u; }
+    __host__ __device__ __forceinline__ bool full() const { return (a >> 30 & 1u) != 0u; }
+    __host__ __device__ __forceinline__ int32_t before() const { return (int32_t)(b & 0xffffu); }
+    __host__ __device__ __forceinline__ int32_t degree() const { return (int32_t)(b >> 16 & 63u); }   // largest
+    __host__ __device__ __forceinline__ int32_t cls() const { return (int32_t)(b >> 22); }
+};
+
 // One VB work unit = one workgroup: a graph in sweep (colour) order and up to
 // eight chains that share it.  The chains' spins live in LDS during a launch,
 // in the VbLayout packing (the same words as `state` between launches).
@@ -46,6 +68,8 @@ struct VbUnit {
     const uint32_t* ent;       // [2m + kVbEntPad] neighbour position | (J < 0) << 31, then zeros
     const uint32_t* entc;      // (cpl) the same entries in the form of vb_cpl_entries, read by the sweep
     const int32_t* cls;        // [ncls+1] first position of each colour class
+    const VbChunk* chunk;      // [chunks]
+    int32_t chunks;            // chunks of a sweep
     int32_t resident;          // 1: whole adjacency kept in LDS for the launch
     int32_t cpl;               // 1: a complemented copy of the spin words is kept in LDS
     int32_t m2;                // 2m entries
