@@ -1687,7 +1687,7 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, hipStream_t s, int32_t 
 {
     const int32_t K = c->K;
     if (c->kind == 0) {
-        hip_check(vb_bond(c->units_d, (int)c->units.size(), k_first, kd, bond, c->unit_chain_ids_d, K,
+        hip_check(vb_bond(c->units_d, (int)c->units.size(), c->n_chains, 32 * c->max_words, k_first, kd, bond, c->unit_chain_ids_d, K,
                           std::min(1024, c->vb_threads), c->bond_lds, s));
         hip_check(vbm_bond(c->vbm_d, (int)c->vbm.size(), k_first, kd, bond, c->vbm_ids_d, K, s));
     } else if (c->sk_real) {

@@ -164,9 +164,10 @@ hipError_t skg_recompute(const SkSample* samples, int n_samples, const SkChain* 
 hipError_t skg_bond(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int max_nch,
                     int k_done, int k_cap, double* part, double* out, hipStream_t s);
 
-// bond sums of the snapshots k_first .. k_done - 1 of every chain:
-// bond_out[chain][k] (the other entries are left as they are)
-hipError_t vb_bond(const VbUnit* units, int n_units, int k_first, int k_done, long long* bond_out,
+// bond sums of the snapshots k_first .. k_done - 1 of every chain of the units:
+// bond_out[chain][k] (the other times are left as they are; bond_out has n_chains
+// rows, and those of other chains become 0 at these times)
+hipError_t vb_bond(const VbUnit* units, int n_units, int n_chains, int max_n, int k_first, int k_done, long long* bond_out,
                    const int32_t* unit_chain_ids, int k_cap, int threads, size_t lds_bytes,
                    hipStream_t s);
 // Counts of unequal spins over every pair of a chain's first k_done snapshots

@@ -218,23 +218,42 @@ __global__ void __launch_bounds__(256) pack_kernel(PackList L, uint32_t* __restr
     }
 }
 
-// grid = (units, k_done).  Snapshot bits of the unit's chains are staged in
-// LDS chain-major; every directed adjacency entry is visited once, so the sum
-// counts each edge twice.
+// Positions of a unit that one workgroup of vb_bond_kernel sums over.
+constexpr int kBondSlice = 32768;
+
+// grid = (units, times, slices of kBondSlice positions).  Snapshot bits of the
+// unit's chains are staged in LDS chain-major; the workgroup visits the adjacency of
+// its slice, each edge from its lower end, and adds its sums to `out` (zero before).
+// A graph's slices each stage all its spins (128 KB for 2^20 spins and one chain, from
+// L2) so that one large graph does not leave the chip to a single workgroup.
+// Measured, one new time: two chains of 985767 spins 250 us (1520 with one workgroup
+// a unit; slices of 16384 290, 8192 390), 512 chains of 2^10 to 2^20 spins 470 (2250).
+// Bound by staging and by the gathers' latency at one workgroup a CU.
 __global__ void __launch_bounds__(1024) vb_bond_kernel(const VbUnit* __restrict__ units,
                                                        const int32_t* __restrict__ chain_ids,
                                                        int k_first, int k_cap, long long* __restrict__ out)
 {
-    extern __shared__ uint32_t bsm[];
+    extern __shared__ __attribute__((aligned(16))) uint32_t bsm[];
     const VbUnit* up = units + blockIdx.x;
     if (up->member != 0) return;   // a split unit is measured once
     const int k = k_first + (int)blockIdx.y;
     const int32_t n = up->n, wn = up->words_n, nch = up->nch;
+    const int32_t p0 = (int32_t)blockIdx.z * kBondSlice, p1 = min(n, p0 + kBondSlice);
+    if (p0 >= n) return;
     long long* red = (long long*)(bsm + ((nch * wn + 1) & ~1));
-    for (int32_t idx = threadIdx.x; idx < nch * wn; idx += blockDim.x) {
-        const int32_t c = idx / wn;
-        const int32_t w = idx - c * wn;
-        bsm[idx] = up->snap[c][(int64_t)k * wn + w];
+    const int bd = (int)blockDim.x;
+    for (int c = 0; c < nch; ++c) {
+        const uint32_t* src = up->snap[c] + (int64_t)k * wn;
+        uint32_t* dst = bsm + c * wn;
+        int32_t w = (int32_t)threadIdx.x;
+        for (; w + 7 * bd < wn; w += 8 * bd) {
+            uint32_t v[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = src[w + j * bd];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) dst[w + j * bd] = v[j];
+        }
+        for (; w < wn; w += bd) dst[w] = src[w];
     }
     if (threadIdx.x < kVbMaxChains) red[threadIdx.x] = 0;
     __syncthreads();
@@ -243,18 +262,46 @@ __global__ void __launch_bounds__(1024) vb_bond_kernel(const VbUnit* __restrict_
     for (int c = 0; c < kVbMaxChains; ++c) sum[c] = 0;
     const int32_t* __restrict__ row = up->row;
     const uint32_t* __restrict__ ent = up->ent;
-    for (int32_t p = threadIdx.x; p < n; p += blockDim.x) {
-        const int32_t e0 = row[p], e1 = row[p + 1];
-        for (int32_t e = e0; e < e1; ++e) {
-            const uint32_t en = ent[e];
-            const int32_t q = (int32_t)(en & 0x7fffffffu);
-            const uint32_t neg = en >> 31;
+    // four positions of a thread at a time, four entries of each (the adjacency is
+    // followed by kVbEntPad zeros): their loads are in flight together
+    for (int32_t p = p0 + (int32_t)threadIdx.x; p < p1; p += 4 * bd) {
+        int32_t e0[4], e1[4];
+        uint32_t own[4];   // bit c: chain c's spin
 #pragma unroll
-            for (int c = 0; c < kVbMaxChains; ++c) {
-                if (c >= nch) break;
-                const uint32_t bp = (bsm[c * wn + (p >> 5)] >> (p & 31)) & 1u;
-                const uint32_t bq = (bsm[c * wn + (q >> 5)] >> (q & 31)) & 1u;
-                sum[c] += 1 - 2 * (int32_t)(bp ^ bq ^ neg);
+        for (int j = 0; j < 4; ++j) {
+            const int32_t pj = p + j * bd;
+            e0[j] = pj < p1 ? row[pj] : 0;
+            e1[j] = pj < p1 ? row[pj + 1] : 0;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int32_t pj = min(p + j * bd, n - 1);
+            own[j] = 0u;
+#pragma unroll
+            for (int c = 0; c < kVbMaxChains; ++c)
+                if (c < nch) own[j] |= ((bsm[c * wn + (pj >> 5)] >> (pj & 31)) & 1u) << c;
+        }
+        while (e0[0] < e1[0] || e0[1] < e1[1] || e0[2] < e1[2] || e0[3] < e1[3]) {
+            uint32_t en[4][4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) en[j][i] = ent[min(e0[j], e1[j]) + i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int32_t q = (int32_t)(en[j][i] & 0x7fffffffu);
+                    if (e0[j] + i >= e1[j] || q < p + j * bd) continue;
+                    const uint32_t neg = en[j][i] >> 31;
+#pragma unroll
+                    for (int c = 0; c < kVbMaxChains; ++c) {
+                        if (c >= nch) break;
+                        const uint32_t bq = bsm[c * wn + (q >> 5)] >> (q & 31);
+                        sum[c] += 1 - 2 * (int32_t)(((own[j] >> c) ^ bq ^ neg) & 1u);
+                    }
+                }
+                e0[j] += 4;
             }
         }
     }
@@ -263,9 +310,17 @@ __global__ void __launch_bounds__(1024) vb_bond_kernel(const VbUnit* __restrict_
         if (c < nch && sum[c] != 0)
             atomicAdd((unsigned long long*)&red[c], (unsigned long long)(long long)sum[c]);
     __syncthreads();
-    if (threadIdx.x < nch)
-        out[(int64_t)chain_ids[blockIdx.x * kVbMaxChains + threadIdx.x] * k_cap + k] =
-            red[threadIdx.x] / 2;
+    if (threadIdx.x < nch && red[threadIdx.x] != 0)
+        atomicAdd((unsigned long long*)&out[(int64_t)chain_ids[blockIdx.x * kVbMaxChains + threadIdx.x] * k_cap + k],
+                  (unsigned long long)red[threadIdx.x]);
+}
+
+// out[i][k_first .. k_done) = 0 for every row of k_cap.
+__global__ void zero_columns_kernel(long long* out, int64_t rows, int k_first, int k_done, int k_cap)
+{
+    const int w = k_done - k_first;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < rows * w; i += (int64_t)gridDim.x * blockDim.x)
+        out[i / w * k_cap + k_first + i % w] = 0;
 }
 
 __global__ void zero_kernel(long long* p, size_t n)
@@ -351,7 +406,7 @@ hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t vb_bond(const VbUnit* units, int n_units, int k_first, int k_done, long long* bond_out,
+hipError_t vb_bond(const VbUnit* units, int n_units, int n_chains, int max_n, int k_first, int k_done, long long* bond_out,
                    const int32_t* unit_chain_ids, int k_cap, int threads, size_t lds_bytes,
                    hipStream_t s)
 {
@@ -360,8 +415,13 @@ hipError_t vb_bond(const VbUnit* units, int n_units, int k_first, int k_done, lo
     static const hipError_t attr = hipFuncSetAttribute((const void*)vb_bond_kernel,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL(vb_bond_kernel, dim3(n_units, k_done - k_first), dim3(threads), lds_bytes, s, units,
-                       unit_chain_ids, k_first, k_cap, bond_out);
+    const int64_t cells = (int64_t)n_chains * (k_done - k_first);
+    hipLaunchKernelGGL(zero_columns_kernel, dim3((unsigned)std::min<int64_t>(1024, (cells + 255) / 256)), dim3(256), 0, s,
+                       bond_out, (int64_t)n_chains, k_first, k_done, k_cap);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(vb_bond_kernel, dim3(n_units, k_done - k_first, (max_n + kBondSlice - 1) / kBondSlice), dim3(threads),
+                       lds_bytes, s, units, unit_chain_ids, k_first, k_cap, bond_out);
     return hipGetLastError();
 }
 
