@@ -939,8 +939,10 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     // split units of all contexts of the process on the device use at most
     // half of the CUs (a process-wide ledger), so that they can all be
     // resident at once next to other work, and an automatic plan takes at
-    // most a quarter of the CUs, so that two large contexts built at the same
-    // time (a server's batches) both split their largest units.
+    // most half of what is left (64 members, then 32, 16, ...), so that every
+    // large context built at the same time (a server's batches) splits its
+    // largest units: contexts of one request of 985767 spins and 2 chains, us per
+    // sweep, 66, 77, 119 and 203 (with 64 members for the first two 66, 66, 565, 565).
     // Members per unit: plan_split (sg_split_plan.h), by cost n (10 + chains).
     // opts.split_members: 0 automatic, 1 never, k >= 2 every unit that has
     // the chunks for k members (tests, tuning).  No effect on any result.
@@ -956,7 +958,7 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         // together stay within half of the CUs (members reserved while their
         // context lives, so that all of them can be resident at once)
         c->split_held = g_split_ledger.reserve(c->device, n_cu / 2, [&](int avail) {
-            const int budget = forced == 0 ? std::min(avail, n_cu / 4) : avail;
+            const int budget = forced == 0 ? avail / 2 : avail;
             std::vector<SplitUnit> su(plan.size());
             for (size_t i = 0; i < plan.size(); ++i) {
                 const VbGraph& g = graphs[(size_t)plan[i].group];

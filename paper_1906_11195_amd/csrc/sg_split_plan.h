@@ -9,7 +9,10 @@
 // shortens a launch only if no unit left whole outlasts the split ones, so
 // the automatic plan splits the units above twice a CU's share of the cost
 // only when all of them get at least two members, or else the largest
-// leading group of them with three times the cost of every unit left whole.
+// leading group of them with three times the cost of every unit left whole, or
+// else as many of the costliest as there is room for, in two each, if that shortens
+// the longest launch by a sixth and more (sizes spread over decades: 256 graphs of
+// 2^10 to 2^20 spins with 2 replicas 446 us per sweep, 610 whole).
 // Their members are shared out in proportion to cost, so that every member
 // carries about the same part of a sweep, with a floor per member that rises
 // with the number of split units: members of many split units meet at their
@@ -18,7 +21,8 @@
 // 1 graph 13 members 33, 4 graphs 8 members 41 (4: 48), 16 graphs 4 members
 // 57 (6: 61, 8: 73), 64 graphs 2 members 78 (whole: 82; with a budget of a
 // quarter of the CUs they stay whole); one request of 985767 spins with 2
-// chains (two units), 8 members each 153, 16 97, 32 78, 64 82.
+// chains (two units), 32 members each 65, whole 565.  (All but the last line were
+// measured with a slower sweep; the order of the alternatives is what they show.)
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -35,6 +39,9 @@ constexpr int64_t kSplitMemberCostFew = 75000;
 constexpr int64_t kSplitMemberCostSome = 130000;
 constexpr int64_t kSplitMemberCostMany = 260000;
 constexpr int kSplitMaxMembers = 32;
+// what a member of a unit split in two adds to half its cost (one chain of 10^6 spins,
+// us per sweep: whole 568, two members 385 for one such unit and 443 for 32 at once)
+constexpr int64_t kSplitPairCost = 2500000;
 
 struct SplitUnit {
     int64_t cost;        // n (10 + chains)
@@ -66,6 +73,24 @@ inline int plan_split(const std::vector<SplitUnit>& units, int64_t share, int bu
             if (m == cand || units[by_cost[m - 1]].cost >= 3 * rest) {
                 n_auto = m;
                 break;
+            }
+        }
+    }
+    // no such group: the costliest units in two, when that shortens the longest
+    // launch by a sixth and more
+    if (forced == 0 && n_auto == 0 && by_cost.size() > 1) {
+        size_t cand = 0;
+        while (cand < by_cost.size() && !units[by_cost[cand]].resident && units[by_cost[cand]].cost >= 2 * share &&
+               units[by_cost[cand]].chunk_cap >= 2)
+            ++cand;
+        const size_t m = std::min(cand, (size_t)(budget / 2));
+        if (m >= 1) {
+            const int64_t most = units[by_cost[0]].cost;
+            const int64_t rest = by_cost.size() > m ? units[by_cost[m]].cost : 0;
+            if (6 * std::max(rest, most / 2 + kSplitPairCost) <= 5 * most) {
+                members.assign(units.size(), 1);
+                for (size_t r = 0; r < m; ++r) members[by_cost[r]] = 2;
+                return 2 * (int)m;
             }
         }
     }

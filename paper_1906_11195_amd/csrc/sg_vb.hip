@@ -559,7 +559,7 @@ __device__ __forceinline__ uint32_t chunk_flip(const Site& site, const VbChunk& 
 }
 
 // Split units: after a colour class, the members publish the words they
-// changed (already written through), meet at a device-scope barrier and read
+// changed (written through by the caller), meet at a device-scope barrier and read
 // the class's words back, so that every member's LDS copy is complete before
 // the next class.  The wait is bounded: a member that does not see all
 // arrivals within kBarrierTicks of the 100 MHz real-time clock raises the
@@ -603,7 +603,23 @@ __device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, int32
     if (L.flag[0] != 0) return false;
     const SG_G uint32_t* gs = gl(up->state);
     const int32_t w0 = lo >> S::LP, w1 = hi > lo ? ((hi - 1) >> S::LP) : w0 - 1;
-    for (int32_t w = w0 + (int32_t)threadIdx.x; w <= w1; w += (int32_t)blockDim.x) L.sp[w] = gs[w];
+    // (eight loads of a thread in flight: one at a time, a class of 3 10^5 spins
+    // waited ten times for HBM)
+    const int32_t bd = (int32_t)blockDim.x;
+    int32_t w = w0 + (int32_t)threadIdx.x;
+    for (; w + 7 * bd <= w1; w += 8 * bd) {
+        uint32_t v[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) v[j] = gs[w + j * bd];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) L.sp[w + j * bd] = v[j];
+    }
+    uint32_t v[7];
+#pragma unroll
+    for (int j = 0; j < 7; ++j) v[j] = w + j * bd <= w1 ? gs[w + j * bd] : 0u;
+#pragma unroll
+    for (int j = 0; j < 7; ++j)
+        if (w + j * bd <= w1) L.sp[w + j * bd] = v[j];
     __syncthreads();
     return true;
 }
@@ -1083,7 +1099,18 @@ __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, P
     int32_t id = min(wave, chunks - 1), cs = wave < step ? 0 : nsw;
     int32_t s = 0, k = 0;
     uint32_t first = 0u;
+    // split units: this wavefront's chunks of the class, the first one's base; their
+    // words are written through to HBM together at the end of the class (a store per
+    // chunk would be waited for with the next chunk's entries)
+    int32_t own_n = 0, own_base = 0;
     auto exchange = [&]() {
+        using S = Sl<RPAD>;
+        constexpr int LW = 6 + (H - 1) - S::LP;   // log2 of a chunk's words
+        for (int32_t i = lane; i < own_n << LW; i += 64) {
+            const uint32_t wi = ((uint32_t)(own_base + (i >> LW) * step * 64 * H) >> S::LP) + (uint32_t)(i & ((1 << LW) - 1));
+            if (wi < (uint32_t)up->state_words) gl(up->state)[wi] = L.sp[wi];
+        }
+        own_n = 0;
         const int32_t lo = cls_at(cls, k), hi = cls_at(cls, k + 1);
         ++k;
         return vb_exchange<RPAD>(up, L, lo, hi, (uint32_t)up->members * (uint32_t)(s * ncls + k));
@@ -1254,12 +1281,8 @@ __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, P
                 const uint32_t fl = chunk_flip<RPAD, CPL, H>(Site{up, key, t, q, nch}, T, L, A, cA, cB, wide, deg, own_ad, own_sh);
                 wave_sync();
                 if (SPLIT) {
-                    // a member of a split unit also writes the chunk's words through to HBM
-                    using S = Sl<RPAD>;
-                    if (ln < 64 * H / S::P) {
-                        const uint32_t wi = ((uint32_t)T.base() >> S::LP) + (uint32_t)ln;
-                        if (wi < (uint32_t)up->state_words) gl(up->state)[wi] = L.sp[wi];
-                    }
+                    own_base = own_n == 0 ? T.base() : own_base;
+                    ++own_n;
                 } else {
                     // (the LDS operations of a wavefront take effect in order)
                     if (ln == 0) __atomic_fetch_add(fin, 1u, __ATOMIC_RELAXED);
