@@ -4,7 +4,7 @@ Workload (one step = one pass of the whole path over the batch): the batched
 Viana-Bray configuration -- 256 Erdos-Renyi graphs (N = 65536, mean degree 4,
 +-1 couplings) x 3 temperatures {0.6, 0.8, 1.2} x 2 replicas = 1536 chains --
 advanced by `--sweeps-per-step` Metropolis sweeps (snapshots at grid times on
-the device), followed by the measurement (bond sums, overlaps, int8-MFMA Gram
+the device), followed by the measurement (bond sums, overlaps, Gram
 matrices of all snapshots).  Inputs are synthetic and seeded; all state is in
 HBM before the timed region starts.
 
@@ -32,7 +32,6 @@ if ROOT not in sys.path:
 METRIC = "spin flips/ns at 1 GPU (VB, SK), batched vs plain; p50/p99 run latency"
 HBM_PEAK_GBS = 8000.0
 HBM_PEAK_BPS = HBM_PEAK_GBS * 1e9
-MFMA_INT8_PEAK_OPS = 5.0e15   # dense int8 MFMA, MI355X
 # VALU issue: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles at 2.4 GHz
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 
@@ -246,18 +245,15 @@ def run_sk(args, torch, sg, workloads):
     upd = 64 * reps * n * args.sk_sweeps
     acc = float(res["accepted"].sum() - a0) / upd
     rate = upd / el
-    # algorithmic HBM bytes per attempted update: one bit-packed coupling row
-    # per accepted flip (a N / 8) plus the int8 J read by the exact recompute
-    # once per sample and period (N^2 / (period N R)); int8 MFMA work of the
-    # recompute: 2 N^2 R per sample and period (2 N / period per update)
-    hbm = rate * (acc * n / 8 + n / (period * reps))
-    mfma = rate * 2.0 * n / period
+    # coupling bytes per attempted update: the sweep streams the bit-packed
+    # couplings once per sweep and chain (N / 8 per update; a sample's replicas
+    # share them in L2, so HBM sees N / (8 R)), the exact recompute once per
+    # sample and period (N / (8 period R))
+    hbm = rate * (n / 8.0 / reps + n / 8.0 / (period * reps))
     return dict(workload="SK: 64 samples x 2 replicas, N=4096, T=0.5, sweeps 64..%d" % (64 + args.sk_sweeps),
                 updates_per_ns=rate / 1e9, accepted_fraction=acc, sweeps=args.sk_sweeps,
                 roofline={"bound": "latency", "hbm_GBps": round(hbm / 1e9, 1),
-                          "hbm_frac": round(hbm / HBM_PEAK_BPS, 4),
-                          "mfma_int8_TOPs": round(mfma / 1e12, 3),
-                          "mfma_frac": round(mfma / MFMA_INT8_PEAK_OPS, 6)})
+                          "hbm_frac": round(hbm / HBM_PEAK_BPS, 4)})
 
 
 def run_sk_gauss(args, torch, sg, workloads):
@@ -770,7 +766,7 @@ def main():
         "data": "synthetic",
         "config": {
             "workload": "VB batched: 256 ER graphs (N=65536, c=4, J=+-1) x T{0.6,0.8,1.2} x 2 replicas "
-                        "= 1536 chains; step = %d sweeps + observables + int8-MFMA Gram" % args.sweeps_per_step,
+                        "= 1536 chains; step = %d sweeps + observables + Gram matrices" % args.sweeps_per_step,
             "sweeps_per_step": args.sweeps_per_step,
             "chains": 1536,
             "spins_per_chain": 65536,
