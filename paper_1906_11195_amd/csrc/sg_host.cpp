@@ -1709,10 +1709,7 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, hipStream_t s, int32_t 
 // copy itself in small calls).
 class HostBlocks {
 public:
-    struct Block {
-        void* p = nullptr;
-        size_t bytes = 0;
-    };
+    typedef HostBlock Block;
     // p null if there is no such memory
     Block get(size_t bytes)
     {
@@ -1768,69 +1765,25 @@ HostBlocks& host_blocks()
     return *p;
 }
 
-// Device words of one measurement, brought to host memory together: by a kernel
-// that writes to mapped host memory, or, where there is none, by copies.
-class Fetch {
-public:
-    explicit Fetch(hipStream_t s) : s_(s) { list_.n = 0; }
-    ~Fetch()
+// The words of a measurement come to host memory by a kernel that writes to mapped
+// host memory, or, where there is none, by copies (sg_stage.h).
+struct StageDev {
+    hipStream_t s;
+    HostBlock get(size_t bytes) { return host_blocks().get(bytes); }
+    void put(const HostBlock& b) { host_blocks().put(b); }
+    void pack(const PackList& list, uint32_t* block)
     {
-        if (pending_) (void)hipStreamSynchronize(s_);
-        host_blocks().put(block_);
+        void* dev = nullptr;
+        if (block) hip_check(hipHostGetDevicePointer(&dev, block, 0));
+        hip_check(observe_pack(list, (uint32_t*)dev, s));
     }
-    Fetch(const Fetch&) = delete;
-    Fetch& operator=(const Fetch&) = delete;
-    // `rows` rows of `width` words, `stride` apart; the index to pass to at()
-    int add(const void* src, size_t rows, size_t width, size_t stride, bool clear = false)
+    void copy(uint32_t* dst, const PackSeg& g)
     {
-        PackSeg& g = list_.seg[list_.n];
-        g.src = (uint32_t*)src;
-        g.dst = words_;
-        g.stride = stride;
-        g.rows = (uint32_t)rows;
-        g.width = (uint32_t)width;
-        g.clear = clear ? 1u : 0u;
-        words_ += (rows * width + 1) & ~(size_t)1;
-        return list_.n++;
+        hip_check(hipMemcpy2DAsync(dst, (size_t)g.width * 4, g.src, g.stride * 4, (size_t)g.width * 4, g.rows,
+                                   hipMemcpyDeviceToHost, s));
     }
-    // enqueues the copies and waits for the stream
-    void run()
-    {
-        block_ = host_blocks().get(std::max<size_t>(8, words_ * 4));
-        pending_ = true;
-        if (block_.p) {
-            void* dev = nullptr;
-            hip_check(hipHostGetDevicePointer(&dev, block_.p, 0));
-            hip_check(observe_pack(list_, (uint32_t*)dev, s_));
-            base_ = (const uint32_t*)block_.p;
-        } else {
-            plain_.resize(std::max<size_t>(2, words_));
-            for (int i = 0; i < list_.n; ++i) {
-                const PackSeg& g = list_.seg[i];
-                if (g.rows && g.width)
-                    hip_check(hipMemcpy2DAsync(plain_.data() + g.dst, (size_t)g.width * 4, g.src, g.stride * 4,
-                                               (size_t)g.width * 4, g.rows, hipMemcpyDeviceToHost, s_));
-            }
-            hip_check(observe_pack(list_, nullptr, s_));
-            base_ = plain_.data();
-        }
-        hip_check(hipStreamSynchronize(s_));
-        pending_ = false;
-    }
-    template <class T>
-    const T* at(int i) const
-    {
-        return reinterpret_cast<const T*>(base_ + list_.seg[i].dst);
-    }
-
-private:
-    hipStream_t s_;
-    PackList list_;
-    size_t words_ = 0;
-    HostBlocks::Block block_;
-    std::vector<uint32_t> plain_;
-    const uint32_t* base_ = nullptr;
-    bool pending_ = false;
+    void sync() { hip_check(hipStreamSynchronize(s)); }
+    void sync_quiet() { (void)hipStreamSynchronize(s); }
 };
 
 // Runs f(first, last) over 0 .. count - 1, `bytes` of output each: on host threads
@@ -2053,7 +2006,7 @@ sg_status sg_measure(sg_ctx* c, uint32_t flags, sg_obs* out, void* stream)
         out->t_done = c->t_done;
         const bool obs = (flags & SG_MEASURE_OBS) != 0, spins = (flags & SG_MEASURE_SPINS) && out->spins;
         if (!obs && !spins) return;
-        Fetch F(s);
+        Fetch<StageDev> F(StageDev{s});
         const size_t nc = (size_t)c->n_chains, np = (size_t)c->n_pairs, tri = (size_t)K * (K - 1) / 2;
         const size_t kt = (size_t)kd * (kd - 1) / 2;
         // windowed sums beyond the interval reached are zero

@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sg_stage.h"
 #include "sg_vb_unit.h"
 
 namespace sg {
@@ -179,18 +180,7 @@ hipError_t observe(const MeasureChain* chains, int n_chains, int count, int R, i
 // The counts as Gram matrices [chain][k_cap][k_cap] and overlaps [pair][k_cap].
 hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs, int R, int k_done, int k_cap,
                           uint32_t* gram_cnt, uint32_t* ovl_cnt, long long* gram, long long* ovl, hipStream_t s);
-// Rows of device words to consecutive words of mapped host memory.
-struct PackSeg {
-    uint32_t* src;
-    uint64_t dst;              // word of the destination
-    uint64_t stride;           // words from row to row
-    uint32_t rows, width;
-    uint32_t clear;            // set the words to zero once read
-};
-struct PackList {
-    PackSeg seg[10];
-    int n;
-};
+// Copies the segments to mapped host memory and clears those that ask for it
 // (dst null: only clears)
 hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s);
 hipError_t zero_i64(long long* p, size_t n, hipStream_t s);

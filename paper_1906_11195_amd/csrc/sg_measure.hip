@@ -208,10 +208,9 @@ __global__ void __launch_bounds__(256) pack_kernel(PackList L, uint32_t* __restr
     const uint64_t step = (uint64_t)gridDim.x * blockDim.x, i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int s = 0; s < L.n; ++s) {
         const PackSeg g = L.seg[s];
-        const uint64_t words = (uint64_t)g.rows * g.width;
+        const uint64_t words = pack_words(g);
         for (uint64_t i = i0; i < words; i += step) {
-            const uint64_t r = words >> 32 ? i / g.width : (uint32_t)i / g.width;
-            uint32_t* p = g.src + r * g.stride + (i - r * g.width);
+            uint32_t* p = g.src + pack_from(g, i);
             if (dst) dst[g.dst + i] = *p;
             if (g.clear) *p = 0u;
         }
@@ -400,7 +399,7 @@ hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs,
 hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s)
 {
     uint64_t most = 0;
-    for (int i = 0; i < list.n; ++i) most = std::max<uint64_t>(most, (uint64_t)list.seg[i].rows * list.seg[i].width);
+    for (int i = 0; i < list.n; ++i) most = std::max(most, pack_words(list.seg[i]));
     const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(512, (most + 255) / 256));
     hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, list, dst);
     return hipGetLastError();
