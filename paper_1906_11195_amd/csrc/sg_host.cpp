@@ -20,6 +20,7 @@
 
 #include "sg.h"
 #include "sg_internal.h"
+#include "sg_layout.h"
 #include "sg_ledger.h"
 #include "sg_split_plan.h"
 #include "sg_philox.h"
@@ -385,17 +386,6 @@ int32_t grid_size(int64_t t_max)
     for (int64_t t = 1; t <= t_max; t <<= 1) ++k;
     return k;
 }
-
-// Device arena: one allocation carved into aligned pieces.
-struct Arena {
-    size_t size = 0;
-    size_t take(size_t bytes)
-    {
-        const size_t off = size;
-        size += (bytes + 255) & ~(size_t)255;
-        return off;
-    }
-};
 
 }  // namespace
 
@@ -1065,13 +1055,12 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
             ms_plan.push_back(std::move(mp));
         }
     }
-    std::vector<size_t> off_mjw(ms_plan.size()), off_mst(ms_plan.size()), off_mthr(ms_plan.size());
+    std::vector<VbmArrays> ms_bytes(ms_plan.size());
     for (size_t u = 0; u < ms_plan.size(); ++u) {
         const VbGraph& g = graphs[(size_t)ms_plan[u].group];
-        off_mjw[u] = A.take((g.ent.size() + kVbEntPad) * 8);
-        off_mst[u] = A.take((size_t)g.n * 8);
-        off_mthr[u] = A.take((size_t)2 * kVbmChains * kVbXMax * 4);
+        ms_bytes[u] = VbmArrays{(size_t)g.n * 8, (g.ent.size() + kVbEntPad) * 8, (size_t)2 * kVbmChains * kVbXMax * 4};
     }
+    const std::vector<VbmArrays> off_ms = vbm_layout(A, ms_bytes);
     const size_t off_vbm = A.take(std::max<size_t>(1, ms_plan.size()) * sizeof(VbmUnit));
     const size_t off_vbm_ids = A.take(std::max<size_t>(1, ms_plan.size()) * kVbmChains * 4);
 
@@ -1206,9 +1195,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         U.row = c->at<int32_t>(off_row[(size_t)mp.group]);
         U.ent = c->at<uint32_t>(off_ent[(size_t)mp.group]);
         U.cls = c->at<int32_t>(off_cls[(size_t)mp.group]);
-        U.jw = c->at<uint64_t>(off_mjw[u]);
-        U.state = c->at<uint64_t>(off_mst[u]);
-        U.thr = c->at<uint32_t>(off_mthr[u]);
+        U.jw = c->at<uint64_t>(off_ms[u].jw);
+        U.state = c->at<uint64_t>(off_ms[u].state);
+        U.thr = c->at<uint32_t>(off_ms[u].thr);
         U.n = (int32_t)g.n;
         U.ncls = g.ncls;
         U.nch = (int32_t)mp.chains.size();
@@ -1240,8 +1229,8 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
                 if (neg) jw[e] |= bit;
             }
         }
-        hip_check(hipMemcpy(c->at<void>(off_mthr[u]), thr.data(), thr.size() * 4, hipMemcpyHostToDevice));
-        hip_check(hipMemcpy(c->at<void>(off_mjw[u]), jw.data(), jw.size() * 8, hipMemcpyHostToDevice));
+        hip_check(hipMemcpy(c->at<void>(off_ms[u].thr), thr.data(), thr.size() * 4, hipMemcpyHostToDevice));
+        hip_check(hipMemcpy(c->at<void>(off_ms[u].jw), jw.data(), jw.size() * 8, hipMemcpyHostToDevice));
         c->vbm[u] = U;
     });
     for (size_t u = 0; u < ms_plan.size(); ++u) {

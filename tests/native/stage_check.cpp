@@ -5,6 +5,7 @@
 #include <cstring>
 #include <vector>
 
+#include "sg_layout.h"
 #include "sg_stage.h"
 
 #define CHECK(x)                                                   \
@@ -59,6 +60,36 @@ int large()
     return 0;
 }
 
+// The states of multispin units of different sizes are one range with nothing else
+// in it, and no array overlaps another.
+int states()
+{
+    sg::Arena A;
+    A.take(1000);
+    std::vector<sg::VbmArrays> bytes;
+    for (size_t u = 0; u < 40; ++u) bytes.push_back(sg::VbmArrays{8 * (100 + 37 * u), 8 * (400 + 99 * u), 32768});
+    const std::vector<sg::VbmArrays> off = sg::vbm_layout(A, bytes);
+    CHECK(off.size() == bytes.size());
+    size_t lo = SIZE_MAX, hi = 0, sum = 0;
+    std::vector<std::pair<size_t, size_t>> all;
+    for (size_t u = 0; u < off.size(); ++u) {
+        lo = std::min(lo, off[u].state);
+        hi = std::max(hi, off[u].state + bytes[u].state);
+        sum += (bytes[u].state + 255) / 256 * 256;
+        all.push_back({off[u].state, bytes[u].state});
+        all.push_back({off[u].jw, bytes[u].jw});
+        all.push_back({off[u].thr, bytes[u].thr});
+    }
+    CHECK(hi - lo <= sum);
+    std::sort(all.begin(), all.end());
+    for (size_t i = 0; i < all.size(); ++i) {
+        CHECK(all[i].first % 256 == 0);
+        CHECK(all[i].first + all[i].second <= (i + 1 < all.size() ? all[i + 1].first : A.size));
+    }
+    CHECK(all[0].first >= 1000);
+    return 0;
+}
+
 }  // namespace
 
 int main(int argc, char** argv)
@@ -66,6 +97,7 @@ int main(int argc, char** argv)
     const char* what = argc > 1 ? argv[1] : "";
     int rc = 2;
     if (!std::strcmp(what, "large")) rc = large();
+    if (!std::strcmp(what, "states")) rc = states();
     if (rc == 0) std::printf("stage ok\n");
     return rc;
 }

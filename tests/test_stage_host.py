@@ -29,3 +29,7 @@ def check(tmp_path_factory):
 
 def test_segments_past_2_to_32_words(check):
     check("large")
+
+
+def test_multispin_states_are_one_range(check):
+    check("states")
