@@ -1766,7 +1766,11 @@ struct StageDev {
         if (block) hip_check(hipHostGetDevicePointer(&dev, block, 0));
         hip_check(observe_pack(list, (uint32_t*)dev, s));
     }
-    void copy(uint32_t* dst, const PackSeg& g)
+    void copy(uint32_t* dst, const uint32_t* src, uint64_t words)
+    {
+        hip_check(hipMemcpyAsync(dst, src, words * 4, hipMemcpyDeviceToHost, s));
+    }
+    void copy_rows(uint32_t* dst, const PackSeg& g)
     {
         hip_check(hipMemcpy2DAsync(dst, (size_t)g.width * 4, g.src, g.stride * 4, (size_t)g.width * 4, g.rows,
                                    hipMemcpyDeviceToHost, s));

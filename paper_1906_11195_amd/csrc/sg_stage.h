@@ -45,8 +45,9 @@ struct HostBlock {
 //   void pack(const PackList&, uint32_t* block)   enqueues the copy of all segments
 //                                       to their places in the block and the clearing
 //                                       (block null: only that)
-//   void copy(uint32_t* dst, const PackSeg&)      enqueues the copy of one segment
-//                                       to ordinary memory
+//   void copy(uint32_t* dst, const uint32_t* src, uint64_t words)    enqueues a copy to
+//                                       ordinary memory
+//   void copy_rows(uint32_t* dst, const PackSeg&)    the same of a segment's rows
 //   void sync()                         waits for what was enqueued
 //   void sync_quiet()                   the same on the way out of an error
 // All but put and sync_quiet may throw.
@@ -84,8 +85,17 @@ public:
             base_ = (const uint32_t*)block_.p;
         } else {
             plain_.resize(std::max<size_t>(2, words_));
-            for (int i = 0; i < list_.n; ++i)
-                if (pack_words(list_.seg[i])) dev_.copy(plain_.data() + list_.seg[i].dst, list_.seg[i]);
+            for (int i = 0; i < list_.n; ++i) {
+                const PackSeg& g = list_.seg[i];
+                uint32_t* dst = plain_.data() + g.dst;
+                if (pack_words(g) == 0) continue;
+                // (a single row's stride means nothing, and a copy by rows takes none
+                // below its width)
+                if (g.rows == 1 || g.stride == g.width)
+                    dev_.copy(dst, g.src, pack_words(g));
+                else
+                    dev_.copy_rows(dst, g);
+            }
             dev_.pack(list_, nullptr);
             base_ = plain_.data();
         }

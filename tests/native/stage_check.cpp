@@ -2,6 +2,7 @@
 // tests/test_stage_host.py; no GPU): a stand-in for the device copies between
 // ordinary arrays and refuses what the device's calls refuse.
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <vector>
 
@@ -28,10 +29,103 @@ struct Recorder {
     sg::HostBlock get(size_t) { return sg::HostBlock{log, 1}; }
     void put(const sg::HostBlock&) {}
     void pack(const sg::PackList& l, uint32_t*) { log->seen.assign(l.seg, l.seg + l.n); }
-    void copy(uint32_t*, const sg::PackSeg&) {}
+    void copy(uint32_t*, const uint32_t*, uint64_t) {}
+    void copy_rows(uint32_t*, const sg::PackSeg&) {}
     void sync() {}
     void sync_quiet() {}
 };
+
+// Copies at once between ordinary arrays.
+struct Bad {};
+struct Copier {
+    bool mapped;
+    sg::HostBlock get(size_t bytes) { return mapped ? sg::HostBlock{std::malloc(bytes), bytes} : sg::HostBlock{}; }
+    void put(const sg::HostBlock& b) { std::free(b.p); }
+    void pack(const sg::PackList& l, uint32_t* block)
+    {
+        for (int s = 0; s < l.n; ++s)
+            for (uint64_t i = 0; i < sg::pack_words(l.seg[s]); ++i) {
+                uint32_t* p = l.seg[s].src + sg::pack_from(l.seg[s], i);
+                if (block) block[l.seg[s].dst + i] = *p;
+                if (l.seg[s].clear) *p = 0u;
+            }
+    }
+    void copy(uint32_t* dst, const uint32_t* src, uint64_t words) { std::memcpy(dst, src, words * 4); }
+    void copy_rows(uint32_t* dst, const sg::PackSeg& g)
+    {
+        if (g.stride < g.width) throw Bad{};   // an invalid pitch
+        for (uint64_t r = 0; r < g.rows; ++r) std::memcpy(dst + r * g.width, g.src + r * g.stride, g.width * 4);
+    }
+    void sync() {}
+    void sync_quiet() {}
+};
+
+// The segments of a measurement, as sg_measure adds them: single words and rows
+// without a stride, the first columns of rows, none at all, counts that are cleared.
+struct Words {
+    std::vector<uint32_t> a, b, c, d, e;
+};
+template <class Dev>
+std::vector<uint32_t> bring(Dev dev, Words& w)
+{
+    sg::Fetch<Dev> F(dev);
+    const int i0 = F.add(w.a.data(), 1, 1, 1);
+    const int i1 = F.add(w.b.data(), 1, 14, 0);
+    const int i2 = F.add(w.c.data(), 7, 6, 10);
+    const int i3 = F.add(w.c.data(), 0, 6, 10);
+    const int i4 = F.add(w.d.data(), 9, 3, 5, true);
+    const int i5 = F.add(w.d.data(), 9, 0, 5, true);
+    const int i6 = F.add(w.e.data(), 5, 4, 4, true);
+    const int i7 = F.add(w.b.data() + 14, 1, 186, 0);
+    F.run();
+    std::vector<uint32_t> out;
+    auto take = [&](int i, size_t n) {
+        const uint32_t* p = F.template at<uint32_t>(i);
+        out.insert(out.end(), p, p + n);
+    };
+    take(i0, 1);
+    take(i1, 14);
+    take(i2, 42);
+    take(i3, 0);
+    take(i4, 27);
+    take(i5, 0);
+    take(i6, 20);
+    take(i7, 186);
+    return out;
+}
+Words some_words()
+{
+    Words w;
+    uint32_t x = 1;
+    auto fill = [&](std::vector<uint32_t>& v, size_t n) {
+        v.resize(n);
+        for (uint32_t& e : v) e = x = x * 1664525u + 1013904223u;
+    };
+    fill(w.a, 1);
+    fill(w.b, 200);
+    fill(w.c, 70);
+    fill(w.d, 45);
+    fill(w.e, 20);
+    return w;
+}
+
+// Without host memory that the device can write to, the copies bring the same words
+// and the counts end up clear.
+int plain()
+{
+    Words v = some_words(), w = v;
+    const std::vector<uint32_t> want = bring(Copier{true}, v);
+    std::vector<uint32_t> got;
+    try {
+        got = bring(Copier{false}, w);
+    } catch (const Bad&) {
+        CHECK(!"a copy by rows whose pitch is below its width");
+    }
+    CHECK(want.size() == 290 && got == want);
+    CHECK(v.d == w.d && v.e == w.e);
+    for (size_t i = 0; i < w.d.size(); ++i) CHECK((w.d[i] == 0) == (i % 5 < 3));
+    return 0;
+}
 
 // Segments past 2^32 words keep their length, their neighbours' places and the
 // words they are read from.
@@ -98,6 +192,7 @@ int main(int argc, char** argv)
     int rc = 2;
     if (!std::strcmp(what, "large")) rc = large();
     if (!std::strcmp(what, "states")) rc = states();
+    if (!std::strcmp(what, "plain")) rc = plain();
     if (rc == 0) std::printf("stage ok\n");
     return rc;
 }

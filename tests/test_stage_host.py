@@ -33,3 +33,7 @@ def test_segments_past_2_to_32_words(check):
 
 def test_multispin_states_are_one_range(check):
     check("states")
+
+
+def test_copies_without_mapped_memory(check):
+    check("plain")
