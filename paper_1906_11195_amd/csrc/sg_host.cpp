@@ -1692,65 +1692,10 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, hipStream_t s, int32_t 
     hip_check(observe(c->mc_d, c->n_chains, c->count, c->R, kd, K, c->max_words, c->gram_cnt_d, c->ovl_cnt_d, s));
 }
 
-// Mapped host memory that measurements are copied through, kept between calls
-// and shared by all contexts, threads and devices of the process: at most 16
-// blocks of 64 MiB together (an allocation costs 0.05 to 0.4 ms, more than the
-// copy itself in small calls).
-class HostBlocks {
-public:
-    typedef HostBlock Block;
-    // p null if there is no such memory
-    Block get(size_t bytes)
-    {
-        {
-            std::lock_guard<std::mutex> lk(mu_);
-            auto best = free_.end();
-            for (auto it = free_.begin(); it != free_.end(); ++it)
-                if (it->bytes >= bytes && (best == free_.end() || it->bytes < best->bytes)) best = it;
-            if (best != free_.end()) {
-                const Block b = *best;
-                free_.erase(best);
-                return b;
-            }
-        }
-        Block b;
-        b.bytes = (bytes + 65535) & ~(size_t)65535;
-        if (hipHostMalloc(&b.p, b.bytes, hipHostMallocPortable | hipHostMallocMapped) != hipSuccess) {
-            (void)hipGetLastError();
-            b = Block{};
-        }
-        return b;
-    }
-    void put(const Block& b)
-    {
-        if (!b.p) return;
-        std::vector<Block> drop;
-        try {
-            std::lock_guard<std::mutex> lk(mu_);
-            free_.push_back(b);
-            size_t held = 0;
-            for (const Block& x : free_) held += x.bytes;
-            while (held > kBytes || free_.size() > kBlocks) {   // the longest unused first
-                drop.push_back(free_.front());
-                held -= free_.front().bytes;
-                free_.erase(free_.begin());
-            }
-        } catch (...) {
-            drop.push_back(b);
-        }
-        for (const Block& x : drop) (void)hipHostFree(x.p);
-    }
-
-private:
-    static constexpr size_t kBytes = (size_t)64 << 20, kBlocks = 16;
-    std::mutex mu_;
-    std::vector<Block> free_;
-};
-
 // (never destroyed: a context may outlive the static objects)
-HostBlocks& host_blocks()
+BlockPool& host_blocks()
 {
-    static HostBlocks* const p = new HostBlocks;
+    static BlockPool* const p = new BlockPool;
     return *p;
 }
 
@@ -1758,13 +1703,21 @@ HostBlocks& host_blocks()
 // host memory, or, where there is none, by copies (sg_stage.h).
 struct StageDev {
     hipStream_t s;
-    HostBlock get(size_t bytes) { return host_blocks().get(bytes); }
+    HostBlock get(size_t bytes)
+    {
+        return host_blocks().get(bytes, [](size_t n) -> void* {
+            void* p = nullptr;
+            if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+            (void)hipGetLastError();
+            return nullptr;
+        });
+    }
     void put(const HostBlock& b) { host_blocks().put(b); }
-    void pack(const PackList& list, uint32_t* block)
+    void pack(const PackList& list, uint32_t* block, uint64_t w0, uint64_t w1)
     {
         void* dev = nullptr;
         if (block) hip_check(hipHostGetDevicePointer(&dev, block, 0));
-        hip_check(observe_pack(list, (uint32_t*)dev, s));
+        hip_check(observe_pack(list, (uint32_t*)dev, w0, w1, s));
     }
     void copy(uint32_t* dst, const uint32_t* src, uint64_t words)
     {
@@ -1774,6 +1727,15 @@ struct StageDev {
     {
         hip_check(hipMemcpy2DAsync(dst, (size_t)g.width * 4, g.src, g.stride * 4, (size_t)g.width * 4, g.rows,
                                    hipMemcpyDeviceToHost, s));
+    }
+    void store(uint32_t* dst, const uint32_t* src, size_t words)
+    {
+        // (fresh pages of dst cost 0.2 ms a MB on one thread)
+        const size_t parts = std::max<size_t>(1, std::min<size_t>(16, words >> 17));
+        parallel_for(parts, [&](size_t i) {
+            const size_t a = words * i / parts, e = words * (i + 1) / parts;
+            std::memcpy(dst + a, src + a, (e - a) * 4);
+        });
     }
     void sync() { hip_check(hipStreamSynchronize(s)); }
     void sync_quiet() { (void)hipStreamSynchronize(s); }

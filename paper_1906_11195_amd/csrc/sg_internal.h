@@ -180,9 +180,9 @@ hipError_t observe(const MeasureChain* chains, int n_chains, int count, int R, i
 // The counts as Gram matrices [chain][k_cap][k_cap] and overlaps [pair][k_cap].
 hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs, int R, int k_done, int k_cap,
                           uint32_t* gram_cnt, uint32_t* ovl_cnt, long long* gram, long long* ovl, hipStream_t s);
-// Copies the segments to mapped host memory and clears those that ask for it
-// (dst null: only clears)
-hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s);
+// Copies the destination words w0 .. w1 - 1 of the segments to mapped host memory (w0
+// to dst[0]) and clears those that ask for it (dst null: only clears)
+hipError_t observe_pack(const PackList& list, uint32_t* dst, uint64_t w0, uint64_t w1, hipStream_t s);
 hipError_t zero_i64(long long* p, size_t n, hipStream_t s);
 // Device address of the fixed staging array (kMeasureScratchElems int64) on
 // the current device; looked up once per device.

@@ -200,18 +200,19 @@ __global__ void __launch_bounds__(256) expand_kernel(const MeasureChain* __restr
     }
 }
 
-// Copies the segments of a measurement, one after another, to mapped host memory
-// (4 bytes a lane: 53 GB/s, the link's rate, as a DMA copy of one piece; without a
-// destination: nothing), and clears those that hold counts.
-__global__ void __launch_bounds__(256) pack_kernel(PackList L, uint32_t* __restrict__ dst)
+// Copies the destination words w0 .. w1 - 1 of a measurement's segments, one segment
+// after another, to mapped host memory (4 bytes a lane: 53 GB/s, the link's rate, as a
+// DMA copy of one piece; without a destination: nothing), and clears those that hold
+// counts.
+__global__ void __launch_bounds__(256) pack_kernel(PackList L, uint32_t* __restrict__ dst, uint64_t w0, uint64_t w1)
 {
     const uint64_t step = (uint64_t)gridDim.x * blockDim.x, i0 = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x;
     for (int s = 0; s < L.n; ++s) {
         const PackSeg g = L.seg[s];
-        const uint64_t words = pack_words(g);
-        for (uint64_t i = i0; i < words; i += step) {
-            uint32_t* p = g.src + pack_from(g, i);
-            if (dst) dst[g.dst + i] = *p;
+        const uint64_t a = max(w0, g.dst), e = min(w1, g.dst + pack_words(g));
+        for (uint64_t w = a + i0; w < e; w += step) {
+            uint32_t* p = g.src + pack_from(g, w - g.dst);
+            if (dst) dst[w - w0] = *p;
             if (g.clear) *p = 0u;
         }
     }
@@ -396,12 +397,12 @@ hipError_t observe_expand(const MeasureChain* chains, int n_chains, int n_pairs,
     return hipGetLastError();
 }
 
-hipError_t observe_pack(const PackList& list, uint32_t* dst, hipStream_t s)
+hipError_t observe_pack(const PackList& list, uint32_t* dst, uint64_t w0, uint64_t w1, hipStream_t s)
 {
     uint64_t most = 0;
-    for (int i = 0; i < list.n; ++i) most = std::max(most, pack_words(list.seg[i]));
+    for (int i = 0; i < list.n; ++i) most = std::max(most, std::min(w1 - w0, pack_words(list.seg[i])));
     const int blocks = (int)std::max<uint64_t>(1, std::min<uint64_t>(512, (most + 255) / 256));
-    hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, list, dst);
+    hipLaunchKernelGGL(pack_kernel, dim3(blocks), dim3(256), 0, s, list, dst, w0, w1);
     return hipGetLastError();
 }
 

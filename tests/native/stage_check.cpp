@@ -1,9 +1,13 @@
 // Host-only check of a measurement's way to host memory (compiled with g++ by
 // tests/test_stage_host.py; no GPU): a stand-in for the device copies between
 // ordinary arrays and refuses what the device's calls refuse.
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
+#include <set>
+#include <thread>
 #include <vector>
 
 #include "sg_layout.h"
@@ -26,11 +30,12 @@ struct Log {
 // Does no copy: for lists whose words exist nowhere.
 struct Recorder {
     Log* log;
-    sg::HostBlock get(size_t) { return sg::HostBlock{log, 1}; }
+    sg::HostBlock get(size_t bytes) { return sg::HostBlock{log, bytes}; }
     void put(const sg::HostBlock&) {}
-    void pack(const sg::PackList& l, uint32_t*) { log->seen.assign(l.seg, l.seg + l.n); }
+    void pack(const sg::PackList& l, uint32_t*, uint64_t, uint64_t) { log->seen.assign(l.seg, l.seg + l.n); }
     void copy(uint32_t*, const uint32_t*, uint64_t) {}
     void copy_rows(uint32_t*, const sg::PackSeg&) {}
+    void store(uint32_t*, const uint32_t*, size_t) {}
     void sync() {}
     void sync_quiet() {}
 };
@@ -38,18 +43,25 @@ struct Recorder {
 // Copies at once between ordinary arrays.
 struct Bad {};
 struct Copier {
-    bool mapped;
-    sg::HostBlock get(size_t bytes) { return mapped ? sg::HostBlock{std::malloc(bytes), bytes} : sg::HostBlock{}; }
+    size_t limit;   // bytes of a block (0: there are none)
+    sg::HostBlock get(size_t bytes)
+    {
+        const size_t n = bytes < limit ? bytes : limit;
+        return n ? sg::HostBlock{std::malloc(n), n} : sg::HostBlock{};
+    }
     void put(const sg::HostBlock& b) { std::free(b.p); }
-    void pack(const sg::PackList& l, uint32_t* block)
+    void pack(const sg::PackList& l, uint32_t* block, uint64_t w0, uint64_t w1)
     {
         for (int s = 0; s < l.n; ++s)
             for (uint64_t i = 0; i < sg::pack_words(l.seg[s]); ++i) {
+                const uint64_t w = l.seg[s].dst + i;
+                if (w < w0 || w >= w1) continue;
                 uint32_t* p = l.seg[s].src + sg::pack_from(l.seg[s], i);
-                if (block) block[l.seg[s].dst + i] = *p;
+                if (block) block[w - w0] = *p;
                 if (l.seg[s].clear) *p = 0u;
             }
     }
+    void store(uint32_t* dst, const uint32_t* src, size_t words) { std::memcpy(dst, src, words * 4); }
     void copy(uint32_t* dst, const uint32_t* src, uint64_t words) { std::memcpy(dst, src, words * 4); }
     void copy_rows(uint32_t* dst, const sg::PackSeg& g)
     {
@@ -114,16 +126,118 @@ Words some_words()
 int plain()
 {
     Words v = some_words(), w = v;
-    const std::vector<uint32_t> want = bring(Copier{true}, v);
+    const std::vector<uint32_t> want = bring(Copier{SIZE_MAX}, v);
     std::vector<uint32_t> got;
     try {
-        got = bring(Copier{false}, w);
+        got = bring(Copier{0}, w);
     } catch (const Bad&) {
         CHECK(!"a copy by rows whose pitch is below its width");
     }
     CHECK(want.size() == 290 && got == want);
     CHECK(v.d == w.d && v.e == w.e);
     for (size_t i = 0; i < w.d.size(); ++i) CHECK((w.d[i] == 0) == (i % 5 < 3));
+    return 0;
+}
+
+// Through a block that is too small, the same words come in pieces.
+int pieces()
+{
+    Words v = some_words();
+    const std::vector<uint32_t> want = bring(Copier{SIZE_MAX}, v);
+    for (size_t limit = 8; limit < 4 * 300; limit += 8) {
+        Words w = some_words();
+        CHECK(bring(Copier{limit}, w) == want);
+        CHECK(v.d == w.d && v.e == w.e);
+    }
+    return 0;
+}
+
+// The pool holds at most its bound, whoever holds its blocks, and gives memory out
+// once.
+int pool()
+{
+    typedef sg::BlockPool P;
+    std::atomic<size_t> total{0};
+    std::atomic<bool> refuse{false};
+    auto alloc = [&](size_t n) -> void* {
+        if (refuse) return nullptr;
+        total += n;
+        return std::malloc(64);   // (its address alone counts)
+    };
+    {
+        P p;
+        const sg::HostBlock a = p.get(100, alloc), b = p.get(3 << 20, alloc);
+        CHECK(a.p && a.bytes == P::kLeast && b.p && b.bytes == (size_t)4 << 20 && total == a.bytes + b.bytes);
+        p.put(b);
+        CHECK(p.get(200, alloc).p == b.p);                 // (in use again)
+        const sg::HostBlock c = p.get(100 << 20, alloc);   // more than a block
+        CHECK(c.p && c.bytes == P::kMost);
+        const sg::HostBlock d = p.get(60 << 20, alloc);    // the largest that fits
+        CHECK(d.p && d.bytes == (size_t)32 << 20);
+        p.put(c);
+        p.put(d);
+        p.put(a);
+        const size_t t = total;
+        CHECK(p.get(100 << 20, alloc).p == c.p);           // to be used in pieces
+        CHECK(p.get(60 << 20, alloc).p == d.p);
+        CHECK(p.get(60000, alloc).p == a.p);
+        CHECK(total == t);
+        // what is left is given out in ever smaller blocks, then nothing
+        size_t n = 0;
+        while (p.get(60 << 20, alloc).p) ++n;
+        CHECK(n >= 3 && n < 100 && total <= P::kBytes && !p.get(60 << 20, alloc).p);
+    }
+    {
+        P p;
+        total = 0;
+        refuse = true;
+        CHECK(!p.get(P::kMost, alloc).p && !p.get(P::kMost, alloc).p);
+        refuse = false;                                    // a refusal leaves nothing reserved
+        const sg::HostBlock a = p.get(P::kMost, alloc), b = p.get(P::kMost, alloc);
+        CHECK(a.p && a.bytes == P::kMost && b.p && b.bytes == P::kMost);
+        CHECK(!p.get(1, alloc).p);
+        p.put(a);
+        CHECK(p.get(1, alloc).p == a.p);
+    }
+    {
+        P p;
+        total = 0;
+        std::atomic<int> twice{0};
+        std::mutex mu;
+        std::set<void*> out;
+        std::vector<std::thread> th;
+        for (int t = 0; t < 16; ++t)
+            th.emplace_back([&, t]() {
+                uint32_t x = 12345u + (uint32_t)t;
+                std::vector<sg::HostBlock> mine;
+                for (int i = 0; i < 4000; ++i) {
+                    x = x * 1664525u + 1013904223u;
+                    if ((x >> 16 & 1) != 0 && !mine.empty()) {
+                        {
+                            std::lock_guard<std::mutex> lk(mu);
+                            out.erase(mine.back().p);
+                        }
+                        p.put(mine.back());
+                        mine.pop_back();
+                        continue;
+                    }
+                    const sg::HostBlock b = p.get((size_t)1 << (x >> 20 & 31) % 28, alloc);
+                    if (!b.p) continue;
+                    std::lock_guard<std::mutex> lk(mu);
+                    if (!out.insert(b.p).second) ++twice;
+                    mine.push_back(b);
+                }
+                for (const sg::HostBlock& b : mine) {
+                    {
+                        std::lock_guard<std::mutex> lk(mu);
+                        out.erase(b.p);
+                    }
+                    p.put(b);
+                }
+            });
+        for (auto& x : th) x.join();
+        CHECK(twice == 0 && total > 0 && total <= P::kBytes);
+    }
     return 0;
 }
 
@@ -193,6 +307,8 @@ int main(int argc, char** argv)
     if (!std::strcmp(what, "large")) rc = large();
     if (!std::strcmp(what, "states")) rc = states();
     if (!std::strcmp(what, "plain")) rc = plain();
+    if (!std::strcmp(what, "pieces")) rc = pieces();
+    if (!std::strcmp(what, "pool")) rc = pool();
     if (rc == 0) std::printf("stage ok\n");
     return rc;
 }

@@ -37,3 +37,11 @@ def test_multispin_states_are_one_range(check):
 
 def test_copies_without_mapped_memory(check):
     check("plain")
+
+
+def test_words_in_pieces(check):
+    check("pieces")
+
+
+def test_pool_of_mapped_memory_is_bounded(check):
+    check("pool")
