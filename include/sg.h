@@ -307,7 +307,9 @@ sg_status sg_create_sk(const sg_sk_desc* d, int32_t count, const sg_opts* o, sg_
 sg_status sg_sweep(sg_ctx* c, int64_t n_sweeps, void* stream);
 
 /* Computes the observables of every grid time reached so far on `stream`,
- * waits for the stream, and fills `out` (see sg_obs).  Returns SG_EPARITY
+ * waits for the stream, and fills `out` (see sg_obs).  With SG_MEASURE_SPINS it
+ * first waits for the context's sweeps on other streams: the spins are those
+ * after every sweep enqueued before the call.  Returns SG_EPARITY
  * if an SK field check has failed since the context was created. */
 sg_status sg_measure(sg_ctx* c, uint32_t flags, sg_obs* out, void* stream);
 

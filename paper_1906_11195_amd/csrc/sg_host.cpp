@@ -1961,6 +1961,10 @@ sg_status sg_measure(sg_ctx* c, uint32_t flags, sg_obs* out, void* stream)
         out->t_done = c->t_done;
         const bool obs = (flags & SG_MEASURE_OBS) != 0, spins = (flags & SG_MEASURE_SPINS) && out->spins;
         if (!obs && !spins) return;
+        // the spins are those after every sweep enqueued so far, on whatever stream
+        if (spins)
+            for (hipStream_t x : c->streams_used)
+                if (x != s) (void)hipStreamSynchronize(x);
         Fetch<StageDev> F(StageDev{s});
         const size_t nc = (size_t)c->n_chains, np = (size_t)c->n_pairs, tri = (size_t)K * (K - 1) / 2;
         const size_t kt = (size_t)kd * (kd - 1) / 2;

@@ -46,3 +46,32 @@ def test_no_other_context_is_waited_for(large):
         assert not done.query()
     finally:
         sg.sg_free(busy)
+
+
+def _vb():
+    return sg.sg_create_vb([sg.VbDesc(n=200000, T=0.9, seed=7, instance_id=0)], t_max=0)
+
+
+def _multispin():
+    return sg.sg_create_vb([sg.VbDesc(n=8192, T=0.9, seed=8, instance_id=i, n_replicas=8) for i in range(2)], t_max=0,
+                           multispin=True)
+
+
+def _sk():
+    return sg.sg_create_sk([sg.SkDesc(n=2048, T=0.7, seed=9, instance_id=0)], t_max=0)
+
+
+@pytest.mark.parametrize("create", [_vb, _multispin, _sk])
+@pytest.mark.parametrize("sweeps_aside", [False, True])
+def test_spins_after_sweeps_on_another_stream(create, sweeps_aside):
+    require_gpu()
+    side, ref, ctx = torch.cuda.Stream(), create(), create()
+    try:
+        sg.sg_sweep(ref, 3000)
+        want = sg.sg_measure(ref, sg.MEASURE_SPINS)["spins"]
+        sg.sg_sweep(ctx, 3000, stream=side if sweeps_aside else None)
+        got = sg.sg_measure(ctx, sg.MEASURE_SPINS, stream=None if sweeps_aside else side)["spins"]
+        assert all(np.array_equal(a, b) for a, b in zip(want, got))
+    finally:
+        sg.sg_free(ref)
+        sg.sg_free(ctx)
