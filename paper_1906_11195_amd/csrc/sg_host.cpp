@@ -23,6 +23,7 @@
 #include "sg_layout.h"
 #include "sg_ledger.h"
 #include "sg_split_plan.h"
+#include "sg_tune.h"
 #include "sg_philox.h"
 
 using namespace sg;
@@ -643,19 +644,13 @@ hipGraphExec_t vb_graph_for(sg_ctx* c, int32_t nsw)
 // Trials run at sweep counters >= 2^31, beyond any measurement time, on a
 // saved copy of the spins and counters that is restored afterwards, so tuning
 // changes no result.  Choices are cached per process by group shape.
-struct TuneKey {
-    int threads, nlog, rpad, resident;
-    bool operator<(const TuneKey& o) const
-    {
-        return std::tie(threads, nlog, rpad, resident) < std::tie(o.threads, o.nlog, o.rpad, o.resident);
-    }
-};
-std::map<TuneKey, int> g_tuned;
-std::mutex g_tuned_mu;
+TuneCache g_tuned;
 
 void vb_autotune(sg_ctx* c)
 {
     const size_t lds_cap = 160 * 1024 - 1024;
+    int n_cu = 0;
+    hip_check(hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, c->device));
     size_t words = 0;
     for (const auto& U : c->units) words += (size_t)U.state_words;
     const size_t bytes = words * 4 + (size_t)c->n_chains * 8;
@@ -682,9 +677,6 @@ void vb_autotune(sg_ctx* c)
         int32_t nmax = 0;
         for (int32_t u = G.first; u < G.first + G.count; ++u) nmax = std::max(nmax, c->units[(size_t)u].n);
         const VbUnit& U0 = c->units[(size_t)G.first];
-        int nlog = 0;
-        while ((1 << (nlog + 1)) <= nmax) ++nlog;
-        const TuneKey key{G.threads, nlog, U0.rpad, U0.resident};
         auto lds_for = [&](int th) {
             size_t l = 0;
             for (int32_t u = G.first; u < G.first + G.count; ++u) {
@@ -694,12 +686,9 @@ void vb_autotune(sg_ctx* c)
             }
             return l;
         };
-        int best = -1;
-        {
-            std::lock_guard<std::mutex> lk(g_tuned_mu);
-            auto it = g_tuned.find(key);
-            if (it != g_tuned.end()) best = it->second;
-        }
+        const TuneKey key = tune_key(G.threads, nmax, U0.rpad, U0.resident != 0, G.count, n_cu, lds_for(G.threads),
+                                     lds_for(2 * G.threads), lds_cap);
+        int best = g_tuned.find(key, [&](int th) { return th >= 64 && th <= 1024 && lds_for(th) <= lds_cap; });
         if (best < 0) {
             const int32_t nsw = (int32_t)std::max<int64_t>(1, std::min<int64_t>(32, ((int64_t)1 << 25) / std::max<int64_t>(1, G.updates)));
             float best_ms = 1e30f;
@@ -718,8 +707,7 @@ void vb_autotune(sg_ctx* c)
                     best = th;
                 }
             }
-            std::lock_guard<std::mutex> lk(g_tuned_mu);
-            g_tuned[key] = best;
+            g_tuned.put(key, best);
         }
         if (best > 0) {
             G.threads = best;
