@@ -22,6 +22,7 @@
 #include "sg_internal.h"
 #include "sg_layout.h"
 #include "sg_ledger.h"
+#include "sg_sk_plan.h"
 #include "sg_split_plan.h"
 #include "sg_tune.h"
 #include "sg_philox.h"
@@ -1910,9 +1911,7 @@ sg_status sg_sweep(sg_ctx* c, int64_t n_sweeps, void* stream)
             int64_t left = n_sweeps;
             while (left > 0) {
                 const int64_t to_check = c->period - (c->t_done % c->period);
-                // (a launch counts its blocks of 64 spins in 32 bits)
-                const int64_t chunk = std::min(std::min(left, to_check),
-                                               std::max<int64_t>(1, ((int64_t)1 << 30) / sk_blocks(c->sk_max_n)));
+                const int64_t chunk = sk_launch_sweeps(left, to_check, sk_blocks(c->sk_max_n));
                 if (c->sk_real)
                     hip_check(skg_sweep(c->sk_d, c->n_chains, c->sk_max_n, c->sk_lds, c->t_done, (int32_t)chunk,
                                         c->t_max, c->err_d, s));

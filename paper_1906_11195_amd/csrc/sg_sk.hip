@@ -54,6 +54,7 @@
 
 #include "sg_internal.h"
 #include "sg_philox.h"
+#include "sg_sk_plan.h"
 
 namespace sg {
 namespace {
@@ -79,6 +80,7 @@ constexpr int kPrepWaves = 3;
 constexpr int kUpdWaves = 12;
 constexpr int kSkThreads = 64 * (1 + kPrepWaves + kUpdWaves);
 constexpr int kSpinLimit = 1 << 22; // bounded waits: a stuck pipeline aborts
+static_assert(64 * kSkLaunchBlocks <= (int64_t)UINT32_MAX, "a launch's accepted flips fit 32 bits");
 static_assert(kWin % 2 == 1 && kWin + 3 <= kHRing, "published fields are read before their slots are used again");
 // An updater's blocks are at most 2 kUpdWaves - 1 apart, and the decider waits for
 // the fields of each, published once the flips kWin + 1 blocks before are applied:
@@ -301,7 +303,7 @@ __device__ __forceinline__ void sk_decide(const SkChain* ch, const SkLds& L, uin
     const int32_t DW = sk_window(NB);
     const unsigned long long lt = (1ull << lane) - 1ull;   // lanes before this one
     const uint32_t ltl = (uint32_t)lt, lth = (uint32_t)(lt >> 32);
-    uint32_t acc = 0;
+    uint32_t acc = 0;   // (kSkLaunchBlocks)
     // flips and new spins of the last kWin blocks (d = 0: the block before)
     unsigned long long pF[kWin], pN[kWin];
 #pragma unroll
