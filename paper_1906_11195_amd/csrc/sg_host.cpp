@@ -974,20 +974,24 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
 
     // device layout
     Arena A;
-    std::vector<size_t> off_row(n_groups), off_ent(n_groups), off_cls(n_groups), off_tab(2 * n_groups);
-    std::vector<std::vector<VbChunk>> tabs(2 * n_groups);
+    std::vector<size_t> off_row(n_groups), off_ent(n_groups), off_cls(n_groups);
     for (size_t gi = 0; gi < n_groups; ++gi) {
         off_row[gi] = A.take(graphs[gi].row.size() * 4);
         off_ent[gi] = A.take((graphs[gi].ent.size() + kVbEntPad) * 4);
         off_cls[gi] = A.take(graphs[gi].cls.size() * 4);
     }
-    // chunk tables: one per graph for its resident and one for its other units
+    // chunk tables, one per graph for its resident and one for its other units, in one
+    // array: a copy for all of them
+    std::vector<VbChunk> tabs;
+    std::vector<std::pair<size_t, size_t>> tab_of(2 * n_groups, {0, 0});   // first, number
     for (const auto& u : plan) {
-        const size_t ti = 2 * (size_t)u.group + (u.resident ? 1 : 0);
-        if (!tabs[ti].empty()) continue;
-        tabs[ti] = vb_chunks(graphs[(size_t)u.group], u.resident ? 1 : 2);
-        off_tab[ti] = A.take(tabs[ti].size() * sizeof(VbChunk));
+        auto& r = tab_of[2 * (size_t)u.group + (u.resident ? 1 : 0)];
+        if (r.second != 0) continue;
+        const std::vector<VbChunk> t = vb_chunks(graphs[(size_t)u.group], u.resident ? 1 : 2);
+        r = {tabs.size(), t.size()};
+        tabs.insert(tabs.end(), t.begin(), t.end());
     }
+    const size_t off_tabs = A.take(tabs.size() * sizeof(VbChunk));
     // entries in the complemented-copy form: one array per graph and slot count
     std::map<std::pair<int32_t, int32_t>, size_t> off_entc;
     for (const auto& u : plan)
@@ -1064,10 +1068,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         std::copy(g.ent.begin(), g.ent.end(), padded.begin());
         hip_check(hipMemcpy(c->at<void>(off_ent[gi]), padded.data(), padded.size() * 4, hipMemcpyHostToDevice));
         hip_check(hipMemcpy(c->at<void>(off_cls[gi]), g.cls.data(), g.cls.size() * 4, hipMemcpyHostToDevice));
-        for (size_t ti = 2 * gi; ti < 2 * gi + 2; ++ti)
-            if (!tabs[ti].empty())
-                hip_check(hipMemcpy(c->at<void>(off_tab[ti]), tabs[ti].data(), tabs[ti].size() * sizeof(VbChunk), hipMemcpyHostToDevice));
     }
+    if (!tabs.empty())
+        hip_check(hipMemcpy(c->at<void>(off_tabs), tabs.data(), tabs.size() * sizeof(VbChunk), hipMemcpyHostToDevice));
     for (const auto& kv : off_entc) {
         const VbGraph& g = graphs[(size_t)kv.first.first];
         std::vector<uint32_t> e(g.ent.size() + kVbEntPad);
@@ -1100,9 +1103,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         U.row = c->at<int32_t>(off_row[(size_t)plan[u].group]);
         U.ent = c->at<uint32_t>(off_ent[(size_t)plan[u].group]);
         U.cls = c->at<int32_t>(off_cls[(size_t)plan[u].group]);
-        const size_t ti = 2 * (size_t)plan[u].group + (plan[u].resident ? 1 : 0);
-        U.chunk = c->at<VbChunk>(off_tab[ti]);
-        U.chunks = (int32_t)tabs[ti].size();
+        const auto& tab = tab_of[2 * (size_t)plan[u].group + (plan[u].resident ? 1 : 0)];
+        U.chunk = c->at<VbChunk>(off_tabs) + tab.first;
+        U.chunks = (int32_t)tab.second;
         U.resident = plan[u].resident ? 1 : 0;
         U.cpl = plan[u].cpl ? 1 : 0;
         if (U.cpl) U.entc = c->at<uint32_t>(off_entc.at({plan[u].group, plan[u].rpad}));
