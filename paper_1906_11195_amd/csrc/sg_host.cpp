@@ -1316,6 +1316,145 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     if (o && (o->flags & SG_OPT_AUTOTUNE) && !o->threads_per_unit) vb_autotune(c);
 }
 
+// (never destroyed: a context may outlive the static objects)
+BlockPool& host_blocks()
+{
+    static BlockPool* const p = new BlockPool;
+    return *p;
+}
+
+// The words of a measurement come to host memory by a kernel that writes to mapped
+// host memory, or, where there is none, by copies (sg_stage.h).
+struct StageDev {
+    hipStream_t s;
+    HostBlock get(size_t bytes)
+    {
+        return host_blocks().get(bytes, [](size_t n) -> void* {
+            void* p = nullptr;
+            if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
+            (void)hipGetLastError();
+            return nullptr;
+        });
+    }
+    void put(const HostBlock& b) { host_blocks().put(b); }
+    void pack(const PackList& list, uint32_t* block, uint64_t w0, uint64_t w1)
+    {
+        void* dev = nullptr;
+        if (block) hip_check(hipHostGetDevicePointer(&dev, block, 0));
+        hip_check(observe_pack(list, (uint32_t*)dev, w0, w1, s));
+    }
+    void copy(uint32_t* dst, const uint32_t* src, uint64_t words)
+    {
+        hip_check(hipMemcpyAsync(dst, src, words * 4, hipMemcpyDeviceToHost, s));
+    }
+    void copy_rows(uint32_t* dst, const PackSeg& g)
+    {
+        hip_check(hipMemcpy2DAsync(dst, (size_t)g.width * 4, g.src, g.stride * 4, (size_t)g.width * 4, g.rows,
+                                   hipMemcpyDeviceToHost, s));
+    }
+    void store(uint32_t* dst, const uint32_t* src, size_t words)
+    {
+        // (fresh pages of dst cost 0.2 ms a MB on one thread)
+        const size_t parts = std::max<size_t>(1, std::min<size_t>(16, words >> 17));
+        parallel_for(parts, [&](size_t i) {
+            const size_t a = words * i / parts, e = words * (i + 1) / parts;
+            std::memcpy(dst + a, src + a, (e - a) * 4);
+        });
+    }
+    void sync() { hip_check(hipStreamSynchronize(s)); }
+    void sync_quiet() { (void)hipStreamSynchronize(s); }
+};
+
+// Rows of a host matrix, padded to skg_pitch(n) floats on the device.
+struct SkgMatrix {
+    const float* src;
+    int64_t n;
+    float* dst;
+};
+
+// Brings matrices whose rows need padding to the device (null stream): rows are laid
+// out on host threads in one half of a block that the device copies from while the
+// other half is filled.  (A strided copy goes row by row, 66 ms for 6 x 1021^2; rows
+// padded in ordinary memory and copied from there took 63 ms for 4 x 4000^2 and 9.5 for
+// 300 x 64^2, creation as a whole, now 36.8 and 1.7.)
+void skg_upload(const std::vector<SkgMatrix>& mats)
+{
+    size_t total = 0, row_most = 0;
+    for (const SkgMatrix& m : mats) {
+        const size_t row = (size_t)skg_pitch((int32_t)m.n) * 4;
+        total += row * (size_t)m.n;
+        row_most = std::max(row_most, row);
+    }
+    if (total == 0) return;
+    struct Stage {
+        StageDev dev{nullptr};
+        HostBlock b;
+        ~Stage()
+        {
+            dev.sync_quiet();
+            dev.put(b);
+        }
+    } st;
+    st.b = st.dev.get(std::max(2 * row_most, std::min<size_t>(2 * total, (size_t)16 << 20)));
+    const bool pinned = st.b.p && st.b.bytes >= 2 * row_most;
+    const size_t half = pinned ? st.b.bytes / 2 : std::max(row_most, std::min<size_t>(total, (size_t)8 << 20));
+    std::vector<char> plain(pinned ? 0 : half);
+    char* const buf[2] = {pinned ? (char*)st.b.p : plain.data(), pinned ? (char*)st.b.p + half : plain.data()};
+    int turn = 0;
+    // a run of rows that lie together on the device, from one or more matrices
+    struct Part {
+        const float* src;
+        int64_t n, np, rows;
+        size_t at;
+    };
+    std::vector<Part> run;
+    char* run_dst = nullptr;
+    size_t run_bytes = 0;
+    int64_t run_rows = 0;
+    auto flush = [&]() {
+        if (run_bytes == 0) return;
+        char* const b = buf[turn];
+        const size_t parts = std::max<size_t>(1, std::min<size_t>(16, run_bytes >> 19));
+        parallel_for(parts, [&](size_t q) {
+            int64_t r0 = run_rows * (int64_t)q / (int64_t)parts, left = run_rows * (int64_t)(q + 1) / (int64_t)parts - r0;
+            for (const Part& p : run) {
+                if (left <= 0) break;
+                if (r0 >= p.rows) {
+                    r0 -= p.rows;
+                    continue;
+                }
+                for (const int64_t m = std::min(left, p.rows - r0), e = r0 + m; r0 < e; ++r0, --left) {
+                    char* row = b + p.at + (size_t)(r0 * p.np) * 4;
+                    std::memcpy(row, p.src + r0 * p.n, (size_t)p.n * 4);
+                    std::memset(row + p.n * 4, 0, (size_t)(p.np - p.n) * 4);
+                }
+                r0 = 0;
+            }
+        });
+        st.dev.sync();   // (the other half's copy)
+        hip_check(hipMemcpyAsync(run_dst, b, run_bytes, hipMemcpyHostToDevice, nullptr));
+        if (!pinned) st.dev.sync();
+        turn ^= 1;
+        run.clear();
+        run_bytes = 0;
+        run_rows = 0;
+    };
+    for (const SkgMatrix& m : mats) {
+        const int64_t np = skg_pitch((int32_t)m.n);
+        for (int64_t r = 0; r < m.n;) {
+            char* const dst = (char*)(m.dst + r * np);
+            if (run_bytes != 0 && (dst != run_dst + run_bytes || run_bytes + (size_t)np * 4 > half)) flush();
+            if (run_bytes == 0) run_dst = dst;
+            const int64_t k = std::min<int64_t>(m.n - r, (int64_t)((half - run_bytes) / ((size_t)np * 4)));
+            run.push_back(Part{m.src + r * m.n, m.n, np, k, run_bytes});
+            run_bytes += (size_t)(k * np) * 4;
+            run_rows += k;
+            r += k;
+        }
+    }
+    flush();
+}
+
 // SK with real couplings: float32 J per distinct array, fields in double.
 void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
 {
@@ -1355,9 +1494,9 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     std::vector<size_t> off_J(jrep.size()), off_Jd(jrep.size());
     for (size_t j = 0; j < jrep.size(); ++j) {
         const int64_t n = d[jrep[j]].n;
-        off_J[j] = A.take((size_t)n * (size_t)skg_pitch((int32_t)n) * 4);
-        off_Jd[j] = A.take((size_t)((n + 63) / 64) * 64 * 64 * 4);
+        off_J[j] = A.take((size_t)n * (size_t)skg_pitch((int32_t)n) * 4);   // (one after another: skg_upload)
     }
+    for (size_t j = 0; j < jrep.size(); ++j) off_Jd[j] = A.take((size_t)((d[jrep[j]].n + 63) / 64) * 64 * 64 * 4);
     std::vector<size_t> off_state((size_t)c->n_chains), off_H((size_t)c->n_chains), off_snap((size_t)c->n_chains),
         off_given((size_t)c->n_chains, 0);
     for (int32_t i = 0; i < count; ++i) {
@@ -1387,28 +1526,15 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     const size_t off_part = A.take((size_t)count * (size_t)skg_row_blocks(c->sk_max_n) * (size_t)c->R * c->K * 8);
     c->arena_bytes = A.size;
     c->arena = c->dev_alloc(A.size);
+    std::vector<SkgMatrix> ragged;
     for (size_t j = 0; j < jrep.size(); ++j) {
         const int64_t n = d[jrep[j]].n;
-        const int64_t np = skg_pitch((int32_t)n);
-        if (np == n) {
+        if (skg_pitch((int32_t)n) == n)
             hip_check(hipMemcpy(c->at<void>(off_J[j]), d[jrep[j]].Jf, (size_t)(n * n) * 4, hipMemcpyHostToDevice));
-        } else {
-            // rows padded on the host, up to 32 MiB at a time (a strided copy to
-            // the device goes row by row: 66 ms against 10 for 6 x 1021^2)
-            const int64_t rows = std::min<int64_t>(n, std::max<int64_t>(1, ((int64_t)1 << 23) / np));
-            std::vector<float> pad((size_t)(rows * np), 0.0f);
-            for (int64_t r0 = 0; r0 < n; r0 += rows) {
-                const int64_t m = std::min(rows, n - r0), parts = (m * n + (1 << 20) - 1) >> 20;
-                maybe_parallel(parts > 1, (size_t)parts, [&](size_t q) {
-                    for (int64_t r = m * (int64_t)q / parts; r < m * ((int64_t)q + 1) / parts; ++r)
-                        std::memcpy(pad.data() + r * np, d[jrep[j]].Jf + (r0 + r) * n, (size_t)n * 4);
-                });
-                hip_check(hipMemcpy(c->at<float>(off_J[j]) + r0 * np, pad.data(), (size_t)(m * np) * 4,
-                                    hipMemcpyHostToDevice));
-            }
-        }
-        hip_check(skg_diag(c->at<float>(off_J[j]), c->at<float>(off_Jd[j]), (int32_t)n, nullptr));
+        else
+            ragged.push_back(SkgMatrix{d[jrep[j]].Jf, n, c->at<float>(off_J[j])});
     }
+    skg_upload(ragged);
     c->sk.resize((size_t)c->n_chains);
     c->sks.resize((size_t)count);
     for (int32_t i = 0; i < count; ++i) {
@@ -1466,6 +1592,7 @@ void create_skg(sg_ctx* c, const sg_sk_desc* d, int32_t count, const sg_opts* o)
     hip_check(zero_i64((long long*)c->acc_d, (size_t)c->n_chains, nullptr));
     hip_check(zero_i64((long long*)c->err_d, 1, nullptr));
     c->sk_lds = skg_lds_bytes(c->sk_max_n);
+    hip_check(skg_diag(c->sks_d, count, c->sk_d, c->sk_max_n, nullptr));
     hip_check(sk_init(c->sk_d, c->n_chains, 256, nullptr));
     hip_check(skg_recompute(c->sks_d, count, c->sk_d, c->sk_max_n, 0, c->err_d, nullptr));
     hip_check(hipStreamSynchronize(nullptr));
@@ -1683,55 +1810,6 @@ void enqueue_obs(sg_ctx* c, int32_t kd, long long* bond, hipStream_t s, int32_t 
     c->cnt_dirty = true;   // until the counts have been read (and cleared)
     hip_check(observe(c->mc_d, c->n_chains, c->count, c->R, kd, K, c->max_words, c->gram_cnt_d, c->ovl_cnt_d, s));
 }
-
-// (never destroyed: a context may outlive the static objects)
-BlockPool& host_blocks()
-{
-    static BlockPool* const p = new BlockPool;
-    return *p;
-}
-
-// The words of a measurement come to host memory by a kernel that writes to mapped
-// host memory, or, where there is none, by copies (sg_stage.h).
-struct StageDev {
-    hipStream_t s;
-    HostBlock get(size_t bytes)
-    {
-        return host_blocks().get(bytes, [](size_t n) -> void* {
-            void* p = nullptr;
-            if (hipHostMalloc(&p, n, hipHostMallocPortable | hipHostMallocMapped) == hipSuccess) return p;
-            (void)hipGetLastError();
-            return nullptr;
-        });
-    }
-    void put(const HostBlock& b) { host_blocks().put(b); }
-    void pack(const PackList& list, uint32_t* block, uint64_t w0, uint64_t w1)
-    {
-        void* dev = nullptr;
-        if (block) hip_check(hipHostGetDevicePointer(&dev, block, 0));
-        hip_check(observe_pack(list, (uint32_t*)dev, w0, w1, s));
-    }
-    void copy(uint32_t* dst, const uint32_t* src, uint64_t words)
-    {
-        hip_check(hipMemcpyAsync(dst, src, words * 4, hipMemcpyDeviceToHost, s));
-    }
-    void copy_rows(uint32_t* dst, const PackSeg& g)
-    {
-        hip_check(hipMemcpy2DAsync(dst, (size_t)g.width * 4, g.src, g.stride * 4, (size_t)g.width * 4, g.rows,
-                                   hipMemcpyDeviceToHost, s));
-    }
-    void store(uint32_t* dst, const uint32_t* src, size_t words)
-    {
-        // (fresh pages of dst cost 0.2 ms a MB on one thread)
-        const size_t parts = std::max<size_t>(1, std::min<size_t>(16, words >> 17));
-        parallel_for(parts, [&](size_t i) {
-            const size_t a = words * i / parts, e = words * (i + 1) / parts;
-            std::memcpy(dst + a, src + a, (e - a) * 4);
-        });
-    }
-    void sync() { hip_check(hipStreamSynchronize(s)); }
-    void sync_quiet() { (void)hipStreamSynchronize(s); }
-};
 
 // Runs f(first, last) over 0 .. count - 1, `bytes` of output each: on host threads
 // of at least 512 KB where that makes two (fresh pages of the caller's arrays cost

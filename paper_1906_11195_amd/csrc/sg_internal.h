@@ -85,7 +85,7 @@ struct SkChain {
     float xslope;              // 2 beta / sqrt(N): thr[x] ~ 2^32 exp(-xslope x)
     // real couplings (sg_skg.hip): Jw, H, thr unused
     const float* Jf;           // [n][skg_pitch(n)], zero past n
-    const float* Jd;           // [ceil(n / 64)][64][64] strict upper triangles of the diagonal tiles
+    float* Jd;                 // [ceil(n / 64)][64][64] strict upper triangles of the diagonal tiles
     double* Hd;                // [n] local fields between launches
     double beta;               // 1 / T
 };
@@ -157,7 +157,7 @@ constexpr size_t kSkOverread = (size_t)12 * 48 * 1024;
 // skg_row_blocks(max_n) doubles; out[chain][k]).
 int skg_row_blocks(int32_t n);
 size_t skg_lds_bytes(int32_t n);
-hipError_t skg_diag(const float* J, float* Jd, int32_t n, hipStream_t s);
+hipError_t skg_diag(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, hipStream_t s);
 hipError_t skg_sweep(const SkChain* chains, int n_chains, int max_n, size_t lds_bytes, int64_t t0, int32_t n_sweeps,
                      int64_t t_max, int* err_flag, hipStream_t s);
 hipError_t skg_recompute(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, int check,

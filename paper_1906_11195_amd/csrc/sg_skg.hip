@@ -534,10 +534,16 @@ __global__ void __launch_bounds__(kSkgThreads) skg_sweep_kernel(const SkChain* _
 
 // The strict upper triangles of the diagonal tiles: Jd[block][row][column],
 // column > row, zero elsewhere (a flip changes the fields of the lanes after it
-// within its block).  grid = (blocks, matrices' samples)
-__global__ void __launch_bounds__(256) skg_diag_kernel(const float* __restrict__ J, float* __restrict__ Jd, int32_t n)
+// within its block).  grid = (blocks, samples); samples that share a matrix write the
+// same tiles
+__global__ void __launch_bounds__(256) skg_diag_kernel(const SkSample* __restrict__ samples,
+                                                       const SkChain* __restrict__ chains)
 {
-    const int32_t b = blockIdx.x, np = skg_pitch(n);
+    const SkSample* sm = samples + blockIdx.y;
+    const int32_t b = blockIdx.x, n = sm->n, np = skg_pitch(n);
+    if (b * 64 >= n) return;
+    const float* J = sm->Jf;
+    float* Jd = chains[sm->chain0].Jd;
     for (int32_t i = threadIdx.x; i < 4096; i += blockDim.x) {
         const int32_t r = i >> 6, c = i & 63;
         Jd[(int64_t)b * 4096 + i] = c > r && b * 64 + c < n ? J[(int64_t)(b * 64 + r) * np + b * 64 + c] : 0.0f;
@@ -743,9 +749,9 @@ __global__ void __launch_bounds__(64) skg_bond_reduce(const SkSample* __restrict
 
 size_t skg_lds_bytes(int32_t n) { return skg_layout(n).total; }
 
-hipError_t skg_diag(const float* J, float* Jd, int32_t n, hipStream_t s)
+hipError_t skg_diag(const SkSample* samples, int n_samples, const SkChain* chains, int max_n, hipStream_t s)
 {
-    hipLaunchKernelGGL(skg_diag_kernel, dim3((n + 63) / 64), dim3(256), 0, s, J, Jd, n);
+    hipLaunchKernelGGL(skg_diag_kernel, dim3((max_n + 63) / 64, n_samples), dim3(256), 0, s, samples, chains);
     return hipGetLastError();
 }
 

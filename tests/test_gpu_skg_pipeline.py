@@ -43,3 +43,26 @@ def test_skg_mixed_sizes_in_one_context():
     require_gpu()
     check([sg.SkDesc(n=n, T=0.3 + 0.1 * i, seed=22, instance_id=i, n_replicas=3, Jf=gaussian_couplings(n, seed=n + 7),
                      recompute_period=4) for i, n in enumerate((3, 64, 900, 130, 4000, 2049))], 9, 8)
+
+
+def test_skg_matrices_of_a_large_context():
+    """Couplings that go up in several pieces, rows of several matrices in one piece
+    among them: the energies of the start configurations, in 64 bits (n terms of
+    variance 1 / n and their sums: rounding far below 1e-9)."""
+    require_gpu()
+    sizes = [1021, 64, 1021, 1021, 300, 1024, 300, 1021, 63, 1021, 2, 1000]
+    descs = []
+    for i, n in enumerate(sizes):
+        z = np.triu(np.random.default_rng(40 + i).standard_normal((n, n)), 1) / np.sqrt(n)
+        Jf = (z + z.T).astype(np.float32)
+        descs.append(sg.SkDesc(n=n, T=0.5, seed=14, instance_id=i, n_replicas=2, Jf=Jf))
+    ctx = sg.sg_create_sk(descs, t_max=0)
+    try:
+        res = sg.sg_measure(ctx, sg.MEASURE_OBS | sg.MEASURE_SPINS)
+    finally:
+        sg.sg_free(ctx)
+    for i, d in enumerate(descs):
+        for r in range(2):
+            s = res["spins"][i][r].astype(np.float64)
+            want = 0.5 * s @ (d.Jf.astype(np.float64) @ s)
+            assert abs(res["bond_real"][i, r, 0] - want) < 1e-9, (i, r)
