@@ -10,8 +10,6 @@
 
 namespace sg {
 
-constexpr int kSkTile = 64;        // SK decision block (one wavefront)
-constexpr int kSkThrLds = 1024;    // SK threshold entries cached in LDS
 constexpr int kWindowBinsMax = 128;  // minor-third intervals of times below 2^32
 constexpr size_t kMeasureScratchElems = (size_t)1 << 20;   // int64 staging of sg_measure_noalloc (8 MiB)
 

@@ -39,7 +39,7 @@ namespace {
 // 65536 spins, 10 times, one pair 91 us (300).  Bound by staging: 2 loads in
 // flight a lane and a barrier before the counting.
 struct ObsPlan {
-    int32_t n_chains, count, R, kd;
+    int32_t n_chains, R, kd;
     int32_t g_tiles, g_words;   // tiles per chain, words per tile (a multiple of 64)
     int32_t o_tiles, o_words;
     int32_t g_stride, o_stride; // entries per chain (all pairs of K rows), per pair of replicas (K)
@@ -370,7 +370,6 @@ hipError_t observe(const MeasureChain* chains, int n_chains, int count, int R, i
     auto words = [&](int rows) { return std::min((max_words + 63) & ~63, (kTile / rows) & ~63); };
     ObsPlan p;
     p.n_chains = k_done > 1 ? n_chains : 0;
-    p.count = count;
     p.R = R;
     p.kd = k_done;
     p.g_words = words(k_done);

@@ -54,24 +54,17 @@
 
 #include "sg_internal.h"
 #include "sg_philox.h"
+#include "sg_pipe.h"
 #include "sg_sk_plan.h"
 
 namespace sg {
 namespace {
 
-#define SG_L __attribute__((address_space(3)))
-
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 typedef unsigned v2u __attribute__((ext_vector_type(2)));
 
-#ifndef SG_SK_WIN
-#define SG_SK_WIN 3
-#endif
-#ifndef SG_SK_RING
-#define SG_SK_RING 6
-#endif
-constexpr int kWin = SG_SK_WIN;     // previous blocks whose flips the decider adds itself (odd)
-constexpr int kRing = SG_SK_RING;   // blocks the prep wavefronts are ahead at most
+constexpr int kWin = 3;             // previous blocks whose flips the decider adds itself (odd)
+constexpr int kRing = 6;            // blocks the prep wavefronts are ahead at most
 constexpr int kHRing = 8;           // published fields of coming blocks
 constexpr int kFRing = 64;          // flips of past blocks
 constexpr int kEmpty = 4;           // blocks of no flips after the last one
@@ -79,7 +72,6 @@ constexpr int kThrCache = 512;      // threshold entries cached in LDS
 constexpr int kPrepWaves = 3;
 constexpr int kUpdWaves = 12;
 constexpr int kSkThreads = 64 * (1 + kPrepWaves + kUpdWaves);
-constexpr int kSpinLimit = 1 << 22; // bounded waits: a stuck pipeline aborts
 static_assert(64 * kSkLaunchBlocks <= (int64_t)UINT32_MAX, "a launch's accepted flips fit 32 bits");
 static_assert(kWin % 2 == 1 && kWin + 3 <= kHRing, "published fields are read before their slots are used again");
 // An updater's blocks are at most 2 kUpdWaves - 1 apart, and the decider waits for
@@ -141,37 +133,6 @@ __host__ __device__ __forceinline__ SkLds sk_layout(int32_t n)
     L.pr = take(kPrepWaves * 64 * 16);
     L.total = off;
     return L;
-}
-
-// LDS accesses of the pipeline.  The LDS executes one wavefront's operations in
-// order, so data written before a flag is there once the flag is seen, and data
-// read after a flag is no older than it: the accesses only have to stay in program
-// order, which volatile accesses do, with no wait between them.
-template <class T>
-__device__ __forceinline__ T lds_get(uint32_t off)
-{
-    return *(const volatile SG_L T*)(size_t)off;
-}
-template <class T>
-__device__ __forceinline__ void lds_put(uint32_t off, T v)
-{
-    *(volatile SG_L T*)(size_t)off = v;
-}
-
-// One poll of a wait that has not been met yet: true when the wait must end
-// without its condition (abort raised, or this wait was the one that ran out
-// of polls: after kSpinLimit polls the pipeline is declared stuck, the abort
-// flag releases every other wait and is reported at the end of the kernel: a
-// global atomic here would count as a memory operation that may be in flight
-// after every wait, and make each wait for the streamed words a wait for all).
-__device__ __forceinline__ bool wait_giveup(uint32_t sync, int& spins)
-{
-    if (__builtin_amdgcn_readfirstlane(lds_get<int32_t>(sync + 4))) return true;
-    if (++spins > kSpinLimit) {
-        lds_put<int32_t>(sync + 4, 1);
-        return true;
-    }
-    return false;
 }
 
 __device__ __forceinline__ void wave_sync_sk()

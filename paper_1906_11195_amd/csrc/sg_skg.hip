@@ -51,11 +51,10 @@
 
 #include "sg_internal.h"
 #include "sg_philox.h"
+#include "sg_pipe.h"
 
 namespace sg {
 namespace {
-
-#define SG_L __attribute__((address_space(3)))
 
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
@@ -68,7 +67,6 @@ constexpr int kBatch = 8;           // flips taken at a time
 constexpr int kPrep = 2;
 constexpr int kUpd = 13;
 constexpr int kSkgThreads = 64 * (1 + kPrep + kUpd);
-constexpr int kSpinLimit = 1 << 22; // bounded waits: a stuck pipeline aborts
 constexpr uint32_t kTile = 65 * 256;   // bytes of a tile: 64 rows of 64 floats and a row of zeros
 // An entry of the decider's own lists (16 bits): flipped lane << 8 (a row's offset
 // in a tile) | (new spin -1) << 15; kNoFlip is none (the row of zeros).  The
@@ -113,33 +111,6 @@ __host__ __device__ __forceinline__ SkgLds skg_layout(int32_t n)
     L.sync = take(8);
     L.total = off;
     return L;
-}
-
-// LDS accesses of the pipeline: the LDS executes one wavefront's operations in
-// order, so data written before a flag is there once the flag is seen, and data
-// read after a flag is no older than it; volatile accesses keep program order.
-template <class T>
-__device__ __forceinline__ T lds_get(uint32_t off)
-{
-    return *(const volatile SG_L T*)(size_t)off;
-}
-template <class T>
-__device__ __forceinline__ void lds_put(uint32_t off, T v)
-{
-    *(volatile SG_L T*)(size_t)off = v;
-}
-
-// One poll of a wait that has not been met yet: true when the wait must end
-// without its condition (abort raised, or this wait ran out of polls: the
-// pipeline is then declared stuck, which the end of the kernel reports).
-__device__ __forceinline__ bool wait_giveup(uint32_t sync, int& spins)
-{
-    if (__builtin_amdgcn_readfirstlane(lds_get<int32_t>(sync + 4))) return true;
-    if (++spins > kSpinLimit) {
-        lds_put<int32_t>(sync + 4, 1);
-        return true;
-    }
-    return false;
 }
 
 // Waits until `target` blocks of the launch are decided.

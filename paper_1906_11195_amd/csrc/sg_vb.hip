@@ -925,16 +925,16 @@ __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 }
 
 // Accepted flips of one wavefront, counted per lane in the flips' own
-// spin-word fields (n += flips of each chunk).  A P-bit field holds the flips
-// of at most 2^P - 1 chunks: with 8 chain slots (4-bit fields) the counts move
-// to byte fields (e: even chains, o: odd chains, chain c at byte c / 2) every
-// 15 chunks; byte and 16-bit fields are summed over the wavefront into the
-// unit's LDS totals every 255 (65535) chunks, and every field at the end of
-// each sweep.
+// spin-word fields (n += flips of each chunk, of H blocks).  A P-bit field holds the
+// flips of at most 2^P - 1 blocks: with 8 chain slots (4-bit fields) the counts move
+// to byte fields (e: even chains, o: odd chains, chain c at byte c / 2) before a
+// chunk could pass 15 blocks, and 17 such moves fill a byte; byte and 16-bit fields
+// are summed over the wavefront into the unit's LDS totals before a chunk could pass
+// 255 (65535) blocks, and every field at the end of each stretch of sweeps.
 template <int RPAD>
 struct VbAcc {
     uint32_t n = 0, e = 0, o = 0;   // per lane
-    int32_t cn = 0, cb = 0;         // wave-uniform chunk counts since the last fold / flush
+    int32_t cn = 0, cb = 0;         // wave-uniform: blocks since the last fold (flush), folds since the last flush
 };
 
 template <int RPAD>
@@ -1052,7 +1052,8 @@ __device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, cons
 // one block a chunk 85.7), 1 chain 49.4 (70.1; 5.5 TB/s of adjacency), 2 chains 54.9
 // (72.8), 4 chains 68.7 (83.2); one unit of 10^6 spins and 1 chain 566 (813).  One
 // resident unit of 1024 spins and 2 chains 2.3 (8.3; the time from counter to
-// counter, about 1000 cycles for each of 5 classes), 2048 of them 11 (27).
+// counter, about 1000 cycles for each of 5 classes; 2.06 in a loop of its own, which
+// went when the streamed units' loop became this one), 2048 of them 11 (27).
 template <int RPAD, bool RES, bool SPLIT, bool CPL, class PR, class PE, class PT>
 __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
                         int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W)
