@@ -566,9 +566,36 @@ __device__ __forceinline__ uint32_t chunk_flip(const Site& site, const VbChunk& 
 // unit's abort flag and the context's error bit, and every member stops.
 constexpr uint64_t kBarrierTicks = 2000000000ull;
 
-template <int RPAD>
-__device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, int32_t lo, int32_t hi,
-                            uint32_t target)
+// What the exchanges of a split unit need of its descriptor, kept in scalar
+// registers over the sweep loop: read at each use they come from memory again after
+// every fence, four dependent reads in each of a sweep's 6 or 7 exchanges.  Measured,
+// us per sweep, one graph of 65536 spins in 13 members: 6 chains 40.2 -> 35.3, 8 chains
+// 43.8 -> 38.9, 2 chains 30.2 -> 28.6.  With one chain slot they are read at each use
+// all the same: kept, the loop's code came out slower (pairs of 10^6 spins 443 -> 469,
+// 13 members of 65536 28.7 and 28.7).
+template <bool KEEP>
+struct SplitRef {
+    SG_G uint32_t* state_;
+    uint32_t* bar_;
+    int32_t words_, members_;
+    __device__ __forceinline__ explicit SplitRef(const VbUnit* up)
+    {
+        if (KEEP) {
+            state_ = gl(uniform(up->state));
+            bar_ = uniform(up->bar);
+            words_ = __builtin_amdgcn_readfirstlane(up->state_words);
+            members_ = __builtin_amdgcn_readfirstlane(up->members);
+        }
+    }
+    __device__ __forceinline__ SG_G uint32_t* state(const VbUnit* up) const { return KEEP ? state_ : gl(up->state); }
+    __device__ __forceinline__ uint32_t* bar(const VbUnit* up) const { return KEEP ? bar_ : up->bar; }
+    __device__ __forceinline__ int32_t words(const VbUnit* up) const { return KEEP ? words_ : up->state_words; }
+    __device__ __forceinline__ int32_t members(const VbUnit* up) const { return KEEP ? members_ : up->members; }
+};
+
+template <int RPAD, bool KEEP>
+__device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, const SplitRef<KEEP>& ref, int32_t lo,
+                            int32_t hi, uint32_t target)
 {
     using S = Sl<RPAD>;
     // One thread fences for the workgroup (as a grid barrier does): the
@@ -578,7 +605,7 @@ __device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, int32
     // the shared caches once per wavefront, slowing every workgroup on them.)
     __syncthreads();
     if (threadIdx.x == 0) {
-        uint32_t* bar = up->bar;
+        uint32_t* bar = ref.bar(up);
         int32_t ab = 0;
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
         __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -601,7 +628,7 @@ __device__ bool vb_exchange(const VbUnit* __restrict__ up, const VbLds& L, int32
     }
     __syncthreads();
     if (L.flag[0] != 0) return false;
-    const SG_G uint32_t* gs = gl(up->state);
+    const SG_G uint32_t* gs = ref.state(up);
     const int32_t w0 = lo >> S::LP, w1 = hi > lo ? ((hi - 1) >> S::LP) : w0 - 1;
     // (eight loads of a thread in flight: one at a time, a class of 3 10^5 spins
     // waited ten times for HBM)
@@ -1104,17 +1131,18 @@ __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, P
     // words are written through to HBM together at the end of the class (a store per
     // chunk would be waited for with the next chunk's entries)
     int32_t own_n = 0, own_base = 0;
+    const SplitRef<SPLIT && (RPAD > 1)> ref(up);
     auto exchange = [&]() {
         using S = Sl<RPAD>;
         constexpr int LW = 6 + (H - 1) - S::LP;   // log2 of a chunk's words
         for (int32_t i = lane; i < own_n << LW; i += 64) {
             const uint32_t wi = ((uint32_t)(own_base + (i >> LW) * step * 64 * H) >> S::LP) + (uint32_t)(i & ((1 << LW) - 1));
-            if (wi < (uint32_t)up->state_words) gl(up->state)[wi] = L.sp[wi];
+            if (wi < (uint32_t)ref.words(up)) ref.state(up)[wi] = L.sp[wi];
         }
         own_n = 0;
         const int32_t lo = cls_at(cls, k), hi = cls_at(cls, k + 1);
         ++k;
-        return vb_exchange<RPAD>(up, L, lo, hi, (uint32_t)up->members * (uint32_t)(s * ncls + k));
+        return vb_exchange<RPAD>(up, L, ref, lo, hi, (uint32_t)ref.members(up) * (uint32_t)(s * ncls + k));
     };
     // ends the sweeps before `to`
     auto sweeps = [&](int32_t to) -> bool {
