@@ -837,6 +837,7 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         bool cpl = false;
         int64_t work = 0;
         int members = 1;
+        int blocks = 2;   // of a chunk
     };
     // Workgroup size first: about three 64-position chunks per wavefront in
     // the graph's largest colour class (up to 16 wavefronts).  Then as many
@@ -980,14 +981,20 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         off_ent[gi] = A.take((graphs[gi].ent.size() + kVbEntPad) * 4);
         off_cls[gi] = A.take(graphs[gi].cls.size() * 4);
     }
-    // chunk tables, one per graph for its resident and one for its other units, in one
-    // array: a copy for all of them
+    for (auto& u : plan) {
+        const VbGraph& g = graphs[(size_t)u.group];
+        int32_t maxcls = 0;
+        for (int32_t k = 0; k < g.ncls; ++k) maxcls = std::max(maxcls, g.cls[(size_t)k + 1] - g.cls[(size_t)k]);
+        u.blocks = u.resident ? 1 : u.members > 1 ? split_chunk_blocks(u.rpad, maxcls, u.members * (u.threads / 64)) : 2;
+    }
+    // chunk tables, one per graph for chunks of one block and one for chunks of two, in
+    // one array: a copy for all of them
     std::vector<VbChunk> tabs;
     std::vector<std::pair<size_t, size_t>> tab_of(2 * n_groups, {0, 0});   // first, number
     for (const auto& u : plan) {
-        auto& r = tab_of[2 * (size_t)u.group + (u.resident ? 1 : 0)];
+        auto& r = tab_of[2 * (size_t)u.group + (size_t)(u.blocks - 1)];
         if (r.second != 0) continue;
-        const std::vector<VbChunk> t = vb_chunks(graphs[(size_t)u.group], u.resident ? 1 : 2);
+        const std::vector<VbChunk> t = vb_chunks(graphs[(size_t)u.group], u.blocks);
         r = {tabs.size(), t.size()};
         tabs.insert(tabs.end(), t.begin(), t.end());
     }
@@ -1103,9 +1110,10 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         U.row = c->at<int32_t>(off_row[(size_t)plan[u].group]);
         U.ent = c->at<uint32_t>(off_ent[(size_t)plan[u].group]);
         U.cls = c->at<int32_t>(off_cls[(size_t)plan[u].group]);
-        const auto& tab = tab_of[2 * (size_t)plan[u].group + (plan[u].resident ? 1 : 0)];
+        const auto& tab = tab_of[2 * (size_t)plan[u].group + (size_t)(plan[u].blocks - 1)];
         U.chunk = c->at<VbChunk>(off_tabs) + tab.first;
         U.chunks = (int32_t)tab.second;
+        U.blocks = plan[u].blocks;
         U.resident = plan[u].resident ? 1 : 0;
         U.cpl = plan[u].cpl ? 1 : 0;
         if (U.cpl) U.entc = c->at<uint32_t>(off_entc.at({plan[u].group, plan[u].rpad}));

@@ -43,6 +43,19 @@ constexpr int kSplitMaxMembers = 32;
 // us per sweep: whole 568, two members 385 for one such unit and 443 for 32 at once)
 constexpr int64_t kSplitPairCost = 2500000;
 
+// Blocks of 64 positions in the chunks of a split unit with `slots` chain slots, whose
+// members have `waves` wavefronts together: two, whose latencies overlap, or one where
+// two would leave wavefronts without a chunk, or with half the work of others, in the
+// largest colour class (`largest` positions).  Measured with 8 slots, us per sweep with
+// one / two blocks and the chunks of two per wavefront: graphs of 65536 spins, 6 chains,
+// 13 members each (0.8) 34.4 / 35.3, 8 members (1.4) 42.6 / 44.6, 4 (2.8) 60.6 / 57.0;
+// of 131072 spins, 28 (0.8) 35.0 / 35.8, 16 (1.4) 56.1 / 59.0, 4 (5.6) 85 / 77.  With
+// fewer slots a chunk of two is as quick as one of one (2 chains, 0.8: 29.1 / 28.6).
+inline int split_chunk_blocks(int slots, int64_t largest, int64_t waves)
+{
+    return slots == 8 && (largest + 127) / 128 < 2 * waves ? 1 : 2;
+}
+
 struct SplitUnit {
     int64_t cost;        // n (10 + chains)
     bool resident;       // adjacency kept in LDS: never split

@@ -13,7 +13,8 @@
 //
 // A sweep visits colour class 0, 1, ...; inside a class all positions are
 // independent (no two are adjacent).  A class is cut into chunks of two aligned
-// blocks of 64 positions (one block where the adjacency is resident in LDS), which
+// blocks of 64 positions (one block where the adjacency is resident in LDS, and in some
+// split units: split_chunk_blocks), which
 // the wavefronts take in turn; lane i of a wavefront updates position i of each
 // block for every chain of the unit.  vb_loop says how the wavefronts keep the
 // order of the classes and what is in flight when.
@@ -850,13 +851,13 @@ __device__ __attribute__((noinline)) void vb_window(const VbUnit* __restrict__ u
     }
 }
 
-template <int RPAD, bool RES, bool SPLIT, bool CPL, class PR, class PE, class PT>
+template <int RPAD, bool RES, bool SPLIT, bool CPL, int H, class PR, class PE, class PT>
 __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
                         int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W);
 
 // (each variant is a function of its own so that its registers are
 // allocated for it alone)
-template <int RPAD, bool RES, bool SPLIT, bool CPL>
+template <int RPAD, bool RES, bool SPLIT, bool CPL, int H>
 __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, uint32_t* smem_arr, uint32_t lds0,
                                                 int64_t t0, int32_t nsw, int64_t t_max)
 {
@@ -910,7 +911,7 @@ __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, 
     if (tid == 0) L.flag[0] = 0;   // chunks finished (split units: abort flag)
     const int32_t* cls = L.cls;
     __syncthreads();
-    if (RES) {
+    if constexpr (RES) {
         // row starts, and the entries in the form of vb_cpl_entries
         const int32_t n = up->n, m2 = up->m2;
         const SG_G int32_t* grow = gl(up->row);
@@ -927,13 +928,13 @@ __device__ __attribute__((noinline)) void vb_run(const VbUnit* __restrict__ up, 
         const SG_G int32_t* gtab = (const SG_G int32_t*)gl(up->chunk);
         for (int32_t i = tid; i < 4 * up->chunks; i += nthr) tab[i] = gtab[i];
         __syncthreads();
-        vb_loop<RPAD, true, false, CPL>(up, L, (const int32_t*)L.area, (const uint32_t*)re, (const VbChunk*)tab, cls, t0, nsw,
+        vb_loop<RPAD, true, false, CPL, H>(up, L, (const int32_t*)L.area, (const uint32_t*)re, (const VbChunk*)tab, cls, t0, nsw,
                                         t_max, lane, wave, W);
     } else {
         // (wave-uniform addresses: the rows and entries are addressed by a scalar
         // base and 32-bit offsets, and the chunk records, in constant memory, come
         // by scalar loads, which do not wait for the entries in flight)
-        vb_loop<RPAD, false, SPLIT, CPL>(up, L, gl(uniform(up->row)), gl(uniform(CPL ? up->entc : up->ent)),
+        vb_loop<RPAD, false, SPLIT, CPL, H>(up, L, gl(uniform(up->row)), gl(uniform(CPL ? up->entc : up->ent)),
                                          (const __attribute__((address_space(4))) VbChunk*)uniform(up->chunk), cls, t0, nsw,
                                          t_max, lane, wave, W);
     }
@@ -1068,8 +1069,8 @@ __device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, cons
 // every 8 cycles whatever else runs, so a small unit is bound by the instructions
 // between the last flip of a class and the first read of the next, and with 4
 // wavefronts a SIMD a large one is bound by exposed latency as much as by issue.  So
-// a large unit's chunk has two blocks, whose latencies overlap (a resident one's has
-// one: fewer instructions between two classes), and chunks of one degree (most:
+// a large unit's chunk has H = 2 blocks, whose latencies overlap (a resident one's has
+// one: fewer instructions between two classes; split_chunk_blocks for split ones), and chunks of one degree (most:
 // positions are sorted by it inside a class) need no rows, no masks and exactly as
 // many reads as neighbours.
 //
@@ -1081,7 +1082,7 @@ __device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, cons
 // resident unit of 1024 spins and 2 chains 2.3 (8.3; the time from counter to
 // counter, about 1000 cycles for each of 5 classes; 2.06 in a loop of its own, which
 // went when the streamed units' loop became this one), 2048 of them 11 (27).
-template <int RPAD, bool RES, bool SPLIT, bool CPL, class PR, class PE, class PT>
+template <int RPAD, bool RES, bool SPLIT, bool CPL, int H, class PR, class PE, class PT>
 __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
                         int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W)
 {
@@ -1104,7 +1105,8 @@ __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, P
     const bool win = __builtin_amdgcn_readfirstlane(up->kw) > 0;
     const int wl = __builtin_amdgcn_readfirstlane(tid >> 6);   // wavefront inside the workgroup
     lds_u32* const fin = (lds_u32*)(uint32_t*)L.flag;
-    constexpr int NE = RES ? kLdsMax : kHbmMax, H = RES ? 1 : 2;
+    constexpr int NE = RES ? kLdsMax : kHbmMax;
+    static_assert(H == 2 || (H == 1 && (RES || (SPLIT && RPAD == 8))), "the variants there are");
     // (wavefronts past the chunks of a sweep only take part in its end)
     const int32_t step = min(W, chunks);
     const int32_t B = vb_batch_chunks(nchains);
@@ -1367,31 +1369,36 @@ __global__ void __launch_bounds__(1024) vb_sweep_kernel(const VbUnit* __restrict
     const int64_t t0 = *gl(t0p);
     if (up->resident) {
         switch (up->rpad) {
-            case 1: vb_run<1, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            case 2: vb_run<2, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            case 4: vb_run<4, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            default: vb_run<8, true, false, true>(up, smem, lds0, t0, nsw, t_max); break;
+            case 1: vb_run<1, true, false, true, 1>(up, smem, lds0, t0, nsw, t_max); break;
+            case 2: vb_run<2, true, false, true, 1>(up, smem, lds0, t0, nsw, t_max); break;
+            case 4: vb_run<4, true, false, true, 1>(up, smem, lds0, t0, nsw, t_max); break;
+            default: vb_run<8, true, false, true, 1>(up, smem, lds0, t0, nsw, t_max); break;
         }
     } else if (up->members > 1) {
         switch (up->rpad) {
-            case 1: vb_run<1, false, true, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 2: vb_run<2, false, true, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 4: vb_run<4, false, true, false>(up, smem, lds0, t0, nsw, t_max); break;
-            default: vb_run<8, false, true, false>(up, smem, lds0, t0, nsw, t_max); break;
+            case 1: vb_run<1, false, true, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 2: vb_run<2, false, true, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 4: vb_run<4, false, true, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            default:
+                if (up->blocks == 1)
+                    vb_run<8, false, true, false, 1>(up, smem, lds0, t0, nsw, t_max);
+                else
+                    vb_run<8, false, true, false, 2>(up, smem, lds0, t0, nsw, t_max);
+                break;
         }
     } else if (up->cpl) {
         switch (up->rpad) {
-            case 1: vb_run<1, false, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            case 2: vb_run<2, false, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            case 4: vb_run<4, false, false, true>(up, smem, lds0, t0, nsw, t_max); break;
-            default: vb_run<8, false, false, true>(up, smem, lds0, t0, nsw, t_max); break;
+            case 1: vb_run<1, false, false, true, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 2: vb_run<2, false, false, true, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 4: vb_run<4, false, false, true, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            default: vb_run<8, false, false, true, 2>(up, smem, lds0, t0, nsw, t_max); break;
         }
     } else {
         switch (up->rpad) {
-            case 1: vb_run<1, false, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 2: vb_run<2, false, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            case 4: vb_run<4, false, false, false>(up, smem, lds0, t0, nsw, t_max); break;
-            default: vb_run<8, false, false, false>(up, smem, lds0, t0, nsw, t_max); break;
+            case 1: vb_run<1, false, false, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 2: vb_run<2, false, false, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            case 4: vb_run<4, false, false, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
+            default: vb_run<8, false, false, false, 2>(up, smem, lds0, t0, nsw, t_max); break;
         }
     }
 }

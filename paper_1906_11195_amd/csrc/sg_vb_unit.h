@@ -39,7 +39,7 @@ struct VbLayout {
 };
 
 // A chunk: the positions of one colour class inside one aligned block of 64 (units
-// whose adjacency is resident) or inside two consecutive ones.  The chunks of a
+// whose adjacency is resident, some split ones) or inside two consecutive ones.  The chunks of a
 // graph stand in sweep order (n <= 2^20: at most 2^14 + 64).
 struct VbChunk {
     uint32_t a;   // block | lo << 16 | (hi - 1) << 22 | even << 29 | full << 30
@@ -70,6 +70,7 @@ struct VbUnit {
     const int32_t* cls;        // [ncls+1] first position of each colour class
     const VbChunk* chunk;      // [chunks]
     int32_t chunks;            // chunks of a sweep
+    int32_t blocks;            // aligned blocks of a chunk
     int32_t resident;          // 1: whole adjacency kept in LDS for the launch
     int32_t cpl;               // 1: a complemented copy of the spin words is kept in LDS
     int32_t m2;                // 2m entries

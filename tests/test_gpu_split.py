@@ -87,3 +87,35 @@ def test_automatic_split_of_several_equal_graphs():
     assert_same(res, ref, "auto split vs unsplit")
     for i, d in enumerate(descs):
         assert_instance_equal(res, i, oracle_vb(d, sum(chunks), 16), label="auto equal i=%d" % i)
+
+
+def _hub_graph(n, hubs, degree, seed):
+    """A ring with `hubs` vertices of `degree` more neighbours each, as edges and couplings."""
+    rng = np.random.default_rng(seed)
+    edges = {(i, (i + 1) % n) if i + 1 < n else (0, i) for i in range(n)}
+    for h in range(0, hubs * 50, 50):
+        for v in rng.choice(np.arange(hubs * 50 + 10, n), degree, replace=False):
+            edges.add((h, int(v)))
+    edges = np.array(sorted(edges), np.int32)
+    return edges, np.where(rng.random(len(edges)) < 0.5, -1, 1).astype(np.int8)
+
+
+@pytest.mark.parametrize("members,threads,chains", [(16, 128, 6), (6, 512, 8), (4, 512, 5), (5, 512, 7), (3, 512, 6)])
+@pytest.mark.parametrize("hubs", [False, True])
+def test_eight_slots_in_chunks_of_one_and_two_blocks(members, threads, chains, hubs):
+    # 5 to 8 chains: chunks of one block where the largest class has fewer chunks of two
+    # than twice the members' wavefronts (all but the last case); degrees above 15
+    # (8-bit counts) with hubs; snapshots and windowed sums between the sweeps
+    require_gpu()
+    n = 20011
+    kw = {}
+    if hubs:
+        kw["edges"], kw["J"] = _hub_graph(n, 40, 30, 5)
+    descs = [sg.VbDesc(n=n, T=0.6 + 0.1 * k, seed=23, instance_id=20 + k, graph_id=4, c=4.0, n_replicas=1, **kw)
+             for k in range(chains)]
+    split = run_lib(descs, [5, 1, 14], 16, threads_per_unit=threads, split_members=members, window_tw_max=4)
+    whole = run_lib(descs, [5, 1, 14], 16, split_members=1, window_tw_max=4)
+    assert_same(split, whole, "members=%d" % members)
+    assert np.array_equal(split["window"], whole["window"])
+    for i in (0, chains - 1):
+        assert_instance_equal(split, i, oracle_vb(descs[i], 20, 16), label="members=%d i=%d" % (members, i))

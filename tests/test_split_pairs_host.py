@@ -69,3 +69,32 @@ def test_units_left_whole(plan):
     assert plan(64, [(8000000, 0, 40)] * 64)[0] == 0                   # equal: nothing gets shorter
     assert plan(64, [(c, 1, 40) for c, _, _ in SPREAD])[0] == 0        # resident
     assert plan(64, [(c, 0, 1) for c, _, _ in SPREAD])[0] == 0         # no chunks for two
+
+
+BLOCKS = r"""
+#include <cstdio>
+#include "sg_split_plan.h"
+int main()
+{
+    for (int slots : {1, 2, 4}) {
+        if (sg::split_chunk_blocks(slots, 1, 512) != 2 || sg::split_chunk_blocks(slots, 1 << 20, 1) != 2) return 1;
+    }
+    // 16 wavefronts: one block up to 31 chunks of two blocks in the largest class
+    if (sg::split_chunk_blocks(8, 1, 16) != 1 || sg::split_chunk_blocks(8, 31 * 128, 16) != 1) return 2;
+    if (sg::split_chunk_blocks(8, 31 * 128 + 1, 16) != 2 || sg::split_chunk_blocks(8, 1 << 20, 16) != 2) return 3;
+    std::puts("blocks ok");
+    return 0;
+}
+"""
+
+
+def test_blocks_of_split_chunks(tmp_path):
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("needs g++")
+    src, exe = str(tmp_path / "blocks.cpp"), str(tmp_path / "blocks")
+    with open(src, "w") as f:
+        f.write(BLOCKS)
+    subprocess.check_call([gxx, "-O1", "-std=c++17", "-I" + CSRC, src, "-o", exe])
+    out = subprocess.run([exe], capture_output=True, text=True, timeout=60)
+    assert out.returncode == 0 and "blocks ok" in out.stdout, out.returncode
