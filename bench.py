@@ -32,7 +32,9 @@ if ROOT not in sys.path:
 METRIC = "spin flips/ns at 1 GPU (VB, SK), batched vs plain; p50/p99 run latency"
 HBM_PEAK_GBS = 8000.0
 HBM_PEAK_BPS = HBM_PEAK_GBS * 1e9
-# VALU issue: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles at 2.4 GHz
+# VALU issue, nominal: 256 CUs x 4 SIMDs, one wave64 instruction per SIMD every 4 cycles
+# at 2.4 GHz.  (Measured by kind an instruction takes 2.4 to 5 cycles, so a fraction of
+# this says how much is issued, not how far the kernel is from a bound.)
 VALU_ISSUE_PEAK = 256 * 4 * 2.4e9 / 4
 
 
@@ -42,14 +44,11 @@ def log(msg):
 
 
 def vb_bytes_per_sweep(descs, R, chains_per_unit):
-    """Algorithmic bytes of one VB sweep, by the scope table's model: per
-    chain-update (c w / 8 + o) / r + 1/4 B -- every work unit (r chains of one
-    graph) streams the graph once (row starts o = 4 B per vertex, entries of
-    w = 32 bits, c per vertex on average), and each chain-update reads and
-    writes its own spin bit-packed (1/4 B).  In this design the spins never
-    leave LDS during a launch, so the own-spin quarter byte is LDS traffic and
-    the HBM counters see only the graph stream.  Units hold up to
-    `chains_per_unit` chains of one graph."""
+    """Bytes that one VB sweep cannot do without: every work unit (up to
+    `chains_per_unit` chains of one graph) streams its graph's entries once, two
+    per edge and 4 B each.  The spins stay in LDS during a launch, and row starts
+    are read only for chunks of more than one degree (on the batched workload
+    FETCH_SIZE is 1.04 times this)."""
     graphs = {}
     for d in descs:
         key = (d.n, d.c, d.seed, d.graph_id, None if d.edges is None else id(d.edges))
@@ -59,7 +58,7 @@ def vb_bytes_per_sweep(descs, R, chains_per_unit):
     total = 0.0
     for n, m, chains in graphs.values():
         units = math.ceil(chains / chains_per_unit)
-        total += units * (4 * (n + 1) + 8 * m) + chains * n / 4.0
+        total += units * 8.0 * m
     return total
 
 
@@ -281,9 +280,10 @@ def run_sk_gauss(args, torch, sg, workloads):
     acc = float(res["accepted"].sum() - a0) / upd
     rate = upd / el
     # bytes per attempted update: one float32 coupling row (4 N B) per
-    # accepted flip, the block's 64 x 64 tile (4 x 64 B per spin), and the
-    # direct recomputation (4 N^2 B per chain every 64 sweeps: 4 N / 64 B)
-    bpu = acc * 4 * n + 4 * 64 + 4 * n / 64
+    # accepted flip, the block's two 64 x 64 tiles (2 x 4 x 64 B per spin), and
+    # the direct recomputation (4 N^2 B per sample every 64 sweeps, its chains
+    # together: 4 N / (64 R) B)
+    bpu = acc * 4 * n + 2 * 4 * 64 + 4 * n / (64 * reps)
     return dict(workload="SK Gaussian: 64 samples x 2 replicas, N=4096, J ~ N(0, 1/N) float32, fields in "
                          "double, T=0.5, sweeps 8..%d" % (8 + S),
                 updates_per_ns=rate / 1e9, accepted_fraction=acc, generate_s=round(gen_s, 2),
@@ -391,11 +391,11 @@ def run_multispin(args, torch, sg, workloads):
         res[name] = r
         out[name] = dict(updates_per_ns=n_total * S / (el * 1e9), sweep_kernel_updates_per_ns=n_total * S / (dev_s * 1e9),
                          create_s=round(create_s, 2), measure_ms=round(measure_ms, 1))
-    # bytes per chain-update by the scope table's model, r chains sharing the
-    # graph stream, plus the per-chain couplings the multispin layout reads
-    # with it (one bit per chain and adjacency entry: c / 8 B)
-    bpu_ms = (4 * 4 + 4) / 64 + 0.25 + 4 / 8
-    bpu_pc = (4 * 4 + 4) / 2 + 0.25
+    # bytes per chain-update, r chains sharing the graph stream: multispin units
+    # read row starts, entries and with them the per-chain couplings (one bit per
+    # chain and adjacency entry: c / 8 B), per-chain units the entries
+    bpu_ms = (4 * 4 + 4) / 64 + 4 / 8
+    bpu_pc = 4 * 4 / 2
     for name, bpu in (("multispin", bpu_ms), ("per_chain", bpu_pc)):
         rate = out[name]["sweep_kernel_updates_per_ns"] * 1e9
         out[name]["roofline"] = dict(bound="hbm", bytes_per_update=round(bpu, 3), achieved=round(rate * bpu / 1e9, 1),
@@ -481,20 +481,18 @@ def run_serving(args, torch, sg, workloads):
 
 
 def served_bytes(results):
-    """Algorithmic bytes of the served runs: VB by the scope table's model
-    (one unit of the request's two chains streams its graph every sweep, two
-    units of one chain each when two chains do not fit in LDS, plus 1/4 B per
-    chain-update); SK by this library's model (one bit-packed coupling row of
-    N / 8 B per accepted flip, plus the int8 couplings the exact recompute
-    reads once per 64 sweeps for both chains)."""
+    """Bytes of the served runs by the models of the VB and SK legs: VB entries
+    once per unit and sweep (one unit of the request's two chains, two units of one
+    chain each when two chains do not fit in LDS); SK packed couplings once per
+    sweep and, for the exact recompute, once per 64 sweeps, for both chains
+    together."""
     total = 0.0
     for r in results:
         if r.kind == "vb":
             units = 2 // vb_chains_per_unit(r.n, 2)
-            total += r.sweeps * (units * (4 * (r.n + 1) + 8 * math.floor(2.0 * r.n)) + 2 * r.n / 4.0)
+            total += r.sweeps * units * 8.0 * math.floor(2.0 * r.n)
         else:
-            acc = float(r.obs["accepted"].sum())
-            total += acc * r.n / 8.0 + r.sweeps * r.n * r.n / 64.0
+            total += r.sweeps * (1.0 + 1.0 / 64.0) * r.n * r.n / 8.0
     return total
 
 

@@ -184,7 +184,7 @@ typedef void (*sg_free_fn)(void* ptr, size_t bytes, void* user);
  *                   units above twice one CU's share of the batch's work,
  *                   when no unit left whole would outlast them), 1 = never,
  *                   k >= 2 =
- *                   k workgroups for every unit with at least 2 k chunks of
+ *                   k workgroups for every unit with at least 2 k blocks of
  *                   64 positions per wavefront in its largest colour class.
  *                   Has no effect on any result; a barrier that times out
  *                   (20 s) makes sg_measure return SG_EDEVICE.

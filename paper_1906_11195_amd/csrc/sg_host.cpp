@@ -896,9 +896,9 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
         // theirs, up to one per chunk of a sweep, and 16 wavefronts in all
         // occupy a CU: shared among the units that a CU holds at once.
         // Measured, 2 chains, us per sweep with 4 / 8 / 16 wavefronts: N = 1024,
-        // one unit a CU 4.4 / 3.1 / 2.6, two 4.8 / 3.6 / 5.1, four 5.9 / 7.0 /
-        // 10.3; N = 2048 (a CU holds 3), four 15.5 / 10.9 / 13.7; N = 4096 (it
-        // holds 1), two 26.8 / 16.4 / 12.6.
+        // one unit a CU 4.8 / 3.3 / 2.7, two 5.1 / 3.9 / 5.4, four 6.1 / 7.3 /
+        // 10.4; N = 2048 (a CU holds 3), two 8.3 / 5.8 / 7.0, four 16.2 / 11.2 /
+        // 13.8; N = 4096 (it holds 1), two 27.0 / 15.6 / 11.2.
         if (!(o && o->threads_per_unit)) {
             auto need = [&](int t) { return vb_lds_bytes(n, u.rpad, nch, t, true) + vb_resident_bytes(n, (int32_t)g.ent.size(), g.ncls); };
             const int64_t held = std::max<int64_t>(1, std::min<int64_t>(per_cu, (int64_t)(lds_cap / need(256))));
@@ -922,10 +922,10 @@ void create_vb(sg_ctx* c, const sg_vb_desc* d, int32_t count, const sg_opts* o)
     // most half of what is left (64 members, then 32, 16, ...), so that every
     // large context built at the same time (a server's batches) splits its
     // largest units: contexts of one request of 985767 spins and 2 chains, us per
-    // sweep, 66, 77, 119 and 203 (with 64 members for the first two 66, 66, 565, 565).
+    // sweep, 66, 76, 115 and 202 (with 64 members for the first two 66, 66, 560, 560).
     // Members per unit: plan_split (sg_split_plan.h), by cost n (10 + chains).
     // opts.split_members: 0 automatic, 1 never, k >= 2 every unit that has
-    // the chunks for k members (tests, tuning).  No effect on any result.
+    // the blocks for k members (tests, tuning).  No effect on any result.
     {
         const int forced = o ? o->split_members : 0;
         auto cost_of = [&](const UnitPlan& u) {

@@ -5,24 +5,25 @@
 // A unit's cost per sweep is weighed as n (10 + chains): its graph (adjacency
 // stream and spin words per vertex) dominates and is shared by its chains,
 // a chain adding about a tenth of it (whole units, us per sweep on MI355X:
-// one chain of 985767 spins 792, six chains of 65536 spins 82).  Splitting
+// one chain of 985767 spins 560, six chains of 65536 spins 67).  Splitting
 // shortens a launch only if no unit left whole outlasts the split ones, so
 // the automatic plan splits the units above twice a CU's share of the cost
 // only when all of them get at least two members, or else the largest
 // leading group of them with three times the cost of every unit left whole, or
 // else as many of the costliest as there is room for, in two each, if that shortens
 // the longest launch by a sixth and more (sizes spread over decades: 256 graphs of
-// 2^10 to 2^20 spins with 2 replicas 446 us per sweep, 610 whole).
+// 2^10 to 2^20 spins with 2 replicas 444 us per sweep, 614 whole).
 // Their members are shared out in proportion to cost, so that every member
 // carries about the same part of a sweep, with a floor per member that rises
 // with the number of split units: members of many split units meet at their
 // barriers at the same time, and thin members then wait more than they
 // compute.  Measured, us per sweep: graphs of 65536 spins with 6 chains,
-// 1 graph 13 members 33, 4 graphs 8 members 41 (4: 48), 16 graphs 4 members
-// 57 (6: 61, 8: 73), 64 graphs 2 members 78 (whole: 82; with a budget of a
-// quarter of the CUs they stay whole); one request of 985767 spins with 2
-// chains (two units), 32 members each 65, whole 565.  (All but the last line were
-// measured with a slower sweep; the order of the alternatives is what they show.)
+// 1 graph 13 members 34 (8: 37, whole: 67), 4 graphs 8 members 44 (4: 48), 16
+// graphs 4 members 57 (6: 68, 8: 82), 64 graphs whole 69 (2 members: 73); one
+// request of 985767 spins with 2 chains (two units), 32 members each 66 (16: 76,
+// 64: 75, whole: 560).  Sizes below about 2^15 are split although they are faster
+// whole by now (one graph of 16384 spins, 6 chains, 26 against 21): the floors are
+// older than the sweep loop.
 #pragma once
 #include <algorithm>
 #include <cstddef>
@@ -33,14 +34,14 @@
 namespace sg {
 
 // the least cost a member carries with at most two, at most eight and more
-// split units (about 8, 14 and 28 us of a sweep on MI355X), and the most
+// split units (about 5, 9 and 17 us of a sweep on MI355X), and the most
 // members of one unit
 constexpr int64_t kSplitMemberCostFew = 75000;
 constexpr int64_t kSplitMemberCostSome = 130000;
 constexpr int64_t kSplitMemberCostMany = 260000;
 constexpr int kSplitMaxMembers = 32;
 // what a member of a unit split in two adds to half its cost (one chain of 10^6 spins,
-// us per sweep: whole 568, two members 385 for one such unit and 443 for 32 at once)
+// us per sweep: whole 560, two members 374 for one such unit and 436 for 32 at once)
 constexpr int64_t kSplitPairCost = 2500000;
 
 // Blocks of 64 positions in the chunks of a split unit with `slots` chain slots, whose
@@ -59,12 +60,12 @@ inline int split_chunk_blocks(int slots, int64_t largest, int64_t waves)
 struct SplitUnit {
     int64_t cost;        // n (10 + chains)
     bool resident;       // adjacency kept in LDS: never split
-    int64_t chunk_cap;   // most members with two 64-position chunks per wavefront of the largest class
+    int64_t chunk_cap;   // most members with two blocks of 64 positions per wavefront in the largest class
 };
 
 // Members of every unit (1: whole) for `budget` workgroups of split members
 // and a CU's share `share` of the batch's cost.  forced: 0 automatic, 1
-// never split, k >= 2 every non-resident unit that has the chunks for k
+// never split, k >= 2 every non-resident unit that has the blocks for k
 // members, within the budget.  Returns the members used (those of split
 // units).
 inline int plan_split(const std::vector<SplitUnit>& units, int64_t share, int budget, int forced,

@@ -1075,13 +1075,13 @@ __device__ __forceinline__ void vb_sweep_end(const VbUnit* __restrict__ up, cons
 // many reads as neighbours.
 //
 // Measured, us per sweep, against one barrier per class, one block per chunk and one
-// masked LDS round trip per neighbour: 256 graphs of 65536 spins with 6 chains 73.4
+// masked LDS round trip per neighbour: 256 graphs of 65536 spins with 6 chains 72.9
 // (90.0: 139 VALU, 108 SALU and 25 LDS instructions a block, 4 wavefronts a SIMD; with
-// one block a chunk 85.7), 1 chain 49.4 (70.1; 5.5 TB/s of adjacency), 2 chains 54.9
-// (72.8), 4 chains 68.7 (83.2); one unit of 10^6 spins and 1 chain 566 (813).  One
-// resident unit of 1024 spins and 2 chains 2.3 (8.3; the time from counter to
+// one block a chunk 85.7), 1 chain 48.6 (70.1; 5.5 TB/s of adjacency), 2 chains 54.1
+// (72.8), 4 chains 68.0 (83.2); one unit of 10^6 spins and 1 chain 560 (813).  One
+// resident unit of 1024 spins and 2 chains 2.2 (8.3; the time from counter to
 // counter, about 1000 cycles for each of 5 classes; 2.06 in a loop of its own, which
-// went when the streamed units' loop became this one), 2048 of them 11 (27).
+// went when the streamed units' loop became this one), 2048 of them 12 (27).
 template <int RPAD, bool RES, bool SPLIT, bool CPL, int H, class PR, class PE, class PT>
 __device__ void vb_loop(const VbUnit* __restrict__ up, const VbLds& L, PR row, PE ent, PT tab, const int32_t* cls,
                         int64_t t0, int32_t nsw, int64_t t_max, int lane, int wave, int W)
